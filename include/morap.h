@@ -212,7 +212,9 @@ typedef struct {
     double  bytes_tail;
     double  ms_sweep_kernel_tail;
     int32_t variant_tail;   /* that kernel's variant (0: no switch)                 */
-    int32_t reserved;
+    int32_t resident_models; /* models whose values the last solve kept in LDS (if   */
+                            /* all: variant 41 and the launches of that kernel in   */
+                            /* ms_sweep_kernel; else these fields are the others')  */
     int64_t refine_pairs;   /* support / query after FP32 solves: unassigned pairs   */
                             /* within the FP32 error of the assignment re-solved in  */
                             /* FP64 ...                                              */

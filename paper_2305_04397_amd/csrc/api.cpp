@@ -49,7 +49,7 @@ void to_abi(const Stats& s, morap_stats* out) {
     out->bytes_tail = s.bytes_tail;
     out->ms_sweep_kernel_tail = s.ms_sweep_kernel_tail;
     out->variant_tail = s.variant_tail;
-    out->reserved = 0;
+    out->resident_models = s.resident_models;
     out->refine_pairs = s.refine_pairs;
     out->refine_columns = s.refine_columns;
 }

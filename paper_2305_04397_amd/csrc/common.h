@@ -136,6 +136,9 @@ struct HostModels {
     std::vector<int32_t> blk_rec;      // [8S]
     std::vector<double>  blk_agent;    // [32 * distinct blocks]
     uint32_t blk_pattern = 0;          // bit 5a + d: some block has P[a][d] != 0
+    // [M] 1: every action has one cost in all states of the model and slot 0
+    // of every state is the state itself
+    std::vector<uint8_t> blk_plain;
     int64_t S() const { return (int64_t)state_row.size() - 1; }
     int64_t R() const { return (int64_t)row_ptr.size() - 1; }
     int64_t N() const { return (int64_t)col.size(); }
@@ -188,6 +191,7 @@ struct Stats {
     int64_t sweeps_tail = 0, sweep_launches_tail = 0;
     double bytes_tail = 0, ms_sweep_kernel_tail = 0;
     int variant_tail = 0;
+    int resident_models = 0;
     // the assignment check after FP32 solves: pairs re-solved, columns reassigned
     int64_t refine_pairs = 0, refine_columns = 0;
 };
@@ -201,6 +205,25 @@ struct ValueSet {
     DevBuf c;           // [K][M] FP64
     int prec = -1, K = 0, Kp = 0;
     bool valid = false;
+};
+
+// The models whose batched value iteration keeps its values in LDS (see the
+// kernel), per precision: launches over `order` (models with states, those of
+// the kernel's faster form first, each part largest first), and the rest.
+struct ResidentPlan {
+    struct Launch {
+        bool fast;
+        int begin, n, max_states;
+    };
+    struct Part {
+        std::vector<Launch> launches;
+        std::vector<int32_t> models;   // of all launches
+        std::vector<uint8_t> rest;     // [M] 1: left to the batched sweeps
+        int n_rest = 0;
+        DevBuf d_rest;                 // the same on the device
+    };
+    DevBuf order;
+    Part part[2];                      // MORAP_F64, MORAP_F32
 };
 
 struct Proposer;  // mlp.hip
@@ -331,6 +354,12 @@ struct morap_ctx {
     std::vector<int32_t> h_live_tiles;              // instance tiles still active
     morap::DevBuf d_live_tiles;
     std::vector<int8_t> h_mu;                       // policies of the last evaluate
+
+    // value iteration with the values in LDS (built per upload)
+    morap::ResidentPlan resident_plan;
+    morap::DevBuf d_weights;                        // [K][d] weights of the solve
+    morap::DevBuf d_rest_mask;                      // [M][Kp] pairs left to the batched sweeps
+    morap::PinnedBuf h_pair_sweeps, h_weights, h_c;
 
     // units of the stage-retiring solve (built on first use per upload)
     morap::StagedLayout staged;
@@ -542,6 +571,46 @@ void compact(hipStream_t s, const ConvergeArgs& a);
 // sweep kernel between the gather and the LDS-staged tiles)
 void relist(hipStream_t s, ConvergeArgs a);
 void init_solve(hipStream_t s, const ConvergeArgs& a);
+// the same without the active lists: no pair is left to the batched sweeps
+void init_pairs(hipStream_t s, const ConvergeArgs& a);
+// mask[m][k] = flag[m]
+void model_mask(hipStream_t s, int M, int Kp, const uint8_t* flag, uint8_t* mask);
+
+// Value iteration with the values resident in LDS (resident.hip): the sweeps
+// sweep0 + 1 .. sweep1 (both even) of the listed models' pairs that have not
+// stopped (pair_sweeps 0), each pair to its stop.
+struct ResidentArgs {
+    const int32_t* order;       // [n_models] models, at most the kernel's states each
+    int n_models, groups;       // groups: column groups of a model (set by the launch)
+    const int32_t* state_base;  // [M+1]
+    const int32_t* init;        // [M]
+    const int32_t* rec;         // neighbourhood-block records [8S]
+    const void* ablk;           // agent blocks (precision of the solve)
+    int32_t zero_row;
+    const double* W;            // [K][d] weights
+    int nI, nJ, d, K, Kp, M;
+    void* x0;                   // [S+1][Kp] start values (warm or sweep0 > 0), final values
+    void* x1;                   // after the last launch: iterate before the last, of pairs still running
+    uint8_t* active;            // [M][Kp] set for pairs still running after the last launch
+    uint8_t* final_par;         // [M][Kp]
+    int32_t* pair_sweeps;       // [M][Kp]
+    double* c;                  // [K][M] values at the initial states
+    double* best_res;           // [M][Kp] FP32 rounding floor, kept between launches
+    int32_t* stall;             // [M][Kp]
+    int64_t* counters;          // [8]: pairs stopped at the rounding floor
+    double eps, unit, floor;
+    int stall_sweeps, warm, sweep0, sweep1, last;
+};
+// every block's nonzero entries lie within the grid pattern
+bool has_grid_pattern(uint32_t union_pattern);
+// largest product (states) the kernel holds; `fast`: every block has the grid
+// pattern, every action one cost and slot 0 of every state is the state itself
+int resident_capacity(int prec, bool fast);
+// register steps (states per thread) of a product of that many states; a
+// launch takes models of one class
+int resident_class(int states);
+// wide: several columns per workgroup (4 in FP32, 2 in FP64), else one
+void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, ResidentArgs a);
 
 // stage retirement (staged.hip)
 struct StageArgs {

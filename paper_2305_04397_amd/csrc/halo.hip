@@ -35,8 +35,6 @@ namespace k {
 
 namespace {
 
-constexpr int NSLOT = 5;
-constexpr int BLK = 32;
 constexpr int WAVES = 4;
 constexpr int ROUNDS = (HALO_MAX + 4 * WAVES - 1) / (4 * WAVES);   // 16 rows per round
 // a load writes four rows from a multiple of 4 below the tile's row count:
@@ -45,15 +43,6 @@ static_assert(HALO_MAX % 4 == 0, "HALO_MAX must be a multiple of 4");
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __attribute__((address_space(1))) const void* gbl_ptr_t;
-
-constexpr uint32_t PAT_DENSE_H = (1u << 25) - 1;
-constexpr uint32_t PAT_GRID_H = (1u << 0) | (1u << 1) | (1u << 3) | (1u << 4) |
-                                (1u << 5) | (1u << 7) | (1u << 8) | (1u << 9) |
-                                (1u << 10) | (1u << 11) | (1u << 12) | (1u << 13) |
-                                (1u << 15) | (1u << 16) | (1u << 17) | (1u << 19) |
-                                (1u << 20);
-template <uint32_t PAT>
-__device__ __forceinline__ constexpr bool nzh(int a, int d) { return (PAT >> (a * NSLOT + d)) & 1u; }
 
 }  // namespace
 
@@ -194,11 +183,11 @@ bellman_halo(const HTile* __restrict__ tiles, const int32_t* __restrict__ act_ti
                         float rp = 0.f;
 #pragma unroll
                         for (int s = 0; s < NSLOT; ++s)
-                            if (nzh<PAT>(a, s) && ((accm >> s) & 1)) rp += B[a * NSLOT + s];
+                            if (nz<PAT>(a, s) && ((accm >> s) & 1)) rp += B[a * NSLOT + s];
                         float acc = fmaf(wp, rp, wc * B[25 + a]);
 #pragma unroll
                         for (int s = 0; s < NSLOT; ++s)
-                            if (nzh<PAT>(a, s)) acc = fmaf(B[a * NSLOT + s], xv[q][s], acc);
+                            if (nz<PAT>(a, s)) acc = fmaf(B[a * NSLOT + s], xv[q][s], acc);
                         best = fmaxf(best, acc);
                     }
                 } else {
@@ -207,7 +196,7 @@ bellman_halo(const HTile* __restrict__ tiles, const int32_t* __restrict__ act_ti
                         float acc = wc * B[25 + a];
 #pragma unroll
                         for (int s = 0; s < NSLOT; ++s)
-                            if (nzh<PAT>(a, s)) acc = fmaf(B[a * NSLOT + s], xv[q][s], acc);
+                            if (nz<PAT>(a, s)) acc = fmaf(B[a * NSLOT + s], xv[q][s], acc);
                         best = fmaxf(best, acc);
                     }
                 }
@@ -226,14 +215,10 @@ bellman_halo(const HTile* __restrict__ tiles, const int32_t* __restrict__ act_ti
     if (cur_m >= 0) flush(cur_m);
 }
 
-static uint32_t halo_pattern(uint32_t union_pattern) {
-    return (union_pattern & ~PAT_GRID_H) == 0 ? PAT_GRID_H : PAT_DENSE_H;
-}
-
 template <int U>
 static const void* halo_fn(uint32_t pattern) {
-    if (halo_pattern(pattern) == PAT_GRID_H) return reinterpret_cast<const void*>(&bellman_halo<U, PAT_GRID_H>);
-    return reinterpret_cast<const void*>(&bellman_halo<U, PAT_DENSE_H>);
+    if (pattern_for(pattern) == PAT_GRID) return reinterpret_cast<const void*>(&bellman_halo<U, PAT_GRID>);
+    return reinterpret_cast<const void*>(&bellman_halo<U, PAT_DENSE>);
 }
 
 int sweep_halo_resident(const Variant& v, uint32_t pattern) {
@@ -254,13 +239,13 @@ void sweep_halo(hipStream_t s, int prec, const Variant& v, int grid, int ktiles,
     MORAP_CHECK(prec == MORAP_F32, MORAP_E_UNSUPPORTED, "the LDS-staged sweep runs FP32 values only");
     MORAP_CHECK(a.htiles && a.hrec && a.hlist && a.ablk, MORAP_E_STATE, "the halo tiles were not built");
     MORAP_CHECK(a.Kp % 64 == 0, MORAP_E_UNSUPPORTED, "the LDS-staged sweep needs k-tiles of 64 columns");
-    const bool grid_pat = halo_pattern(a.pattern) == PAT_GRID_H;
+    const bool grid_pat = pattern_for(a.pattern) == PAT_GRID;
     if (v.unroll == 4) {
-        if (grid_pat) launch_halo_p<4, PAT_GRID_H>(s, grid, ktiles, a);
-        else launch_halo_p<4, PAT_DENSE_H>(s, grid, ktiles, a);
+        if (grid_pat) launch_halo_p<4, PAT_GRID>(s, grid, ktiles, a);
+        else launch_halo_p<4, PAT_DENSE>(s, grid, ktiles, a);
     } else {
-        if (grid_pat) launch_halo_p<2, PAT_GRID_H>(s, grid, ktiles, a);
-        else launch_halo_p<2, PAT_DENSE_H>(s, grid, ktiles, a);
+        if (grid_pat) launch_halo_p<2, PAT_GRID>(s, grid, ktiles, a);
+        else launch_halo_p<2, PAT_DENSE>(s, grid, ktiles, a);
     }
     MORAP_HIP(hipGetLastError());
 }

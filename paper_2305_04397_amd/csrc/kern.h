@@ -6,6 +6,28 @@ namespace morap {
 namespace k {
 
 // ---------------------------------------------------------------------------
+// neighbourhood blocks
+// ---------------------------------------------------------------------------
+constexpr int NSLOT = 5;
+constexpr int BLK = 32;   // values per agent block
+
+// Sparsity patterns of the blocks (bit 5a + d = entry P[a][d] may be nonzero):
+// every entry, or the grid pattern of the host's slot order (slot 0 = stay,
+// 1 + a = the cell move a aims at; the N/S moves slip E/W and vice versa).
+constexpr uint32_t PAT_DENSE = (1u << 25) - 1;
+constexpr uint32_t PAT_GRID = (1u << 0) | (1u << 1) | (1u << 3) | (1u << 4) |        // N: stay, N, E, W
+                              (1u << 5) | (1u << 7) | (1u << 8) | (1u << 9) |        // S: stay, S, E, W
+                              (1u << 10) | (1u << 11) | (1u << 12) | (1u << 13) |    // E: stay, N, S, E
+                              (1u << 15) | (1u << 16) | (1u << 17) | (1u << 19) |    // W: stay, N, S, W
+                              (1u << 20);                                            // stay
+template <uint32_t PAT>
+__device__ __forceinline__ constexpr bool nz(int a, int d) { return (PAT >> (a * NSLOT + d)) & 1u; }
+
+inline uint32_t pattern_for(uint32_t union_pattern) {
+    return (union_pattern & ~PAT_GRID) == 0 ? PAT_GRID : PAT_DENSE;
+}
+
+// ---------------------------------------------------------------------------
 // vector helpers: CPL consecutive columns per lane
 // ---------------------------------------------------------------------------
 template <class T, int CPL> struct Vec { T v[CPL]; };

@@ -569,6 +569,7 @@ static void build_blocks(morap_ctx* c, const morap_agent* agents, int nI, const 
     const int M = hm.M;
     const int32_t S = (int32_t)hm.S();
     std::vector<int32_t> recs((size_t)S * 8, 0);
+    hm.blk_plain.assign((size_t)M, 0);
     std::atomic<int> next{0};
     auto worker = [&] {
         std::vector<int32_t> map;
@@ -584,6 +585,8 @@ static void build_blocks(morap_ctx* c, const morap_agent* agents, int nI, const 
             map.assign((size_t)a.n_states * t.n_locs, -1);
             for (int32_t g = s0; g < s1; ++g)
                 map[(size_t)hm.states_sq[2 * (size_t)g + 1] * a.n_states + hm.states_sq[2 * (size_t)g]] = g;
+            bool plain = true;
+            const double* cost0 = nullptr;
             for (int32_t g = s0; g < s1; ++g) {
                 const int s = hm.states_sq[2 * (size_t)g], q = hm.states_sq[2 * (size_t)g + 1];
                 const int64_t ab = abase[i] + s;
@@ -603,7 +606,11 @@ static void build_blocks(morap_ctx* c, const morap_agent* agents, int nI, const 
                 r[5] = uniq[(size_t)ab];
                 r[6] = acc | ((int32_t)amask[ab] << 8);
                 r[7] = g;
+                const double* cost = &ublk[(size_t)r[5] * 32 + 25];
+                if (!cost0) cost0 = cost;
+                plain &= r[0] == g && (cost == cost0 || std::equal(cost, cost + NS, cost0));
             }
+            hm.blk_plain[(size_t)m] = plain ? 1 : 0;
         }
     };
     const int nt = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
@@ -791,6 +798,52 @@ static void order_records(morap_ctx* c) {
     hm.blk_rec.swap(out);
 }
 
+// Which models' solves keep their values in LDS, per precision: products of
+// the block form that fit a workgroup, in launches of one class (states per
+// thread) each.
+static void plan_resident(morap_ctx* c) {
+    const HostModels& hm = c->hm;
+    ResidentPlan& P = c->resident_plan;
+    auto states = [&](int m) { return hm.state_base[m + 1] - hm.state_base[m]; };
+    const bool grid = k::has_grid_pattern(hm.blk_pattern);
+    std::vector<int32_t> order;
+    if (c->has_blocks)
+        for (int m = 0; m < hm.M; ++m)
+            if (states(m) > 0) order.push_back(m);
+    auto fast = [&](int m) { return grid && hm.blk_plain[(size_t)m] != 0; };
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+        return fast(a) != fast(b) ? fast(a) : states(a) > states(b);
+    });
+    upload(P.order, order, c->stream);
+    for (int prec : {MORAP_F64, MORAP_F32}) {
+        ResidentPlan::Part& part = P.part[prec];
+        part.launches.clear();
+        part.models.clear();
+        part.rest.assign((size_t)hm.M, 0);
+        part.n_rest = 0;
+        for (int b = 0; b < (int)order.size(); ++b) {
+            const int m = order[b];
+            if (states(m) > k::resident_capacity(prec, fast(m))) {
+                part.rest[(size_t)m] = 1;
+                ++part.n_rest;
+                continue;
+            }
+            part.models.push_back(m);
+            if (!part.launches.empty()) {
+                ResidentPlan::Launch& l = part.launches.back();
+                if (l.fast == fast(m) && l.begin + l.n == b &&
+                    k::resident_class(l.max_states) == k::resident_class(states(m))) {
+                    ++l.n;
+                    continue;
+                }
+            }
+            part.launches.push_back({fast(m), b, 1, states(m)});
+        }
+        upload(part.d_rest, part.rest, c->stream);
+    }
+    MORAP_HIP(hipStreamSynchronize(c->stream));   // order goes out of scope
+}
+
 void upload_models(morap_ctx* c) {
     const HostModels& hm = c->hm;
     hipStream_t s = c->stream;
@@ -882,6 +935,7 @@ void upload_models(morap_ctx* c) {
         c->d_blk32.ensure(hm.blk_agent.size() * 4 + 16);
         k::to_f32(s, c->d_blk64.as<double>(), c->d_blk32.as<float>(), (int64_t)hm.blk_agent.size());
     }
+    plan_resident(c);
     MORAP_HIP(hipStreamSynchronize(s));
     c->loaded = true;
 }

@@ -395,7 +395,10 @@ static double time_variant(morap_ctx* c, ValueSet& vs, const uint8_t* mask, cons
 
 // autotuner: the fastest candidate variant for (precision, padded width,
 // restricted or not), timed on the loaded models and cached on the context
-static const Variant& choose_variant(morap_ctx* c, ValueSet& vs, const uint8_t* mask, double eps, int schedule) {
+// (`refine`: the masked re-solve of assigned pairs; a mask without it holds the
+// models whose values do not fit LDS)
+static const Variant& choose_variant(morap_ctx* c, ValueSet& vs, const uint8_t* mask, bool refine, double eps,
+                                     int schedule) {
     if (schedule > 0) {
         const Variant& v = variant_by_id(schedule);
         MORAP_CHECK(vs.Kp % kt_of(v) == 0, MORAP_E_INVALID, "variant does not divide the padded column count");
@@ -406,10 +409,10 @@ static const Variant& choose_variant(morap_ctx* c, ValueSet& vs, const uint8_t* 
                     "the LDS-staged sweep needs halo tiles (built with the block form) and FP32 values");
         return v;
     }
-    const int64_t key = ((int64_t)vs.prec << 40) | ((int64_t)(mask != nullptr) << 32) | vs.Kp;
+    const int64_t key = ((int64_t)vs.prec << 40) | ((int64_t)(refine ? 1 : (mask ? 2 : 0)) << 32) | vs.Kp;
     for (auto& t : c->tuned)
         if (t.first == key) return variant_by_id(t.second);
-    auto cand = candidates(vs.Kp, mask != nullptr, c->has_blocks, c->has_halo && vs.prec == MORAP_F32);
+    auto cand = candidates(vs.Kp, refine, c->has_blocks, c->has_halo && vs.prec == MORAP_F32);
     MORAP_CHECK(!cand.empty(), MORAP_E_UNSUPPORTED, "no sweep variant for this column count");
     int best = cand[0].id;
     if (cand.size() > 1) {
@@ -418,7 +421,7 @@ static const Variant& choose_variant(morap_ctx* c, ValueSet& vs, const uint8_t* 
         // also gets the LDS-staged kernel for the last sweeps of a solve
         // (~4 % of its time saved on the 50 x 100 workload), so the others
         // must beat it by 3 %
-        const bool tail_possible = !mask && c->has_halo && vs.prec == MORAP_F32 && vs.Kp % 64 == 0;
+        const bool tail_possible = !refine && c->has_halo && vs.prec == MORAP_F32 && vs.Kp % 64 == 0;
         for (const auto& v : cand) {
             const bool gets_tail = tail_possible && v.kind == SWEEP_BLOCK && v.cpl == 1 && v.lps == 64;
             const double raw = time_variant(c, vs, mask, v, eps);
@@ -496,9 +499,8 @@ static std::string describe_active(morap_ctx* c, ValueSet& vs) {
 // The LDS-staged sweep for the last sweeps of a solve whose kernel is the
 // wave-per-state gather sweep: the two give identical values, and once few
 // tiles stay active (the last large models) the staged one is faster.
-static const Variant* tail_variant(morap_ctx* c, const ValueSet& vs, const uint8_t* mask, const Variant& v,
-                                   int schedule) {
-    if (mask || schedule != 0 || !c->has_halo || vs.prec != MORAP_F32 || vs.Kp % 64 != 0) return nullptr;
+static const Variant* tail_variant(morap_ctx* c, const ValueSet& vs, bool refine, const Variant& v, int schedule) {
+    if (refine || schedule != 0 || !c->has_halo || vs.prec != MORAP_F32 || vs.Kp % 64 != 0) return nullptr;
     if (v.kind != SWEEP_BLOCK || v.cpl != 1 || v.lps != 64) return nullptr;
     for (const auto& t : variants())
         if (t.kind == SWEEP_HALO && t.unroll == 2) return &t;
@@ -514,15 +516,166 @@ static int tail_percent() {
     return p;
 }
 
+// id reported for a solve whose values all stayed in LDS
+constexpr int kResidentVariant = 41;
+
+// sweeps of one launch of the LDS-resident iteration: the host looks in
+// between, so that a solve that does not converge stays interruptible
+constexpr int kResidentSweeps = 4096;
+
+// What a solve reports, in pinned memory behind one synchronisation: the
+// sweeps of every pair, the values at the initial states and the counters.
+static void read_results(morap_ctx* c, const ValueSet& vs) {
+    const size_t ps = (size_t)c->hm.M * vs.Kp * 4, cv = (size_t)vs.K * c->hm.M * 8;
+    c->h_pair_sweeps.ensure(ps);
+    c->h_c.ensure(cv);
+    MORAP_HIP(hipMemcpyAsync(c->h_pair_sweeps.p, c->d_pair_sweeps.p, ps, hipMemcpyDeviceToHost, c->stream));
+    MORAP_HIP(hipMemcpyAsync(c->h_c.p, vs.c.p, cv, hipMemcpyDeviceToHost, c->stream));
+    read_counters(c);
+}
+
+// The pairs of the plan's models to their stop with the values in LDS
+// (pair_sweeps cleared before), up to `limit` sweeps each; their statistics
+// as the batched sweeps count them.  The values land in vs.x[0].
+static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& part, const morap_vi_opts& o,
+                         bool warm, int64_t limit, int chunk, Stats& st) {
+    const HostModels& hm = c->hm;
+    const bool f32 = vs.prec == MORAP_F32;
+    const k::ConvergeArgs ca = converge_args(c, vs, nullptr, o.eps_vi, 0, false);
+    k::ResidentArgs a{};
+    a.state_base = c->d_state_base.as<int32_t>();
+    a.init = c->d_init.as<int32_t>();
+    a.rec = c->d_blk_rec.as<int32_t>();
+    a.ablk = f32 ? c->d_blk32.p : c->d_blk64.p;
+    a.zero_row = (int32_t)c->S;
+    a.W = c->d_weights.as<double>();
+    a.nI = hm.nI;
+    a.nJ = hm.nJ;
+    a.d = hm.nI + hm.nJ;
+    a.K = vs.K;
+    a.Kp = vs.Kp;
+    a.M = hm.M;
+    a.x0 = vs.x[0].p;
+    a.x1 = vs.x[1].p;
+    a.active = ca.active;
+    a.final_par = ca.final_par;
+    a.pair_sweeps = ca.pair_sweeps;
+    a.c = ca.c;
+    a.best_res = ca.best_res;
+    a.stall = ca.stall;
+    a.counters = ca.counters;
+    a.eps = ca.eps;
+    a.unit = ca.unit;
+    a.floor = ca.floor;
+    a.stall_sweeps = ca.stall_sweeps;
+    a.warm = warm ? 1 : 0;
+    // several columns per workgroup share a state's probabilities and rows,
+    // unless all pairs run at once anyway: one column each ends sooner then
+    const int cus = c->prop.multiProcessorCount;
+    const bool wide = (int64_t)part.models.size() * vs.K > 2 * (int64_t)cus;
+    PooledEvents held(c);
+    int64_t done = 0, running = 0;
+    const int32_t* ps = nullptr;
+    for (int64_t s0 = 0; s0 < limit; s0 = done) {
+        done = std::min<int64_t>(limit, s0 + kResidentSweeps);
+        a.sweep0 = (int)s0;
+        a.sweep1 = (int)done;
+        a.last = done == limit ? 1 : 0;
+        for (const auto& l : part.launches) {
+            a.order = c->resident_plan.order.as<int32_t>() + l.begin;
+            a.n_models = l.n;
+            if (o.time_kernels) {
+                held.v.emplace_back(take_event(c), nullptr);
+                held.v.back().second = take_event(c);
+                MORAP_HIP(hipEventRecord(held.v.back().first, c->stream));
+            }
+            k::resident(c->stream, vs.prec, l.fast, wide, l.max_states, a);
+            if (o.time_kernels) MORAP_HIP(hipEventRecord(held.v.back().second, c->stream));
+        }
+        read_results(c, vs);
+        ps = c->h_pair_sweeps.as<int32_t>();
+        running = 0;
+        for (int32_t m : part.models)
+            for (int k = 0; k < vs.K; ++k) running += ps[(size_t)m * vs.Kp + k] == 0;
+        if (running == 0) break;
+    }
+    if (running > 0)
+        fail(MORAP_E_NOT_CONVERGED, "value iteration: " + std::to_string(running) +
+                                        " (model, column) pairs still active after " + std::to_string(limit) +
+                                        " sweeps" + describe_active(c, vs));
+    const double el = f32 ? 4 : 8;
+    int64_t longest = 0;
+    for (int32_t m : part.models) {
+        int64_t sum = 0, top = 0;
+        for (int k = 0; k < vs.K; ++k) {
+            const int64_t n = ps[(size_t)m * vs.Kp + k];
+            sum += n;
+            top = std::max(top, n);
+        }
+        const int32_t b = hm.state_base[m], e = hm.state_base[m + 1];
+        const int64_t rows = hm.state_row[e] - hm.state_row[b];
+        const int64_t nnz = hm.row_ptr[hm.state_row[e]] - hm.row_ptr[hm.state_row[b]];
+        st.backups += rows * sum;
+        st.bytes += (double)top * (4.0 * (e - b) + 4.0 * rows + 4.0 * nnz + el * nnz + 2.0 * el * rows) +
+                    2.0 * el * (double)(e - b) * (double)sum;
+        longest = std::max(longest, top);
+    }
+    st.max_pair_sweeps = std::max(st.max_pair_sweeps, longest);
+    st.sweeps = std::max<int64_t>(st.sweeps, (longest + chunk - 1) / chunk * chunk);
+    st.resident_models = (int)part.models.size();
+    if (part.n_rest == 0) {
+        st.variant = kResidentVariant;
+        for (auto& e : held.v) {
+            float t = 0;
+            MORAP_HIP(hipEventElapsedTime(&t, e.first, e.second));
+            st.ms_sweep_kernel += t;
+            st.sweep_launches += 1;
+        }
+    }
+}
+
+// The plan of the models whose values stay in LDS in a solve, nullptr with a
+// fixed schedule and where the block form or its models are missing.
+static const ResidentPlan::Part* resident_part(morap_ctx* c, int prec, const morap_vi_opts& o) {
+    const ResidentPlan::Part& part = c->resident_plan.part[prec];
+    return c->team || o.schedule != 0 || part.launches.empty() ? nullptr : &part;
+}
+
 static void run_vi(morap_ctx* c, int g, ValueSet& vs, const uint8_t* mask, const morap_vi_opts& o, Stats& st,
                    bool warm = false) {
-    const Variant& v0 = choose_variant(c, vs, mask, o.eps_vi, o.schedule);
+    const bool refine = mask != nullptr;
+    const int chunk = std::max(2, (o.check_every + 1) / 2 * 2);
+    // products that fit keep their values in LDS; the batched sweeps take the
+    // rest (all of them with a fixed schedule)
+    const ResidentPlan::Part* part = refine ? nullptr : resident_part(c, vs.prec, o);
+    const int64_t limit = ((int64_t)o.max_sweeps + chunk - 1) / chunk * chunk;
+    if (part && part->n_rest == 0) {
+        EventPair wall;
+        if (warm) {
+            swap_buf(vs.x[0], c->d_xwarm);
+            ++c->buf_gen;   // graphs hold the value buffers' addresses
+        }
+        k::init_pairs(c->stream, converge_args(c, vs, nullptr, o.eps_vi, 0, false));
+        MORAP_HIP(hipEventRecord(wall.a, c->stream));
+        run_resident(c, vs, *part, o, warm, limit, chunk, st);
+        MORAP_HIP(hipEventRecord(wall.b, c->stream));
+        MORAP_HIP(hipEventSynchronize(wall.b));
+        st.floor_stops += c->h_counters.as<int64_t>()[8];
+        st.ms_vi += wall.elapsed_ms();
+        vs.valid = true;
+        return;
+    }
+    if (part) {
+        if (c->d_rest_mask.ensure((size_t)c->hm.M * vs.Kp)) ++c->buf_gen;
+        k::model_mask(c->stream, c->hm.M, vs.Kp, part->d_rest.as<uint8_t>(), c->d_rest_mask.as<uint8_t>());
+        mask = c->d_rest_mask.as<uint8_t>();
+    }
+    const Variant& v0 = choose_variant(c, vs, mask, refine, o.eps_vi, o.schedule);
     c->last_variant = v0.id;
-    const Variant* vt = tail_variant(c, vs, mask, v0, o.schedule);
+    const Variant* vt = tail_variant(c, vs, refine, v0, o.schedule);
     const Variant* vp = &v0;   // the kernel of the next chunk
     double bytes_at_switch = -1;
     int64_t sweeps_at_switch = 0;
-    const int chunk = std::max(2, (o.check_every + 1) / 2 * 2);
     EventPair wall;
     reset_solve(c, vs, mask, o.eps_vi, v0);
     if (warm) {
@@ -536,6 +689,7 @@ static void run_vi(morap_ctx* c, int g, ValueSet& vs, const uint8_t* mask, const
                       c->d_team_E.as<double>(), vs.prec, vs.x[0].p);
     }
     MORAP_HIP(hipEventRecord(wall.a, c->stream));
+    if (part) run_resident(c, vs, *part, o, warm, limit, chunk, st);
     int64_t launched = 0;
     int64_t* h = c->h_counters.as<int64_t>();
     PooledEvents held(c);
@@ -548,7 +702,7 @@ static void run_vi(morap_ctx* c, int g, ValueSet& vs, const uint8_t* mask, const
             if (sweep_log() && i < 4096)
                 std::fprintf(sweep_log(), "sweep prec=%d mask=%d variant=%d tiles=%lld ms=%.4f\n", vs.prec,
                              mask != nullptr, vp->id, (long long)c->h_log.as<int64_t>()[i], t);
-            if (mask) {
+            if (refine) {
                 st.ms_sweep_kernel_refine += t;
                 st.sweep_launches_refine += 1;
             } else if (vp != &v0) {
@@ -592,7 +746,7 @@ static void run_vi(morap_ctx* c, int g, ValueSet& vs, const uint8_t* mask, const
     st.backups += h[4];
     st.floor_stops += h[8];
     const double bytes = (double)h[6] + 2.0 * el * (double)h[7];
-    if (mask) {
+    if (refine) {
         st.bytes_refine += bytes;
     } else if (bytes_at_switch >= 0) {
         st.bytes += bytes_at_switch;
@@ -604,10 +758,10 @@ static void run_vi(morap_ctx* c, int g, ValueSet& vs, const uint8_t* mask, const
     }
     st.max_pair_sweeps = std::max<int64_t>(st.max_pair_sweeps, *std::max_element(ps.begin(), ps.end()));
     st.ms_vi += ms;
-    if (mask) st.variant_refine = v0.id;
+    if (refine) st.variant_refine = v0.id;
     else st.variant = v0.id;
-    if (mask) st.polish_sweeps += h[5];
-    else st.sweeps += h[5];
+    if (refine) st.polish_sweeps += h[5];
+    else st.sweeps = std::max<int64_t>(st.sweeps, h[5]);   // (a solve's own statistics)
     vs.valid = true;
 }
 
@@ -639,6 +793,7 @@ static void add_stats(Stats& a, const Stats& b) {
     a.refine_pairs += b.refine_pairs;
     a.refine_columns += b.refine_columns;
     a.variant = b.variant ? b.variant : a.variant;
+    a.resident_models = b.variant ? b.resident_models : a.resident_models;
     a.variant_refine = b.variant_refine ? b.variant_refine : a.variant_refine;
 }
 
@@ -759,12 +914,21 @@ static void solve_impl(morap_ctx* c, const double* W, int K, const morap_vi_opts
     c->prec = prec;
     c->W.assign(W, W + (size_t)K * d);
 
+    const ResidentPlan::Part* part = resident_part(c, prec, o);
+    const bool batched = !part || part->n_rest > 0;   // some models take the batched sweeps
+    if (part) {
+        c->d_weights.ensure((size_t)K * d * 8);
+        c->h_weights.ensure((size_t)K * d * 8);
+        std::memcpy(c->h_weights.p, W, (size_t)K * d * 8);
+        MORAP_HIP(hipMemcpyAsync(c->d_weights.p, c->h_weights.p, (size_t)K * d * 8, hipMemcpyHostToDevice, c->stream));
+    }
     // per-(model, column) weights of the model's two objectives (a team
     // model: its rows are scalarised per column on the device instead, and
     // (1, 0) marks the column in use)
-    std::vector<double> wc((size_t)M * Kp, 0.0), wp((size_t)M * Kp, 0.0);
-    std::vector<float> wc32((size_t)M * Kp, 0.f), wp32((size_t)M * Kp, 0.f);
-    for (int m = 0; m < M; ++m) {
+    const size_t nw = batched ? (size_t)M * Kp : 0;
+    std::vector<double> wc(nw, 0.0), wp(nw, 0.0);
+    std::vector<float> wc32(nw, 0.f), wp32(nw, 0.f);
+    for (int m = 0; batched && m < M; ++m) {
         const int i = m / nJ, j = m % nJ;
         for (int k = 0; k < K; ++k) {
             wc[(size_t)m * Kp + k] = c->team ? 1.0 : W[(size_t)k * d + i];
@@ -773,10 +937,12 @@ static void solve_impl(morap_ctx* c, const double* W, int K, const morap_vi_opts
             wp32[(size_t)m * Kp + k] = (float)wp[(size_t)m * Kp + k];
         }
     }
-    MORAP_HIP(hipMemcpyAsync(c->d_wc64.p, wc.data(), wc.size() * 8, hipMemcpyHostToDevice, c->stream));
-    MORAP_HIP(hipMemcpyAsync(c->d_wp64.p, wp.data(), wp.size() * 8, hipMemcpyHostToDevice, c->stream));
-    MORAP_HIP(hipMemcpyAsync(c->d_wc32.p, wc32.data(), wc32.size() * 4, hipMemcpyHostToDevice, c->stream));
-    MORAP_HIP(hipMemcpyAsync(c->d_wp32.p, wp32.data(), wp32.size() * 4, hipMemcpyHostToDevice, c->stream));
+    if (batched) {
+        MORAP_HIP(hipMemcpyAsync(c->d_wc64.p, wc.data(), wc.size() * 8, hipMemcpyHostToDevice, c->stream));
+        MORAP_HIP(hipMemcpyAsync(c->d_wp64.p, wp.data(), wp.size() * 8, hipMemcpyHostToDevice, c->stream));
+        MORAP_HIP(hipMemcpyAsync(c->d_wc32.p, wc32.data(), wc32.size() * 4, hipMemcpyHostToDevice, c->stream));
+        MORAP_HIP(hipMemcpyAsync(c->d_wp32.p, wp32.data(), wp32.size() * 4, hipMemcpyHostToDevice, c->stream));
+    }
     if (c->team) {
         // every (row, column)'s reward w[obj[r][0]] rew[r][0] + w[obj[r][1]] rew[r][1]
         const int64_t R = c->hm.state_row.back();
@@ -800,12 +966,14 @@ static void solve_impl(morap_ctx* c, const double* W, int K, const morap_vi_opts
                         c->vmain.final_par.as<uint8_t>(), Kp_old, c->d_xwarm.as<float>());
     }
     ensure_values(c, c->vmain, K, Kp, prec);
-    MORAP_HIP(hipStreamSynchronize(c->stream));   // the host weight vectors go out of scope
+    if (batched || warm_ok) MORAP_HIP(hipStreamSynchronize(c->stream));   // the host vectors go out of scope
 
     run_vi(c, 0, c->vmain, nullptr, o, st, warm_ok);
-    if (c_out)
+    if (c_out && !batched)
+        std::memcpy(c_out, c->h_c.p, (size_t)K * M * 8);   // read with the end of the solve
+    else if (c_out)
         MORAP_HIP(hipMemcpyAsync(c_out, c->vmain.c.p, (size_t)K * M * 8, hipMemcpyDeviceToHost, c->stream));
-    MORAP_HIP(hipStreamSynchronize(c->stream));
+    if (batched) MORAP_HIP(hipStreamSynchronize(c->stream));
     st.ms_total += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     c->solved = true;
 }

@@ -646,6 +646,39 @@ void init_solve(hipStream_t s, const ConvergeArgs& a) {
     compact(s, a);
 }
 
+__global__ void init_pairs_kernel(ConvergeArgs a) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t n = (int64_t)a.M * a.Kp;
+    if (i < n) {
+        const int m = (int)(i / a.Kp);
+        const int k = (int)(i % a.Kp);
+        a.active[i] = 0;
+        a.final_par[i] = 0;
+        a.pair_sweeps[i] = 0;
+        a.best_res[i] = INFINITY;
+        a.stall[i] = 0;
+        if (k < a.K) a.c[(int64_t)k * a.M + m] = 0.0;
+    }
+    if (i < 9) a.counters[i] = 0;
+}
+
+void init_pairs(hipStream_t s, const ConvergeArgs& a) {
+    const int64_t n = std::max<int64_t>((int64_t)a.M * a.Kp, 9);
+    hipLaunchKernelGGL(init_pairs_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+    MORAP_HIP(hipGetLastError());
+}
+
+__global__ void model_mask_kernel(int64_t n, int Kp, const uint8_t* __restrict__ flag, uint8_t* __restrict__ mask) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) mask[i] = flag[i / Kp];
+}
+
+void model_mask(hipStream_t s, int M, int Kp, const uint8_t* flag, uint8_t* mask) {
+    const int64_t n = (int64_t)M * Kp;
+    hipLaunchKernelGGL(model_mask_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, Kp, flag, mask);
+    MORAP_HIP(hipGetLastError());
+}
+
 // ---------------------------------------------------------------------------
 // instances: (column, model) pairs, one thread per state
 // ---------------------------------------------------------------------------

@@ -208,12 +208,17 @@ struct ValueSet {
 };
 
 // The models whose batched value iteration keeps its values in LDS (see the
-// kernel), per precision: launches over `order` (models with states, those of
-// the kernel's faster form first, each part largest first), and the rest.
+// kernels), per precision: launches over `order` (models with states, those of
+// the kernels' faster form first, each part largest first), and the rest.
+// Products too large for the first kernel have their states sorted by block
+// and padded to steps of 64 (`rec`: per position the LDS rows of the slots, 16
+// bits each -- row 0 is the zero row, row 1 + p position p --, the accepting
+// slots, and the state in its product, bit 31 for padding).
 struct ResidentPlan {
     struct Launch {
         bool fast;
-        int begin, n, max_states;
+        int columns;            // > 0: larger products, that many columns per workgroup
+        int begin, n, max_states;   // (larger products: positions)
     };
     struct Part {
         std::vector<Launch> launches;
@@ -222,7 +227,7 @@ struct ResidentPlan {
         int n_rest = 0;
         DevBuf d_rest;                 // the same on the device
     };
-    DevBuf order;
+    DevBuf order, big_base, big_block, big_rec, big_init, grid_blk32, grid_blk64;
     Part part[2];                      // MORAP_F64, MORAP_F32
 };
 
@@ -576,6 +581,10 @@ void init_pairs(hipStream_t s, const ConvergeArgs& a);
 // mask[m][k] = flag[m]
 void model_mask(hipStream_t s, int M, int Kp, const uint8_t* flag, uint8_t* mask);
 
+// a block of the grid pattern: its 17 nonzero probabilities in (action, slot)
+// order, the 5 costs, padding
+constexpr int GRID_BLK = 24;
+
 // Value iteration with the values resident in LDS (resident.hip): the sweeps
 // sweep0 + 1 .. sweep1 (both even) of the listed models' pairs that have not
 // stopped (pair_sweeps 0), each pair to its stop.
@@ -600,6 +609,12 @@ struct ResidentArgs {
     int64_t* counters;          // [8]: pairs stopped at the rounding floor
     double eps, unit, floor;
     int stall_sweeps, warm, sweep0, sweep1, last;
+    const void* grid_blk;       // compact blocks (precision of the solve), see GRID_BLK
+    // larger products: states sorted by block, padded to steps of 64
+    const int32_t* big_base;    // [M+1] first position (a multiple of 64)
+    const int32_t* big_block;   // [positions / 64] block of the step
+    const uint4* big_rec;       // [positions] LDS rows of the slots (see the plan)
+    const int32_t* big_init;    // [M] position of the initial state in its product
 };
 // every block's nonzero entries lie within the grid pattern
 bool has_grid_pattern(uint32_t union_pattern);
@@ -609,6 +624,14 @@ int resident_capacity(int prec, bool fast);
 // register steps (states per thread) of a product of that many states; a
 // launch takes models of one class
 int resident_class(int states);
+// entry e = 5 action + slot of a block belongs to the grid pattern
+bool grid_entry(int e);
+// largest number of sorted and padded states that fits with one FP32 column
+int resident_most_positions();
+// columns per workgroup of a larger product of that many sorted and padded
+// states, 0 if it does not fit
+int resident_big_columns(int prec, int positions);
+void resident_large(hipStream_t s, int prec, int columns, int max_positions, ResidentArgs a);
 // wide: several columns per workgroup (4 in FP32, 2 in FP64), else one
 void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, ResidentArgs a);
 

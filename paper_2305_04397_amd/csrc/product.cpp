@@ -798,23 +798,137 @@ static void order_records(morap_ctx* c) {
     hm.blk_rec.swap(out);
 }
 
+// Positions of a product's states sorted by block, each block's padded to
+// steps of 64.
+struct SortedStates {
+    std::vector<int32_t> block;    // per step
+    std::vector<uint32_t> rec;     // [4 positions]
+    int32_t init = 0;
+};
+
+static SortedStates sort_states(const HostModels& hm, int m) {
+    SortedStates out;
+    const int32_t s0 = hm.state_base[m], n = hm.state_base[m + 1] - s0;
+    const int32_t zero = (int32_t)hm.S();
+    // records of the model by state, and the states of every block in order
+    std::vector<const int32_t*> rec((size_t)n);
+    for (int32_t p = 0; p < n; ++p) {
+        const int32_t* r = &hm.blk_rec[(size_t)(s0 + p) * 8];
+        rec[(size_t)(r[7] - s0)] = r;
+    }
+    std::vector<int32_t> ids;
+    for (int32_t l = 0; l < n; ++l) ids.push_back(rec[(size_t)l][5]);
+    std::sort(ids.begin(), ids.end());
+    ids.erase(std::unique(ids.begin(), ids.end()), ids.end());
+    std::vector<int32_t> first(ids.size() + 1, 0), which((size_t)n);
+    for (int32_t l = 0; l < n; ++l) {
+        which[(size_t)l] = (int32_t)(std::lower_bound(ids.begin(), ids.end(), rec[(size_t)l][5]) - ids.begin());
+        ++first[(size_t)which[(size_t)l] + 1];
+    }
+    for (size_t b = 0; b < ids.size(); ++b) {
+        const int32_t steps = (first[b + 1] + 63) / 64;
+        out.block.insert(out.block.end(), (size_t)steps, ids[b]);
+        first[b + 1] = first[b] + 64 * steps;
+    }
+    std::vector<int32_t> place((size_t)n), at((size_t)out.block.size() * 64, -1);
+    std::vector<int32_t> next(first.begin(), first.end() - 1);
+    for (int32_t l = 0; l < n; ++l) {
+        place[(size_t)l] = next[(size_t)which[(size_t)l]]++;
+        at[(size_t)place[(size_t)l]] = l;
+    }
+    out.rec.resize(at.size() * 4);
+    uint32_t last = 0;   // padding repeats the block's last state (a block has one)
+    for (size_t p = 0; p < at.size(); ++p) {
+        const bool pad = at[p] < 0;
+        if (!pad) last = (uint32_t)at[p];
+        const int32_t* r = rec[last];
+        auto row = [&](int d) { return r[d] == zero ? 0u : (uint32_t)place[(size_t)(r[d] - s0)] + 1u; };
+        out.rec[p * 4] = row(0) | row(1) << 16;
+        out.rec[p * 4 + 1] = row(2) | row(3) << 16;
+        out.rec[p * 4 + 2] = row(4) | ((uint32_t)r[6] & 31u) << 16;
+        out.rec[p * 4 + 3] = last | (pad ? 0x80000000u : 0u);
+    }
+    out.init = hm.init[m] >= 0 ? place[(size_t)(hm.init[m] - s0)] : 0;
+    return out;
+}
+
 // Which models' solves keep their values in LDS, per precision: products of
 // the block form that fit a workgroup, in launches of one class (states per
-// thread) each.
+// thread, or columns of the larger products) each.
 static void plan_resident(morap_ctx* c) {
     const HostModels& hm = c->hm;
     ResidentPlan& P = c->resident_plan;
+    hipStream_t s = c->stream;
     auto states = [&](int m) { return hm.state_base[m + 1] - hm.state_base[m]; };
     const bool grid = k::has_grid_pattern(hm.blk_pattern);
+    auto fast = [&](int m) { return grid && hm.blk_plain[(size_t)m] != 0; };
     std::vector<int32_t> order;
     if (c->has_blocks)
         for (int m = 0; m < hm.M; ++m)
             if (states(m) > 0) order.push_back(m);
-    auto fast = [&](int m) { return grid && hm.blk_plain[(size_t)m] != 0; };
+    // sorted states of the products some precision's first kernel cannot hold
+    std::vector<SortedStates> sorted((size_t)hm.M);
+    {
+        std::vector<int32_t> todo;
+        const int most = k::resident_most_positions();
+        for (int32_t m : order)
+            if (fast(m) && states(m) > k::resident_capacity(MORAP_F64, true) && states(m) <= most) todo.push_back(m);
+        std::atomic<size_t> next{0};
+        std::atomic<bool> bad{false};
+        auto worker = [&] {
+            try {
+                for (size_t t; (t = next++) < todo.size();) {
+                    SortedStates x = sort_states(hm, todo[t]);
+                    // (blocks of a few states each would be mostly padding)
+                    const size_t pos = x.block.size() * 64;
+                    if (pos <= (size_t)most && pos <= (size_t)states(todo[t]) * 3 / 2) sorted[(size_t)todo[t]] = std::move(x);
+                }
+            } catch (...) {
+                bad = true;
+            }
+        };
+        const int nt = (int)std::min<size_t>(std::max<size_t>(todo.size(), 1),
+                                             std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
+        std::vector<std::thread> th;
+        for (int k = 1; k < nt; ++k) th.emplace_back(worker);
+        worker();
+        for (auto& k : th) k.join();
+        MORAP_CHECK(!bad, MORAP_E_OOM, "sorting the states failed (host memory)");
+    }
+    std::vector<int32_t> base((size_t)hm.M + 1, 0), block, init((size_t)hm.M, 0);
+    std::vector<uint32_t> rec;
+    for (int m = 0; m < hm.M; ++m) {
+        const SortedStates& x = sorted[(size_t)m];
+        block.insert(block.end(), x.block.begin(), x.block.end());
+        rec.insert(rec.end(), x.rec.begin(), x.rec.end());
+        init[(size_t)m] = x.init;
+        base[(size_t)m + 1] = base[(size_t)m] + 64 * (int32_t)x.block.size();
+    }
+    // compact blocks: what a step loads in one go
+    std::vector<double> gblk;
+    if (grid)
+        for (size_t b = 0; b < hm.blk_agent.size() / 32; ++b) {
+            const double* B = &hm.blk_agent[b * 32];
+            const size_t at = gblk.size();
+            for (int e = 0; e < 25; ++e)
+                if (k::grid_entry(e)) gblk.push_back(B[e]);
+            gblk.insert(gblk.end(), B + 25, B + 30);
+            gblk.resize(at + k::GRID_BLK, 0.0);
+        }
+    upload(P.grid_blk64, gblk, s);
+    P.grid_blk32.ensure(gblk.size() * 4 + 16);
+    k::to_f32(s, P.grid_blk64.as<double>(), P.grid_blk32.as<float>(), (int64_t)gblk.size());
+    upload(P.big_base, base, s);
+    upload(P.big_block, block, s);
+    upload(P.big_rec, rec, s);
+    upload(P.big_init, init, s);
+
+    auto positions = [&](int m) { return base[(size_t)m + 1] - base[(size_t)m]; };
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-        return fast(a) != fast(b) ? fast(a) : states(a) > states(b);
+        if (fast(a) != fast(b)) return fast(a);
+        return std::max(positions(a), states(a)) > std::max(positions(b), states(b));
     });
-    upload(P.order, order, c->stream);
+    upload(P.order, order, s);
     for (int prec : {MORAP_F64, MORAP_F32}) {
         ResidentPlan::Part& part = P.part[prec];
         part.launches.clear();
@@ -823,25 +937,29 @@ static void plan_resident(morap_ctx* c) {
         part.n_rest = 0;
         for (int b = 0; b < (int)order.size(); ++b) {
             const int m = order[b];
-            if (states(m) > k::resident_capacity(prec, fast(m))) {
+            const bool first = states(m) <= k::resident_capacity(prec, fast(m));
+            const int columns = first || positions(m) == 0 ? 0 : k::resident_big_columns(prec, positions(m));
+            if (!first && columns == 0) {
                 part.rest[(size_t)m] = 1;
                 ++part.n_rest;
                 continue;
             }
             part.models.push_back(m);
+            const int size = first ? states(m) : positions(m);
             if (!part.launches.empty()) {
                 ResidentPlan::Launch& l = part.launches.back();
-                if (l.fast == fast(m) && l.begin + l.n == b &&
-                    k::resident_class(l.max_states) == k::resident_class(states(m))) {
+                if (l.fast == fast(m) && l.begin + l.n == b && l.columns == columns &&
+                    (columns > 0 || k::resident_class(l.max_states) == k::resident_class(size))) {
                     ++l.n;
+                    l.max_states = std::max(l.max_states, size);
                     continue;
                 }
             }
-            part.launches.push_back({fast(m), b, 1, states(m)});
+            part.launches.push_back({fast(m), columns, b, 1, size});
         }
-        upload(part.d_rest, part.rest, c->stream);
+        upload(part.d_rest, part.rest, s);
     }
-    MORAP_HIP(hipStreamSynchronize(c->stream));   // order goes out of scope
+    MORAP_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
 }
 
 void upload_models(morap_ctx* c) {

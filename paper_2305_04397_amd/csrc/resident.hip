@@ -28,6 +28,9 @@ namespace {
 
 constexpr int MAXW = 8;                       // waves of a workgroup
 constexpr int RES_MAX_THREADS = 64 * MAXW;
+constexpr int BIG_THREADS = 1024;             // of the kernel for larger products
+constexpr int GRID_NNZ = 17;                  // nonzero entries of the grid pattern
+constexpr size_t LDS_BYTES = 160 * 1024;      // of a compute unit
 
 // rows of one LDS buffer with ns states per thread (row 0 is the zero row):
 // the second buffer lies at this fixed distance, which the 16-bit offset of
@@ -152,6 +155,26 @@ template <class T, int KC>
 struct Row {
     T v[KC];
 };
+
+// The stop test of one column: its largest change within max(eps, a few units
+// in the last place of its largest value), or FP32's rounding floor: no new
+// smallest change for stall_sweeps sweeps and within floor |y|.
+template <bool F32>
+__device__ __forceinline__ bool stop_test(const ResidentArgs& a, double res, double ym, double& best, int& stall,
+                                          bool& floor_stop) {
+    const double tol = fmax(a.eps, a.unit * ym);
+    if (F32 && res > tol) {
+        if (res < best) {
+            best = res;
+            stall = 0;
+        } else {
+            const int st = stall + 1;
+            stall = st;
+            floor_stop = st >= a.stall_sweeps && res <= a.floor * ym;
+        }
+    }
+    return res <= tol || floor_stop;
+}
 
 // waves per SIMD the registers are held to, so that the probabilities of NS
 // states fit with room for a step: 128 registers, 168 or 256
@@ -401,21 +424,8 @@ resident_vi(ResidentArgs a) {
         // lane c < KC tests column c
         bool now = false;
         if (ln < KC && (judged >> ln & 1)) {
-            const double res = (double)rr, ym = (double)yy;
-            const double tol = fmax(a.eps, a.unit * ym);
             bool floor_stop = false;
-            if (want_y && res > tol) {
-                // the rounding floor: no new smallest change for stall_sweeps sweeps
-                if (res < best[ln]) {
-                    best[ln] = res;
-                    stall[ln] = 0;
-                } else {
-                    const int st = stall[ln] + 1;
-                    stall[ln] = st;
-                    floor_stop = st >= a.stall_sweeps && res <= a.floor * ym;
-                }
-            }
-            now = res <= tol || floor_stop;
+            now = stop_test<want_y>(a, (double)rr, (double)yy, best[ln], stall[ln], floor_stop);
             if (now) {
                 const int64_t i = (int64_t)m * a.Kp + k0 + ln;
                 if (floor_stop) atomicAdd((unsigned long long*)&a.counters[8], 1ull);
@@ -483,6 +493,262 @@ resident_vi(ResidentArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// larger products
+// ---------------------------------------------------------------------------
+// A product too large for two iterates in LDS and its probabilities in
+// registers: one iterate in LDS (up to 160 KB), the new values of a sweep in
+// registers until every wave has read the old ones.  Its states are sorted
+// by block and padded to steps of 64 states of one block, so that a step's
+// probabilities are scalar loads shared by the wave; the LDS rows of a
+// state's slots are read from the sorted records every sweep (12 of 16 bytes
+// a state, from L2: the columns of a product go to one XCD).  Sorting costs
+// up to a step of padding per block and scatters the neighbours' rows over the
+// banks; reading the 17 probabilities per lane instead would cost 1.5 (FP32)
+// or 3 (FP64) times the LDS traffic of the values themselves.
+//
+// 24 agents on 32 x 32 .. 128 x 128 grids x 32 tasks, 64 columns, FP32: 0.80
+// (4 columns), 0.53 (2) and 0.28 (1) 10^12 state-columns a second against 0.34
+// of the batched sweeps on all products of that problem; 37 FP64 columns of 49
+// products of up to 2,429 states: 2.3 ms, 10 ms before.
+template <class T, int KC, int NS>
+__global__ void __launch_bounds__(BIG_THREADS)
+resident_big(ResidentArgs a) {
+    constexpr int ROWB = sizeof(T) * KC;
+    constexpr int SH = ROWB == 4 ? 2 : (ROWB == 8 ? 3 : 4);
+    constexpr bool want_y = sizeof(T) == 4;
+    constexpr int NW = BIG_THREADS / 64;
+    extern __shared__ __align__(16) unsigned char lds[];
+
+    const int slot = blockIdx.x >> 3;
+    const int mi = slot / a.groups * 8 + (int)(blockIdx.x & 7);
+    if (mi >= a.n_models) return;
+    const int m = a.order[mi];
+    const int k0 = slot % a.groups * KC;
+    const int64_t pair0 = (int64_t)m * a.Kp + k0;
+    unsigned live = 0;   // columns still running
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+        if (k0 + c < a.K && a.pair_sweeps[pair0 + c] == 0) live |= 1u << c;
+    if (!live) return;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sb = a.state_base[m];
+    const int pos0 = a.big_base[m], n_steps = (a.big_base[m + 1] - pos0) >> 6;
+    // this wave's steps: a contiguous run, so consecutive ones mostly share
+    // their block
+    const int s_begin = wave * n_steps / NW, cnt = (wave + 1) * n_steps / NW - s_begin;
+    using CInt = const __attribute__((address_space(4))) int32_t*;
+    using CVal = const __attribute__((address_space(4))) T*;
+    const CInt blk = (CInt)(a.big_block + (pos0 >> 6) + s_begin);
+    const CVal ablk = (CVal)(static_cast<const T*>(a.grid_blk));
+    const uint4* rec = a.big_rec + pos0 + s_begin * 64 + lane;
+    unsigned char* hdr = lds + (((n_steps * 64 + 1) * ROWB + 15) & ~15);
+    T* part = reinterpret_cast<T*>(hdr);                                     // [4 NW rows][4][res, |y|]
+    double* best = reinterpret_cast<double*>(hdr + 4 * NW * 8 * sizeof(T));  // [4] smallest change so far
+    int* stall = reinterpret_cast<int*>(best + 4);                           // [4] sweeps since it was set
+    unsigned* flag = reinterpret_cast<unsigned*>(stall + 4);
+    using V = T __attribute__((ext_vector_type(KC)));
+    auto get = [&](unsigned addr) -> Row<T, KC> {
+        const V v = *(__attribute__((address_space(3))) const V*)addr;
+        Row<T, KC> r;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) r.v[c] = v[c];
+        return r;
+    };
+    auto put = [&](unsigned addr, const Row<T, KC>& r) {
+        V v;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) v[c] = r.v[c];
+        *(__attribute__((address_space(3))) V*)addr = v;
+    };
+
+    T wp[KC], first[KC][5];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+        const int k = k0 + c < a.K ? k0 + c : 0;
+        const double* W = a.W + (int64_t)k * a.d;
+        const T wc = (T)W[m / a.nJ];
+        wp[c] = scalar((T)W[a.nI + m % a.nJ]);
+        // every state of the product has the same action costs
+#pragma unroll
+        for (int q = 0; q < 5; ++q) first[c][q] = wc * ablk[(int64_t)blk[-s_begin] * GRID_BLK + GRID_NNZ + q];
+    }
+    T* x0 = static_cast<T*>(a.x0);
+    T* x1 = static_cast<T*>(a.x1);
+    const bool load = a.warm || a.sweep0 > 0;
+    const unsigned own0 = (unsigned)(s_begin * 64 + lane + 1) << SH;   // LDS row of the first step's state
+    for (int i = 0; i < cnt; ++i) {
+        const unsigned w = rec[i * 64].w & 0x7fffffffu;
+        Row<T, KC> v;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) v.v[c] = load ? x0[(int64_t)(sb + (int)w) * a.Kp + k0 + c] : (T)0;
+        put(own0 + ((unsigned)i << (6 + SH)), v);
+    }
+    if (tid == 0) {
+        Row<T, KC> z;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) z.v[c] = 0;
+        put(0, z);
+    }
+    if (want_y && tid < KC) {
+        best[tid] = a.best_res[pair0 + tid];
+        stall[tid] = a.stall[pair0 + tid];
+    }
+    __syncthreads();
+
+    // the values of the columns in `cols`, each thread its own states
+    auto store = [&](T* x, unsigned cols) {
+        unsigned own = own0;
+        asm volatile("" : "+v"(own));   // (no addresses kept over the sweeps)
+        for (int i = 0; i < cnt; ++i) {
+            const unsigned w = rec[i * 64].w;
+            const Row<T, KC> v = get(own + ((unsigned)i << (6 + SH)));
+            if (w >> 31) continue;   // padding
+#pragma unroll
+            for (int c = 0; c < KC; ++c)
+                if (cols >> c & 1) x[(int64_t)(sb + (int)w) * a.Kp + k0 + c] = v.v[c];
+        }
+    };
+
+    Row<T, KC> out[NS];
+    for (int n = a.sweep0 + 1; n <= a.sweep1; ++n) {
+        T r[KC], y[KC];
+#pragma unroll
+        for (int c = 0; c < KC; ++c) r[c] = y[c] = 0;
+        uint3 q = *reinterpret_cast<const uint3*>(rec);
+        int b = blk[0];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            if (i < cnt) {
+            uint3 qn = q;
+            int bn = b;
+            if (i + 1 < cnt) {   // the next step's records and block are on their way
+                qn = *reinterpret_cast<const uint3*>(rec + (i + 1) * 64);
+                bn = blk[i + 1];
+            }
+            const CVal B = ablk + (int64_t)b * GRID_BLK;
+            T P[GRID_NNZ];
+#pragma unroll
+            for (int e = 0; e < GRID_NNZ; ++e) P[e] = B[e];
+            Row<T, KC> xv[NSLOT];
+            xv[0] = get(low_row<SH>(q.x));
+            xv[1] = get(high_row<SH>(q.x));
+            xv[2] = get(low_row<SH>(q.y));
+            xv[3] = get(high_row<SH>(q.y));
+            xv[4] = get(low_row<SH>(q.z));
+            const unsigned accm = q.z >> 16;
+            auto backup = [&](auto ACC) {
+                T rp[5];
+                if constexpr (decltype(ACC)::value) {
+                    // probability reward: the action's mass on accepting slots
+                    int e = 0;
+#pragma unroll
+                    for (int act = 0; act < 5; ++act) {
+                        bool first_term = true;
+#pragma unroll
+                        for (int d = 0; d < NSLOT; ++d)
+                            if (nz<PAT_GRID>(act, d)) {
+                                const T p = (accm >> d & 1) ? P[e] : (T)0;
+                                rp[act] = first_term ? p : rp[act] + p;
+                                first_term = false;
+                                ++e;
+                            }
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < KC; ++c) {
+                    T v[5];
+                    int e = 0;
+#pragma unroll
+                    for (int act = 0; act < 5; ++act) {
+                        v[act] = first[c][act];
+                        if constexpr (decltype(ACC)::value) v[act] = fma(wp[c], rp[act], v[act]);
+#pragma unroll
+                        for (int d = 0; d < NSLOT; ++d)
+                            if (nz<PAT_GRID>(act, d)) v[act] = fma(P[e++], xv[d].v[c], v[act]);
+                    }
+                    out[i].v[c] = max3(max3(v[0], v[1], v[2]), v[3], v[4]);
+                    r[c] = max_abs(r[c], out[i].v[c] - xv[0].v[c]);   // slot 0 is the state itself
+                    if (want_y) y[c] = max_abs(y[c], out[i].v[c]);
+                }
+            };
+            if (__ballot(accm != 0)) backup(std::true_type{});
+            else backup(std::false_type{});
+            q = qn;
+            b = bn;
+            }
+        }
+        const T rr = row_max<T, KC>(r);
+        const T yy = want_y ? row_max<T, KC>(y) : (T)0;
+        if ((lane & 15) < 4) {
+            T* p = part + ((wave * 4 + (lane >> 4)) * 4 + (lane & 3)) * 2;
+            p[0] = rr;
+            p[1] = yy;
+        }
+        // the iterate before the last, of a solve over its limit
+        if (a.last && n == a.sweep1) store(x1, live);
+        __syncthreads();   // every wave has read the old values
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            if (i < cnt) put(own0 + ((unsigned)i << (6 + SH)), out[i]);
+        if (wave == NW - 1) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            T res_t = 0, y_t = 0;
+            for (int z = ln >> 2; z < 4 * NW; z += 16) {
+                const T* p = part + (z * 4 + (ln & 3)) * 2;
+                res_t = mx(res_t, p[0]);
+                y_t = mx(y_t, p[1]);
+            }
+            res_t = mx(res_t, dpp<DPP_ROR4>(res_t));
+            res_t = mx(res_t, dpp<DPP_ROR8>(res_t));
+            res_t = mx(res_t, __shfl_xor(res_t, 16, 64));
+            res_t = mx(res_t, __shfl_xor(res_t, 32, 64));
+            if (want_y) {
+                y_t = mx(y_t, dpp<DPP_ROR4>(y_t));
+                y_t = mx(y_t, dpp<DPP_ROR8>(y_t));
+                y_t = mx(y_t, __shfl_xor(y_t, 16, 64));
+                y_t = mx(y_t, __shfl_xor(y_t, 32, 64));
+            }
+            bool now = false;
+            if (ln < KC && (live >> ln & 1)) {
+                bool floor_stop = false;
+                now = stop_test<want_y>(a, (double)res_t, (double)y_t, best[ln], stall[ln], floor_stop);
+                if (now) {
+                    const int64_t i = (int64_t)m * a.Kp + k0 + ln;
+                    if (floor_stop) atomicAdd((unsigned long long*)&a.counters[8], 1ull);
+                    a.final_par[i] = 0;
+                    a.pair_sweeps[i] = n;
+                }
+            }
+            const unsigned fresh = (unsigned)__ballot(now);
+            if (ln == 0) *flag = fresh;
+        }
+        __syncthreads();
+        const unsigned f = *flag;
+        if (f) {
+            store(x0, f);
+            if (tid < KC && (f >> tid & 1))
+                a.c[(int64_t)(k0 + tid) * a.M + m] =
+                    (double)reinterpret_cast<const T*>(lds + ((unsigned)(a.big_init[m] + 1) << SH))[tid];
+            live &= ~f;
+            if (!live) return;
+        }
+    }
+    // the launch ends with columns running: their iterate
+    store(x0, live);
+    if (tid < KC && (live >> tid & 1)) {
+        const int64_t i = pair0 + tid;
+        if (want_y) {
+            a.best_res[i] = best[tid];
+            a.stall[i] = stall[tid];
+        }
+        if (a.last) a.active[i] = 1;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // dispatch
 // ---------------------------------------------------------------------------
 // States a workgroup can hold: 512 per register step.  The grid pattern with
@@ -507,11 +773,11 @@ void launch_res(hipStream_t s, const ResidentArgs& a, int max_states) {
     const int threads = 64 * ((max_states + 64 * NS - 1) / (64 * NS));
     const size_t bytes = (size_t)res_rows(NS) * ROWB + (((size_t)(threads * NS + 1) * ROWB + 15) & ~(size_t)15) +
                          2 * 4 * MAXW * 8 * sizeof(T) + 64;
-    MORAP_CHECK(threads <= RES_MAX_THREADS && max_states < res_rows(NS) && bytes <= 160 * 1024, MORAP_E_UNSUPPORTED,
+    MORAP_CHECK(threads <= RES_MAX_THREADS && max_states < res_rows(NS) && bytes <= LDS_BYTES, MORAP_E_UNSUPPORTED,
                 "a product does not fit the LDS-resident iteration");
     // dynamic LDS beyond 64 KB has to be asked for, once per kernel
     static const hipError_t granted =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
     MORAP_HIP(granted);
     const unsigned blocks = 8u * (unsigned)((a.n_models + 7) / 8) * (unsigned)a.groups;
     hipLaunchKernelGGL(fn, dim3(blocks), dim3((unsigned)threads), bytes, s, a);
@@ -554,6 +820,59 @@ void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, Res
         else if (fast) launch_steps<double, 1, true, 4>(s, a, ns, max_states);
         else if (wide) launch_steps<double, 2, false, 2>(s, a, ns, max_states);
         else launch_steps<double, 1, false, 2>(s, a, ns, max_states);
+    }
+}
+
+bool grid_entry(int e) { return (PAT_GRID >> e) & 1u; }
+
+int resident_most_positions() {
+    int p = BIG_THREADS * 40;
+    while (resident_big_columns(MORAP_F32, p) == 0) p -= 64;
+    return p;
+}
+
+// Columns a workgroup takes of a larger product of `positions` sorted and
+// padded states (0: it does not fit): as many as LDS holds one iterate of,
+// at most 4 (FP32) or 2 (FP64), 40 words of new values per thread.
+int resident_big_columns(int prec, int positions) {
+    const int el = prec == MORAP_F32 ? 4 : 8;
+    for (int kc = 16 / el; kc >= 1; kc /= 2) {
+        const size_t bytes = (((size_t)positions + 1) * kc * el + 15) / 16 * 16 + 4 * (BIG_THREADS / 64) * 8 * el + 64;
+        if (bytes <= LDS_BYTES && positions <= BIG_THREADS * 160 / (el * kc)) return kc;
+    }
+    return 0;
+}
+
+namespace {
+
+template <class T, int KC>
+void launch_big(hipStream_t s, const ResidentArgs& a, int max_positions) {
+    constexpr int NS = 160 / (sizeof(T) * KC);
+    auto* fn = &resident_big<T, KC, NS>;
+    const size_t bytes = (((size_t)max_positions + 1) * sizeof(T) * KC + 15) / 16 * 16 +
+                         4 * (BIG_THREADS / 64) * 8 * sizeof(T) + 64;
+    MORAP_CHECK(max_positions % 64 == 0 && bytes <= LDS_BYTES && max_positions <= BIG_THREADS * NS,
+                MORAP_E_UNSUPPORTED, "a product does not fit the LDS-resident iteration");
+    static const hipError_t granted =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
+    MORAP_HIP(granted);
+    const unsigned blocks = 8u * (unsigned)((a.n_models + 7) / 8) * (unsigned)a.groups;
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(BIG_THREADS), bytes, s, a);
+    MORAP_HIP(hipGetLastError());
+}
+
+}  // namespace
+
+void resident_large(hipStream_t s, int prec, int columns, int max_positions, ResidentArgs a) {
+    if (a.n_models <= 0) return;
+    a.groups = (a.K + columns - 1) / columns;
+    if (prec == MORAP_F32) {
+        if (columns == 4) launch_big<float, 4>(s, a, max_positions);
+        else if (columns == 2) launch_big<float, 2>(s, a, max_positions);
+        else launch_big<float, 1>(s, a, max_positions);
+    } else {
+        if (columns == 2) launch_big<double, 2>(s, a, max_positions);
+        else launch_big<double, 1>(s, a, max_positions);
     }
 }
 

@@ -548,6 +548,12 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
     a.rec = c->d_blk_rec.as<int32_t>();
     a.ablk = f32 ? c->d_blk32.p : c->d_blk64.p;
     a.zero_row = (int32_t)c->S;
+    const ResidentPlan& plan = c->resident_plan;
+    a.grid_blk = f32 ? plan.grid_blk32.p : plan.grid_blk64.p;
+    a.big_base = plan.big_base.as<int32_t>();
+    a.big_block = plan.big_block.as<int32_t>();
+    a.big_rec = plan.big_rec.as<uint4>();
+    a.big_init = plan.big_init.as<int32_t>();
     a.W = c->d_weights.as<double>();
     a.nI = hm.nI;
     a.nJ = hm.nJ;
@@ -582,14 +588,15 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
         a.sweep1 = (int)done;
         a.last = done == limit ? 1 : 0;
         for (const auto& l : part.launches) {
-            a.order = c->resident_plan.order.as<int32_t>() + l.begin;
+            a.order = plan.order.as<int32_t>() + l.begin;
             a.n_models = l.n;
             if (o.time_kernels) {
                 held.v.emplace_back(take_event(c), nullptr);
                 held.v.back().second = take_event(c);
                 MORAP_HIP(hipEventRecord(held.v.back().first, c->stream));
             }
-            k::resident(c->stream, vs.prec, l.fast, wide, l.max_states, a);
+            if (l.columns > 0) k::resident_large(c->stream, vs.prec, wide ? l.columns : 1, l.max_states, a);
+            else k::resident(c->stream, vs.prec, l.fast, wide, l.max_states, a);
             if (o.time_kernels) MORAP_HIP(hipEventRecord(held.v.back().second, c->stream));
         }
         read_results(c, vs);
@@ -623,13 +630,24 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
     st.max_pair_sweeps = std::max(st.max_pair_sweeps, longest);
     st.sweeps = std::max<int64_t>(st.sweeps, (longest + chunk - 1) / chunk * chunk);
     st.resident_models = (int)part.models.size();
-    if (part.n_rest == 0) {
-        st.variant = kResidentVariant;
-        for (auto& e : held.v) {
-            float t = 0;
-            MORAP_HIP(hipEventElapsedTime(&t, e.first, e.second));
+    if (part.n_rest == 0) st.variant = kResidentVariant;
+    for (size_t q = 0; q < held.v.size(); ++q) {
+        float t = 0;
+        MORAP_HIP(hipEventElapsedTime(&t, held.v[q].first, held.v[q].second));
+        if (part.n_rest == 0) {
             st.ms_sweep_kernel += t;
             st.sweep_launches += 1;
+        }
+        if (sweep_log()) {
+            const auto& l = part.launches[q % part.launches.size()];
+            double work = 0;   // state-columns of the launch's models
+            for (int b = l.begin; b < l.begin + l.n; ++b) {
+                const int32_t m = part.models[(size_t)b - (size_t)part.launches[0].begin];
+                for (int k = 0; k < vs.K; ++k)
+                    work += (double)ps[(size_t)m * vs.Kp + k] * (hm.state_base[m + 1] - hm.state_base[m]);
+            }
+            std::fprintf(sweep_log(), "resident prec=%d fast=%d columns=%d models=%d states=%d ms=%.4f state_columns=%.4g\n",
+                         vs.prec, l.fast, l.columns, l.n, l.max_states, t, work);
         }
     }
 }

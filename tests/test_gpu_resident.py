@@ -92,12 +92,21 @@ def test_register_steps_f64(ctx, morap, sizes, K):
     _compare(ctx, morap, wl, K, "f64", 1e-9, _block(morap, K), seed=K)
 
 
-@pytest.mark.parametrize("prec,largest", [("f32", 3584), ("f64", 2048)])
-def test_larger_products_take_the_batched_sweeps(ctx, morap, prec, largest):
-    """Products beyond a workgroup beside products within it."""
-    wl = _corridor((100, largest, largest + 1, 5000), width=80)
+@pytest.mark.parametrize("prec,K", [("f32", 64), ("f32", 1), ("f64", 5)])
+def test_larger_products(ctx, morap, prec, K):
+    """Products beyond the first kernel: states sorted by block, one iterate
+    in LDS, four, two or one columns per workgroup."""
+    wl = _corridor((100, 2049, 3585, 4161, 9700, 11000, 19000), width=80)
     ctx.build_products(wl)
-    st = _compare(ctx, morap, wl, 64, prec, 1e-6, 37, resident=2)
+    _compare(ctx, morap, wl, K, prec, 1e-6, _block(morap, K), seed=K)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_largest_products_take_the_batched_sweeps(ctx, morap, prec):
+    """Products beyond a workgroup's LDS beside products within it."""
+    wl = _corridor((100, 3000, 21000, 39000, 45000), width=200)
+    ctx.build_products(wl)
+    st = _compare(ctx, morap, wl, 64, prec, 1e-6, 37, resident=4 if prec == "f32" else 2)
     assert 18 < st["variant"] <= 40
 
 
@@ -106,8 +115,7 @@ def test_many_products(ctx, morap, prec):
     """More column groups than workgroups fit at once (several columns each)."""
     wl = make_workload(2, n_agents=5, n_tasks=12)
     ctx.build_products(wl)
-    big = sum(ctx.model_info(m)["n_states"] > (3584 if prec == "f32" else 2048) for m in range(60))
-    _compare(ctx, morap, wl, 70, prec, 1e-6, 37, resident=60 - big)
+    _compare(ctx, morap, wl, 70, prec, 1e-6, 37)
 
 
 @pytest.mark.parametrize("prec", ["f32", "f64"])

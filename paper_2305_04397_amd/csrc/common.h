@@ -139,6 +139,9 @@ struct HostModels {
     // [M] 1: every action has one cost in all states of the model and slot 0
     // of every state is the state itself
     std::vector<uint8_t> blk_plain;
+    // [M] 1: the model's agent lists a successor with probability 0 (the
+    // blocks do not tell it from an unused slot; attractor ranks do)
+    std::vector<uint8_t> blk_zero_prob;
     int64_t S() const { return (int64_t)state_row.size() - 1; }
     int64_t R() const { return (int64_t)row_ptr.size() - 1; }
     int64_t N() const { return (int64_t)col.size(); }
@@ -227,6 +230,9 @@ struct ResidentPlan {
         int n_rest = 0;
         DevBuf d_rest;                 // the same on the device
     };
+    std::vector<int32_t> rank;         // [M] place of the model in `order`
+    int n_order = 0;
+    std::vector<uint8_t> inst_ok;      // [M] 1: an instance's values, policy and evaluation all fit LDS
     DevBuf order, big_base, big_block, big_rec, big_init, grid_blk32, grid_blk64;
     Part part[2];                      // MORAP_F64, MORAP_F32
 };
@@ -329,7 +335,8 @@ struct morap_ctx {
     std::vector<int32_t> assign;                    // [K][nJ]
     std::vector<int32_t> inst_k, inst_m;            // instances (column, model)
     std::vector<int64_t> inst_base;                 // [n_inst+1] state offsets
-    morap::DevBuf d_inst_model, d_inst_k, d_inst_base, d_inst_tiles;
+    morap::DevBuf d_inst_pack, d_inst_out;          // the instances' host arrays; what their LDS iterations report
+    morap::PinnedBuf h_inst_pack, h_inst_out;
     morap::DevBuf d_xi;                             // final FP64 values [inst states]
     morap::DevBuf d_ires, d_iactive, d_ipar;        // per (instance, objective)
     morap::DevBuf d_mask, d_rank, d_mu;             // per instance state
@@ -337,8 +344,6 @@ struct morap_ctx {
     // the last evaluation's final values and instance layout (a warm start
     // of the next one)
     morap::DevBuf d_xe_prev, d_warm_copy;
-    morap::DevBuf d_iwarm;                          // per instance: warm-started (evaluation start)
-    morap::DevBuf d_ieps;                           // per instance: stop of the FP64 policy values
     std::vector<int64_t> prev_inst_base;
     std::vector<int32_t> prev_inst_m;
     int prev_per_col = 0;
@@ -349,12 +354,10 @@ struct morap_ctx {
     // the re-solve of other pairs for the assignment check
     std::vector<double> last_c64;
     bool last_c64_valid = false;
-    morap::DevBuf d_cand_model, d_cand_k, d_cand_base, d_cand_tiles, d_cand_iwc, d_cand_iwp, d_cand_iscale;
-    morap::DevBuf d_cand_x0, d_cand_x1, d_cand_res, d_cand_act, d_cand_par, d_cand_init, d_cand_val;
-    morap::DevBuf d_iwc, d_iwp;                     // per instance FP64 weights
-    morap::DevBuf d_iscale;                         // per instance 1 / (w_i + w_j) (warm start)
+    morap::DevBuf d_cand_pack, d_cand_x0, d_cand_x1, d_cand_res, d_cand_act, d_cand_par, d_cand_sweeps, d_cand_val;
+    morap::PinnedBuf h_cand_pack;
     morap::DevBuf d_ichanged;                       // per instance: ranks changed in the last round
-    morap::DevBuf d_init_idx, d_init_val;           // instance initial states, their values
+    morap::DevBuf d_init_val;                       // values at the instances' initial states
     morap::DevBuf d_xr;                             // second buffer of the instance value iteration
     std::vector<int32_t> h_live_tiles;              // instance tiles still active
     morap::DevBuf d_live_tiles;
@@ -615,6 +618,16 @@ struct ResidentArgs {
     const int32_t* big_block;   // [positions / 64] block of the step
     const uint4* big_rec;       // [positions] LDS rows of the slots (see the plan)
     const int32_t* big_init;    // [M] position of the initial state in its product
+    // instances (FP64, one column each: see the instance kernels): `order`
+    // lists instances, pair_sweeps is per instance, x0 their values
+    const int32_t* inst_model;
+    const int32_t* inst_k;
+    const int64_t* inst_base;
+    const double *iwc, *iwp, *ieps;   // weights and stop of every instance
+    const double* iscale;             // scale of the start from `start` (with iwc > 0, else from 0)
+    const float *start0, *start1;     // an FP32 solve's values (nullable: from 0)
+    const uint8_t* start_par;
+    int start_Kp;
 };
 // every block's nonzero entries lie within the grid pattern
 bool has_grid_pattern(uint32_t union_pattern);
@@ -628,12 +641,47 @@ int resident_class(int states);
 bool grid_entry(int e);
 // largest number of sorted and padded states that fits with one FP32 column
 int resident_most_positions();
+// the same for instances of products of one class, and of larger products
+void resident_inst(hipStream_t s, bool fast, int max_states, ResidentArgs a);
+void resident_inst_large(hipStream_t s, int max_positions, ResidentArgs a);
 // columns per workgroup of a larger product of that many sorted and padded
 // states, 0 if it does not fit
 int resident_big_columns(int prec, int positions);
 void resident_large(hipStream_t s, int prec, int columns, int max_positions, ResidentArgs a);
 // wide: several columns per workgroup (4 in FP32, 2 in FP64), else one
 void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, ResidentArgs a);
+
+// Policies and evaluations of instances in LDS (instance.hip), one workgroup
+// per listed instance
+struct InstanceArgs {
+    const int32_t* order;       // [n] instances of this launch
+    int n;
+    const int32_t* inst_model;
+    const int64_t* inst_base;
+    const int32_t* state_base;
+    const int32_t* rec;         // neighbourhood-block records
+    const double* ablk;         // agent blocks
+    int32_t zero_row;
+    const double *iwc, *iwp;    // the instance's weights
+    const double* xi;           // final values of the instances
+    int8_t* mu;                 // policies
+    double tau;
+    int widenings;              // of the tie tolerance
+    int64_t* counters;          // [0] states without a rank, [1] relaxation rounds (largest)
+    // evaluation
+    double* xe;                 // [instance state][2] values
+    const double* xe_prev;      // the last evaluation's values
+    const int64_t* prev_src;    // first state of an instance's start there (-1: none; nullable)
+    int from_values;            // start from xi
+    int32_t* sweeps;            // [2 instances] sweep of the stop, 0: running
+    double eps;
+    int sweep0, sweep1;
+};
+int policy_capacity();          // states
+void inst_policy(hipStream_t s, int max_states, const InstanceArgs& a);
+int eval_capacity();            // states
+int eval_class(int states);     // a launch takes instances of one class
+void inst_eval(hipStream_t s, int max_states, const InstanceArgs& a);
 
 // stage retirement (staged.hip)
 struct StageArgs {
@@ -690,6 +738,7 @@ struct InstArgs {
     int rewk_ld;
     const int32_t* row_obj;
     const int32_t* inst_obj;
+    const uint8_t* resident;       // [n_inst] instances whose iterations run in LDS (nullable)
 };
 // team models: one Jacobi sweep of the per-objective evaluation of the fixed
 // policy pi (E[s][o], res = max change as FP64 bits), and the start values

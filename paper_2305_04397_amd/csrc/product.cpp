@@ -570,6 +570,13 @@ static void build_blocks(morap_ctx* c, const morap_agent* agents, int nI, const 
     const int32_t S = (int32_t)hm.S();
     std::vector<int32_t> recs((size_t)S * 8, 0);
     hm.blk_plain.assign((size_t)M, 0);
+    hm.blk_zero_prob.assign((size_t)M, 0);
+    for (int i = 0; i < nI; ++i) {
+        const morap_agent& a = agents[i];
+        const bool zero = std::find(a.prob, a.prob + a.sa_ptr[(size_t)a.n_states * a.n_actions], 0.0) !=
+                          a.prob + a.sa_ptr[(size_t)a.n_states * a.n_actions];
+        std::fill(hm.blk_zero_prob.begin() + (size_t)i * nJ, hm.blk_zero_prob.begin() + (size_t)(i + 1) * nJ, zero);
+    }
     std::atomic<int> next{0};
     auto worker = [&] {
         std::vector<int32_t> map;
@@ -929,6 +936,9 @@ static void plan_resident(morap_ctx* c) {
         return std::max(positions(a), states(a)) > std::max(positions(b), states(b));
     });
     upload(P.order, order, s);
+    P.rank.assign((size_t)hm.M, 0);
+    P.n_order = (int)order.size();
+    for (int b = 0; b < P.n_order; ++b) P.rank[(size_t)order[b]] = b;
     for (int prec : {MORAP_F64, MORAP_F32}) {
         ResidentPlan::Part& part = P.part[prec];
         part.launches.clear();
@@ -960,6 +970,10 @@ static void plan_resident(morap_ctx* c) {
         upload(part.d_rest, part.rest, s);
     }
     MORAP_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
+    P.inst_ok.assign((size_t)hm.M, 0);
+    const int most = std::min(k::policy_capacity(), k::eval_capacity());
+    for (int32_t m : order)
+        P.inst_ok[(size_t)m] = !P.part[MORAP_F64].rest[(size_t)m] && !hm.blk_zero_prob[(size_t)m] && states(m) <= most;
 }
 
 void upload_models(morap_ctx* c) {

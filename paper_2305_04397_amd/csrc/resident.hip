@@ -17,6 +17,7 @@
 // pair and its value at the initial state are the same bits.
 #include "common.h"
 #include "kern.h"
+#include "resident.h"
 
 #include <cfloat>
 #include <type_traits>
@@ -25,136 +26,6 @@ namespace morap {
 namespace k {
 
 namespace {
-
-constexpr int MAXW = 8;                       // waves of a workgroup
-constexpr int RES_MAX_THREADS = 64 * MAXW;
-constexpr int BIG_THREADS = 1024;             // of the kernel for larger products
-constexpr int GRID_NNZ = 17;                  // nonzero entries of the grid pattern
-constexpr size_t LDS_BYTES = 160 * 1024;      // of a compute unit
-
-// rows of one LDS buffer with ns states per thread (row 0 is the zero row):
-// the second buffer lies at this fixed distance, which the 16-bit offset of
-// an LDS access reaches
-__host__ __device__ constexpr int res_rows(int ns) { return RES_MAX_THREADS * ns + 1; }
-
-// nonzero entries of a sparsity pattern and the place of entry (a, d)
-__host__ __device__ constexpr int pat_count(uint32_t pat, int below = 25) {
-    int n = 0;
-    for (int e = 0; e < below; ++e) n += (pat >> e) & 1u;
-    return n;
-}
-
-// a value all lanes share, kept in scalar registers
-__device__ __forceinline__ float scalar(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
-}
-__device__ __forceinline__ double scalar(double v) {
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)b);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
-    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
-}
-
-// a register of its own: values taken out of a wide load otherwise keep the
-// whole load's registers, the unused ones among them
-__device__ __forceinline__ float own_reg(float v) {
-    float r;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(v));
-    return r;
-}
-__device__ __forceinline__ double own_reg(double v) {
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    unsigned lo, hi;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(lo) : "v"((unsigned)b));
-    asm volatile("v_mov_b32 %0, %1" : "=v"(hi) : "v"((unsigned)(b >> 32)));
-    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)b, CTRL, 0xf, 0xf, true);
-    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
-}
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;
-
-// maximum of two values >= 0 (which order like their bits: fmaxf would quiet
-// each operand first)
-__device__ __forceinline__ float mx(float a, float b) {
-    return __builtin_bit_cast(float, max(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b)));
-}
-__device__ __forceinline__ double mx(double a, double b) { return fmax(a, b); }
-__device__ __forceinline__ float max3(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-__device__ __forceinline__ double max3(double a, double b, double c) { return fmax(fmax(a, b), c); }
-// max(a, |b|)
-__device__ __forceinline__ float max_abs(float a, float b) {
-    float r;
-    asm("v_max_f32 %0, %1, |%2|" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ double max_abs(double a, double b) {
-    double r;
-    asm("v_max_f64 %0, %1, |%2|" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-// (v's low or high half) << SH
-template <int SH>
-__device__ __forceinline__ unsigned low_row(unsigned v) {
-    unsigned r;
-    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
-        : "=v"(r) : "s"(SH), "v"(v));
-    return r;
-}
-template <int SH>
-__device__ __forceinline__ unsigned high_row(unsigned v) {
-    unsigned r;
-    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
-        : "=v"(r) : "s"(SH), "v"(v));
-    return r;
-}
-
-// Maxima of KC per-lane values >= 0 over each row of 16 lanes; afterwards lane
-// l holds the maximum of value l % KC.  The values come out of max_abs, whose
-// instruction the compiler does not see as one a lane-moving read has to wait
-// for: the moves below read selections, and with one value a copy behind the
-// two wait states.
-template <class T, int KC>
-__device__ __forceinline__ T row_max(const T (&v)[KC]) {
-    const int lane = threadIdx.x & 63;
-    T r;
-    if constexpr (KC == 1) {
-        T c = v[0];
-        asm volatile("s_nop 1" : "+v"(c));
-        r = mx(c, dpp<DPP_XOR1>(c));
-        r = mx(r, dpp<DPP_XOR2>(r));
-    } else if constexpr (KC == 2) {
-        const bool odd = lane & 1;
-        const T keep = odd ? v[1] : v[0], give = odd ? v[0] : v[1];
-        r = mx(keep, dpp<DPP_XOR1>(give));
-        r = mx(r, dpp<DPP_XOR2>(r));
-    } else {
-        const bool odd = lane & 1, high = lane & 2;
-        const T a = mx(odd ? v[1] : v[0], dpp<DPP_XOR1>(odd ? v[0] : v[1]));
-        const T b = mx(odd ? v[3] : v[2], dpp<DPP_XOR1>(odd ? v[2] : v[3]));
-        r = mx(high ? b : a, dpp<DPP_XOR2>(high ? a : b));
-    }
-    r = mx(r, dpp<DPP_ROR4>(r));
-    return mx(r, dpp<DPP_ROR8>(r));
-}
-
-template <class T, int KC>
-struct Row {
-    T v[KC];
-};
 
 // The stop test of one column: its largest change within max(eps, a few units
 // in the last place of its largest value), or FP32's rounding floor: no new
@@ -176,6 +47,77 @@ __device__ __forceinline__ bool stop_test(const ResidentArgs& a, double res, dou
     return res <= tol || floor_stop;
 }
 
+// What a workgroup works on: the columns k0 .. k0 + KC - 1 of model m, or (INST)
+// instance q.
+template <class T, int KC, bool INST>
+struct Item {
+    bool ok;
+    int m, k0, q;
+    int64_t pair0, base;
+    __device__ __forceinline__ explicit Item(const ResidentArgs& a) {
+        if constexpr (INST) {
+            ok = true;
+            q = a.order[blockIdx.x];
+            m = a.inst_model[q];
+            k0 = 0;
+            pair0 = q;
+            base = a.inst_base[q];
+        } else {
+            // the columns of one product go to one XCD: its records meet in that L2
+            const int slot = blockIdx.x >> 3;
+            const int mi = slot / a.groups * 8 + (int)(blockIdx.x & 7);
+            ok = mi < a.n_models;
+            m = ok ? a.order[mi] : 0;
+            k0 = slot % a.groups * KC;
+            pair0 = (int64_t)m * a.Kp + k0;
+            q = 0;
+            base = 0;
+        }
+    }
+    __device__ __forceinline__ bool running(const ResidentArgs& a, int c) const {
+        return (INST || k0 + c < a.K) && a.pair_sweeps[pair0 + c] == 0;
+    }
+    __device__ __forceinline__ void weights(const ResidentArgs& a, int c, T& wc, T& wp) const {
+        if constexpr (INST) {
+            wc = scalar(a.iwc[q]);
+            wp = scalar(a.iwp[q]);
+        } else {
+            const int k = k0 + c < a.K ? k0 + c : 0;
+            const double* W = a.W + (int64_t)k * a.d;
+            wc = scalar((T)W[m / a.nJ]);
+            wp = scalar((T)W[a.nI + m % a.nJ]);
+        }
+    }
+    // place of the value of the product's state l in column c
+    __device__ __forceinline__ int64_t place(const ResidentArgs& a, int sb, int l, int c) const {
+        return INST ? base + l : (int64_t)(sb + l) * a.Kp + k0 + c;
+    }
+    __device__ __forceinline__ T start(const ResidentArgs& a, int sb, int l, int c) const {
+        if (a.sweep0 > 0 || (!INST && a.warm)) return static_cast<const T*>(a.x0)[place(a, sb, l, c)];
+        if constexpr (INST) {
+            // the FP32 solve's values scaled to the instance's weights, where
+            // its cost weight is positive (the values scale with the weights)
+            if (!a.start0 || !(a.iwc[q] > 0.0)) return 0;
+            const int k = a.inst_k[q];
+            const float* x = a.start_par[(int64_t)m * a.start_Kp + k] ? a.start1 : a.start0;
+            return (double)x[(int64_t)(sb + l) * a.start_Kp + k] * a.iscale[q];
+        }
+        return 0;
+    }
+    __device__ __forceinline__ bool stop(const ResidentArgs& a, double res, double ym, double& best, int& stall,
+                                         bool& floor_stop) const {
+        if constexpr (INST) return res <= a.ieps[q];
+        else return stop_test<sizeof(T) == 4>(a, res, ym, best, stall, floor_stop);
+    }
+    __device__ __forceinline__ void stopped(const ResidentArgs& a, int c, int n, bool floor_stop) const {
+        if constexpr (!INST) {
+            if (floor_stop) atomicAdd((unsigned long long*)&a.counters[8], 1ull);
+            a.final_par[pair0 + c] = 0;
+        }
+        a.pair_sweeps[pair0 + c] = n;
+    }
+};
+
 // waves per SIMD the registers are held to, so that the probabilities of NS
 // states fit with room for a step: 128 registers, 168 or 256
 __host__ __device__ constexpr int res_waves_per_simd(int bytes, int ns, bool fast) {
@@ -192,7 +134,9 @@ __host__ __device__ constexpr int res_waves_per_simd(int bytes, int ns, bool fas
 // by one wave while the others run sweep n + 1, and seen by all behind the
 // barrier of n + 1, when buffer n & 1 still holds iterate n: a column's final
 // values leave from there, each thread its own states.
-template <class T, int KC, int NS, bool FAST>
+// With INST an item is a (column, model) instance: FP64, its own two weights
+// and stop, values contiguous.
+template <class T, int KC, int NS, bool FAST, bool INST = false>
 __global__ void __launch_bounds__(RES_MAX_THREADS, res_waves_per_simd(sizeof(T), NS, FAST))
 resident_vi(ResidentArgs a) {
     constexpr uint32_t PAT = FAST ? PAT_GRID : PAT_DENSE;
@@ -205,18 +149,14 @@ resident_vi(ResidentArgs a) {
     static_assert(BUF <= 65535, "the second buffer must lie within an LDS offset");
     extern __shared__ __align__(16) unsigned char lds[];
 
-    // the columns of one product go to one XCD: its records meet in that L2
-    const int slot = blockIdx.x >> 3;
-    const int mi = slot / a.groups * 8 + (int)(blockIdx.x & 7);
-    if (mi >= a.n_models) return;
-    const int m = a.order[mi];
-    const int k0 = slot % a.groups * KC;
-    const int64_t pair0 = (int64_t)m * a.Kp + k0;
+    const Item<T, KC, INST> it(a);
+    if (!it.ok) return;
+    const int m = it.m;
     bool on[KC];
     bool any = false;
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-        on[c] = k0 + c < a.K && a.pair_sweeps[pair0 + c] == 0;
+        on[c] = it.running(a, c);
         any |= on[c];
     }
     if (!any) return;
@@ -230,22 +170,8 @@ resident_vi(ResidentArgs a) {
     double* best = reinterpret_cast<double*>(hdr + 2 * 4 * MAXW * 8 * sizeof(T));       // [4] smallest change so far
     int* stall = reinterpret_cast<int*>(best + 4);                                      // [4] sweeps since it was set
     unsigned* flag = reinterpret_cast<unsigned*>(stall + 4);                            // [2] results of the stop test
-    // (the kernel has no other LDS: the dynamic part starts at address 0)
-    auto get = [&](int buf, unsigned addr) -> Row<T, KC> {
-        using V = T __attribute__((ext_vector_type(KC)));
-        const V v = *(__attribute__((address_space(3))) const V*)(addr + buf * BUF);
-        Row<T, KC> r;
-#pragma unroll
-        for (int c = 0; c < KC; ++c) r.v[c] = v[c];
-        return r;
-    };
-    auto put = [&](int buf, unsigned addr, const Row<T, KC>& r) {
-        using V = T __attribute__((ext_vector_type(KC)));
-        V v;
-#pragma unroll
-        for (int c = 0; c < KC; ++c) v[c] = r.v[c];
-        *(__attribute__((address_space(3))) V*)(addr + buf * BUF) = v;
-    };
+    auto get = [&](int buf, unsigned addr) { return lds_get<T, KC>(addr + buf * BUF); };
+    auto put = [&](int buf, unsigned addr, const Row<T, KC>& r) { lds_put<T, KC>(addr + buf * BUF, r); };
 
     // the record of every state (they are stored in tile order: each names
     // its state)
@@ -280,12 +206,7 @@ resident_vi(ResidentArgs a) {
 
     T wc[KC], wp[KC];
 #pragma unroll
-    for (int c = 0; c < KC; ++c) {
-        const int k = k0 + c < a.K ? k0 + c : 0;
-        const double* W = a.W + (int64_t)k * a.d;
-        wc[c] = scalar((T)W[m / a.nJ]);
-        wp[c] = scalar((T)W[a.nI + m % a.nJ]);
-    }
+    for (int c = 0; c < KC; ++c) it.weights(a, c, wc[c], wp[c]);
     // every state of the product has the same action costs: w_c (-cost) once
     T first[UC ? KC : 1][5];
     if constexpr (UC) {
@@ -294,14 +215,11 @@ resident_vi(ResidentArgs a) {
 #pragma unroll
             for (int q = 0; q < 5; ++q) first[c][q] = scalar(wc[c] * cost[0][q]);
     }
-    T* x0 = static_cast<T*>(a.x0);
-    T* x1 = static_cast<T*>(a.x1);
-    const bool load = a.warm || a.sweep0 > 0;
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
         Row<T, KC> v;
 #pragma unroll
-        for (int c = 0; c < KC; ++c) v.v[c] = load ? x0[(int64_t)(sb + min(own0 - 1 + 64 * i, S - 1)) * a.Kp + k0 + c] : (T)0;
+        for (int c = 0; c < KC; ++c) v.v[c] = it.start(a, sb, min(own0 - 1 + 64 * i, S - 1), c);
         put(0, (unsigned)(own0 + 64 * i) << SH, v);
     }
     if (tid == 0) {
@@ -315,8 +233,8 @@ resident_vi(ResidentArgs a) {
     // the stop test is taken by the last wave, whose last steps may be empty
     const bool judge = wave == nw - 1;
     if (want_y && tid < KC) {
-        best[tid] = a.best_res[pair0 + tid];
-        stall[tid] = a.stall[pair0 + tid];
+        best[tid] = a.best_res[it.pair0 + tid];
+        stall[tid] = a.stall[it.pair0 + tid];
     }
     unsigned live = 0;   // columns still running
 #pragma unroll
@@ -405,36 +323,20 @@ resident_vi(ResidentArgs a) {
         constexpr int CUR = decltype(PAR)::value;
         int ln = lane;
         asm volatile("" : "+v"(ln));   // (as above: no addresses kept over the sweeps)
-        T rr = 0, yy = 0;
-        for (int q = ln >> 2; q < 4 * nw; q += 16) {
-            const T* p = part + ((CUR * 4 * MAXW + q) * 4 + (ln & 3)) * 2;
-            rr = mx(rr, p[0]);
-            yy = mx(yy, p[1]);
-        }
-        rr = mx(rr, dpp<DPP_ROR4>(rr));
-        rr = mx(rr, dpp<DPP_ROR8>(rr));
-        rr = mx(rr, __shfl_xor(rr, 16, 64));
-        rr = mx(rr, __shfl_xor(rr, 32, 64));
-        if (want_y) {
-            yy = mx(yy, dpp<DPP_ROR4>(yy));
-            yy = mx(yy, dpp<DPP_ROR8>(yy));
-            yy = mx(yy, __shfl_xor(yy, 16, 64));
-            yy = mx(yy, __shfl_xor(yy, 32, 64));
-        }
+        const T* p = part + CUR * 4 * MAXW * 8;
+        const T rr = part_max(p, nw, 2, ln), yy = want_y ? part_max(p + 1, nw, 2, ln) : (T)0;
         // lane c < KC tests column c
         bool now = false;
         if (ln < KC && (judged >> ln & 1)) {
             bool floor_stop = false;
-            now = stop_test<want_y>(a, (double)rr, (double)yy, best[ln], stall[ln], floor_stop);
+            now = it.stop(a, (double)rr, (double)yy, best[ln], stall[ln], floor_stop);
             if (now) {
-                const int64_t i = (int64_t)m * a.Kp + k0 + ln;
-                if (floor_stop) atomicAdd((unsigned long long*)&a.counters[8], 1ull);
-                a.final_par[i] = 0;
-                a.pair_sweeps[i] = n;
+                it.stopped(a, ln, n, floor_stop);
                 // (a product with states has a live initial state)
                 const int s_init = a.init[m] - sb + 1;
-                a.c[(int64_t)(k0 + ln) * a.M + m] =
-                    (double)reinterpret_cast<const T*>(lds + CUR * BUF + ((unsigned)s_init << SH))[ln];
+                if constexpr (!INST)
+                    a.c[(int64_t)(it.k0 + ln) * a.M + m] =
+                        (double)reinterpret_cast<const T*>(lds + CUR * BUF + ((unsigned)s_init << SH))[ln];
             }
         }
         const unsigned fresh = (unsigned)__ballot(now);
@@ -444,7 +346,7 @@ resident_vi(ResidentArgs a) {
 
     // final (or, at the end of the launch, current) values of the columns in
     // `cols` from buffer `buf`, each thread its own states
-    auto store = [&](T* x, int buf, unsigned cols) {
+    auto store = [&](void* x, int buf, unsigned cols) {
         int l = own0 - 1;
         asm volatile("" : "+v"(l));   // (as above: no addresses kept over the sweeps)
 #pragma clang loop unroll(disable)
@@ -452,7 +354,7 @@ resident_vi(ResidentArgs a) {
             const Row<T, KC> v = get(buf, (unsigned)(l + 1) << SH);
 #pragma unroll
             for (int c = 0; c < KC; ++c)
-                if (cols >> c & 1) x[(int64_t)(sb + l) * a.Kp + k0 + c] = v.v[c];
+                if (cols >> c & 1) static_cast<T*>(x)[it.place(a, sb, l, c)] = v.v[c];
         }
     };
 
@@ -464,22 +366,24 @@ resident_vi(ResidentArgs a) {
         __syncthreads();
         const unsigned f = flag[IN];             // the stop test of sweep n - 1
         if (f & 0xffu) {
-            store(x0, IN, f & 0xffu);
+            store(a.x0, IN, f & 0xffu);
             live &= ~f;
         }
         if (f & 0x100u) return true;
         if (!more) {
             // the launch ends with columns running: their iterate, and after
             // the last launch of a solve the iterate before it
-            store(x0, IN, live);
-            if (a.last) store(x1, 1 - IN, live);
-            if (judge && lane < KC && (live >> lane & 1)) {
-                const int64_t i = (int64_t)m * a.Kp + k0 + lane;
-                if (want_y) {
-                    a.best_res[i] = best[lane];
-                    a.stall[i] = stall[lane];
+            store(a.x0, IN, live);
+            if constexpr (!INST) {
+                if (a.last) store(a.x1, 1 - IN, live);
+                if (judge && lane < KC && (live >> lane & 1)) {
+                    const int64_t i = it.pair0 + lane;
+                    if (want_y) {
+                        a.best_res[i] = best[lane];
+                        a.stall[i] = stall[lane];
+                    }
+                    if (a.last) a.active[i] = 1;
                 }
-                if (a.last) a.active[i] = 1;
             }
             return true;
         }
@@ -510,7 +414,7 @@ resident_vi(ResidentArgs a) {
 // (4 columns), 0.53 (2) and 0.28 (1) 10^12 state-columns a second against 0.34
 // of the batched sweeps on all products of that problem; 37 FP64 columns of 49
 // products of up to 2,429 states: 2.3 ms, 10 ms before.
-template <class T, int KC, int NS>
+template <class T, int KC, int NS, bool INST = false>
 __global__ void __launch_bounds__(BIG_THREADS)
 resident_big(ResidentArgs a) {
     constexpr int ROWB = sizeof(T) * KC;
@@ -519,16 +423,13 @@ resident_big(ResidentArgs a) {
     constexpr int NW = BIG_THREADS / 64;
     extern __shared__ __align__(16) unsigned char lds[];
 
-    const int slot = blockIdx.x >> 3;
-    const int mi = slot / a.groups * 8 + (int)(blockIdx.x & 7);
-    if (mi >= a.n_models) return;
-    const int m = a.order[mi];
-    const int k0 = slot % a.groups * KC;
-    const int64_t pair0 = (int64_t)m * a.Kp + k0;
+    const Item<T, KC, INST> it(a);
+    if (!it.ok) return;
+    const int m = it.m;
     unsigned live = 0;   // columns still running
 #pragma unroll
     for (int c = 0; c < KC; ++c)
-        if (k0 + c < a.K && a.pair_sweeps[pair0 + c] == 0) live |= 1u << c;
+        if (it.running(a, c)) live |= 1u << c;
     if (!live) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -548,41 +449,24 @@ resident_big(ResidentArgs a) {
     double* best = reinterpret_cast<double*>(hdr + 4 * NW * 8 * sizeof(T));  // [4] smallest change so far
     int* stall = reinterpret_cast<int*>(best + 4);                           // [4] sweeps since it was set
     unsigned* flag = reinterpret_cast<unsigned*>(stall + 4);
-    using V = T __attribute__((ext_vector_type(KC)));
-    auto get = [&](unsigned addr) -> Row<T, KC> {
-        const V v = *(__attribute__((address_space(3))) const V*)addr;
-        Row<T, KC> r;
-#pragma unroll
-        for (int c = 0; c < KC; ++c) r.v[c] = v[c];
-        return r;
-    };
-    auto put = [&](unsigned addr, const Row<T, KC>& r) {
-        V v;
-#pragma unroll
-        for (int c = 0; c < KC; ++c) v[c] = r.v[c];
-        *(__attribute__((address_space(3))) V*)addr = v;
-    };
+    auto get = [&](unsigned addr) { return lds_get<T, KC>(addr); };
+    auto put = [&](unsigned addr, const Row<T, KC>& r) { lds_put<T, KC>(addr, r); };
 
     T wp[KC], first[KC][5];
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-        const int k = k0 + c < a.K ? k0 + c : 0;
-        const double* W = a.W + (int64_t)k * a.d;
-        const T wc = (T)W[m / a.nJ];
-        wp[c] = scalar((T)W[a.nI + m % a.nJ]);
+        T wc;
+        it.weights(a, c, wc, wp[c]);
         // every state of the product has the same action costs
 #pragma unroll
         for (int q = 0; q < 5; ++q) first[c][q] = wc * ablk[(int64_t)blk[-s_begin] * GRID_BLK + GRID_NNZ + q];
     }
-    T* x0 = static_cast<T*>(a.x0);
-    T* x1 = static_cast<T*>(a.x1);
-    const bool load = a.warm || a.sweep0 > 0;
     const unsigned own0 = (unsigned)(s_begin * 64 + lane + 1) << SH;   // LDS row of the first step's state
     for (int i = 0; i < cnt; ++i) {
         const unsigned w = rec[i * 64].w & 0x7fffffffu;
         Row<T, KC> v;
 #pragma unroll
-        for (int c = 0; c < KC; ++c) v.v[c] = load ? x0[(int64_t)(sb + (int)w) * a.Kp + k0 + c] : (T)0;
+        for (int c = 0; c < KC; ++c) v.v[c] = it.start(a, sb, (int)w, c);
         put(own0 + ((unsigned)i << (6 + SH)), v);
     }
     if (tid == 0) {
@@ -592,13 +476,13 @@ resident_big(ResidentArgs a) {
         put(0, z);
     }
     if (want_y && tid < KC) {
-        best[tid] = a.best_res[pair0 + tid];
-        stall[tid] = a.stall[pair0 + tid];
+        best[tid] = a.best_res[it.pair0 + tid];
+        stall[tid] = a.stall[it.pair0 + tid];
     }
     __syncthreads();
 
     // the values of the columns in `cols`, each thread its own states
-    auto store = [&](T* x, unsigned cols) {
+    auto store = [&](void* x, unsigned cols) {
         unsigned own = own0;
         asm volatile("" : "+v"(own));   // (no addresses kept over the sweeps)
         for (int i = 0; i < cnt; ++i) {
@@ -607,7 +491,7 @@ resident_big(ResidentArgs a) {
             if (w >> 31) continue;   // padding
 #pragma unroll
             for (int c = 0; c < KC; ++c)
-                if (cols >> c & 1) x[(int64_t)(sb + (int)w) * a.Kp + k0 + c] = v.v[c];
+                if (cols >> c & 1) static_cast<T*>(x)[it.place(a, sb, (int)w, c)] = v.v[c];
         }
     };
 
@@ -687,7 +571,7 @@ resident_big(ResidentArgs a) {
             p[1] = yy;
         }
         // the iterate before the last, of a solve over its limit
-        if (a.last && n == a.sweep1) store(x1, live);
+        if (!INST && a.last && n == a.sweep1) store(a.x1, live);
         __syncthreads();   // every wave has read the old values
 #pragma unroll
         for (int i = 0; i < NS; ++i)
@@ -695,32 +579,12 @@ resident_big(ResidentArgs a) {
         if (wave == NW - 1) {
             int ln = lane;
             asm volatile("" : "+v"(ln));
-            T res_t = 0, y_t = 0;
-            for (int z = ln >> 2; z < 4 * NW; z += 16) {
-                const T* p = part + (z * 4 + (ln & 3)) * 2;
-                res_t = mx(res_t, p[0]);
-                y_t = mx(y_t, p[1]);
-            }
-            res_t = mx(res_t, dpp<DPP_ROR4>(res_t));
-            res_t = mx(res_t, dpp<DPP_ROR8>(res_t));
-            res_t = mx(res_t, __shfl_xor(res_t, 16, 64));
-            res_t = mx(res_t, __shfl_xor(res_t, 32, 64));
-            if (want_y) {
-                y_t = mx(y_t, dpp<DPP_ROR4>(y_t));
-                y_t = mx(y_t, dpp<DPP_ROR8>(y_t));
-                y_t = mx(y_t, __shfl_xor(y_t, 16, 64));
-                y_t = mx(y_t, __shfl_xor(y_t, 32, 64));
-            }
+            const T res_t = part_max(part, NW, 2, ln), y_t = want_y ? part_max(part + 1, NW, 2, ln) : (T)0;
             bool now = false;
             if (ln < KC && (live >> ln & 1)) {
                 bool floor_stop = false;
-                now = stop_test<want_y>(a, (double)res_t, (double)y_t, best[ln], stall[ln], floor_stop);
-                if (now) {
-                    const int64_t i = (int64_t)m * a.Kp + k0 + ln;
-                    if (floor_stop) atomicAdd((unsigned long long*)&a.counters[8], 1ull);
-                    a.final_par[i] = 0;
-                    a.pair_sweeps[i] = n;
-                }
+                now = it.stop(a, (double)res_t, (double)y_t, best[ln], stall[ln], floor_stop);
+                if (now) it.stopped(a, ln, n, floor_stop);
             }
             const unsigned fresh = (unsigned)__ballot(now);
             if (ln == 0) *flag = fresh;
@@ -728,24 +592,26 @@ resident_big(ResidentArgs a) {
         __syncthreads();
         const unsigned f = *flag;
         if (f) {
-            store(x0, f);
-            if (tid < KC && (f >> tid & 1))
-                a.c[(int64_t)(k0 + tid) * a.M + m] =
-                    (double)reinterpret_cast<const T*>(lds + ((unsigned)(a.big_init[m] + 1) << SH))[tid];
+            store(a.x0, f);
+            if constexpr (!INST)
+                if (tid < KC && (f >> tid & 1))
+                    a.c[(int64_t)(it.k0 + tid) * a.M + m] =
+                        (double)reinterpret_cast<const T*>(lds + ((unsigned)(a.big_init[m] + 1) << SH))[tid];
             live &= ~f;
             if (!live) return;
         }
     }
     // the launch ends with columns running: their iterate
-    store(x0, live);
-    if (tid < KC && (live >> tid & 1)) {
-        const int64_t i = pair0 + tid;
-        if (want_y) {
-            a.best_res[i] = best[tid];
-            a.stall[i] = stall[tid];
+    store(a.x0, live);
+    if constexpr (!INST)
+        if (tid < KC && (live >> tid & 1)) {
+            const int64_t i = it.pair0 + tid;
+            if (want_y) {
+                a.best_res[i] = best[tid];
+                a.stall[i] = stall[tid];
+            }
+            if (a.last) a.active[i] = 1;
         }
-        if (a.last) a.active[i] = 1;
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -766,9 +632,9 @@ int resident_capacity(int prec, bool fast) {
 
 namespace {
 
-template <class T, int KC, int NS, bool FAST>
+template <class T, int KC, int NS, bool FAST, bool INST = false>
 void launch_res(hipStream_t s, const ResidentArgs& a, int max_states) {
-    auto* fn = &resident_vi<T, KC, NS, FAST>;
+    auto* fn = &resident_vi<T, KC, NS, FAST, INST>;
     constexpr int ROWB = sizeof(T) * KC;
     const int threads = 64 * ((max_states + 64 * NS - 1) / (64 * NS));
     const size_t bytes = (size_t)res_rows(NS) * ROWB + (((size_t)(threads * NS + 1) * ROWB + 15) & ~(size_t)15) +
@@ -779,22 +645,22 @@ void launch_res(hipStream_t s, const ResidentArgs& a, int max_states) {
     static const hipError_t granted =
         hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
     MORAP_HIP(granted);
-    const unsigned blocks = 8u * (unsigned)((a.n_models + 7) / 8) * (unsigned)a.groups;
+    const unsigned blocks = INST ? (unsigned)a.n_models : 8u * (unsigned)((a.n_models + 7) / 8) * (unsigned)a.groups;
     hipLaunchKernelGGL(fn, dim3(blocks), dim3((unsigned)threads), bytes, s, a);
     MORAP_HIP(hipGetLastError());
 }
 
-template <class T, int KC, bool FAST, int MAXNS>
+template <class T, int KC, bool FAST, int MAXNS, bool INST = false>
 void launch_steps(hipStream_t s, const ResidentArgs& a, int ns, int max_states) {
-    if (ns == 1) return launch_res<T, KC, 1, FAST>(s, a, max_states);
+    if (ns == 1) return launch_res<T, KC, 1, FAST, INST>(s, a, max_states);
     if constexpr (MAXNS >= 2)
-        if (ns == 2) return launch_res<T, KC, 2, FAST>(s, a, max_states);
+        if (ns == 2) return launch_res<T, KC, 2, FAST, INST>(s, a, max_states);
     if constexpr (MAXNS >= 3)
-        if (ns == 3) return launch_res<T, KC, 3, FAST>(s, a, max_states);
+        if (ns == 3) return launch_res<T, KC, 3, FAST, INST>(s, a, max_states);
     if constexpr (MAXNS >= 4)
-        if (ns == 4) return launch_res<T, KC, 4, FAST>(s, a, max_states);
+        if (ns == 4) return launch_res<T, KC, 4, FAST, INST>(s, a, max_states);
     if constexpr (MAXNS >= 7)
-        if (ns == 7) return launch_res<T, KC, 7, FAST>(s, a, max_states);
+        if (ns == 7) return launch_res<T, KC, 7, FAST, INST>(s, a, max_states);
     fail(MORAP_E_UNSUPPORTED, "a product does not fit the LDS-resident iteration");
 }
 
@@ -823,6 +689,14 @@ void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, Res
     }
 }
 
+void resident_inst(hipStream_t s, bool fast, int max_states, ResidentArgs a) {
+    if (a.n_models <= 0) return;
+    const int ns = resident_class(max_states);
+    a.groups = 1;
+    if (fast) launch_steps<double, 1, true, 4, true>(s, a, ns, max_states);
+    else launch_steps<double, 1, false, 2, true>(s, a, ns, max_states);
+}
+
 bool grid_entry(int e) { return (PAT_GRID >> e) & 1u; }
 
 int resident_most_positions() {
@@ -845,10 +719,10 @@ int resident_big_columns(int prec, int positions) {
 
 namespace {
 
-template <class T, int KC>
+template <class T, int KC, bool INST = false>
 void launch_big(hipStream_t s, const ResidentArgs& a, int max_positions) {
     constexpr int NS = 160 / (sizeof(T) * KC);
-    auto* fn = &resident_big<T, KC, NS>;
+    auto* fn = &resident_big<T, KC, NS, INST>;
     const size_t bytes = (((size_t)max_positions + 1) * sizeof(T) * KC + 15) / 16 * 16 +
                          4 * (BIG_THREADS / 64) * 8 * sizeof(T) + 64;
     MORAP_CHECK(max_positions % 64 == 0 && bytes <= LDS_BYTES && max_positions <= BIG_THREADS * NS,
@@ -856,7 +730,7 @@ void launch_big(hipStream_t s, const ResidentArgs& a, int max_positions) {
     static const hipError_t granted =
         hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
     MORAP_HIP(granted);
-    const unsigned blocks = 8u * (unsigned)((a.n_models + 7) / 8) * (unsigned)a.groups;
+    const unsigned blocks = INST ? (unsigned)a.n_models : 8u * (unsigned)((a.n_models + 7) / 8) * (unsigned)a.groups;
     hipLaunchKernelGGL(fn, dim3(blocks), dim3(BIG_THREADS), bytes, s, a);
     MORAP_HIP(hipGetLastError());
 }
@@ -874,6 +748,12 @@ void resident_large(hipStream_t s, int prec, int columns, int max_positions, Res
         if (columns == 2) launch_big<double, 2>(s, a, max_positions);
         else launch_big<double, 1>(s, a, max_positions);
     }
+}
+
+void resident_inst_large(hipStream_t s, int max_positions, ResidentArgs a) {
+    if (a.n_models <= 0) return;
+    a.groups = 1;
+    launch_big<double, 1, true>(s, a, max_positions);
 }
 
 }  // namespace k

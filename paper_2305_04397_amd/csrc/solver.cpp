@@ -1001,10 +1001,6 @@ static void solve_impl(morap_ctx* c, const double* W, int K, const morap_vi_opts
 // ---------------------------------------------------------------------------
 static k::InstArgs inst_args(morap_ctx* c, int n_tiles, int n_inst) {
     k::InstArgs a{};
-    a.inst_model = c->d_inst_model.as<int32_t>();
-    a.inst_k = c->d_inst_k.as<int32_t>();
-    a.inst_base = c->d_inst_base.as<int64_t>();
-    a.inst_tiles = c->d_inst_tiles.as<int32_t>();
     a.n_tiles = n_tiles;
     a.n_inst = n_inst;
     a.state_base = c->d_state_base.as<int32_t>();
@@ -1041,6 +1037,226 @@ static double policy_eps(double eps_vi, double wc, double wp) {
     return eps_vi;
 }
 
+// Host arrays of a set of instances, sent to the device in one copy.
+struct InstancePack {
+    std::vector<char> bytes;
+    template <class T> size_t add(const std::vector<T>& v) {
+        const size_t at = (bytes.size() + 15) / 16 * 16;
+        bytes.resize(at + v.size() * sizeof(T) + 16);
+        if (!v.empty()) std::memcpy(bytes.data() + at, v.data(), v.size() * sizeof(T));
+        return at;
+    }
+    char* send(DevBuf& d, PinnedBuf& h, hipStream_t s) const {
+        d.ensure(bytes.size() + 16);
+        h.ensure(bytes.size() + 16);
+        std::memcpy(h.p, bytes.data(), bytes.size());
+        MORAP_HIP(hipMemcpyAsync(d.p, h.p, bytes.size(), hipMemcpyHostToDevice, s));
+        return d.as<char>();
+    }
+};
+
+// Instances (column, model): weights scaled to sum 1, state offsets, and how
+// their iterations run: in LDS, one workgroup each (`order`, in launches), or
+// over tiles of 256 states of the others.
+struct Instances {
+    struct Run {
+        int begin, n, max_states;
+        bool fast, large;
+    };
+    int n = 0, n_general = 0;
+    std::vector<int32_t> k, m, tiles, order;
+    std::vector<int64_t> base, init_idx;
+    std::vector<double> wc, wp, scale, eps;
+    std::vector<uint8_t> resident;
+    std::vector<Run> vi;
+    int64_t states() const { return base[(size_t)n]; }
+
+    // d_model, ... of the device copy
+    const int32_t *d_model = nullptr, *d_k = nullptr, *d_tiles = nullptr, *d_order = nullptr;
+    const int64_t *d_base = nullptr, *d_init = nullptr;
+    const double *d_wc = nullptr, *d_wp = nullptr, *d_scale = nullptr, *d_eps = nullptr;
+    const uint8_t* d_resident = nullptr;
+
+    void build(morap_ctx* c, std::vector<int32_t> ks, std::vector<int32_t> ms, bool policies, const morap_vi_opts& o) {
+        const HostModels& hm = c->hm;
+        const bool team = c->team;
+        const int nI = hm.nI, nJ = hm.nJ, d = nI + nJ;
+        k = std::move(ks);
+        m = std::move(ms);
+        n = (int)k.size();
+        base.assign((size_t)n + 1, 0);
+        init_idx.assign((size_t)n, -1);
+        wc.resize((size_t)n);
+        wp.resize((size_t)n);
+        scale.assign((size_t)n, 0.0);
+        eps.resize((size_t)n);
+        resident.assign((size_t)n, 0);
+        const bool lds = c->has_blocks && !team;
+        // instances that run in LDS by the place of their model in the plan's
+        // order (largest first within a launch class)
+        const std::vector<int32_t>& rank = c->resident_plan.rank;
+        std::vector<int32_t> first(lds ? c->resident_plan.n_order + 2 : 0, 0);
+        for (int q = 0; q < n; ++q) {
+            const int mq = m[q], i = mq / nJ, j = mq % nJ;
+            const int S_m = hm.state_base[mq + 1] - hm.state_base[mq];
+            base[q + 1] = base[q] + S_m;
+            wc[q] = team ? 1.0 : c->W[(size_t)k[q] * d + i];
+            wp[q] = team ? 0.0 : c->W[(size_t)k[q] * d + nI + j];
+            const double sum = wc[q] + wp[q];   // policies come from the weights scaled to sum 1
+            if (sum > 0) {
+                wc[q] /= sum;
+                wp[q] /= sum;
+                scale[q] = 1.0 / sum;
+            }
+            eps[q] = policies && !team ? policy_eps(o.eps_vi, wc[q], wp[q]) : o.eps_vi;
+            if (hm.init[mq] >= 0) init_idx[q] = base[q] + (hm.init[mq] - hm.state_base[mq]);
+            if (S_m == 0) continue;
+            if (lds && c->resident_plan.inst_ok[(size_t)mq]) {
+                resident[q] = 1;
+                ++first[(size_t)rank[(size_t)mq] + 1];
+                continue;
+            }
+            ++n_general;
+            for (int b = 0; b < S_m; b += 256) {
+                tiles.push_back(q);
+                tiles.push_back(b);
+            }
+        }
+        if (!lds) return;
+        for (size_t r = 1; r < first.size(); ++r) first[r] += first[r - 1];
+        for (const auto& l : c->resident_plan.part[MORAP_F64].launches) {
+            const int b = first[(size_t)l.begin], e = first[(size_t)(l.begin + l.n)];
+            if (e > b) vi.push_back({b, e - b, l.max_states, l.fast, l.columns > 0});
+        }
+        order.resize((size_t)first.back());
+        for (int q = 0; q < n; ++q)
+            if (resident[q]) order[(size_t)first[(size_t)rank[(size_t)m[q]]]++] = q;
+    }
+
+    // launches over `order` of instances whose sizes fall in one class
+    template <class F>
+    std::vector<Run> runs(morap_ctx* c, F&& size_class) const {
+        std::vector<Run> out;
+        for (int p = 0; p < (int)order.size(); ++p) {
+            const int mq = m[(size_t)order[p]];
+            const int S_m = c->hm.state_base[mq + 1] - c->hm.state_base[mq];
+            if (!out.empty() && size_class(out.back().max_states) == size_class(S_m)) {
+                ++out.back().n;
+                out.back().max_states = std::max(out.back().max_states, S_m);
+            } else {
+                out.push_back({p, 1, S_m, false, false});
+            }
+        }
+        return out;
+    }
+
+    // everything above (and what `p` already holds) on the device
+    char* send(InstancePack& p, DevBuf& d, PinnedBuf& h, hipStream_t s) {
+        const size_t at[] = {p.add(m),  p.add(k),  p.add(tiles), p.add(order), p.add(base),    p.add(init_idx),
+                             p.add(wc), p.add(wp), p.add(scale), p.add(eps),   p.add(resident)};
+        char* b = p.send(d, h, s);
+        d_model = reinterpret_cast<int32_t*>(b + at[0]);
+        d_k = reinterpret_cast<int32_t*>(b + at[1]);
+        d_tiles = reinterpret_cast<int32_t*>(b + at[2]);
+        d_order = reinterpret_cast<int32_t*>(b + at[3]);
+        d_base = reinterpret_cast<int64_t*>(b + at[4]);
+        d_init = reinterpret_cast<int64_t*>(b + at[5]);
+        d_wc = reinterpret_cast<double*>(b + at[6]);
+        d_wp = reinterpret_cast<double*>(b + at[7]);
+        d_scale = reinterpret_cast<double*>(b + at[8]);
+        d_eps = reinterpret_cast<double*>(b + at[9]);
+        d_resident = reinterpret_cast<uint8_t*>(b + at[10]);
+        return b;
+    }
+
+    k::InstArgs args(morap_ctx* c) const {
+        k::InstArgs a = inst_args(c, (int)(tiles.size() / 2), n);
+        a.inst_model = d_model;
+        a.inst_k = d_k;
+        a.inst_base = d_base;
+        a.inst_tiles = d_tiles;
+        a.resident = d_resident;
+        return a;
+    }
+
+    // value iteration in LDS, sweeps s0 + 1 .. s1 of the instances without a
+    // stop in `sweeps`, from the FP32 solve's values (after an FP64 solve from 0)
+    void launch_vi(morap_ctx* c, double* x, int32_t* sweeps, int64_t s0, int64_t s1, EventPairs* ev) const {
+        k::ResidentArgs a{};
+        a.state_base = c->d_state_base.as<int32_t>();
+        a.init = c->d_init.as<int32_t>();
+        a.rec = c->d_blk_rec.as<int32_t>();
+        a.ablk = c->d_blk64.p;
+        a.zero_row = (int32_t)c->S;
+        a.grid_blk = c->resident_plan.grid_blk64.p;
+        a.big_base = c->resident_plan.big_base.as<int32_t>();
+        a.big_block = c->resident_plan.big_block.as<int32_t>();
+        a.big_rec = c->resident_plan.big_rec.as<uint4>();
+        a.big_init = c->resident_plan.big_init.as<int32_t>();
+        a.K = 1;
+        a.x0 = x;
+        a.pair_sweeps = sweeps;
+        a.inst_model = d_model;
+        a.inst_k = d_k;
+        a.inst_base = d_base;
+        a.iwc = d_wc;
+        a.iwp = d_wp;
+        a.ieps = d_eps;
+        a.iscale = d_scale;
+        if (c->prec == MORAP_F32 && c->vmain.valid) {
+            a.start0 = c->vmain.x[0].as<float>();
+            a.start1 = c->vmain.x[1].as<float>();
+            a.start_par = c->vmain.final_par.as<uint8_t>();
+            a.start_Kp = c->vmain.Kp;
+        }
+        a.sweep0 = (int)s0;
+        a.sweep1 = (int)s1;
+        for (const Run& r : vi) {
+            a.order = d_order + r.begin;
+            a.n_models = r.n;
+            if (ev) {
+                ev->emplace_back(take_event(c), nullptr);
+                ev->back().second = take_event(c);
+                MORAP_HIP(hipEventRecord(ev->back().first, c->stream));
+            }
+            if (r.large) k::resident_inst_large(c->stream, r.max_states, a);
+            else k::resident_inst(c->stream, r.fast, r.max_states, a);
+            if (ev) MORAP_HIP(hipEventRecord(ev->back().second, c->stream));
+        }
+    }
+
+    // sweeps the value iteration took as the tiled iteration counts them
+    // (whole chunks), and the bytes it would have moved; still running: > 0
+    int64_t account(morap_ctx* c, const int32_t* sweeps, int chunk, Stats& st) const {
+        int64_t longest = 0;
+        for (int32_t q : order) {
+            const int64_t up = ((int64_t)sweeps[q] + chunk - 1) / chunk * chunk;
+            longest = std::max(longest, up);
+            // record + own value read + write per state
+            st.bytes_refine += (double)up * (double)(base[q + 1] - base[q]) * 48.0;
+        }
+        return longest;
+    }
+    int64_t running(const int32_t* sweeps, int width) const {
+        int64_t r = 0;
+        for (int32_t q : order)
+            for (int w = 0; w < width; ++w) r += sweeps[(size_t)q * width + w] == 0;
+        return r;
+    }
+};
+
+static void harvest_refine(morap_ctx* c, EventPairs& ev, Stats& st) {
+    for (auto& e : ev) {
+        float t = 0;
+        MORAP_HIP(hipEventElapsedTime(&t, e.first, e.second));
+        st.ms_sweep_kernel_refine += t;
+        st.sweep_launches_refine += 1;
+        give_events(c, e);
+        e = {nullptr, nullptr};
+    }
+    ev.clear();
+}
+
 static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const morap_vi_opts& o, double* r_out,
                           Stats& st, const int32_t* warm) {
     MORAP_CHECK(c->solved, MORAP_E_STATE, "morap_evaluate needs a morap_solve first");
@@ -1071,72 +1287,37 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
     // instances (k, m), task-major within each column
     const int n = K * nJ;
     c->assign.assign(assign, assign + (size_t)K * nJ);
-    c->inst_k.resize(n);
-    c->inst_m.resize(n);
-    c->inst_base.assign(n + 1, 0);
-    std::vector<int32_t> tiles;
-    std::vector<double> iwc(n), iwp(n), iscale(n, 0.0);
-    std::vector<int64_t> init_idx(n, -1);
-    for (int kk = 0; kk < K; ++kk)
-        for (int j = 0; j < nJ; ++j) {
-            const int q = kk * nJ + j;
-            const int i = assign[q];
-            const int m = team ? 0 : i * nJ + j;
-            c->inst_k[q] = kk;
-            c->inst_m[q] = m;
-            const int S_m = c->hm.state_base[m + 1] - c->hm.state_base[m];
-            c->inst_base[q + 1] = c->inst_base[q] + S_m;
-            for (int b = 0; b < S_m; b += 256) {
-                tiles.push_back(q);
-                tiles.push_back(b);
+    Instances I;
+    {
+        std::vector<int32_t> ks((size_t)n), ms((size_t)n);
+        for (int kk = 0; kk < K; ++kk)
+            for (int j = 0; j < nJ; ++j) {
+                ks[(size_t)kk * nJ + j] = kk;
+                ms[(size_t)kk * nJ + j] = team ? 0 : assign[(size_t)kk * nJ + j] * nJ + j;
             }
-            iwc[q] = team ? 1.0 : c->W[(size_t)kk * d + i];
-            iwp[q] = team ? 0.0 : c->W[(size_t)kk * d + nI + j];
-            const double sc = iwc[q] + iwp[q];   // policies come from the weights scaled to sum 1
-            if (sc > 0) {
-                iwc[q] /= sc;
-                iwp[q] /= sc;
-                iscale[q] = 1.0 / sc;
-            }
-            if (c->hm.init[m] >= 0) init_idx[q] = c->inst_base[q] + (c->hm.init[m] - c->hm.state_base[m]);
-        }
-    const int64_t NS = c->inst_base[n];
-    const int n_tiles = (int)(tiles.size() / 2);
-    c->d_inst_model.ensure((size_t)n * 4);
-    c->d_inst_k.ensure((size_t)n * 4);
-    c->d_inst_base.ensure((size_t)(n + 1) * 8);
-    c->d_inst_tiles.ensure(tiles.size() * 4 + 8);
-    c->d_iwc.ensure((size_t)n * 8);
-    c->d_iwp.ensure((size_t)n * 8);
-    c->d_iscale.ensure((size_t)n * 8);
+        I.build(c, std::move(ks), std::move(ms), true, o);
+    }
+    c->inst_k = I.k;
+    c->inst_m = I.m;
+    c->inst_base = I.base;
+    const std::vector<int32_t>& tiles = I.tiles;
+    const std::vector<double>&iwc = I.wc, &iwp = I.wp, &iscale = I.scale;
+    const int64_t NS = I.states();
+    const bool lds = !I.order.empty(), general = I.n_general > 0;
+    double eps_pol = o.eps_vi;
+    for (double e : I.eps) eps_pol = std::min(eps_pol, e);
     c->d_xi.ensure((size_t)NS * 8 + 8);
     c->d_ires.ensure((size_t)2 * n * 8);
     c->d_iactive.ensure((size_t)2 * n);
     c->d_ipar.ensure((size_t)2 * n);
-    c->d_mask.ensure((size_t)NS * 4 + 4);
-    c->d_rank.ensure((size_t)NS * 4 + 4);
+    if (general) {
+        c->d_mask.ensure((size_t)NS * 4 + 4);
+        c->d_rank.ensure((size_t)NS * 4 + 4);
+        c->d_xe[1].ensure((size_t)NS * 16 + 16);
+    }
     c->d_mu.ensure((size_t)NS + 4);
     c->d_xe[0].ensure((size_t)NS * 16 + 16);
-    c->d_xe[1].ensure((size_t)NS * 16 + 16);
-    c->d_init_idx.ensure((size_t)n * 8);
-    c->d_init_val.ensure((size_t)2 * n * 8);
-    MORAP_HIP(hipMemcpyAsync(c->d_inst_model.p, c->inst_m.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_inst_k.p, c->inst_k.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_inst_base.p, c->inst_base.data(), (size_t)(n + 1) * 8, hipMemcpyHostToDevice, s));
-    if (!tiles.empty())
-        MORAP_HIP(hipMemcpyAsync(c->d_inst_tiles.p, tiles.data(), tiles.size() * 4, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_iwc.p, iwc.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_iwp.p, iwp.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_iscale.p, iscale.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
-    std::vector<double> ieps(n);
-    double eps_pol = o.eps_vi;
-    for (int q = 0; q < n; ++q) {
-        ieps[q] = team ? o.eps_vi : policy_eps(o.eps_vi, iwc[q], iwp[q]);
-        eps_pol = std::min(eps_pol, ieps[q]);
-    }
-    c->d_ieps.ensure((size_t)n * 8 + 8);
-    MORAP_HIP(hipMemcpyAsync(c->d_ieps.p, ieps.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_init_idx.p, init_idx.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
+    c->d_init_val.ensure((size_t)3 * n * 8);
     std::vector<int32_t> iobj;
     if (team) {
         iobj.resize((size_t)2 * n);
@@ -1148,7 +1329,28 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
         c->d_inst_obj.ensure((size_t)2 * n * 4);
         MORAP_HIP(hipMemcpyAsync(c->d_inst_obj.p, iobj.data(), iobj.size() * 4, hipMemcpyHostToDevice, s));
     }
-    const k::InstArgs a = inst_args(c, n_tiles, n);
+    // evaluations that start from the previous one's values of the same pair
+    std::vector<uint8_t> iwarm(n, 0);
+    std::vector<int64_t> prev_src(n, -1);
+    if (warm && c->eval_prev_valid && c->prev_per_col == nJ) {
+        const int K_prev = (int)(c->prev_inst_m.size() / std::max(1, nJ));
+        for (int kk = 0; kk < K; ++kk) {
+            const int kp = warm[kk];
+            MORAP_CHECK(kp >= -1, MORAP_E_INVALID, "warm-start column out of range");
+            if (kp < 0 || kp >= K_prev) continue;
+            for (int j = 0; j < nJ; ++j) {
+                const int q = kk * nJ + j, qp = kp * nJ + j;
+                if (c->prev_inst_m[qp] != c->inst_m[q]) continue;
+                iwarm[q] = 1;
+                prev_src[q] = c->prev_inst_base[qp];
+            }
+        }
+    }
+    InstancePack pack;
+    const size_t at_warm = pack.add(iwarm), at_prev = pack.add(prev_src);
+    const char* packed = I.send(pack, c->d_inst_pack, c->h_inst_pack, s);
+    const uint8_t* d_iwarm = reinterpret_cast<const uint8_t*>(packed + at_warm);
+    const k::InstArgs a = I.args(c);
     int64_t* dctr = c->d_counters.as<int64_t>();
     int64_t* h = c->h_counters.as<int64_t>();
     unsigned long long* ires = c->d_ires.as<unsigned long long>();
@@ -1192,24 +1394,50 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
     // form the instances iterate in their own (instance-major) values;
     // otherwise the batched sweep re-solves the marked pairs.
     double* xi = c->d_xi.as<double>();
-    if (c->has_blocks) {
+    // what the iterations in LDS report: sweeps of the values [n] and of the
+    // evaluation [2 n], then two counters
+    const size_t out_words = (size_t)3 * n + 3;   // (3: room to align the counters)
+    c->d_inst_out.ensure(out_words * 4 + 16);
+    c->h_inst_out.ensure(out_words * 4 + 16);
+    int32_t* vi_sweeps = c->d_inst_out.as<int32_t>();
+    int32_t* ev_sweeps = vi_sweeps + n;
+    int64_t* inst_ctr = reinterpret_cast<int64_t*>(vi_sweeps + ((size_t)3 * n + 1) / 2 * 2);
+    const int32_t* h_sweeps = c->h_inst_out.as<int32_t>();
+    const int64_t* h_ctr = reinterpret_cast<const int64_t*>(h_sweeps + ((size_t)3 * n + 1) / 2 * 2);
+    const int64_t vi_limit = ((int64_t)o.max_sweeps + chunk - 1) / chunk * chunk;
+    auto read_out = [&] {
+        MORAP_HIP(hipMemcpyAsync(c->h_inst_out.p, c->d_inst_out.p, out_words * 4 + 16, hipMemcpyDeviceToHost, s));
+        MORAP_HIP(hipStreamSynchronize(s));
+    };
+    const bool warm_values = c->prec == MORAP_F32 && c->vmain.valid;
+    if (c->has_blocks && general && !warm_values) k::fill_f64(s, xi, 0.0, NS);
+    EventPair vi_wall;
+    PooledEvents vi_events(c);
+    if (lds) {
+        k::fill_i32(s, vi_sweeps, 0, (int64_t)out_words + 4);
+        MORAP_HIP(hipEventRecord(vi_wall.a, s));
+        I.launch_vi(c, xi, vi_sweeps, 0, std::min<int64_t>(vi_limit, kResidentSweeps), o.time_kernels ? &vi_events.v : nullptr);
+        MORAP_HIP(hipEventRecord(vi_wall.b, s));
+    }
+    int64_t vsweeps = 0;
+    c->last_c64_valid = false;
+    if (c->has_blocks && general) {
         c->d_xr.ensure((size_t)NS * 8 + 8);
         double* x0 = xi;
         double* x1 = c->d_xr.as<double>();
         // after an FP32 solve the re-solve starts from its values (scaled to
         // the instance's weights); after an FP64 solve from 0, as Alg. 3
-        if (c->prec == MORAP_F32 && c->vmain.valid)
-            k::warm_start(s, a, c->vmain.x[0].p, c->vmain.x[1].p, c->vmain.final_par.as<uint8_t>(), c->vmain.Kp,
-                          c->d_iscale.as<double>(), c->d_iwc.as<double>(), x0);
-        else
-            k::fill_f64(s, x0, 0.0, NS);
+        if (warm_values)
+            k::warm_start(s, a, c->vmain.x[0].p, c->vmain.x[1].p, c->vmain.final_par.as<uint8_t>(), c->vmain.Kp, I.d_scale,
+                          I.d_wc, x0);
         k::fill_f64(s, x1, 0.0, NS);
         k::set_active(s, n, a, iact, ires, ipar, 1);
         EventPair wall;
         MORAP_HIP(hipEventRecord(wall.a, s));
         k::InstArgs av = a;
-        int64_t live_states = NS;
-        int64_t vsweeps = 0;
+        int64_t live_states = 0;
+        for (int q = 0; q < n; ++q)
+            if (!I.resident[q]) live_states += I.base[q + 1] - I.base[q];
         PooledEvents held(c);
         EventPairs& ev = held.v;
         while (true) {
@@ -1221,25 +1449,16 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
                     ev.back().second = take_event(c);
                     MORAP_HIP(hipEventRecord(ev.back().first, s));
                 }
-                k::inst_vi_sweep(s, av, c->d_blk_rec.as<int32_t>(), c->d_blk64.as<double>(), c->d_iwc.as<double>(),
-                                 c->d_iwp.as<double>(), iact, even ? x0 : x1, even ? x1 : x0, ires, (int32_t)c->S,
-                                 c->hm.blk_pattern);
+                k::inst_vi_sweep(s, av, c->d_blk_rec.as<int32_t>(), c->d_blk64.as<double>(), I.d_wc, I.d_wp, iact,
+                                 even ? x0 : x1, even ? x1 : x0, ires, (int32_t)c->S, c->hm.blk_pattern);
                 if (timed) MORAP_HIP(hipEventRecord(ev.back().second, s));
-                k::inst_converge(s, n, ires, iact, ipar, even ? 1 : 0, o.eps_vi, dctr, c->d_ieps.as<double>());
+                k::inst_converge(s, n, ires, iact, ipar, even ? 1 : 0, o.eps_vi, dctr, I.d_eps);
             }
             vsweeps += chunk;
             // record + own value read + write per live instance state
             st.bytes_refine += (double)chunk * (double)live_states * 48.0;
             read_counters(c);
-            for (auto& e : ev) {
-                float t = 0;
-                MORAP_HIP(hipEventElapsedTime(&t, e.first, e.second));
-                st.ms_sweep_kernel_refine += t;
-                st.sweep_launches_refine += 1;
-                give_events(c, e);
-                e = {nullptr, nullptr};
-            }
-            ev.clear();
+            harvest_refine(c, ev, st);
             if (h[0] == 0) break;
             MORAP_CHECK(vsweeps < o.max_sweeps, MORAP_E_NOT_CONVERGED,
                         "value iteration of the assigned pairs: " + std::to_string(h[0]) +
@@ -1250,21 +1469,7 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
         MORAP_HIP(hipEventRecord(wall.b, s));
         MORAP_HIP(hipEventSynchronize(wall.b));
         st.ms_vi += wall.elapsed_ms();
-        st.polish_sweeps += vsweeps;
-        st.variant_refine = -1;   // instance-major block iteration
-        // the assigned pairs' FP64 values at their initial states, for the
-        // weights of the column (the re-solve scaled them to sum 1)
-        c->last_c64_valid = false;
-        if (c->prec == MORAP_F32 && !team) {
-            double* v = c->d_init_val.as<double>();
-            k::gather_values(s, n, c->d_init_idx.as<int64_t>(), x0, v);
-            c->last_c64.resize(n);
-            MORAP_HIP(hipMemcpyAsync(c->last_c64.data(), v, (size_t)n * 8, hipMemcpyDeviceToHost, s));
-            MORAP_HIP(hipStreamSynchronize(s));
-            for (int q = 0; q < n; ++q) c->last_c64[q] = iscale[q] > 0 ? c->last_c64[q] / iscale[q] : 0.0;
-            c->last_c64_valid = true;
-        }
-    } else {
+    } else if (!c->has_blocks) {
         const int M = c->hm.M, Kp = c->Kp;
         std::vector<double> wc((size_t)M * Kp, 0.0), wp((size_t)M * Kp, 0.0);
         for (int kk = 0; kk < K; ++kk)
@@ -1296,76 +1501,68 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
 
     EventPair wall;
     MORAP_HIP(hipEventRecord(wall.a, s));
-
-    // Attractor rounds with the tolerance tau; states left unranked get the
-    // tolerance widened tenfold (up to tau * 1e6) while ranked states keep
-    // their choice.
-    uint32_t* mask = c->d_mask.as<uint32_t>();
-    int32_t* rank = c->d_rank.as<int32_t>();
-    c->d_ichanged.ensure((size_t)n + 8);
-    uint8_t* ichg = c->d_ichanged.as<uint8_t>();
+    double* xe0 = c->d_xe[0].as<double>();
+    double* xe1 = c->d_xe[1].as<double>();
     int8_t* mu = c->d_mu.as<int8_t>();
-    k::opt_mask(s, a, c->d_iwc.as<double>(), c->d_iwp.as<double>(), xi, o.tau, mask, rank, mu, false);
-    int base = 0, relax_sweeps = 0;
-    double tau = o.tau;
-    for (int widen = 0;; ++widen) {
-        // ranks of this phase: relax to the fixed point (8 sweeps per check,
-        // alternating direction; converged when the last sweep changed
-        // nothing).  After a round only the tiles of instances that changed
-        // in it are relaxed again: ranks spread only inside an instance.
-        k::InstArgs ar = a;
-        for (int round = 0;; ++round) {
-            k::fill_i64(s, dctr, 0, 8);
-            k::fill_u8(s, ichg, 0, n);
-            for (int i = 0; i < 8; ++i) k::relax_ranks(s, ar, mask, rank, base, (i & 1) != 0, 16, dctr + i, ichg);
-            relax_sweeps += 8;
-            read_counters(c);
-            if (h[7] == 0) break;
-            MORAP_CHECK(round < 1000000, MORAP_E_IMPROPER, "attractor ranks did not settle");
-            live_tiles(ichg, 1, ar);
-        }
-        k::fill_i64(s, dctr, 0, 1);
-        k::choose_actions(s, a, mask, rank, mu, base, dctr);
-        read_counters(c);
-        base = std::max<int64_t>(base, h[0]);
-        k::fill_i64(s, dctr, 0, 1);
-        k::count_unranked(s, a, rank, dctr);
-        read_counters(c);
-        if (h[0] == 0 || widen == kTauSteps) break;
-        tau *= 10.0;
-        k::opt_mask(s, a, c->d_iwc.as<double>(), c->d_iwp.as<double>(), xi, tau, mask, rank, mu, true);
-    }
-    st.rank_rounds += relax_sweeps;
-    if (h[0] != 0) {
-        fail(MORAP_E_IMPROPER, std::to_string(h[0]) + " states cannot reach done through tau-optimal actions");
-    }
 
+    // the instances in LDS: policies, then the first sweeps of the evaluation;
+    // all launched before the host looks at how the values ended
+    k::InstanceArgs ia{};
+    ia.inst_model = I.d_model;
+    ia.inst_base = I.d_base;
+    ia.state_base = c->d_state_base.as<int32_t>();
+    ia.rec = c->d_blk_rec.as<int32_t>();
+    ia.ablk = c->d_blk64.as<double>();
+    ia.zero_row = (int32_t)c->S;
+    ia.iwc = I.d_wc;
+    ia.iwp = I.d_wp;
+    ia.xi = xi;
+    ia.mu = mu;
+    ia.tau = o.tau;
+    ia.widenings = kTauSteps;
+    ia.counters = inst_ctr;
+    ia.xe = xe0;
+    ia.xe_prev = c->d_xe_prev.as<double>();
+    ia.prev_src = reinterpret_cast<const int64_t*>(packed + at_prev);
+    ia.from_values = o.eval_start ? 1 : 0;
+    ia.sweeps = ev_sweeps;
+    ia.eps = o.eps_eval;
+    auto launch = [&](const std::vector<Instances::Run>& runs, auto&& kernel) {
+        for (const auto& r : runs) {
+            ia.order = I.d_order + r.begin;
+            ia.n = r.n;
+            kernel(s, r.max_states, ia);
+        }
+    };
+    // (a policy instance's LDS use follows its size: classes of one, two, four
+    // and more workgroups a compute unit)
+    const auto policy_runs = I.runs(c, [](int S_m) { return S_m <= 2500 ? 0 : (S_m <= 5000 ? 1 : 2); });
+    const auto eval_runs = I.runs(c, [](int S_m) { return k::eval_class(S_m); });
+    const int64_t eval_limit = ((int64_t)o.max_sweeps + chunk - 1) / chunk * chunk;
+    int64_t esweeps = 0;
+    std::string unfinished;   // instances in LDS whose evaluation hit its limit
+    auto policies_and_values = [&] {
+        launch(policy_runs, k::inst_policy);
+        ia.sweep0 = 0;
+        ia.sweep1 = (int)std::min<int64_t>(eval_limit, kResidentSweeps);
+        launch(eval_runs, k::inst_eval);
+        read_out();
+    };
     // Alg. 4 per objective, from 0, or (warm) each instance whose column's
     // previous column had an instance of the same task on the same model from
     // that instance's final values, and (eval_start) from the scalarised
     // values: the evaluation of a proper policy reaches its values from any
     // start, with the same bound on the error at its stop
-    double* xe0 = c->d_xe[0].as<double>();
-    double* xe1 = c->d_xe[1].as<double>();
-    k::fill_f64(s, xe0, 0.0, 2 * NS);
-    k::fill_f64(s, xe1, 0.0, 2 * NS);
-    std::vector<uint8_t> iwarm(n, 0);
-    if (warm && c->eval_prev_valid && c->prev_per_col == nJ) {
+    if (general) {
         std::vector<int64_t> runs;
-        const int K_prev = (int)(c->prev_inst_m.size() / std::max(1, nJ));
-        for (int kk = 0; kk < K; ++kk) {
-            const int kp = warm[kk];
-            MORAP_CHECK(kp >= -1, MORAP_E_INVALID, "warm-start column out of range");
-            if (kp < 0 || kp >= K_prev) continue;
-            for (int j = 0; j < nJ; ++j) {
-                const int q = kk * nJ + j, qp = kp * nJ + j;
-                if (c->prev_inst_m[qp] != c->inst_m[q]) continue;
-                iwarm[q] = 1;
-                runs.push_back(c->inst_base[q]);
-                runs.push_back(c->prev_inst_base[qp]);
-                runs.push_back(c->inst_base[q + 1] - c->inst_base[q]);
-            }
+        for (int q = 0; q < n; ++q) {
+            if (I.resident[q] || !iwarm[q]) continue;
+            runs.push_back(I.base[q]);
+            runs.push_back(prev_src[q]);
+            runs.push_back(I.base[q + 1] - I.base[q]);
         }
+        k::fill_f64(s, xe0, 0.0, 2 * NS);
+        k::fill_f64(s, xe1, 0.0, 2 * NS);
         if (!runs.empty()) {
             c->d_warm_copy.ensure(runs.size() * 8);
             MORAP_HIP(hipMemcpyAsync(c->d_warm_copy.p, runs.data(), runs.size() * 8, hipMemcpyHostToDevice, s));
@@ -1373,73 +1570,157 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
             MORAP_HIP(hipStreamSynchronize(s));   // the host run list goes out of scope
         }
     }
-    if (o.eval_start && !team) {
+    if (lds) {
+        policies_and_values();
+        for (int64_t s0 = kResidentSweeps; I.running(h_sweeps, 1) > 0; s0 += kResidentSweeps) {
+            if (s0 < vi_limit) {
+                I.launch_vi(c, xi, vi_sweeps, s0, std::min<int64_t>(vi_limit, s0 + kResidentSweeps), nullptr);
+                read_out();
+            }
+            MORAP_CHECK(s0 + kResidentSweeps < vi_limit || I.running(h_sweeps, 1) == 0, MORAP_E_NOT_CONVERGED,
+                        "value iteration of the assigned pairs: " + std::to_string(I.running(h_sweeps, 1)) +
+                            " instances still active after " + std::to_string(vi_limit) + " sweeps");
+            if (I.running(h_sweeps, 1) == 0) {
+                // again from the final values
+                k::fill_i32(s, ev_sweeps, 0, (int64_t)out_words + 4 - n);
+                policies_and_values();
+            }
+        }
+        harvest_refine(c, vi_events.v, st);
+        st.ms_vi += vi_wall.elapsed_ms();
+        vsweeps = std::max(vsweeps, I.account(c, h_sweeps, chunk, st));
+        st.rank_rounds += h_ctr[1];
+        if (h_ctr[0] != 0)
+            fail(MORAP_E_IMPROPER, std::to_string(h_ctr[0]) + " states cannot reach done through tau-optimal actions");
+        for (int64_t s0 = ia.sweep1; I.running(h_sweeps + n, 2) > 0 && s0 < eval_limit; s0 = ia.sweep1) {
+            ia.sweep0 = (int)s0;
+            ia.sweep1 = (int)std::min<int64_t>(eval_limit, s0 + kResidentSweeps);
+            launch(eval_runs, k::inst_eval);
+            read_out();
+        }
+        for (int32_t q : I.order)
+            for (int w = 0; w < 2; ++w) {
+                const int64_t e = h_sweeps[(size_t)n + 2 * (size_t)q + w];
+                esweeps = std::max(esweeps, e > 0 ? (e + chunk - 1) / chunk * chunk : eval_limit);
+            }
+    }
+    if (c->has_blocks) {
+        st.polish_sweeps += vsweeps;
+        st.variant_refine = -1;   // instance-major block iteration
+    }
+
+    if (general) {
+        // Attractor rounds with the tolerance tau; states left unranked get
+        // the tolerance widened tenfold (up to tau * 1e6) while ranked states
+        // keep their choice.
+        uint32_t* mask = c->d_mask.as<uint32_t>();
+        int32_t* rank = c->d_rank.as<int32_t>();
+        c->d_ichanged.ensure((size_t)n + 8);
+        uint8_t* ichg = c->d_ichanged.as<uint8_t>();
+        k::opt_mask(s, a, I.d_wc, I.d_wp, xi, o.tau, mask, rank, mu, false);
+        int base = 0, relax_sweeps = 0;
+        double tau = o.tau;
+        for (int widen = 0;; ++widen) {
+            // ranks of this phase: relax to the fixed point (8 sweeps per check,
+            // alternating direction; converged when the last sweep changed
+            // nothing).  After a round only the tiles of instances that changed
+            // in it are relaxed again: ranks spread only inside an instance.
+            k::InstArgs ar = a;
+            for (int round = 0;; ++round) {
+                k::fill_i64(s, dctr, 0, 8);
+                k::fill_u8(s, ichg, 0, n);
+                for (int i = 0; i < 8; ++i)
+                    k::relax_ranks(s, ar, mask, rank, base, (i & 1) != 0, 16, dctr + i, ichg);
+                relax_sweeps += 8;
+                read_counters(c);
+                if (h[7] == 0) break;
+                MORAP_CHECK(round < 1000000, MORAP_E_IMPROPER, "attractor ranks did not settle");
+                live_tiles(ichg, 1, ar);
+            }
+            k::fill_i64(s, dctr, 0, 1);
+            k::choose_actions(s, a, mask, rank, mu, base, dctr);
+            read_counters(c);
+            base = std::max<int64_t>(base, h[0]);
+            k::fill_i64(s, dctr, 0, 1);
+            k::count_unranked(s, a, rank, dctr);
+            read_counters(c);
+            if (h[0] == 0 || widen == kTauSteps) break;
+            tau *= 10.0;
+            k::opt_mask(s, a, I.d_wc, I.d_wp, xi, tau, mask, rank, mu, true);
+        }
+        st.rank_rounds += relax_sweeps;
+        if (h[0] != 0)
+            fail(MORAP_E_IMPROPER, std::to_string(h[0]) + " states cannot reach done through tau-optimal actions");
+
         // from the scalarised values the policies were chosen from (R15)
-        c->d_iwarm.ensure((size_t)n + 16);
-        MORAP_HIP(hipMemcpyAsync(c->d_iwarm.p, iwarm.data(), (size_t)n, hipMemcpyHostToDevice, s));
-        k::eval_start(s, a, xi, c->d_iwc.as<double>(), c->d_iwp.as<double>(), c->d_iwarm.as<uint8_t>(), xe0);
-        MORAP_HIP(hipStreamSynchronize(s));   // iwarm goes out of scope
-    }
-    k::set_active(s, n, a, iact, ires, ipar, 2);
-    int64_t esweeps = 0;
-    k::InstArgs ae = a;
-    while (true) {
-        for (int i = 0; i < chunk; ++i) {
-            const bool even = (i & 1) == 0;
-            if (c->has_blocks)
-                k::eval_block_sweep(s, ae, c->d_blk_rec.as<int32_t>(), c->d_blk64.as<double>(), mu, iact,
-                                    even ? xe0 : xe1, even ? xe1 : xe0, ires, (int32_t)c->S, c->hm.blk_pattern);
-            else
-                k::eval_sweep(s, ae, mu, iact, even ? xe0 : xe1, even ? xe1 : xe0, ires);
-            k::inst_converge(s, 2 * n, ires, iact, ipar, even ? 1 : 0, o.eps_eval, dctr);
-        }
-        esweeps += chunk;
-        read_counters(c);
-        if (h[0] == 0) break;
-        if (esweeps < o.max_sweeps) {
+        if (o.eval_start && !team) k::eval_start(s, a, xi, I.d_wc, I.d_wp, d_iwarm, xe0);
+        k::set_active(s, n, a, iact, ires, ipar, 2);
+        int64_t tiled = 0;
+        k::InstArgs ae = a;
+        while (true) {
+            for (int i = 0; i < chunk; ++i) {
+                const bool even = (i & 1) == 0;
+                if (c->has_blocks)
+                    k::eval_block_sweep(s, ae, c->d_blk_rec.as<int32_t>(), c->d_blk64.as<double>(), mu, iact,
+                                        even ? xe0 : xe1, even ? xe1 : xe0, ires, (int32_t)c->S, c->hm.blk_pattern);
+                else
+                    k::eval_sweep(s, ae, mu, iact, even ? xe0 : xe1, even ? xe1 : xe0, ires);
+                k::inst_converge(s, 2 * n, ires, iact, ipar, even ? 1 : 0, o.eps_eval, dctr);
+            }
+            tiled += chunk;
+            read_counters(c);
+            if (h[0] == 0 || tiled >= o.max_sweeps) break;
             live_tiles(iact, 2, ae);
-            continue;
         }
-        {
-            // name the (column, task, objective) entries still running; the
-            // policies stay readable through morap_get_policy
-            std::vector<uint8_t> still((size_t)2 * n);
-            MORAP_HIP(hipMemcpy(still.data(), iact, still.size(), hipMemcpyDeviceToHost));
-            // current iterate at the initial states, for the message
-            k::select_final(s, a, xe0, xe1, ipar, 2);
-            k::gather_init(s, n, c->d_init_idx.as<int64_t>(), xe0, c->d_init_val.as<double>());
-            std::vector<double> now((size_t)2 * n);
-            MORAP_HIP(hipMemcpyAsync(now.data(), c->d_init_val.p, now.size() * 8, hipMemcpyDeviceToHost, s));
-            MORAP_HIP(hipStreamSynchronize(s));
-            std::string who;
-            int shown = 0;
-            for (int q = 0; q < 2 * n && shown < 8; ++q)
-                if (still[q]) {
-                    const int inst = q / 2;
-                    char buf[256];
-                    std::snprintf(buf, sizeof buf,
-                                  " (k=%d, j=%d, %s: model %d, weights %.17g, %.17g, value at the initial state "
-                                  "now %.6g / %.6g)",
-                                  inst / nJ, inst % nJ, q % 2 ? "probability" : "cost", c->inst_m[inst],
-                                  iwc[inst], iwp[inst], now[2 * inst], now[2 * inst + 1]);
-                    who += buf;
-                    ++shown;
-                }
-            c->eK = K;
-            c->evaluated = true;
-            fail(MORAP_E_NOT_CONVERGED, "policy evaluation did not converge after " + std::to_string(esweeps) +
-                                            " sweeps:" + who);
-        }
+        esweeps = std::max(esweeps, tiled);
+        k::select_final(s, a, xe0, xe1, ipar, 2);
     }
-    st.eval_sweeps += esweeps;
-    k::select_final(s, a, xe0, xe1, ipar, 2);
+
+    // values at the initial states: of the policy values (an FP32 solve's
+    // assignment is checked against them, for the weights of the column, which
+    // the re-solve scaled to sum 1) and of both objectives
     double* ival = c->d_init_val.as<double>();
-    k::gather_init(s, n, c->d_init_idx.as<int64_t>(), xe0, ival);
-    std::vector<double> vals((size_t)2 * n);
-    MORAP_HIP(hipMemcpyAsync(vals.data(), ival, vals.size() * 8, hipMemcpyDeviceToHost, s));
+    const bool keep_c64 = c->has_blocks && c->prec == MORAP_F32 && !team;
+    if (keep_c64) k::gather_values(s, n, I.d_init, xi, ival);
+    k::gather_init(s, n, I.d_init, xe0, ival + n);
+    c->h_c.ensure((size_t)3 * n * 8);
+    MORAP_HIP(hipMemcpyAsync(c->h_c.p, ival, (size_t)3 * n * 8, hipMemcpyDeviceToHost, s));
     MORAP_HIP(hipEventRecord(wall.b, s));
     MORAP_HIP(hipEventSynchronize(wall.b));
     const float ms = wall.elapsed_ms();
+    const double* vals = c->h_c.as<double>() + n;
+    if (keep_c64) {
+        c->last_c64.resize(n);
+        for (int q = 0; q < n; ++q) c->last_c64[q] = iscale[q] > 0 ? c->h_c.as<double>()[q] / iscale[q] : 0.0;
+        c->last_c64_valid = true;
+    }
+    if ((lds && I.running(h_sweeps + n, 2) > 0) || (general && h[0] != 0)) {
+        // name the (column, task, objective) entries still running; the
+        // policies stay readable through morap_get_policy
+        std::vector<uint8_t> still((size_t)2 * n, 0);
+        if (general) MORAP_HIP(hipMemcpy(still.data(), iact, still.size(), hipMemcpyDeviceToHost));
+        for (int32_t q : I.order)
+            for (int w = 0; w < 2; ++w) still[(size_t)2 * q + w] = h_sweeps[(size_t)n + 2 * (size_t)q + w] == 0;
+        std::string who;
+        int shown = 0;
+        for (int q = 0; q < 2 * n && shown < 8; ++q)
+            if (still[q]) {
+                const int inst = q / 2;
+                char buf[256];
+                std::snprintf(buf, sizeof buf,
+                              " (k=%d, j=%d, %s: model %d, weights %.17g, %.17g, value at the initial state "
+                              "now %.6g / %.6g)",
+                              inst / nJ, inst % nJ, q % 2 ? "probability" : "cost", c->inst_m[inst], iwc[inst],
+                              iwp[inst], vals[2 * inst], vals[2 * inst + 1]);
+                who += buf;
+                ++shown;
+            }
+        c->eK = K;
+        c->evaluated = true;
+        fail(MORAP_E_NOT_CONVERGED,
+             "policy evaluation did not converge after " + std::to_string(esweeps) + " sweeps:" + who);
+    }
+    st.eval_sweeps += esweeps;
 
     if (r_out) {
         std::fill(r_out, r_out + (size_t)K * d, 0.0);
@@ -1479,91 +1760,75 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
 // Uses buffers of its own: the last evaluation stays readable.
 static std::vector<double> resolve_pairs(morap_ctx* c, const std::vector<int32_t>& pk,
                                          const std::vector<int32_t>& pm, const morap_vi_opts& o, Stats& st) {
-    const int n = (int)pk.size();
-    const int nI = c->hm.nI, nJ = c->hm.nJ, d = nI + nJ;
     hipStream_t s = c->stream;
-    std::vector<int64_t> base(n + 1, 0), init_idx(n, -1);
-    std::vector<int32_t> tiles;
-    std::vector<double> iwc(n), iwp(n), iscale(n, 0.0);
-    for (int q = 0; q < n; ++q) {
-        const int m = pm[q], i = m / nJ, j = m % nJ;
-        const int S_m = c->hm.state_base[m + 1] - c->hm.state_base[m];
-        base[q + 1] = base[q] + S_m;
-        for (int b = 0; b < S_m; b += 256) {
-            tiles.push_back(q);
-            tiles.push_back(b);
-        }
-        iwc[q] = c->W[(size_t)pk[q] * d + i];
-        iwp[q] = c->W[(size_t)pk[q] * d + nI + j];
-        const double sc = iwc[q] + iwp[q];
-        if (sc > 0) {
-            iwc[q] /= sc;
-            iwp[q] /= sc;
-            iscale[q] = 1.0 / sc;
-        }
-        if (c->hm.init[m] >= 0) init_idx[q] = base[q] + (c->hm.init[m] - c->hm.state_base[m]);
-    }
-    const int64_t NS = base[n];
-    c->d_cand_model.ensure((size_t)n * 4);
-    c->d_cand_k.ensure((size_t)n * 4);
-    c->d_cand_base.ensure((size_t)(n + 1) * 8);
-    c->d_cand_tiles.ensure(tiles.size() * 4 + 8);
-    c->d_cand_iwc.ensure((size_t)n * 8);
-    c->d_cand_iwp.ensure((size_t)n * 8);
-    c->d_cand_iscale.ensure((size_t)n * 8);
+    Instances I;
+    I.build(c, pk, pm, false, o);
+    const int n = I.n;
+    const int64_t NS = I.states();
+    const bool general = I.n_general > 0, lds = !I.order.empty();
     c->d_cand_x0.ensure((size_t)NS * 8 + 8);
-    c->d_cand_x1.ensure((size_t)NS * 8 + 8);
-    c->d_cand_res.ensure((size_t)n * 8);
-    c->d_cand_act.ensure((size_t)n);
-    c->d_cand_par.ensure((size_t)n);
-    c->d_cand_init.ensure((size_t)n * 8);
     c->d_cand_val.ensure((size_t)n * 8);
-    MORAP_HIP(hipMemcpyAsync(c->d_cand_model.p, pm.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_cand_k.p, pk.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_cand_base.p, base.data(), (size_t)(n + 1) * 8, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_cand_tiles.p, tiles.data(), tiles.size() * 4, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_cand_iwc.p, iwc.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_cand_iwp.p, iwp.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_cand_iscale.p, iscale.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
-    MORAP_HIP(hipMemcpyAsync(c->d_cand_init.p, init_idx.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
-    k::InstArgs a = inst_args(c, (int)(tiles.size() / 2), n);
-    a.inst_model = c->d_cand_model.as<int32_t>();
-    a.inst_k = c->d_cand_k.as<int32_t>();
-    a.inst_base = c->d_cand_base.as<int64_t>();
-    a.inst_tiles = c->d_cand_tiles.as<int32_t>();
+    c->d_cand_sweeps.ensure((size_t)n * 4 + 8);
+    InstancePack pack;
+    I.send(pack, c->d_cand_pack, c->h_cand_pack, s);
+    const k::InstArgs a = I.args(c);
     double* x0 = c->d_cand_x0.as<double>();
-    double* x1 = c->d_cand_x1.as<double>();
-    unsigned long long* res = c->d_cand_res.as<unsigned long long>();
-    uint8_t* act = c->d_cand_act.as<uint8_t>();
-    uint8_t* par = c->d_cand_par.as<uint8_t>();
-    int64_t* dctr = c->d_counters.as<int64_t>();
-    int64_t* h = c->h_counters.as<int64_t>();
-    k::warm_start(s, a, c->vmain.x[0].p, c->vmain.x[1].p, c->vmain.final_par.as<uint8_t>(), c->vmain.Kp,
-                  c->d_cand_iscale.as<double>(), c->d_cand_iwc.as<double>(), x0);
-    k::fill_f64(s, x1, 0.0, NS);
-    k::set_active(s, n, a, act, res, par, 1);
     const int chunk = std::max(2, (o.check_every + 1) / 2 * 2);
     int64_t sweeps = 0;
-    while (true) {
-        for (int i = 0; i < chunk; ++i) {
-            const bool even = (i & 1) == 0;
-            k::inst_vi_sweep(s, a, c->d_blk_rec.as<int32_t>(), c->d_blk64.as<double>(), c->d_cand_iwc.as<double>(),
-                             c->d_cand_iwp.as<double>(), act, even ? x0 : x1, even ? x1 : x0, res, (int32_t)c->S,
-                             c->hm.blk_pattern);
-            k::inst_converge(s, n, res, act, par, even ? 1 : 0, o.eps_vi, dctr);
+    if (lds) {
+        const int64_t limit = ((int64_t)o.max_sweeps + chunk - 1) / chunk * chunk;
+        int32_t* ps = c->d_cand_sweeps.as<int32_t>();
+        c->h_inst_out.ensure((size_t)n * 4 + 16);
+        const int32_t* h_ps = c->h_inst_out.as<int32_t>();
+        k::fill_i32(s, ps, 0, n);
+        for (int64_t s0 = 0; s0 < limit; s0 += kResidentSweeps) {
+            I.launch_vi(c, x0, ps, s0, std::min<int64_t>(limit, s0 + kResidentSweeps), nullptr);
+            MORAP_HIP(hipMemcpyAsync(c->h_inst_out.p, ps, (size_t)n * 4, hipMemcpyDeviceToHost, s));
+            MORAP_HIP(hipStreamSynchronize(s));
+            if (I.running(h_ps, 1) == 0) break;
         }
-        sweeps += chunk;
-        read_counters(c);
-        if (h[0] == 0) break;
-        MORAP_CHECK(sweeps < o.max_sweeps, MORAP_E_NOT_CONVERGED,
+        MORAP_CHECK(I.running(h_ps, 1) == 0, MORAP_E_NOT_CONVERGED,
                     "value iteration of the pairs of the assignment check did not converge");
+        Stats ignored;   // (their bytes are not counted)
+        sweeps = I.account(c, h_ps, chunk, ignored);
     }
-    k::select_final(s, a, x0, x1, par, 1);
-    k::gather_values(s, n, c->d_cand_init.as<int64_t>(), x0, c->d_cand_val.as<double>());
+    if (general) {
+        c->d_cand_x1.ensure((size_t)NS * 8 + 8);
+        c->d_cand_res.ensure((size_t)n * 8);
+        c->d_cand_act.ensure((size_t)n);
+        c->d_cand_par.ensure((size_t)n);
+        double* x1 = c->d_cand_x1.as<double>();
+        unsigned long long* res = c->d_cand_res.as<unsigned long long>();
+        uint8_t* act = c->d_cand_act.as<uint8_t>();
+        uint8_t* par = c->d_cand_par.as<uint8_t>();
+        int64_t* dctr = c->d_counters.as<int64_t>();
+        int64_t* h = c->h_counters.as<int64_t>();
+        k::warm_start(s, a, c->vmain.x[0].p, c->vmain.x[1].p, c->vmain.final_par.as<uint8_t>(), c->vmain.Kp, I.d_scale,
+                      I.d_wc, x0);
+        k::fill_f64(s, x1, 0.0, NS);
+        k::set_active(s, n, a, act, res, par, 1);
+        int64_t tiled = 0;
+        while (true) {
+            for (int i = 0; i < chunk; ++i) {
+                const bool even = (i & 1) == 0;
+                k::inst_vi_sweep(s, a, c->d_blk_rec.as<int32_t>(), c->d_blk64.as<double>(), I.d_wc, I.d_wp, act,
+                                 even ? x0 : x1, even ? x1 : x0, res, (int32_t)c->S, c->hm.blk_pattern);
+                k::inst_converge(s, n, res, act, par, even ? 1 : 0, o.eps_vi, dctr);
+            }
+            tiled += chunk;
+            read_counters(c);
+            if (h[0] == 0) break;
+            MORAP_CHECK(tiled < o.max_sweeps, MORAP_E_NOT_CONVERGED,
+                        "value iteration of the pairs of the assignment check did not converge");
+        }
+        k::select_final(s, a, x0, x1, par, 1);
+        sweeps = std::max(sweeps, tiled);
+    }
+    k::gather_values(s, n, I.d_init, x0, c->d_cand_val.as<double>());
     std::vector<double> out(n);
     MORAP_HIP(hipMemcpyAsync(out.data(), c->d_cand_val.p, (size_t)n * 8, hipMemcpyDeviceToHost, s));
     MORAP_HIP(hipStreamSynchronize(s));
-    for (int q = 0; q < n; ++q) out[q] = iscale[q] > 0 ? out[q] / iscale[q] : 0.0;
+    for (int q = 0; q < n; ++q) out[q] = I.scale[q] > 0 ? out[q] / I.scale[q] : 0.0;
     st.polish_sweeps += sweeps;
     return out;
 }

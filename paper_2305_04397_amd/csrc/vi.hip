@@ -1085,7 +1085,7 @@ __global__ void set_active_kernel(int n, k::InstArgs a, uint8_t* active, unsigne
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n * width) return;
     const int m = a.inst_model[i / width];
-    active[i] = a.init[m] >= 0 ? 1 : 0;
+    active[i] = a.init[m] >= 0 && !(a.resident && a.resident[i / width]) ? 1 : 0;
     res[i] = 0ull;
     par[i] = 0;
 }

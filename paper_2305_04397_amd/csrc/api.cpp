@@ -18,6 +18,11 @@ morap_ctx::~morap_ctx() {
         if (chunk_graph[g]) (void)hipGraphDestroy(chunk_graph[g]);
     }
     for (hipEvent_t e : event_pool) (void)hipEventDestroy(e);
+    for (int i = 0; i < 3; ++i) {
+        if (join_event[i]) (void)hipEventDestroy(join_event[i]);
+        if (side[i]) (void)hipStreamDestroy(side[i]);
+    }
+    if (fork_event) (void)hipEventDestroy(fork_event);
     if (prop_mlp) proposer_destroy(prop_mlp);
     if (own_stream && stream) (void)hipStreamDestroy(stream);
 }

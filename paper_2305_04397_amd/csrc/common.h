@@ -363,6 +363,11 @@ struct morap_ctx {
     morap::DevBuf d_live_tiles;
     std::vector<int8_t> h_mu;                       // policies of the last evaluate
 
+    // streams beside the context's own for launches that share nothing
+    // (created when first needed; always joined back before a call returns)
+    hipStream_t side[3] = {nullptr, nullptr, nullptr};
+    hipEvent_t fork_event = nullptr, join_event[3] = {nullptr, nullptr, nullptr};
+
     // value iteration with the values in LDS (built per upload)
     morap::ResidentPlan resident_plan;
     morap::DevBuf d_weights;                        // [K][d] weights of the solve

@@ -292,6 +292,47 @@ static FILE* sweep_log() {
     return f;
 }
 
+// Launches that share nothing (products of different sizes take different
+// kernels) spread over the context's stream and up to three beside it: one
+// after the other on one stream each would wait for the last workgroup of
+// the one before (64 columns of 10 x 20 products: 3.18 ms a solve on one
+// stream, 2.92 on two, 2.87 on four; a support step of 12 x 24: 42.2 / 37.7 /
+// 37.1 ms).  Work enqueued on the stream before the fork is seen by all;
+// join() (or the end of the scope) makes the stream wait for them.
+struct Fork {
+    morap_ctx* c;
+    int n;   // streams beside the context's in use
+    Fork(morap_ctx* ctx, int launches) : c(ctx), n(std::max(0, std::min(launches - 1, 3))) {
+        if (n == 0) return;
+        if (!c->fork_event) MORAP_HIP(hipEventCreateWithFlags(&c->fork_event, hipEventDisableTiming));
+        for (int i = 0; i < n; ++i) {
+            if (!c->side[i]) MORAP_HIP(hipStreamCreateWithFlags(&c->side[i], hipStreamNonBlocking));
+            if (!c->join_event[i]) MORAP_HIP(hipEventCreateWithFlags(&c->join_event[i], hipEventDisableTiming));
+        }
+        const int used = n;
+        n = 0;
+        MORAP_HIP(hipEventRecord(c->fork_event, c->stream));
+        for (int i = 0; i < used; ++i) {
+            MORAP_HIP(hipStreamWaitEvent(c->side[i], c->fork_event, 0));
+            n = i + 1;
+        }
+    }
+    Fork(const Fork&) = delete;
+    Fork& operator=(const Fork&) = delete;
+    ~Fork() {
+        for (int i = 0; i < n; ++i)   // (an error on the way out: nothing may outlive the call)
+            (void)hipStreamSynchronize(c->side[i]);
+    }
+    hipStream_t stream(int i) const { return i % (n + 1) == 0 ? c->stream : c->side[i % (n + 1) - 1]; }
+    void join() {
+        for (int i = 0; i < n; ++i) {
+            MORAP_HIP(hipEventRecord(c->join_event[i], c->side[i]));
+            MORAP_HIP(hipStreamWaitEvent(c->stream, c->join_event[i], 0));
+        }
+        n = 0;
+    }
+};
+
 // one chunk of `n` sweeps (n even): sweep, converge, compact per sweep;
 // `ev` (optional) receives an event pair around every sweep kernel
 static void enqueue_chunk(morap_ctx* c, ValueSet& vs, const uint8_t* mask, const Variant& v, double eps, int n,
@@ -412,6 +453,10 @@ static const Variant& choose_variant(morap_ctx* c, ValueSet& vs, const uint8_t* 
     const int64_t key = ((int64_t)vs.prec << 40) | ((int64_t)(refine ? 1 : (mask ? 2 : 0)) << 32) | vs.Kp;
     for (auto& t : c->tuned)
         if (t.first == key) return variant_by_id(t.second);
+    // the largest products beside products in LDS: the wave gather sweep (two
+    // states in flight) hands over to the LDS-staged kernel at the first
+    // check that finds under 20 % of the tiles active, as a rule the first
+    if (mask && !refine && c->has_halo && vs.prec == MORAP_F32 && vs.Kp % 64 == 0) return variant_by_id(37);
     auto cand = candidates(vs.Kp, refine, c->has_blocks, c->has_halo && vs.prec == MORAP_F32);
     MORAP_CHECK(!cand.empty(), MORAP_E_UNSUPPORTED, "no sweep variant for this column count");
     int best = cand[0].id;
@@ -587,7 +632,10 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
         a.sweep0 = (int)s0;
         a.sweep1 = (int)done;
         a.last = done == limit ? 1 : 0;
-        for (const auto& l : part.launches) {
+        // (timed launches one by one)
+        Fork fork(c, o.time_kernels ? 1 : (int)part.launches.size());
+        for (size_t q = 0; q < part.launches.size(); ++q) {
+            const auto& l = part.launches[q];
             a.order = plan.order.as<int32_t>() + l.begin;
             a.n_models = l.n;
             if (o.time_kernels) {
@@ -595,10 +643,12 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
                 held.v.back().second = take_event(c);
                 MORAP_HIP(hipEventRecord(held.v.back().first, c->stream));
             }
-            if (l.columns > 0) k::resident_large(c->stream, vs.prec, wide ? l.columns : 1, l.max_states, a);
-            else k::resident(c->stream, vs.prec, l.fast, wide, l.max_states, a);
+            const hipStream_t s = fork.stream((int)q);
+            if (l.columns > 0) k::resident_large(s, vs.prec, wide ? l.columns : 1, l.max_states, a);
+            else k::resident(s, vs.prec, l.fast, wide, l.max_states, a);
             if (o.time_kernels) MORAP_HIP(hipEventRecord(held.v.back().second, c->stream));
         }
+        fork.join();
         read_results(c, vs);
         ps = c->h_pair_sweeps.as<int32_t>();
         running = 0;
@@ -1211,7 +1261,9 @@ struct Instances {
         }
         a.sweep0 = (int)s0;
         a.sweep1 = (int)s1;
-        for (const Run& r : vi) {
+        Fork fork(c, ev ? 1 : (int)vi.size());   // (timed launches one by one)
+        for (size_t q = 0; q < vi.size(); ++q) {
+            const Run& r = vi[q];
             a.order = d_order + r.begin;
             a.n_models = r.n;
             if (ev) {
@@ -1219,10 +1271,11 @@ struct Instances {
                 ev->back().second = take_event(c);
                 MORAP_HIP(hipEventRecord(ev->back().first, c->stream));
             }
-            if (r.large) k::resident_inst_large(c->stream, r.max_states, a);
-            else k::resident_inst(c->stream, r.fast, r.max_states, a);
+            if (r.large) k::resident_inst_large(fork.stream((int)q), r.max_states, a);
+            else k::resident_inst(fork.stream((int)q), r.fast, r.max_states, a);
             if (ev) MORAP_HIP(hipEventRecord(ev->back().second, c->stream));
         }
+        fork.join();
     }
 
     // sweeps the value iteration took as the tiled iteration counts them
@@ -1528,11 +1581,13 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
     ia.sweeps = ev_sweeps;
     ia.eps = o.eps_eval;
     auto launch = [&](const std::vector<Instances::Run>& runs, auto&& kernel) {
-        for (const auto& r : runs) {
-            ia.order = I.d_order + r.begin;
-            ia.n = r.n;
-            kernel(s, r.max_states, ia);
+        Fork fork(c, (int)runs.size());
+        for (size_t q = 0; q < runs.size(); ++q) {
+            ia.order = I.d_order + runs[q].begin;
+            ia.n = runs[q].n;
+            kernel(fork.stream((int)q), runs[q].max_states, ia);
         }
+        fork.join();
     };
     // (a policy instance's LDS use follows its size: classes of one, two, four
     // and more workgroups a compute unit)

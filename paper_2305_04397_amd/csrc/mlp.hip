@@ -13,15 +13,21 @@
 // biases, logits, softmax, weight gradients and Adam state, FP32 master
 // weights (the BF16 copies are refreshed by every Adam step).
 //
-// Kernels:
+// Kernels, for networks of up to 1024 inputs and 512 outputs:
+//   * mlp_rows: everything that is local to a row, 16 rows per workgroup: the
+//     four layers, softmax, and for training the loss, the output gradient and
+//     its way back to the first layer, with the activations in LDS and the
+//     weights read from L2 in the order the matrix instruction takes them;
+//   * weight_grads: the weight and bias gradients of all layers in one launch;
+//   * adam: the update of every parameter and its BF16 copies.
+// Kernels of larger networks, layer by layer:
 //   * gemm_bf16: C[M][N] = sum_k A(m, k) B(k, n) for strided BF16 operands,
 //     one wave per 16 x 64 output strip (4 MFMA accumulators), with the
 //     epilogue of the layer: +bias and ReLU to BF16 (hidden forward), +bias to
 //     FP32 (logits), ReLU-derivative mask to BF16 (backward data), FP32 store
 //     (weight gradients);
 //   * softmax_xent: per row softmax, cross-entropy and (P - T) / B;
-//   * bias_grad: column sums of a BF16 gradient;
-//   * adam: the update of every parameter and its BF16 copy.
+//   * bias_grad: column sums of a BF16 gradient.
 #include "common.h"
 
 #include <mutex>
@@ -168,11 +174,6 @@ __global__ void bias_grad(const uint16_t* G, float* db, int n, int cols) {
     db[c] = s;
 }
 
-__global__ void to_bf16_kernel(const float* in, uint16_t* out, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = f2bf(in[i]);
-}
-
 // network input: (x - mu) / sd per column, rounded to BF16
 __global__ void input_kernel(const float* x, const float* mu, const float* sd, uint16_t* out, int64_t n,
                              int cols) {
@@ -182,10 +183,49 @@ __global__ void input_kernel(const float* x, const float* mu, const float* sd, u
     out[i] = f2bf((x[i] - mu[c]) / sd[c]);
 }
 
+// Places of a weight in the BF16 copies the matrix instructions read: a
+// fragment is 16 outputs x 32 inputs as lane (l % 16, l / 16) holds it, 8
+// consecutive inputs of one output, fragments of an output tile in input
+// order (forward); the backward copy is the same of the transposed matrix.
+struct Packed {
+    uint16_t *fwd[NLAYER], *bwd[NLAYER];   // bwd[0] unused
+    int ks_f[NLAYER], ks_b[NLAYER];        // 32-deep steps
+    int fan_in[NLAYER];
+    int64_t w_off[NLAYER], b_off[NLAYER];
+};
+__device__ __forceinline__ int64_t frag_at(int out, int in, int ks) {
+    return (((int64_t)(out >> 4) * ks + (in >> 5)) * 64 + ((in & 31) >> 3) * 16 + (out & 15)) * 8 + (in & 7);
+}
+__device__ __forceinline__ void store_copies(const Packed& k, uint16_t* pb, int64_t i, float v) {
+#pragma unroll
+    for (int l = 0; l < NLAYER; ++l) {
+        if (i < k.w_off[l] || i >= k.b_off[l]) continue;
+        const uint16_t h = f2bf(v);
+        if (pb) {
+            pb[i] = h;
+            return;
+        }
+        const int e = (int)(i - k.w_off[l]), out = e / k.fan_in[l], in = e - out * k.fan_in[l];
+        k.fwd[l][frag_at(out, in, k.ks_f[l])] = h;
+        if (l > 0) k.bwd[l][frag_at(in, out, k.ks_b[l])] = h;
+    }
+}
+
+__global__ void copy_kernel(const float* from, float* to, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) to[i] = from[i];
+}
+
+// BF16 copies of the FP32 parameters: row-major (pb, larger networks) or packed
+__global__ void copies_kernel(const float* p, uint16_t* pb, Packed k, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) store_copies(k, pb, i, p[i]);
+}
+
 // Adam with bias correction (c1 = 1 - beta1^t, c2 = 1 - beta2^t); weights
-// (is_w != 0) refresh their BF16 copy
-__global__ void adam_kernel(float* p, const float* g, float* m, float* v, uint16_t* pb, const uint8_t* is_w,
-                            int64_t n, float lr, float b1, float b2, float eps, float c1, float c2) {
+// refresh their BF16 copies
+__global__ void adam_kernel(float* p, const float* g, float* m, float* v, uint16_t* pb, Packed k, int64_t n, float lr,
+                            float b1, float b2, float eps, float c1, float c2) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float gi = g[i];
@@ -195,7 +235,336 @@ __global__ void adam_kernel(float* p, const float* g, float* m, float* v, uint16
     v[i] = vi;
     const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
     p[i] = pi;
-    if (is_w[i]) pb[i] = f2bf(pi);
+    store_copies(k, pb, i, pi);
+}
+
+// ---------------------------------------------------------------------------
+// the fused kernels
+// ---------------------------------------------------------------------------
+// The largest network: at both limits a training workgroup holds 158 of the
+// CU's 160 KB of LDS.  A step of 4,096 host rows there takes 1.44 ms (64 rows:
+// 0.29 ms); one input more, layer by layer, 6.5 ms (0.98 ms).
+constexpr int FUSED_IN = 1024, FUSED_OUT = 512;
+constexpr int ROWS = 16;                          // rows of a workgroup
+constexpr int LDH = HID + 8;                      // LDS row of a hidden layer (8: banks)
+constexpr int KSH = HID / 32;
+
+struct RowArgs {
+    const float *x, *mu, *sd, *T;
+    const uint16_t* fwd[NLAYER];
+    const uint16_t* bwd[NLAYER];
+    const float* bias[NLAYER];
+    float *prob, *loss;
+    // training: transposed copies [features][ld] of the input, the hidden
+    // activations and the gradients of the layers' outputs; rows past n are 0
+    uint16_t *xt, *ht[NLAYER - 1], *gt[NLAYER];
+    int n, n_in, d, ld;
+    float inv_b;
+};
+
+__host__ __device__ constexpr int up(int v, int to) { return (v + to - 1) / to * to; }
+// LDS of a workgroup, in bytes: input, three hidden layers, logits; training:
+// targets, output gradient, two hidden gradients
+__host__ __device__ inline int rows_ldx(int n_in) { return up(n_in, 32) + 8; }
+__host__ __device__ inline int rows_ldz(int d) { return up(d, 16) + 4; }
+__host__ __device__ inline int rows_ldg(int d) { return up(d, 32) + 8; }
+inline size_t rows_lds(int n_in, int d, bool train) {
+    return (size_t)ROWS * (rows_ldx(n_in) * 2 + (NLAYER - 1) * LDH * 2 + rows_ldz(d) * 4 +
+                           (train ? rows_ldz(d) * 4 + rows_ldg(d) * 2 + 2 * LDH * 2 : 0));
+}
+
+__device__ __forceinline__ s16x8 frag(const uint16_t* w, int64_t at, int lane) {
+    return *reinterpret_cast<const s16x8*>(w + (at * 64 + lane) * 8);
+}
+__device__ __forceinline__ f32x4 mfma(const s16x8& a, const s16x8& b, const f32x4& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// 16 rows, one 16-wide output tile per wave and layer.  The rows are few and
+// the weights (0.3-0.4 MB) are read from L2 by every workgroup, so what bounds
+// it is the latency of a layer's loads: each wave has the next layer's
+// fragments on their way before the barrier that ends a layer.  Products are
+// accumulated over the inputs in ascending steps of 32.  4,000 rows of
+// 182 -> 150: 13.5 us; 4,096 training rows of 62 -> 30: 22 us.  (Layer by
+// layer, with the activations in memory, a pass of 64 rows of 62 -> 30 took
+// 42.7 us and takes 4.3.)
+template <bool TRAIN>
+__global__ void __launch_bounds__(1024) mlp_rows(RowArgs a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, kg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row0 = blockIdx.x * ROWS;
+    const int ldx = rows_ldx(a.n_in), ldz = rows_ldz(a.d), ldg = rows_ldg(a.d);
+    uint16_t* xs = reinterpret_cast<uint16_t*>(lds);
+    uint16_t* h = xs + ROWS * ldx;                                   // [3][ROWS][LDH]
+    float* z = reinterpret_cast<float*>(h + (NLAYER - 1) * ROWS * LDH);
+    float* tt = z + ROWS * ldz;
+    uint16_t* go = reinterpret_cast<uint16_t*>(tt + ROWS * ldz);     // [ROWS][ldg]
+    uint16_t* gh = go + ROWS * ldg;                                  // [2][ROWS][LDH]
+
+    s16x8 w[KSH];
+    auto ahead = [&](const uint16_t* W, int tile) {   // a 256-input layer's fragments of one tile
+#pragma unroll
+        for (int s = 0; s < KSH; ++s) w[s] = frag(W, (int64_t)tile * KSH + s, lane);
+    };
+    auto product = [&](const uint16_t* in) {          // 16 x 256 in LDS times w
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KSH; ++s)
+            acc = mfma(*reinterpret_cast<const s16x8*>(in + r * LDH + s * 32 + 8 * kg), w[s], acc);
+        return acc;
+    };
+    // result lanes: rows 4 kg .. + 3 of column c; transposed: one 8-byte store
+    auto put = [&](uint16_t* out, uint16_t* t, int c, const float (&v)[4]) {
+        ushort4 q;
+        uint16_t* e = reinterpret_cast<uint16_t*>(&q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint16_t b = f2bf(v[i]);
+            out[(4 * kg + i) * LDH + c] = b;
+            e[i] = row0 + 4 * kg + i < a.n ? b : (uint16_t)0;
+        }
+        if (TRAIN) *reinterpret_cast<ushort4*>(t + (int64_t)c * a.ld + row0 + 4 * kg) = q;
+    };
+
+    ahead(a.fwd[1], wave);
+    // input: (x - mu) / sd per column, rounded to BF16; 0 in the padding
+    for (int i = tid; i < ROWS * up(a.n_in, 32); i += 1024) {
+        const int q = i / up(a.n_in, 32), c = i - q * up(a.n_in, 32);
+        const bool in = c < a.n_in && row0 + q < a.n;
+        xs[q * ldx + c] = in ? f2bf((a.x[(int64_t)(row0 + q) * a.n_in + c] - a.mu[c]) / a.sd[c]) : (uint16_t)0;
+    }
+    __syncthreads();
+    if (TRAIN)
+        for (int c = tid; c < a.n_in; c += 1024) {
+            __align__(16) uint16_t v[ROWS];
+#pragma unroll
+            for (int q = 0; q < ROWS; ++q) v[q] = xs[q * ldx + c];
+            uint4* o = reinterpret_cast<uint4*>(a.xt + (int64_t)c * a.ld + row0);
+            o[0] = reinterpret_cast<const uint4*>(v)[0];
+            o[1] = reinterpret_cast<const uint4*>(v)[1];
+        }
+    auto hidden = [&](const f32x4& acc, int l) {
+        const int c = wave * 16 + r;
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = fmaxf(acc[i] + a.bias[l][c], 0.f);
+        put(h + l * ROWS * LDH, TRAIN ? a.ht[l] : nullptr, c, v);
+    };
+    {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        const int ks = up(a.n_in, 32) / 32;
+#pragma unroll 4
+        for (int s = 0; s < ks; ++s)
+            acc = mfma(*reinterpret_cast<const s16x8*>(xs + r * ldx + s * 32 + 8 * kg),
+                       frag(a.fwd[0], (int64_t)wave * ks + s, lane), acc);
+        hidden(acc, 0);
+    }
+    __syncthreads();
+    {
+        const f32x4 acc = product(h);
+        ahead(a.fwd[2], wave);
+        hidden(acc, 1);
+    }
+    __syncthreads();
+    const int tiles = up(a.d, 16) / 16;
+    {
+        const f32x4 acc = product(h + ROWS * LDH);
+        if (wave < tiles) ahead(a.fwd[3], wave);
+        hidden(acc, 2);
+    }
+    __syncthreads();
+    for (int t = wave; t < tiles; t += 16) {
+        if (t != wave) ahead(a.fwd[3], t);
+        const f32x4 acc = product(h + 2 * ROWS * LDH);
+        const int c = t * 16 + r;
+        if (c < a.d)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z[(4 * kg + i) * ldz + c] = acc[i] + a.bias[3][c];
+    }
+    if (TRAIN) {
+        for (int i = tid; i < ROWS * a.d; i += 1024) {
+            const int q = i / a.d, c = i - q * a.d;
+            tt[q * ldz + c] = row0 + q < a.n ? a.T[(int64_t)(row0 + q) * a.d + c] : 0.f;
+        }
+        for (int i = tid; i < ROWS * ldg; i += 1024) go[i] = 0;   // the padding
+    }
+    __syncthreads();
+
+    // softmax, one row per wave: sums in column order, as one thread adds them
+    {
+        const int row = row0 + wave;
+        float* zr = z + wave * ldz;
+        float mx = -INFINITY;
+        for (int c = lane; c < a.d; c += 64) mx = fmaxf(mx, zr[c]);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        float zc[FUSED_OUT / 64], ec[FUSED_OUT / 64];
+#pragma unroll
+        for (int j = 0; j < FUSED_OUT / 64; ++j) {
+            const int c = j * 64 + lane;
+            zc[j] = ec[j] = 0.f;
+            if (j * 64 >= a.d) continue;
+            if (c < a.d) {
+                zc[j] = zr[c];
+                ec[j] = expf(zc[j] - mx);
+                zr[c] = ec[j];
+            }
+        }
+        float sum = 0.f;
+        int c = 0;
+        for (; c + 4 <= a.d; c += 4) {
+            const float4 v = *reinterpret_cast<const float4*>(zr + c);
+            sum += v.x;
+            sum += v.y;
+            sum += v.z;
+            sum += v.w;
+        }
+        for (; c < a.d; ++c) sum += zr[c];
+        const float lse = logf(sum);
+        const float* tr = tt + wave * ldz;
+#pragma unroll
+        for (int j = 0; j < FUSED_OUT / 64; ++j) {
+            const int k = j * 64 + lane;
+            if (j * 64 >= a.d) continue;
+            if (k < a.d && row < a.n) {
+                const float p = ec[j] / sum;
+                a.prob[(int64_t)row * a.d + k] = p;
+                if (TRAIN) {
+                    const float t = tr[k];
+                    go[wave * ldg + k] = f2bf((p - t) * a.inv_b);
+                    zr[k] = zc[j] - mx - lse;
+                }
+            }
+        }
+        if (TRAIN && row < a.n) {
+            float l = 0.f;
+            for (int k = 0; k < a.d; ++k) {
+                const float t = tr[k], v = zr[k];
+                if (t != 0.f) l -= t * v;
+            }
+            if (lane == 0) a.loss[row] = l;
+        }
+    }
+    if (!TRAIN) return;
+    // the output gradient back through the layers
+    ahead(a.bwd[2], wave);   // (layer 2's; layer 3's input is the d outputs)
+    __syncthreads();
+    for (int c = tid; c < a.d; c += 1024) {
+        __align__(16) uint16_t v[ROWS];
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) v[q] = go[q * ldg + c];
+        uint4* o = reinterpret_cast<uint4*>(a.gt[3] + (int64_t)c * a.ld + row0);
+        o[0] = reinterpret_cast<const uint4*>(v)[0];
+        o[1] = reinterpret_cast<const uint4*>(v)[1];
+    }
+    // gradient of layer l's output, masked by its activation
+    auto masked = [&](const f32x4& acc, int l, uint16_t* out) {
+        const int c = wave * 16 + r;
+        const uint16_t* hl = h + l * ROWS * LDH;
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = bf2f(hl[(4 * kg + i) * LDH + c]) > 0.f ? acc[i] : 0.f;
+        put(out, a.gt[l], c, v);
+    };
+    {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        const int ks = up(a.d, 32) / 32;
+#pragma unroll 4
+        for (int s = 0; s < ks; ++s)
+            acc = mfma(*reinterpret_cast<const s16x8*>(go + r * ldg + s * 32 + 8 * kg),
+                       frag(a.bwd[3], (int64_t)wave * ks + s, lane), acc);
+        masked(acc, 2, gh);
+    }
+    __syncthreads();
+    {
+        const f32x4 acc = product(gh);
+        ahead(a.bwd[1], wave);
+        masked(acc, 1, gh + ROWS * LDH);
+    }
+    __syncthreads();
+    masked(product(gh + ROWS * LDH), 0, gh);
+}
+
+// Weight gradients dW[N][K] = sum over the rows of G[r][N] H[r][K], and bias
+// gradients sum over the rows of G, of all layers in one launch: a workgroup
+// per 32 x 32 tile, its 16 waves taking every 16th step of 32 rows and adding
+// up in a fixed order.  The outputs are few (170 tiles at 62 -> 30) and the
+// rows many, so the split over rows is what gives the loads company: 18.6 us
+// at 4,096 rows, the transposed copies making every fragment one 16-byte load
+// (a step with gradients took 4.32 ms with one workgroup per tile and strided
+// operands, and takes 0.17).  16 short sums also err less than one long one:
+// 3e-8 against 3e-7 at most, on sums of up to 0.6.
+struct GradLayer {
+    const uint16_t *g, *h;   // [N][ld], [K][ld]
+    float *dw, *db;
+    int N, K, first;         // first workgroup
+};
+struct GradArgs {
+    GradLayer l[NLAYER];
+    int ld;
+};
+__global__ void __launch_bounds__(1024) weight_grads(GradArgs a) {
+    __shared__ f32x4 red[8][6][64];
+    int q = 0;
+#pragma unroll
+    for (int l = 1; l < NLAYER; ++l)
+        if ((int)blockIdx.x >= a.l[l].first) q = l;
+    const GradLayer L = a.l[q];
+    const int tiles_k = (L.K + 31) / 32, b = (int)blockIdx.x - L.first;
+    const int n0 = b / tiles_k * 32, k0 = b % tiles_k * 32;
+    const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool bias = k0 == 0;
+    const uint16_t* gp[2];
+    const uint16_t* hp[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {   // (rows past the last repeat it; not stored)
+        gp[i] = L.g + (int64_t)min(n0 + 16 * i + r, L.N - 1) * a.ld + 8 * kg;
+        hp[i] = L.h + (int64_t)min(k0 + 16 * i + r, L.K - 1) * a.ld + 8 * kg;
+    }
+    s16x8 ones;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ones[i] = (short)0x3F80;
+    f32x4 acc[6] = {};   // [2 x 2] tiles, then the bias of both
+    for (int s = wave; s < a.ld / 32; s += 16) {
+        s16x8 g[2], h[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            g[i] = *reinterpret_cast<const s16x8*>(gp[i] + s * 32);
+            h[i] = *reinterpret_cast<const s16x8*>(hp[i] + s * 32);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[2 * i + j] = mfma(g[i], h[j], acc[2 * i + j]);
+            if (bias) acc[4 + i] = mfma(g[i], ones, acc[4 + i]);
+        }
+    }
+    for (int half = 8; half >= 1; half >>= 1) {
+        if (wave >= half && wave < 2 * half)
+#pragma unroll
+            for (int t = 0; t < 6; ++t) red[wave - half][t][lane] = acc[t];
+        __syncthreads();
+        if (wave < half)
+#pragma unroll
+            for (int t = 0; t < 6; ++t) acc[t] += red[wave][t][lane];
+        __syncthreads();
+    }
+    if (wave != 0) return;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int n = n0 + 16 * i + 4 * kg + e;
+            if (n >= L.N) continue;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int k = k0 + 16 * j + r;
+                if (k < L.K) L.dw[(int64_t)n * L.K + k] = acc[2 * i + j][e];
+            }
+            if (bias && r == 0) L.db[n] = acc[4 + i][e];
+        }
 }
 
 unsigned blocks_for(int64_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
@@ -209,16 +578,69 @@ uint64_t splitmix64(uint64_t x) {
 
 }  // namespace
 
+// Host rows reach the device through pinned memory, checked while they are
+// copied there; calls of more than this many floats are checked in place and
+// copied from where they are (pinned memory is kept, so it is bounded).
+constexpr size_t STAGED = (size_t)8 << 20;
+
+// infinite or NaN among X[0 .. count), which is copied to `to` (or not: null)
+static bool nonfinite(const float* __restrict X, float* __restrict to, size_t count) {
+    uint32_t bad = 0;
+    auto one = [&](size_t i) {
+        uint32_t u;
+        std::memcpy(&u, X + i, 4);
+        bad |= (u & 0x7F800000u) == 0x7F800000u ? 1u : 0u;
+    };
+    if (!to)
+        for (size_t i = 0; i < count; ++i) one(i);
+    else
+        for (size_t i = 0; i < count; ++i) {
+            one(i);
+            to[i] = X[i];
+        }
+    return bad != 0;
+}
+// Rows of T are >= 0 and sum to 1 (added in column order, four rows at a time
+// for the adds' latency).
+static void check_targets(const float* T, int n, int d) {
+    bool sums = true;
+    for (int r = 0; r < n; r += 4) {
+        const float* t[4];
+        for (int q = 0; q < 4; ++q) t[q] = T + (size_t)std::min(r + q, n - 1) * d;
+        double sum[4] = {0, 0, 0, 0};
+        bool ok = true;
+        for (int k = 0; k < d; ++k)
+            for (int q = 0; q < 4; ++q) {
+                ok &= t[q][k] >= 0.f && t[q][k] <= std::numeric_limits<float>::max();
+                sum[q] += t[q][k];
+            }
+        MORAP_CHECK(ok, MORAP_E_INVALID, "targets must be finite and >= 0");
+        for (int q = 0; q < 4; ++q) sums &= std::fabs(sum[q] - 1.0) <= 1e-4;
+        MORAP_CHECK(sums, MORAP_E_INVALID, "target rows must sum to 1");
+    }
+}
+static void check_rows(const float* X, const float* T, int n, int n_in, int d) {
+    MORAP_CHECK(X && n >= 1, MORAP_E_INVALID, "need X and n >= 1");
+    MORAP_CHECK(!nonfinite(X, nullptr, (size_t)n * n_in), MORAP_E_INVALID, "X must be finite");
+    if (T) check_targets(T, n, d);
+}
+
 struct Proposer {
     int n_in = 0, d = 0;
     int fan_in[NLAYER], fan_out[NLAYER];
     int64_t w_off[NLAYER], b_off[NLAYER], n_params = 0;
     int64_t t = 0;                    // Adam steps taken
-    DevBuf p32, pb16, grad, m, v, is_w;
+    bool fused;                       // small enough for the fused kernels
+    DevBuf p32, pb16, grad, m, v;     // (pb16: larger networks)
+    DevBuf packed;                    // the weights' BF16 fragments
+    Packed frags{};
     std::vector<float> h_mu, h_sd;    // input standardisation (x - mu) / sd
     DevBuf mu, sd;
     int rows = 0;                     // capacity of the activation buffers
     DevBuf xb, h[NLAYER - 1], g[NLAYER - 1], logits, prob, target, gout, loss, xf;
+    int ld = 0;                       // rows of the transposed copies (fused training)
+    DevBuf xt, ht[NLAYER - 1], gt[NLAYER];
+    PinnedBuf stage_x, stage_t, stage_out;   // host rows on their way
 
     Proposer(int n_in_, int d_) : n_in(n_in_), d(d_) {
         const int sizes[NLAYER + 1] = {n_in, HID, HID, HID, d};
@@ -230,12 +652,37 @@ struct Proposer {
             b_off[l] = n_params;
             n_params += fan_out[l];
         }
+        fused = n_in <= FUSED_IN && d <= FUSED_OUT;
         p32.ensure(n_params * 4);
-        pb16.ensure(n_params * 2);
         grad.ensure(n_params * 4);
         m.ensure(n_params * 4);
         v.ensure(n_params * 4);
-        is_w.ensure(n_params);
+        int64_t at_f[NLAYER], at_b[NLAYER], elems = 0;
+        for (int l = 0; l < NLAYER; ++l) {
+            frags.fan_in[l] = fan_in[l];
+            frags.w_off[l] = w_off[l];
+            frags.b_off[l] = b_off[l];
+            frags.ks_f[l] = up(fan_in[l], 32) / 32;
+            frags.ks_b[l] = up(fan_out[l], 32) / 32;
+            at_f[l] = elems;
+            elems += (int64_t)up(fan_out[l], 16) / 16 * frags.ks_f[l] * 512;
+            at_b[l] = elems;
+            if (l > 0) elems += (int64_t)up(fan_in[l], 16) / 16 * frags.ks_b[l] * 512;
+        }
+        if (fused) {
+            packed.ensure((size_t)elems * 2);
+            for (int l = 0; l < NLAYER; ++l) {
+                frags.fwd[l] = packed.as<uint16_t>() + at_f[l];
+                frags.bwd[l] = packed.as<uint16_t>() + at_b[l];
+            }
+            // LDS beyond 64 KB has to be asked for (not while a stream captures)
+            MORAP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_rows<false>),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+            MORAP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_rows<true>),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+        } else {
+            pb16.ensure(n_params * 2);
+        }
         mu.ensure((size_t)n_in * 4);
         sd.ensure((size_t)n_in * 4);
         h_mu.assign(n_in, 0.f);
@@ -252,34 +699,92 @@ struct Proposer {
 
     void ensure_rows(int n) {
         if (n <= rows) return;
-        xb.ensure((size_t)n * n_in * 2);
         xf.ensure((size_t)n * n_in * 4);
-        for (int l = 0; l < NLAYER - 1; ++l) {
-            h[l].ensure((size_t)n * HID * 2);
-            g[l].ensure((size_t)n * HID * 2);
-        }
-        logits.ensure((size_t)n * d * 4);
         prob.ensure((size_t)n * d * 4);
         target.ensure((size_t)n * d * 4);
-        gout.ensure((size_t)n * d * 2);
         loss.ensure((size_t)n * 4);
+        if (!fused) {
+            xb.ensure((size_t)n * n_in * 2);
+            for (int l = 0; l < NLAYER - 1; ++l) {
+                h[l].ensure((size_t)n * HID * 2);
+                g[l].ensure((size_t)n * HID * 2);
+            }
+            logits.ensure((size_t)n * d * 4);
+            gout.ensure((size_t)n * d * 2);
+        }
         rows = n;
     }
 
     // upload FP32 parameters, reset Adam state, refresh BF16 copies
     void set(hipStream_t s, const float* host) {
         MORAP_HIP(hipMemcpyAsync(p32.p, host, n_params * 4, hipMemcpyHostToDevice, s));
-        std::vector<uint8_t> w(n_params, 0);
-        for (int l = 0; l < NLAYER; ++l)
-            std::fill(w.begin() + w_off[l], w.begin() + b_off[l], (uint8_t)1);
-        MORAP_HIP(hipMemcpyAsync(is_w.p, w.data(), n_params, hipMemcpyHostToDevice, s));
         MORAP_HIP(hipMemsetAsync(m.p, 0, n_params * 4, s));
         MORAP_HIP(hipMemsetAsync(v.p, 0, n_params * 4, s));
-        hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks_for(n_params)), dim3(256), 0, s, p32.as<float>(),
-                           pb16.as<uint16_t>(), n_params);
+        if (fused) MORAP_HIP(hipMemsetAsync(packed.p, 0, packed.bytes, s));   // the fragments' padding
+        hipLaunchKernelGGL(copies_kernel, dim3(blocks_for(n_params)), dim3(256), 0, s, p32.as<float>(),
+                           fused ? nullptr : pb16.as<uint16_t>(), frags, n_params);
         MORAP_HIP(hipGetLastError());
         MORAP_HIP(hipStreamSynchronize(s));
         t = 0;
+    }
+
+    // everything local to a row, 16 rows per workgroup (train: targets given)
+    void fused_rows(hipStream_t s, int n, const float* x, float* out, const float* T_dev) {
+        RowArgs a{};
+        a.x = x;
+        a.mu = mu.as<float>();
+        a.sd = sd.as<float>();
+        a.T = T_dev;
+        for (int l = 0; l < NLAYER; ++l) {
+            a.fwd[l] = frags.fwd[l];
+            a.bwd[l] = frags.bwd[l];
+            a.bias[l] = p32.as<float>() + b_off[l];
+        }
+        a.prob = out;
+        a.n = n;
+        a.n_in = n_in;
+        a.d = d;
+        a.inv_b = 1.f / (float)n;
+        const size_t bytes = rows_lds(n_in, d, T_dev != nullptr);
+        MORAP_CHECK(bytes <= 160 * 1024, MORAP_E_UNSUPPORTED, "the network does not fit the fused kernel");
+        if (!T_dev) {
+            hipLaunchKernelGGL(mlp_rows<false>, dim3(blocks_for(n, ROWS)), dim3(1024), bytes, s, a);
+            MORAP_HIP(hipGetLastError());
+            return;
+        }
+        // rows in whole steps of 32: the workgroups past the last row write zeros
+        a.loss = loss.as<float>();
+        a.ld = up(n, 32);
+        xt.ensure((size_t)n_in * a.ld * 2);
+        for (int l = 0; l < NLAYER; ++l) {
+            if (l < NLAYER - 1) ht[l].ensure((size_t)HID * a.ld * 2);
+            gt[l].ensure((size_t)fan_out[l] * a.ld * 2);
+            if (l < NLAYER - 1) a.ht[l] = ht[l].as<uint16_t>();
+            a.gt[l] = gt[l].as<uint16_t>();
+        }
+        a.xt = xt.as<uint16_t>();
+        ld = a.ld;
+        hipLaunchKernelGGL(mlp_rows<true>, dim3((unsigned)(a.ld / ROWS)), dim3(1024), bytes, s, a);
+        MORAP_HIP(hipGetLastError());
+    }
+
+    void fused_grads(hipStream_t s) {
+        GradArgs a{};
+        a.ld = ld;
+        int first = 0;
+        for (int l = 0; l < NLAYER; ++l) {
+            GradLayer& L = a.l[l];
+            L.g = gt[l].as<uint16_t>();
+            L.h = l == 0 ? xt.as<uint16_t>() : ht[l - 1].as<uint16_t>();
+            L.dw = grad.as<float>() + w_off[l];
+            L.db = grad.as<float>() + b_off[l];
+            L.N = fan_out[l];
+            L.K = fan_in[l];
+            L.first = first;
+            first += (up(L.N, 32) / 32) * (up(L.K, 32) / 32);
+        }
+        hipLaunchKernelGGL(weight_grads, dim3((unsigned)first), dim3(1024), 0, s, a);
+        MORAP_HIP(hipGetLastError());
     }
 
     const uint16_t* act(int l) const {   // input of layer l
@@ -301,7 +806,10 @@ struct Proposer {
     }
 
     // forward of n rows already in xf (FP32); logits then softmax into prob
-    void forward(hipStream_t s, int n, const float* T_dev) { forward_into(s, n, own_acts(), T_dev); }
+    void forward(hipStream_t s, int n, const float* T_dev) {
+        if (fused) fused_rows(s, n, xf.as<float>(), prob.as<float>(), T_dev);
+        else forward_into(s, n, own_acts(), T_dev);
+    }
 
     // the same into the buffers of `b` (T_dev, when given, also fills the
     // loss and the output gradient of the context's own buffers)
@@ -339,6 +847,7 @@ struct Proposer {
 
     // gradients of the mean cross-entropy into grad (after forward with T)
     void backward(hipStream_t s, int n) {
+        if (fused) return fused_grads(s);
         for (int l = NLAYER - 1; l >= 0; --l) {
             const uint16_t* G = l == NLAYER - 1 ? gout.as<uint16_t>() : g[l].as<uint16_t>();
             const int N = fan_out[l], K = fan_in[l];
@@ -386,35 +895,72 @@ struct Proposer {
         const float c1 = (float)(1.0 - std::pow((double)o.beta1, (double)t));
         const float c2 = (float)(1.0 - std::pow((double)o.beta2, (double)t));
         hipLaunchKernelGGL(adam_kernel, dim3(blocks_for(n_params)), dim3(256), 0, s, p32.as<float>(),
-                           grad.as<float>(), m.as<float>(), v.as<float>(), pb16.as<uint16_t>(), is_w.as<uint8_t>(),
+                           grad.as<float>(), m.as<float>(), v.as<float>(), fused ? nullptr : pb16.as<uint16_t>(), frags,
                            n_params, o.lr, o.beta1, o.beta2, o.adam_eps, c1, c2);
         MORAP_HIP(hipGetLastError());
+    }
+
+    // n x n_in host rows to xf; finite is what they have to be if `check`
+    void upload_rows(hipStream_t s, const float* X, int n, bool check) {
+        const size_t count = (size_t)n * n_in;
+        const bool staged = count <= STAGED;
+        float* to = nullptr;
+        if (staged) {
+            stage_x.ensure(count * 4);
+            to = stage_x.as<float>();
+        }
+        const bool bad = nonfinite(X, to, count);
+        MORAP_CHECK(!check || !bad, MORAP_E_INVALID, "X must be finite");
+        ensure_rows(n);
+        MORAP_HIP(hipMemcpyAsync(xf.p, staged ? to : X, count * 4, hipMemcpyHostToDevice, s));
+    }
+    void upload_targets(hipStream_t s, const float* T, int n) {
+        const size_t count = (size_t)n * d;
+        check_targets(T, n, d);
+        if (count <= STAGED) {
+            stage_t.ensure(count * 4);
+            std::memcpy(stage_t.p, T, count * 4);
+            T = stage_t.as<float>();
+        }
+        MORAP_HIP(hipMemcpyAsync(target.p, T, count * 4, hipMemcpyHostToDevice, s));
     }
 
     // one step on n host rows; returns the mean loss
     double step(hipStream_t s, const float* X, const float* T, int n, const morap_train_opts* o, bool apply,
                 float* grads_out) {
-        ensure_rows(n);
-        MORAP_HIP(hipMemcpyAsync(xf.p, X, (size_t)n * n_in * 4, hipMemcpyHostToDevice, s));
-        MORAP_HIP(hipMemcpyAsync(target.p, T, (size_t)n * d * 4, hipMemcpyHostToDevice, s));
+        upload_rows(s, X, n, true);
+        upload_targets(s, T, n);
         forward(s, n, target.as<float>());
         backward(s, n);
         if (apply) adam(s, *o);
-        std::vector<float> l(n);
-        MORAP_HIP(hipMemcpyAsync(l.data(), loss.p, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-        if (grads_out) MORAP_HIP(hipMemcpyAsync(grads_out, grad.p, n_params * 4, hipMemcpyDeviceToHost, s));
+        std::vector<float> far;
+        const size_t got = (size_t)n + (grads_out ? n_params : 0);
+        float* l;
+        if (got <= STAGED) {
+            stage_out.ensure(got * 4);
+            l = stage_out.as<float>();
+        } else {
+            far.resize(got);
+            l = far.data();
+        }
+        MORAP_HIP(hipMemcpyAsync(l, loss.p, (size_t)n * 4, hipMemcpyDeviceToHost, s));
+        if (grads_out) MORAP_HIP(hipMemcpyAsync(l + n, grad.p, n_params * 4, hipMemcpyDeviceToHost, s));
         MORAP_HIP(hipStreamSynchronize(s));
+        if (grads_out) std::memcpy(grads_out, l + n, n_params * 4);
         double sum = 0;
-        for (float x : l) sum += x;
+        for (int i = 0; i < n; ++i) sum += l[i];
         return sum / n;
     }
 
-    void infer(hipStream_t s, const float* X, int n, float* out) {
-        ensure_rows(n);
-        MORAP_HIP(hipMemcpyAsync(xf.p, X, (size_t)n * n_in * 4, hipMemcpyHostToDevice, s));
+    void infer(hipStream_t s, const float* X, int n, float* out, bool check) {
+        upload_rows(s, X, n, check);
         forward(s, n, nullptr);
-        MORAP_HIP(hipMemcpyAsync(out, prob.p, (size_t)n * d * 4, hipMemcpyDeviceToHost, s));
+        const size_t count = (size_t)n * d;
+        const bool staged = count <= STAGED;
+        if (staged) stage_out.ensure(count * 4);
+        MORAP_HIP(hipMemcpyAsync(staged ? stage_out.p : out, prob.p, count * 4, hipMemcpyDeviceToHost, s));
         MORAP_HIP(hipStreamSynchronize(s));
+        if (staged) std::memcpy(out, stage_out.p, count * 4);
     }
 };
 
@@ -462,27 +1008,12 @@ bool proposer_ready(const morap_ctx* c, int n_in, int d) {
 
 void proposer_infer_host(morap_ctx* c, const float* X, int n, float* out) {
     MORAP_CHECK(c->prop_mlp, MORAP_E_STATE, "no proposer");
-    c->prop_mlp->infer(c->stream, X, n, out);
+    c->prop_mlp->infer(c->stream, X, n, out, false);
 }
 
 static Proposer& need(morap_ctx* c) {
     MORAP_CHECK(c->prop_mlp, MORAP_E_STATE, "no proposer: call morap_proposer_init or morap_proposer_load");
     return *c->prop_mlp;
-}
-
-static void check_rows(const float* X, const float* T, int n, int n_in, int d) {
-    MORAP_CHECK(X && n >= 1, MORAP_E_INVALID, "need X and n >= 1");
-    for (int64_t i = 0; i < (int64_t)n * n_in; ++i) MORAP_CHECK(std::isfinite(X[i]), MORAP_E_INVALID, "X must be finite");
-    if (!T) return;
-    for (int r = 0; r < n; ++r) {
-        double sum = 0;
-        for (int k = 0; k < d; ++k) {
-            const float t = T[(int64_t)r * d + k];
-            MORAP_CHECK(std::isfinite(t) && t >= 0.f, MORAP_E_INVALID, "targets must be finite and >= 0");
-            sum += t;
-        }
-        MORAP_CHECK(std::fabs(sum - 1.0) <= 1e-4, MORAP_E_INVALID, "target rows must sum to 1");
-    }
 }
 
 static void check_opts(const morap_train_opts* o) {
@@ -555,9 +1086,9 @@ int morap_proposer_set_input_norm(morap_ctx* ctx, const float* mu, const float* 
 int morap_proposer_infer(morap_ctx* ctx, const float* X, int n, float* W_out) {
     return guarded(ctx, [&] {
         Proposer& p = need(ctx);
-        check_rows(X, nullptr, n, p.n_in, p.d);
+        MORAP_CHECK(X && n >= 1, MORAP_E_INVALID, "need X and n >= 1");
         MORAP_CHECK(W_out, MORAP_E_INVALID, "NULL output");
-        p.infer(ctx->stream, X, n, W_out);
+        p.infer(ctx->stream, X, n, W_out, true);
     });
 }
 
@@ -573,6 +1104,21 @@ int morap_proposer_infer_noalloc(morap_ctx* ctx, const float* X_dev, int n, floa
                                           " bytes of inference scratch; the fixed scratch holds " +
                                           std::to_string(kScratchBytes) + " bytes (at most " +
                                           std::to_string(max_rows) + " rows for this network)");
+        }
+        if (p.fused) {
+            // (the input may share memory with the output: then the rows'
+            // outputs wait in the scratch until every row has been read)
+            const uintptr_t x0 = reinterpret_cast<uintptr_t>(X_dev), w0 = reinterpret_cast<uintptr_t>(W_out_dev);
+            const size_t count = (size_t)n * p.d;
+            const bool shared = x0 < w0 + count * 4 && w0 < x0 + (size_t)n * p.n_in * 4;
+            float* out = shared ? reinterpret_cast<float*>(scratch_of(ctx->device)) : W_out_dev;
+            p.fused_rows(ctx->stream, n, X_dev, out, nullptr);
+            if (shared) {
+                hipLaunchKernelGGL(copy_kernel, dim3(blocks_for((int64_t)count)), dim3(256), 0, ctx->stream, out,
+                                   W_out_dev, (int64_t)count);
+                MORAP_HIP(hipGetLastError());
+            }
+            return;
         }
         unsigned char* base = scratch_of(ctx->device);
         Proposer::Acts a{};
@@ -595,7 +1141,7 @@ int morap_proposer_step(morap_ctx* ctx, const float* X, const float* T, int n, c
     return guarded(ctx, [&] {
         Proposer& p = need(ctx);
         MORAP_CHECK(T, MORAP_E_INVALID, "NULL targets");
-        check_rows(X, T, n, p.n_in, p.d);
+        MORAP_CHECK(X && n >= 1, MORAP_E_INVALID, "need X and n >= 1");
         if (apply) check_opts(opts);
         const double l = p.step(ctx->stream, X, T, n, opts, apply != 0, grads_out);
         if (loss_out) *loss_out = (float)l;

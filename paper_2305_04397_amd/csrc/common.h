@@ -237,6 +237,16 @@ struct ResidentPlan {
     Part part[2];                      // MORAP_F64, MORAP_F32
 };
 
+// Positions of a product's states sorted by block, each block's padded to
+// steps of 64 (empty: the product was not sorted, or fits no workgroup).
+struct SortedStates {
+    std::vector<int32_t> block;    // per step; with stages: its lowest << 20 and its highest << 26
+    std::vector<uint32_t> rec;     // [4 positions]; with stages: the state's << 16 in word 3
+    int32_t init = 0;              // position of the initial state
+};
+// The models `todo` sorted, [M]; by (block, stage) with `stage` (per state)
+std::vector<SortedStates> sort_models(const HostModels& hm, const std::vector<int32_t>& todo, const int32_t* stage);
+
 struct Proposer;  // mlp.hip
 
 // Stage retirement inside the iteration (the staged form of Alg. 3): the
@@ -252,6 +262,15 @@ struct StagedLayout {
     DevBuf tiles, tile_base, rec;         // unit tiles, [U+1], records [8S]
     DevBuf rows, states, csr, live;       // [U] rows, states, CSR bytes (FP64), 0 / -1 (dead model)
     DevBuf unit_base_d, init_unit;        // [M+1], [M] unit of the initial state (-1: done)
+    uint64_t tiles_gen = ~0ull;           // the same of the unit tiles (built when the batched sweeps run)
+    std::vector<int32_t> stage;           // [S]
+    std::vector<int32_t> h_init_unit, h_rows, h_states;   // on the host too
+    std::vector<int64_t> h_csr;
+    // products whose values stay in LDS: sorted states, and the models by
+    // falling number of positions (every live model, or none)
+    std::vector<int32_t> lds_order, lds_positions;   // [n], [M]
+    DevBuf order, lds_base, lds_block, lds_rec, lds_init;
+    PinnedBuf h_unit_sweeps;
     // solve state
     DevBuf active, res, ymax, wc, wp, final_par, pair_sweeps, best_res, stall;   // [U][Kp]
     DevBuf c_units;                       // [K][U] (cleared at the start, unused)
@@ -716,6 +735,18 @@ struct StageArgs {
     int M, K, Kp, out_par, slot, prec;   // slot: 9 or 10, the list count of this sweep
     double eps, unit;
 };
+// stage retirement with the values in LDS: best_res, stall and unit_sweeps per
+// (unit, column), big_block with the stages of a step
+struct StagedLdsArgs : ResidentArgs {
+    const int32_t* unit_base;   // [M+1]
+    const int32_t* init_unit;   // [M]
+    int32_t* unit_sweeps;       // [U][Kp] sweep in which the unit retired, 0 before
+};
+// columns per workgroup of a product of that many positions and stages (0: it
+// does not fit), one kernel class per (columns, threads)
+int staged_columns(int prec, int positions, int stages);
+int staged_threads(int prec, int columns, int positions);
+void staged_lds(hipStream_t s, int prec, int columns, int threads, int max_positions, const StagedLdsArgs& a);
 void stage_converge(hipStream_t s, const StageArgs& a);
 void stage_copy(hipStream_t s, const StageArgs& a);
 

@@ -14,6 +14,7 @@
 #include <cstring>
 #include <functional>
 #include <cmath>
+#include <numeric>
 #include <thread>
 #include <unordered_map>
 
@@ -805,15 +806,8 @@ static void order_records(morap_ctx* c) {
     hm.blk_rec.swap(out);
 }
 
-// Positions of a product's states sorted by block, each block's padded to
-// steps of 64.
-struct SortedStates {
-    std::vector<int32_t> block;    // per step
-    std::vector<uint32_t> rec;     // [4 positions]
-    int32_t init = 0;
-};
-
-static SortedStates sort_states(const HostModels& hm, int m) {
+// (stage, when given: the states of a block by stage, which the records name)
+static SortedStates sort_states(const HostModels& hm, int m, const int32_t* stage) {
     SortedStates out;
     const int32_t s0 = hm.state_base[m], n = hm.state_base[m + 1] - s0;
     const int32_t zero = (int32_t)hm.S();
@@ -838,8 +832,11 @@ static SortedStates sort_states(const HostModels& hm, int m) {
         first[b + 1] = first[b] + 64 * steps;
     }
     std::vector<int32_t> place((size_t)n), at((size_t)out.block.size() * 64, -1);
-    std::vector<int32_t> next(first.begin(), first.end() - 1);
-    for (int32_t l = 0; l < n; ++l) {
+    std::vector<int32_t> next(first.begin(), first.end() - 1), seq((size_t)n);
+    std::iota(seq.begin(), seq.end(), 0);
+    if (stage)
+        std::stable_sort(seq.begin(), seq.end(), [&](int32_t a, int32_t b) { return stage[s0 + a] < stage[s0 + b]; });
+    for (int32_t l : seq) {
         place[(size_t)l] = next[(size_t)which[(size_t)l]]++;
         at[(size_t)place[(size_t)l]] = l;
     }
@@ -854,9 +851,41 @@ static SortedStates sort_states(const HostModels& hm, int m) {
         out.rec[p * 4 + 1] = row(2) | row(3) << 16;
         out.rec[p * 4 + 2] = row(4) | ((uint32_t)r[6] & 31u) << 16;
         out.rec[p * 4 + 3] = last | (pad ? 0x80000000u : 0u);
+        if (!stage) continue;
+        const uint32_t st = (uint32_t)stage[s0 + (int32_t)last];
+        out.rec[p * 4 + 3] |= st << 16;
+        // lowest and highest stage of the step
+        uint32_t& b = reinterpret_cast<uint32_t&>(out.block[p / 64]);
+        if (p % 64 == 0) b = (b & 0xfffffu) | st << 20;
+        b = (b & 0x3ffffffu) | st << 26;
     }
     out.init = hm.init[m] >= 0 ? place[(size_t)(hm.init[m] - s0)] : 0;
     return out;
+}
+
+std::vector<SortedStates> sort_models(const HostModels& hm, const std::vector<int32_t>& todo, const int32_t* stage) {
+    std::vector<SortedStates> sorted((size_t)hm.M);
+    const int most = k::resident_most_positions();
+    std::atomic<size_t> next{0};
+    std::atomic<bool> bad{false};
+    auto worker = [&] {
+        try {
+            for (size_t t; (t = next++) < todo.size();) {
+                SortedStates x = sort_states(hm, todo[t], stage);
+                if (x.block.size() * 64 <= (size_t)most) sorted[(size_t)todo[t]] = std::move(x);
+            }
+        } catch (...) {
+            bad = true;
+        }
+    };
+    const int nt = (int)std::min<size_t>(std::max<size_t>(todo.size(), 1),
+                                         std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
+    std::vector<std::thread> th;
+    for (int k = 1; k < nt; ++k) th.emplace_back(worker);
+    worker();
+    for (auto& k : th) k.join();
+    MORAP_CHECK(!bad, MORAP_E_OOM, "sorting the states failed (host memory)");
+    return sorted;
 }
 
 // Which models' solves keep their values in LDS, per precision: products of
@@ -874,33 +903,16 @@ static void plan_resident(morap_ctx* c) {
         for (int m = 0; m < hm.M; ++m)
             if (states(m) > 0) order.push_back(m);
     // sorted states of the products some precision's first kernel cannot hold
-    std::vector<SortedStates> sorted((size_t)hm.M);
+    std::vector<SortedStates> sorted;
     {
         std::vector<int32_t> todo;
         const int most = k::resident_most_positions();
         for (int32_t m : order)
             if (fast(m) && states(m) > k::resident_capacity(MORAP_F64, true) && states(m) <= most) todo.push_back(m);
-        std::atomic<size_t> next{0};
-        std::atomic<bool> bad{false};
-        auto worker = [&] {
-            try {
-                for (size_t t; (t = next++) < todo.size();) {
-                    SortedStates x = sort_states(hm, todo[t]);
-                    // (blocks of a few states each would be mostly padding)
-                    const size_t pos = x.block.size() * 64;
-                    if (pos <= (size_t)most && pos <= (size_t)states(todo[t]) * 3 / 2) sorted[(size_t)todo[t]] = std::move(x);
-                }
-            } catch (...) {
-                bad = true;
-            }
-        };
-        const int nt = (int)std::min<size_t>(std::max<size_t>(todo.size(), 1),
-                                             std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
-        std::vector<std::thread> th;
-        for (int k = 1; k < nt; ++k) th.emplace_back(worker);
-        worker();
-        for (auto& k : th) k.join();
-        MORAP_CHECK(!bad, MORAP_E_OOM, "sorting the states failed (host memory)");
+        sorted = sort_models(hm, todo, nullptr);
+        // (blocks of a few states each would be mostly padding)
+        for (int32_t m : todo)
+            if (sorted[(size_t)m].block.size() * 64 > (size_t)states(m) * 3 / 2) sorted[(size_t)m] = SortedStates();
     }
     std::vector<int32_t> base((size_t)hm.M + 1, 0), block, init((size_t)hm.M, 0);
     std::vector<uint32_t> rec;

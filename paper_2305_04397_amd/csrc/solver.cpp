@@ -579,14 +579,9 @@ static void read_results(morap_ctx* c, const ValueSet& vs) {
     read_counters(c);
 }
 
-// The pairs of the plan's models to their stop with the values in LDS
-// (pair_sweeps cleared before), up to `limit` sweeps each; their statistics
-// as the batched sweeps count them.  The values land in vs.x[0].
-static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& part, const morap_vi_opts& o,
-                         bool warm, int64_t limit, int chunk, Stats& st) {
+static k::ResidentArgs resident_args(morap_ctx* c, ValueSet& vs, const k::ConvergeArgs& ca) {
     const HostModels& hm = c->hm;
     const bool f32 = vs.prec == MORAP_F32;
-    const k::ConvergeArgs ca = converge_args(c, vs, nullptr, o.eps_vi, 0, false);
     k::ResidentArgs a{};
     a.state_base = c->d_state_base.as<int32_t>();
     a.init = c->d_init.as<int32_t>();
@@ -619,6 +614,18 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
     a.unit = ca.unit;
     a.floor = ca.floor;
     a.stall_sweeps = ca.stall_sweeps;
+    return a;
+}
+
+// The pairs of the plan's models to their stop with the values in LDS
+// (pair_sweeps cleared before), up to `limit` sweeps each; their statistics
+// as the batched sweeps count them.  The values land in vs.x[0].
+static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& part, const morap_vi_opts& o,
+                         bool warm, int64_t limit, int chunk, Stats& st) {
+    const HostModels& hm = c->hm;
+    const bool f32 = vs.prec == MORAP_F32;
+    const ResidentPlan& plan = c->resident_plan;
+    k::ResidentArgs a = resident_args(c, vs, converge_args(c, vs, nullptr, o.eps_vi, 0, false));
     a.warm = warm ? 1 : 0;
     // several columns per workgroup share a state's probabilities and rows,
     // unless all pairs run at once anyway: one column each ends sooner then
@@ -2033,7 +2040,9 @@ static int model_stages(const HostModels& hm, int m, std::vector<int32_t>& stage
     return top + 1;
 }
 
-static void build_stage_layout(morap_ctx* c) {
+// The units of every model, and the states of products that fit LDS sorted
+// for the kernel that keeps their values there.
+static void build_stages(morap_ctx* c) {
     StagedLayout& L = c->staged;
     if (L.gen == c->load_gen) return;
     const HostModels& hm = c->hm;
@@ -2043,27 +2052,76 @@ static void build_stage_layout(morap_ctx* c) {
                 "stage retirement runs on the neighbourhood-block form (products built by morap_build_products)");
     MORAP_CHECK((int64_t)hm.states_sq.size() == 2 * S, MORAP_E_UNSUPPORTED,
                 "stage retirement needs the DFA location of every state");
-    std::vector<int32_t> stage((size_t)S, 0);
+    L.stage.assign((size_t)S, 0);
     L.unit_base.assign(M + 1, 0);
-    std::vector<int32_t> init_unit(M, -1);
+    L.h_init_unit.assign(M, -1);
     for (int m = 0; m < M; ++m) {
-        L.unit_base[m + 1] = L.unit_base[m] + model_stages(hm, m, stage);
-        if (hm.init[m] >= 0) init_unit[m] = L.unit_base[m] + stage[hm.init[m]];
+        L.unit_base[m + 1] = L.unit_base[m] + model_stages(hm, m, L.stage);
+        if (hm.init[m] >= 0) L.h_init_unit[m] = L.unit_base[m] + L.stage[hm.init[m]];
     }
     const int U = L.unit_base[M];
-    std::vector<int32_t> rows(U, 0), states(U, 0), live(U, -1);
-    std::vector<int64_t> csr(U, 0);
+    L.h_rows.assign(U, 0);
+    L.h_states.assign(U, 0);
+    L.h_csr.assign(U, 0);
     for (int m = 0; m < M; ++m)
         for (int32_t g = hm.state_base[m]; g < hm.state_base[m + 1]; ++g) {
-            const int u = L.unit_base[m] + stage[g];
+            const int u = L.unit_base[m] + L.stage[g];
             const int32_t nr = hm.state_row[g + 1] - hm.state_row[g];
             const int64_t nnz = hm.row_ptr[hm.state_row[g + 1]] - hm.row_ptr[hm.state_row[g]];
-            rows[u] += nr;
-            states[u] += 1;
+            L.h_rows[u] += nr;
+            L.h_states[u] += 1;
             // state_row + row_ptr + col (int32) + prob and two rewards (FP64)
-            csr[u] += 4 + 4 * (int64_t)nr + 12 * nnz + 16 * (int64_t)nr;
-            live[u] = hm.init[m] >= 0 ? 0 : -1;
+            L.h_csr[u] += 4 + 4 * (int64_t)nr + 12 * nnz + 16 * (int64_t)nr;
         }
+    hipStream_t s = c->stream;
+    upload_vec(L.unit_base_d, L.unit_base, s);
+    upload_vec(L.init_unit, L.h_init_unit, s);
+    L.lds_order.clear();
+    L.lds_positions.assign(M, 0);
+    std::vector<int32_t> base((size_t)M + 1, 0), block, init((size_t)M, 0);
+    std::vector<uint32_t> rec;
+    bool fit = k::has_grid_pattern(hm.blk_pattern) && hm.blk_agent.size() / 32 < (1u << 20);
+    for (int m = 0; m < M && fit; ++m) {
+        if (hm.init[m] < 0) continue;
+        fit = hm.blk_plain[(size_t)m] != 0 && L.unit_base[m + 1] - L.unit_base[m] <= 64 &&
+              hm.state_base[m + 1] - hm.state_base[m] <= k::resident_most_positions();
+        L.lds_order.push_back(m);
+    }
+    if (fit) {
+        const std::vector<SortedStates> sorted = sort_models(hm, L.lds_order, L.stage.data());
+        for (int m = 0; m < M; ++m) {
+            const SortedStates& x = sorted[(size_t)m];
+            block.insert(block.end(), x.block.begin(), x.block.end());
+            rec.insert(rec.end(), x.rec.begin(), x.rec.end());
+            init[(size_t)m] = x.init;
+            L.lds_positions[m] = 64 * (int32_t)x.block.size();
+            base[(size_t)m + 1] = base[(size_t)m] + L.lds_positions[m];
+        }
+        for (int32_t m : L.lds_order) fit = fit && L.lds_positions[m] > 0;
+        std::stable_sort(L.lds_order.begin(), L.lds_order.end(),
+                         [&](int32_t x, int32_t y) { return L.lds_positions[x] > L.lds_positions[y]; });
+    }
+    if (!fit) L.lds_order.clear();
+    upload_vec(L.order, L.lds_order, s);
+    upload_vec(L.lds_base, base, s);
+    upload_vec(L.lds_block, block, s);
+    upload_vec(L.lds_rec, rec, s);
+    upload_vec(L.lds_init, init, s);
+    MORAP_HIP(hipStreamSynchronize(s));
+    L.U = U;
+    L.gen = c->load_gen;
+}
+
+// The records regrouped by unit and the units' tiles (batched sweeps).
+static void build_unit_tiles(morap_ctx* c) {
+    StagedLayout& L = c->staged;
+    if (L.tiles_gen == c->load_gen) return;
+    const HostModels& hm = c->hm;
+    const int M = hm.M, U = L.U;
+    const std::vector<int32_t>& stage = L.stage;
+    std::vector<int32_t> live(U, -1);
+    for (int m = 0; m < M; ++m)
+        for (int u = L.unit_base[m]; u < L.unit_base[m + 1]; ++u) live[u] = hm.init[m] >= 0 ? 0 : -1;
     // records regrouped by unit inside every tile (stable), and the unit
     // tiles, consecutive per unit
     std::vector<int32_t> rec(hm.blk_rec.size());
@@ -2098,16 +2156,133 @@ static void build_stage_layout(morap_ctx* c) {
     upload_vec(L.tiles, tiles, s);
     upload_vec(L.tile_base, tile_base, s);
     upload_vec(L.rec, rec, s);
-    upload_vec(L.rows, rows, s);
-    upload_vec(L.states, states, s);
-    upload_vec(L.csr, csr, s);
+    upload_vec(L.rows, L.h_rows, s);
+    upload_vec(L.states, L.h_states, s);
+    upload_vec(L.csr, L.h_csr, s);
     upload_vec(L.live, live, s);
-    upload_vec(L.unit_base_d, L.unit_base, s);
-    upload_vec(L.init_unit, init_unit, s);
     MORAP_HIP(hipStreamSynchronize(s));
-    L.U = U;
     L.n_tiles = (int64_t)tiles.size();
-    L.gen = c->load_gen;
+    L.tiles_gen = c->load_gen;
+}
+
+// What a workgroup takes of model m: columns, and the class of its launch.
+struct StagedClass {
+    int columns, threads, size;
+    bool operator==(const StagedClass& o) const {
+        return columns == o.columns && threads == o.threads && size == o.size;
+    }
+};
+static StagedClass staged_class(const StagedLayout& L, int m, int prec, bool wide) {
+    const int pos = L.lds_positions[m];
+    int columns = k::staged_columns(prec, pos, L.unit_base[m + 1] - L.unit_base[m]);
+    if (!wide) columns = std::min(columns, 1);
+    StagedClass r{columns, columns ? k::staged_threads(prec, columns, pos) : 0, 0};
+    // (a launch's LDS is its largest product's: at most twice the smallest's)
+    while (pos >> r.size > 512) ++r.size;
+    return r;
+}
+
+// Stage retirement with every product's values in LDS, one launch per class of
+// products; statistics as the batched sweeps count them.
+static void run_staged_lds(morap_ctx* c, ValueSet& vs, const morap_vi_opts& o, bool wide, Stats& st) {
+    StagedLayout& L = c->staged;
+    const HostModels& hm = c->hm;
+    const int M = hm.M, K = vs.K, Kp = vs.Kp, U = L.U;
+    hipStream_t s = c->stream;
+    const size_t pairs = (size_t)U * Kp;
+    L.pair_sweeps.ensure(pairs * 4);
+    L.best_res.ensure(pairs * 8);
+    L.stall.ensure(pairs * 4);
+    L.h_unit_sweeps.ensure(pairs * 4);
+    const k::ConvergeArgs ca = converge_args(c, vs, nullptr, o.eps_vi, 0, false);
+    EventPair wall;
+    MORAP_HIP(hipEventRecord(wall.a, s));
+    k::init_pairs(s, ca);
+    k::fill_i32(s, L.pair_sweeps.as<int32_t>(), 0, (int64_t)pairs);
+    k::StagedLdsArgs a{};
+    static_cast<k::ResidentArgs&>(a) = resident_args(c, vs, ca);
+    a.big_base = L.lds_base.as<int32_t>();
+    a.big_block = L.lds_block.as<int32_t>();
+    a.big_rec = L.lds_rec.as<uint4>();
+    a.big_init = L.lds_init.as<int32_t>();
+    a.best_res = L.best_res.as<double>();
+    a.stall = L.stall.as<int32_t>();
+    a.unit_base = L.unit_base_d.as<int32_t>();
+    a.init_unit = L.init_unit.as<int32_t>();
+    a.unit_sweeps = L.pair_sweeps.as<int32_t>();
+    struct Launch {
+        StagedClass c;
+        int begin, n;
+    };
+    std::vector<Launch> launches;
+    for (int b = 0; b < (int)L.lds_order.size(); ++b) {
+        const StagedClass q = staged_class(L, L.lds_order[b], vs.prec, wide);
+        if (launches.empty() || !(launches.back().c == q)) launches.push_back({q, b, 0});
+        ++launches.back().n;
+    }
+    const int32_t* us = L.h_unit_sweeps.as<int32_t>();
+    PooledEvents held(c);
+    int64_t done = 0, running = 0;
+    for (int64_t s0 = 0; s0 < o.max_sweeps; s0 = done) {
+        done = std::min<int64_t>(o.max_sweeps, s0 + kResidentSweeps);
+        a.sweep0 = (int)s0;
+        a.sweep1 = (int)done;
+        Fork fork(c, o.time_kernels ? 1 : (int)launches.size());
+        for (size_t q = 0; q < launches.size(); ++q) {
+            const Launch& l = launches[q];
+            a.order = L.order.as<int32_t>() + l.begin;
+            a.n_models = l.n;
+            if (o.time_kernels) {
+                held.v.emplace_back(take_event(c), nullptr);
+                held.v.back().second = take_event(c);
+                MORAP_HIP(hipEventRecord(held.v.back().first, s));
+            }
+            k::staged_lds(fork.stream((int)q), vs.prec, l.c.columns, l.c.threads, L.lds_positions[L.lds_order[l.begin]], a);
+            if (o.time_kernels) MORAP_HIP(hipEventRecord(held.v.back().second, s));
+        }
+        fork.join();
+        MORAP_HIP(hipMemcpyAsync(L.h_unit_sweeps.p, L.pair_sweeps.p, pairs * 4, hipMemcpyDeviceToHost, s));
+        read_results(c, vs);
+        running = 0;
+        for (int32_t m : L.lds_order)
+            for (int u = L.unit_base[m]; u < L.unit_base[m + 1]; ++u)
+                for (int k = 0; k < K; ++k) running += us[(size_t)u * Kp + k] == 0;
+        if (running == 0) break;
+    }
+    if (running > 0)
+        fail(MORAP_E_NOT_CONVERGED, "value iteration with stage retirement: " + std::to_string(running) +
+                                        " (unit, column) pairs still active after " + std::to_string(o.max_sweeps) +
+                                        " sweeps");
+    MORAP_HIP(hipEventRecord(wall.b, s));
+    MORAP_HIP(hipEventSynchronize(wall.b));
+    const double el = vs.prec == MORAP_F32 ? 4 : 8;
+    int64_t longest = 0;
+    for (int32_t m : L.lds_order)
+        for (int u = L.unit_base[m]; u < L.unit_base[m + 1]; ++u) {
+            int64_t sum = 0, top = 0;
+            for (int k = 0; k < K; ++k) {
+                const int64_t n = us[(size_t)u * Kp + k];
+                sum += n;
+                top = std::max(top, n);
+            }
+            st.backups += L.h_rows[u] * sum;
+            st.bytes += (double)L.h_csr[u] * (double)top + 2.0 * el * (double)L.h_states[u] * (double)sum;
+            longest = std::max(longest, top);
+        }
+    // (counted as the batched sweeps are: to the next look at the counters)
+    const int64_t check = std::max(2, o.check_every);
+    st.sweeps += std::min<int64_t>(o.max_sweeps, std::max<int64_t>((longest + check - 1) / check * check, std::min<int64_t>(check, o.max_sweeps)));
+    const int32_t* ps = c->h_pair_sweeps.as<int32_t>();
+    st.max_pair_sweeps = std::max<int64_t>(st.max_pair_sweeps, *std::max_element(ps, ps + (size_t)M * Kp));
+    st.floor_stops += c->h_counters.as<int64_t>()[8];
+    st.resident_models = (int)L.lds_order.size();
+    st.ms_vi += wall.elapsed_ms();
+    for (auto& e : held.v) {
+        float t = 0;
+        MORAP_HIP(hipEventElapsedTime(&t, e.first, e.second));
+        st.ms_sweep_kernel += t;
+        st.sweep_launches += 1;
+    }
 }
 
 // Alg. 3 for K columns with stage retirement: each sweep backs up the
@@ -2126,7 +2301,7 @@ static void solve_staged_impl(morap_ctx* c, const double* W, int K, const morap_
     const int nI = c->hm.nI, nJ = c->hm.nJ, M = c->hm.M, d = nI + nJ;
     check_weight_rows(W, K, d);
     const auto t0 = std::chrono::steady_clock::now();
-    build_stage_layout(c);
+    build_stages(c);
     StagedLayout& L = c->staged;
     const int U = L.U, Kp = padded_k(K), prec = o.precision;
     const size_t el = prec == MORAP_F32 ? 4 : 8;
@@ -2161,6 +2336,25 @@ static void solve_staged_impl(morap_ctx* c, const double* W, int K, const morap_
     ValueSet& vs = c->vmain;
     ensure_values(c, vs, K, Kp, prec);
 
+    // every live product in LDS, unless the caller fixed the sweep kernel;
+    // several columns per workgroup unless all pairs run at once anyway
+    const bool wide = (int64_t)L.lds_order.size() * K > 2 * (int64_t)c->prop.multiProcessorCount;
+    bool lds = o.schedule == 0 && !L.lds_order.empty();
+    for (int32_t m : L.lds_order) lds = lds && staged_class(L, m, prec, wide).columns > 0;
+    if (lds) {
+        c->d_weights.ensure((size_t)K * d * 8);
+        MORAP_HIP(hipMemcpyAsync(c->d_weights.p, W, (size_t)K * d * 8, hipMemcpyHostToDevice, s));
+        if (prec == MORAP_F32) k::fill_f32(s, vs.x[0].as<float>(), 0.f, (c->S + 1) * Kp);
+        else k::fill_f64(s, vs.x[0].as<double>(), 0.0, (c->S + 1) * Kp);
+        run_staged_lds(c, vs, o, wide, st);
+        st.variant = v->id;
+        if (c_out) std::memcpy(c_out, c->h_c.p, (size_t)K * M * 8);
+        st.ms_total += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+        vs.valid = true;
+        c->solved = true;
+        return;
+    }
+    build_unit_tiles(c);
     const size_t pairs = (size_t)U * Kp;
     L.active.ensure(pairs);
     L.res.ensure(pairs * 8);

@@ -220,7 +220,8 @@ struct ValueSet {
 struct ResidentPlan {
     struct Launch {
         bool fast;
-        int columns;            // > 0: larger products, that many columns per workgroup
+        bool rows;              // products given as rows of entries: short rows, or streamed (columns > 0)
+        int columns;            // > 0: larger products or rows, that many columns per workgroup
         int begin, n, max_states;   // (larger products: positions)
     };
     struct Part {
@@ -234,7 +235,28 @@ struct ResidentPlan {
     int n_order = 0;
     std::vector<uint8_t> inst_ok;      // [M] 1: an instance's values, policy and evaluation all fit LDS
     DevBuf order, big_base, big_block, big_rec, big_init, grid_blk32, grid_blk64;
+    // products given as rows: see RowsArgs
+    bool unsolved = false;             // a model with states has none to solve for (its values are 0)
+    DevBuf row_slice, row_batch, row_desc, row_place, row_value32, row_value64, short_rec, short_val32, short_val64;
     Part part[2];                      // MORAP_F64, MORAP_F32
+
+    void clear(int M) {   // every model to the batched sweeps
+        for (Part& q : part) {
+            q.launches.clear();
+            q.models.clear();
+            q.rest.assign((size_t)M, 0);
+            q.n_rest = 0;
+        }
+        inst_ok.assign((size_t)M, 0);
+        unsolved = false;
+    }
+    void drop(int M) {    // the device's memory too
+        clear(M);
+        for (DevBuf* b : {&order, &big_base, &big_block, &big_rec, &big_init, &grid_blk32, &grid_blk64, &row_slice,
+                          &row_batch, &row_desc, &row_place, &row_value32, &row_value64, &short_rec, &short_val32,
+                          &short_val64})
+            b->release();
+    }
 };
 
 // Positions of a product's states sorted by block, each block's padded to
@@ -636,6 +658,8 @@ struct ResidentArgs {
     int64_t* counters;          // [8]: pairs stopped at the rounding floor
     double eps, unit, floor;
     int stall_sweeps, warm, sweep0, sweep1, last;
+    const uint4* short_rec;     // products given as short rows: [S][2] LDS rows of the entries, 16 bits each
+    const void* short_val;      // [S][SHORT_VALUES] (precision of the solve)
     const void* grid_blk;       // compact blocks (precision of the solve), see GRID_BLK
     // larger products: states sorted by block, padded to steps of 64
     const int32_t* big_base;    // [M+1] first position (a multiple of 64)
@@ -653,6 +677,28 @@ struct ResidentArgs {
     const uint8_t* start_par;
     int start_Kp;
 };
+// Products given as rows, 64 consecutive states a slice; the rows and entries
+// of a slice in lockstep, every lane its own state's.  A row is its probability
+// reward, its cost reward and its entries, as many as the longest of the 64
+// lanes has (a shorter one ends in entries of probability 0 at the zero row; a
+// state with fewer rows than the slice's most repeats its first).  The rewards
+// name two rows behind the product's (rounded up to slices), which hold the
+// columns' weights.  Four places make a batch; a slice starts a new one, and an
+// empty one lies behind the last.
+struct RowsArgs : ResidentArgs {
+    const int32_t* slice;       // [M+1] first slice of the model
+    const int32_t* batch;       // [slices+1] first batch of the slice
+    const int32_t* desc;        // [batches] bits 0-3: a row ends at that place, bit 4: the slice does
+    const uint2* place;         // [batches][64] four LDS rows, 16 bits each
+    const void* value;          // [batches][64][4] rewards and probabilities
+};
+// columns per workgroup of a product of that many states, 0 if it does not fit
+int rows_columns(int prec, int states);
+void resident_rows(hipStream_t s, int prec, int columns, int max_states, const RowsArgs& a);
+// products given as rows whose states have at most five rows of at most three
+// entries (resident_capacity with `fast` false, classes as the block form's)
+void resident_short(hipStream_t s, int prec, bool wide, int max_states, ResidentArgs a);
+constexpr int SHORT_VALUES = 26;   // probabilities [5][3], cost and probability rewards [5]; one unused
 // every block's nonzero entries lie within the grid pattern
 bool has_grid_pattern(uint32_t union_pattern);
 // largest product (states) the kernel holds; `fast`: every block has the grid

@@ -888,6 +888,208 @@ std::vector<SortedStates> sort_models(const HostModels& hm, const std::vector<in
     return sorted;
 }
 
+// The products as rows and entries in lockstep (see k::RowsArgs) when every
+// live one fits a workgroup and the padding leaves the layout at no more than
+// eight times the entries and rewards.  Its memory draws that line: with it
+// lifted, 48 products of 4,000 states of which one in 64 has 30 rows and the
+// others 2 (12.7 times the entries) took 28.7 ms in LDS and 42.6 with the
+// batched sweeps; at 1.1 to 4 times LDS takes 4.7 to 6.8 against 18 to 42.
+static void plan_rows(morap_ctx* c) {
+    const HostModels& hm = c->hm;
+    ResidentPlan& P = c->resident_plan;
+    hipStream_t s = c->stream;
+    std::vector<int32_t> order;
+    auto states = [&](int m) { return hm.state_base[m + 1] - hm.state_base[m]; };
+    int most = 0;
+    for (int m = 0; m < hm.M; ++m) {
+        if (hm.init[m] >= 0 && states(m) > 0) order.push_back(m);
+        else if (states(m) > 0) P.unsolved = true;
+        if (hm.init[m] >= 0) most = std::max(most, states(m));
+    }
+    if (order.empty() || k::rows_columns(MORAP_F32, most) == 0) return;
+    struct Model {
+        std::vector<int32_t> batch, desc;   // per slice, per batch
+        std::vector<uint16_t> place;
+        std::vector<double> value;
+        std::vector<uint16_t> brief;        // [states][16], empty: the rows are not short
+        std::vector<double> brief_value;    // [states][SHORT_VALUES]
+        bool fit = false;
+    };
+    // at most five rows of at most three entries a state, a missing entry at
+    // the zero row, a missing row as the state's first
+    auto short_rows = [&](int m, Model& x) {
+        const int32_t s0 = hm.state_base[m], n = states(m);
+        std::vector<uint16_t> place((size_t)n * 16, 0);
+        std::vector<double> val((size_t)n * k::SHORT_VALUES, 0.0);
+        for (int32_t l = 0; l < n; ++l) {
+            const int32_t r0 = hm.state_row[s0 + l], nr = hm.state_row[s0 + l + 1] - r0;
+            if (nr > 5) return;
+            double* v = &val[(size_t)l * k::SHORT_VALUES];
+            for (int j = 0; j < 5; ++j) {
+                const int32_t r = r0 + (j < nr ? j : 0), e = hm.row_ptr[r], ne = hm.row_ptr[r + 1] - e;
+                if (ne > 3) return;
+                for (int u = 0; u < ne; ++u) {
+                    place[(size_t)l * 16 + 3 * j + u] = (uint16_t)(hm.col[(size_t)e + u] - s0 + 1);
+                    v[3 * j + u] = hm.prob[(size_t)e + u];
+                }
+                v[15 + j] = hm.rew[2 * (size_t)r];
+                v[20 + j] = hm.rew[2 * (size_t)r + 1];
+            }
+        }
+        x.brief.swap(place);
+        x.brief_value.swap(val);
+    };
+    std::vector<Model> built((size_t)hm.M);
+    std::atomic<size_t> next{0};
+    std::atomic<bool> bad{false}, fit{true};
+    auto build = [&](int m, Model& x) {
+        const int32_t s0 = hm.state_base[m], n = states(m);
+        const int64_t nnz = hm.row_ptr[hm.state_row[s0 + n]] - hm.row_ptr[hm.state_row[s0]];
+        const int64_t n_rows = hm.state_row[s0 + n] - hm.state_row[s0];
+        const int32_t wp_row = (n + 63) / 64 * 64 + 1;
+        std::vector<int32_t> len;
+        for (int32_t b = 0; b < n; b += 64) {
+            auto state = [&](int q) { return s0 + std::min(b + q, n - 1); };
+            auto rows = [&](int q) { return hm.state_row[state(q) + 1] - hm.state_row[state(q)]; };
+            // row j of lane q (its first where it has no such row)
+            auto row_of = [&](int q, int j) { return hm.state_row[state(q)] + (j < rows(q) ? j : 0); };
+            int nr = 0;
+            for (int q = 0; q < 64; ++q) nr = std::max(nr, rows(q));
+            len.assign((size_t)nr, 0);
+            int64_t total = 0;
+            for (int j = 0; j < nr; ++j) {
+                for (int q = 0; q < 64; ++q) {
+                    const int32_t r = row_of(q, j);
+                    len[(size_t)j] = std::max(len[(size_t)j], hm.row_ptr[r + 1] - hm.row_ptr[r]);
+                }
+                total += 2 + len[(size_t)j];
+            }
+            const int64_t batches = (total + 3) / 4;
+            const size_t at = x.value.size(), d0 = x.desc.size();
+            // (the lanes of a last slice of few states repeat one of them)
+            if ((double)(at + (size_t)batches * 256) > 8.0 * (double)(nnz + 2 * n_rows) * ((n + 63) / 64 * 64) / n + 512) return;
+            x.place.resize(at + (size_t)batches * 256, 0);
+            x.value.resize(at + (size_t)batches * 256, 0.0);
+            x.desc.resize(d0 + (size_t)batches, 0);
+            int64_t e0 = 0;   // the row's first place in the slice
+            for (int j = 0; j < nr; ++j) {
+                for (int q = 0; q < 64; ++q) {
+                    const int32_t r = row_of(q, j), e = hm.row_ptr[r], n_e = hm.row_ptr[r + 1] - e;
+                    auto index = [&](int64_t u) {
+                        const int64_t f = e0 + u;
+                        return at + (size_t)(f / 4) * 256 + (size_t)q * 4 + (size_t)(f & 3);
+                    };
+                    x.place[index(0)] = (uint16_t)wp_row;
+                    x.value[index(0)] = hm.rew[2 * (size_t)r + 1];
+                    x.place[index(1)] = (uint16_t)(wp_row + 1);
+                    x.value[index(1)] = hm.rew[2 * (size_t)r];
+                    for (int u = 0; u < n_e; ++u) {
+                        x.place[index(2 + u)] = (uint16_t)(hm.col[(size_t)e + u] - s0 + 1);
+                        x.value[index(2 + u)] = hm.prob[(size_t)e + u];
+                    }
+                }
+                e0 += 2 + len[(size_t)j];
+                x.desc[d0 + (size_t)((e0 - 1) / 4)] |= 1 << ((e0 - 1) & 3);
+            }
+            x.desc.back() |= 16;
+            x.batch.push_back((int32_t)batches);
+        }
+        x.fit = true;
+    };
+    auto worker = [&] {
+        try {
+            for (size_t t; (t = next++) < order.size();) {
+                Model& x = built[(size_t)order[t]];
+                if (states(order[t]) <= k::resident_capacity(MORAP_F32, false)) short_rows(order[t], x);
+                if (x.brief.empty() || states(order[t]) > k::resident_capacity(MORAP_F64, false)) build(order[t], x);
+                else x.fit = true;
+                if (!x.fit) fit = false;
+            }
+        } catch (...) {
+            bad = true;
+        }
+    };
+    const int nt = (int)std::min<size_t>(order.size(), std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
+    std::vector<std::thread> th;
+    for (int k = 1; k < nt; ++k) th.emplace_back(worker);
+    worker();
+    for (auto& k : th) k.join();
+    MORAP_CHECK(!bad, MORAP_E_OOM, "laying out the rows failed (host memory)");
+    if (!fit) return;
+    std::vector<int32_t> slice((size_t)hm.M + 1, 0), batch(1, 0), desc;
+    size_t total = 0;
+    for (const Model& x : built) total += x.value.size();
+    if (total / 256 >= (1u << 30)) return;
+    bool any_short = false;
+    for (const Model& x : built) any_short |= !x.brief.empty();
+    const size_t n_short = any_short ? (size_t)hm.S() : 0;
+    std::vector<uint16_t> brief(n_short * 16, 0);
+    std::vector<double> brief_value(n_short * k::SHORT_VALUES, 0.0);
+    for (int m = 0; m < hm.M; ++m) {
+        const Model& x = built[(size_t)m];
+        if (x.brief.empty()) continue;
+        std::copy(x.brief.begin(), x.brief.end(), brief.begin() + (int64_t)hm.state_base[m] * 16);
+        std::copy(x.brief_value.begin(), x.brief_value.end(),
+                  brief_value.begin() + (int64_t)hm.state_base[m] * k::SHORT_VALUES);
+    }
+    upload(P.short_rec, brief, s);
+    upload(P.short_val64, brief_value, s);
+    P.short_val32.ensure(brief_value.size() * 4 + 16);
+    k::to_f32(s, P.short_val64.as<double>(), P.short_val32.as<float>(), (int64_t)brief_value.size());
+    std::vector<uint16_t> place;
+    std::vector<double> value;
+    place.reserve(total + 256);
+    value.reserve(total + 256);
+    for (int m = 0; m < hm.M; ++m) {
+        const Model& x = built[(size_t)m];
+        for (int32_t n : x.batch) batch.push_back(batch.back() + n);
+        slice[(size_t)m + 1] = slice[(size_t)m] + (int32_t)x.batch.size();
+        desc.insert(desc.end(), x.desc.begin(), x.desc.end());
+        place.insert(place.end(), x.place.begin(), x.place.end());
+        value.insert(value.end(), x.value.begin(), x.value.end());
+    }
+    // an empty batch behind the last one
+    desc.push_back(0);
+    place.insert(place.end(), 256, 0);
+    value.insert(value.end(), 256, 0.0);
+    upload(P.row_slice, slice, s);
+    upload(P.row_batch, batch, s);
+    upload(P.row_desc, desc, s);
+    upload(P.row_place, place, s);
+    upload(P.row_value64, value, s);
+    P.row_value32.ensure(value.size() * 4 + 16);
+    k::to_f32(s, P.row_value64.as<double>(), P.row_value32.as<float>(), (int64_t)value.size());
+    auto brief_of = [&](int m) { return !built[(size_t)m].brief.empty(); };
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+        return brief_of(a) != brief_of(b) ? brief_of(b) : states(a) > states(b);
+    });
+    upload(P.order, order, s);
+    P.rank.assign((size_t)hm.M, 0);
+    P.n_order = (int)order.size();
+    for (int b = 0; b < P.n_order; ++b) P.rank[(size_t)order[b]] = b;
+    for (int prec : {MORAP_F64, MORAP_F32}) {
+        if (k::rows_columns(prec, most) == 0) continue;
+        ResidentPlan::Part& part = P.part[prec];
+        part.models = order;
+        for (int b = 0; b < (int)order.size(); ++b) {
+            const int m = order[b], n = states(m);
+            const int columns = brief_of(m) && n <= k::resident_capacity(prec, false) ? 0 : k::rows_columns(prec, n);
+            if (!part.launches.empty()) {
+                ResidentPlan::Launch& l = part.launches.back();
+                // (a streamed launch's LDS is its largest product's: at most twice the smallest's)
+                if (l.columns == columns && (columns == 0 ? k::resident_class(l.max_states) == k::resident_class(n)
+                                                          : l.max_states <= std::max(2 * n, 256))) {
+                    ++l.n;
+                    l.max_states = std::max(l.max_states, n);
+                    continue;
+                }
+            }
+            part.launches.push_back({false, true, columns, b, 1, n});
+        }
+    }
+    MORAP_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
+}
+
 // Which models' solves keep their values in LDS, per precision: products of
 // the block form that fit a workgroup, in launches of one class (states per
 // thread, or columns of the larger products) each.
@@ -896,12 +1098,13 @@ static void plan_resident(morap_ctx* c) {
     ResidentPlan& P = c->resident_plan;
     hipStream_t s = c->stream;
     auto states = [&](int m) { return hm.state_base[m + 1] - hm.state_base[m]; };
+    P.clear(hm.M);
+    if (!c->has_blocks) return plan_rows(c);
     const bool grid = k::has_grid_pattern(hm.blk_pattern);
     auto fast = [&](int m) { return grid && hm.blk_plain[(size_t)m] != 0; };
     std::vector<int32_t> order;
-    if (c->has_blocks)
-        for (int m = 0; m < hm.M; ++m)
-            if (states(m) > 0) order.push_back(m);
+    for (int m = 0; m < hm.M; ++m)
+        if (states(m) > 0) order.push_back(m);
     // sorted states of the products some precision's first kernel cannot hold
     std::vector<SortedStates> sorted;
     {
@@ -953,10 +1156,6 @@ static void plan_resident(morap_ctx* c) {
     for (int b = 0; b < P.n_order; ++b) P.rank[(size_t)order[b]] = b;
     for (int prec : {MORAP_F64, MORAP_F32}) {
         ResidentPlan::Part& part = P.part[prec];
-        part.launches.clear();
-        part.models.clear();
-        part.rest.assign((size_t)hm.M, 0);
-        part.n_rest = 0;
         for (int b = 0; b < (int)order.size(); ++b) {
             const int m = order[b];
             const bool first = states(m) <= k::resident_capacity(prec, fast(m));
@@ -977,12 +1176,11 @@ static void plan_resident(morap_ctx* c) {
                     continue;
                 }
             }
-            part.launches.push_back({fast(m), columns, b, 1, size});
+            part.launches.push_back({fast(m), false, columns, b, 1, size});
         }
         upload(part.d_rest, part.rest, s);
     }
     MORAP_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
-    P.inst_ok.assign((size_t)hm.M, 0);
     const int most = std::min(k::policy_capacity(), k::eval_capacity());
     for (int32_t m : order)
         P.inst_ok[(size_t)m] = !P.part[MORAP_F64].rest[(size_t)m] && !hm.blk_zero_prob[(size_t)m] && states(m) <= most;
@@ -1079,7 +1277,14 @@ void upload_models(morap_ctx* c) {
         c->d_blk32.ensure(hm.blk_agent.size() * 4 + 16);
         k::to_f32(s, c->d_blk64.as<double>(), c->d_blk32.as<float>(), (int64_t)hm.blk_agent.size());
     }
-    plan_resident(c);
+    try {
+        plan_resident(c);
+    } catch (const MorapError& e) {
+        if (e.code != MORAP_E_OOM) throw;
+        // no memory for the layouts in LDS order: the batched sweeps need none
+        MORAP_HIP(hipStreamSynchronize(s));
+        c->resident_plan.drop(hm.M);
+    }
     MORAP_HIP(hipStreamSynchronize(s));
     c->loaded = true;
 }

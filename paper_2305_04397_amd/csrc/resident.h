@@ -1,6 +1,7 @@
 // Device helpers of the kernels that keep the values of an iteration in LDS
-// (resident.hip, instance.hip).
+// (resident.hip, instance.hip, staged.hip, rows.hip).
 #pragma once
+#include "common.h"
 #include "kern.h"
 
 #include <type_traits>
@@ -78,6 +79,13 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
     return r;
 }
 __device__ __forceinline__ double max3(double a, double b, double c) { return fmax(fmax(a, b), c); }
+// maximum of two values (fmaxf quiets each operand first)
+__device__ __forceinline__ float max2(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double max2(double a, double b) { return fmax(a, b); }
 // max(a, |b|)
 __device__ __forceinline__ float max_abs(float a, float b) {
     float r;
@@ -171,6 +179,97 @@ __device__ __forceinline__ T part_max(const T* part, int nw, int stride, int ln)
     r = mx(r, __shfl_xor(r, 16, 64));
     return mx(r, __shfl_xor(r, 32, 64));
 }
+
+// The stop test of one column: its largest change within max(eps, a few units
+// in the last place of its largest value), or FP32's rounding floor: no new
+// smallest change for stall_sweeps sweeps and within floor |y|.
+template <bool F32>
+__device__ __forceinline__ bool stop_test(const ResidentArgs& a, double res, double ym, double& best, int& stall,
+                                          bool& floor_stop) {
+    const double tol = fmax(a.eps, a.unit * ym);
+    if (F32 && res > tol) {
+        if (res < best) {
+            best = res;
+            stall = 0;
+        } else {
+            const int st = stall + 1;
+            stall = st;
+            floor_stop = st >= a.stall_sweeps && res <= a.floor * ym;
+        }
+    }
+    return res <= tol || floor_stop;
+}
+
+// What a workgroup works on: the columns k0 .. k0 + KC - 1 of model m, or (INST)
+// instance q.
+template <class T, int KC, bool INST>
+struct Item {
+    bool ok;
+    int m, k0, q;
+    int64_t pair0, base;
+    __device__ __forceinline__ explicit Item(const ResidentArgs& a) {
+        if constexpr (INST) {
+            ok = true;
+            q = a.order[blockIdx.x];
+            m = a.inst_model[q];
+            k0 = 0;
+            pair0 = q;
+            base = a.inst_base[q];
+        } else {
+            // the columns of one product go to one XCD: its records meet in that L2
+            const int slot = blockIdx.x >> 3;
+            const int mi = slot / a.groups * 8 + (int)(blockIdx.x & 7);
+            ok = mi < a.n_models;
+            m = ok ? a.order[mi] : 0;
+            k0 = slot % a.groups * KC;
+            pair0 = (int64_t)m * a.Kp + k0;
+            q = 0;
+            base = 0;
+        }
+    }
+    __device__ __forceinline__ bool running(const ResidentArgs& a, int c) const {
+        return (INST || k0 + c < a.K) && a.pair_sweeps[pair0 + c] == 0;
+    }
+    __device__ __forceinline__ void weights(const ResidentArgs& a, int c, T& wc, T& wp) const {
+        if constexpr (INST) {
+            wc = scalar(a.iwc[q]);
+            wp = scalar(a.iwp[q]);
+        } else {
+            const int k = k0 + c < a.K ? k0 + c : 0;
+            const double* W = a.W + (int64_t)k * a.d;
+            wc = scalar((T)W[m / a.nJ]);
+            wp = scalar((T)W[a.nI + m % a.nJ]);
+        }
+    }
+    // place of the value of the product's state l in column c
+    __device__ __forceinline__ int64_t place(const ResidentArgs& a, int sb, int l, int c) const {
+        return INST ? base + l : (int64_t)(sb + l) * a.Kp + k0 + c;
+    }
+    __device__ __forceinline__ T start(const ResidentArgs& a, int sb, int l, int c) const {
+        if (a.sweep0 > 0 || (!INST && a.warm)) return static_cast<const T*>(a.x0)[place(a, sb, l, c)];
+        if constexpr (INST) {
+            // the FP32 solve's values scaled to the instance's weights, where
+            // its cost weight is positive (the values scale with the weights)
+            if (!a.start0 || !(a.iwc[q] > 0.0)) return 0;
+            const int k = a.inst_k[q];
+            const float* x = a.start_par[(int64_t)m * a.start_Kp + k] ? a.start1 : a.start0;
+            return (double)x[(int64_t)(sb + l) * a.start_Kp + k] * a.iscale[q];
+        }
+        return 0;
+    }
+    __device__ __forceinline__ bool stop(const ResidentArgs& a, double res, double ym, double& best, int& stall,
+                                         bool& floor_stop) const {
+        if constexpr (INST) return res <= a.ieps[q];
+        else return stop_test<sizeof(T) == 4>(a, res, ym, best, stall, floor_stop);
+    }
+    __device__ __forceinline__ void stopped(const ResidentArgs& a, int c, int n, bool floor_stop) const {
+        if constexpr (!INST) {
+            if (floor_stop) atomicAdd((unsigned long long*)&a.counters[8], 1ull);
+            a.final_par[pair0 + c] = 0;
+        }
+        a.pair_sweeps[pair0 + c] = n;
+    }
+};
 
 }  // namespace k
 }  // namespace morap

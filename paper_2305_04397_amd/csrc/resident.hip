@@ -27,101 +27,10 @@ namespace k {
 
 namespace {
 
-// The stop test of one column: its largest change within max(eps, a few units
-// in the last place of its largest value), or FP32's rounding floor: no new
-// smallest change for stall_sweeps sweeps and within floor |y|.
-template <bool F32>
-__device__ __forceinline__ bool stop_test(const ResidentArgs& a, double res, double ym, double& best, int& stall,
-                                          bool& floor_stop) {
-    const double tol = fmax(a.eps, a.unit * ym);
-    if (F32 && res > tol) {
-        if (res < best) {
-            best = res;
-            stall = 0;
-        } else {
-            const int st = stall + 1;
-            stall = st;
-            floor_stop = st >= a.stall_sweeps && res <= a.floor * ym;
-        }
-    }
-    return res <= tol || floor_stop;
-}
-
-// What a workgroup works on: the columns k0 .. k0 + KC - 1 of model m, or (INST)
-// instance q.
-template <class T, int KC, bool INST>
-struct Item {
-    bool ok;
-    int m, k0, q;
-    int64_t pair0, base;
-    __device__ __forceinline__ explicit Item(const ResidentArgs& a) {
-        if constexpr (INST) {
-            ok = true;
-            q = a.order[blockIdx.x];
-            m = a.inst_model[q];
-            k0 = 0;
-            pair0 = q;
-            base = a.inst_base[q];
-        } else {
-            // the columns of one product go to one XCD: its records meet in that L2
-            const int slot = blockIdx.x >> 3;
-            const int mi = slot / a.groups * 8 + (int)(blockIdx.x & 7);
-            ok = mi < a.n_models;
-            m = ok ? a.order[mi] : 0;
-            k0 = slot % a.groups * KC;
-            pair0 = (int64_t)m * a.Kp + k0;
-            q = 0;
-            base = 0;
-        }
-    }
-    __device__ __forceinline__ bool running(const ResidentArgs& a, int c) const {
-        return (INST || k0 + c < a.K) && a.pair_sweeps[pair0 + c] == 0;
-    }
-    __device__ __forceinline__ void weights(const ResidentArgs& a, int c, T& wc, T& wp) const {
-        if constexpr (INST) {
-            wc = scalar(a.iwc[q]);
-            wp = scalar(a.iwp[q]);
-        } else {
-            const int k = k0 + c < a.K ? k0 + c : 0;
-            const double* W = a.W + (int64_t)k * a.d;
-            wc = scalar((T)W[m / a.nJ]);
-            wp = scalar((T)W[a.nI + m % a.nJ]);
-        }
-    }
-    // place of the value of the product's state l in column c
-    __device__ __forceinline__ int64_t place(const ResidentArgs& a, int sb, int l, int c) const {
-        return INST ? base + l : (int64_t)(sb + l) * a.Kp + k0 + c;
-    }
-    __device__ __forceinline__ T start(const ResidentArgs& a, int sb, int l, int c) const {
-        if (a.sweep0 > 0 || (!INST && a.warm)) return static_cast<const T*>(a.x0)[place(a, sb, l, c)];
-        if constexpr (INST) {
-            // the FP32 solve's values scaled to the instance's weights, where
-            // its cost weight is positive (the values scale with the weights)
-            if (!a.start0 || !(a.iwc[q] > 0.0)) return 0;
-            const int k = a.inst_k[q];
-            const float* x = a.start_par[(int64_t)m * a.start_Kp + k] ? a.start1 : a.start0;
-            return (double)x[(int64_t)(sb + l) * a.start_Kp + k] * a.iscale[q];
-        }
-        return 0;
-    }
-    __device__ __forceinline__ bool stop(const ResidentArgs& a, double res, double ym, double& best, int& stall,
-                                         bool& floor_stop) const {
-        if constexpr (INST) return res <= a.ieps[q];
-        else return stop_test<sizeof(T) == 4>(a, res, ym, best, stall, floor_stop);
-    }
-    __device__ __forceinline__ void stopped(const ResidentArgs& a, int c, int n, bool floor_stop) const {
-        if constexpr (!INST) {
-            if (floor_stop) atomicAdd((unsigned long long*)&a.counters[8], 1ull);
-            a.final_par[pair0 + c] = 0;
-        }
-        a.pair_sweeps[pair0 + c] = n;
-    }
-};
-
 // waves per SIMD the registers are held to, so that the probabilities of NS
 // states fit with room for a step: 128 registers, 168 or 256
-__host__ __device__ constexpr int res_waves_per_simd(int bytes, int ns, bool fast) {
-    const int need = ns * (bytes / 4) * (fast ? 2 : 3);
+__host__ __device__ constexpr int res_waves_per_simd(int bytes, int ns, bool fast, bool rows) {
+    const int need = ns * (bytes / 4) * (fast ? 2 : (rows ? 4 : 3));
     return need <= 6 ? 4 : (need <= 8 ? 3 : 2);
 }
 
@@ -135,13 +44,17 @@ __host__ __device__ constexpr int res_waves_per_simd(int bytes, int ns, bool fas
 // barrier of n + 1, when buffer n & 1 still holds iterate n: a column's final
 // values leave from there, each thread its own states.
 // With INST an item is a (column, model) instance: FP64, its own two weights
-// and stop, values contiguous.
-template <class T, int KC, int NS, bool FAST, bool INST = false>
-__global__ void __launch_bounds__(RES_MAX_THREADS, res_waves_per_simd(sizeof(T), NS, FAST))
+// and stop, values contiguous.  With ROWS the product is given as rows, at most
+// five a state of three entries each: these take the place of the block, an LDS
+// row and a gather each, in the order given.  48 products of 16 x 16 grids x 8
+// tasks, 24 FP32 columns: 0.35 ms; 0.50 streamed (see rows.hip) and 3.7 with the
+// batched CSR sweeps.
+template <class T, int KC, int NS, bool FAST, bool INST = false, bool ROWS = false>
+__global__ void __launch_bounds__(RES_MAX_THREADS, res_waves_per_simd(sizeof(T), NS, FAST, ROWS))
 resident_vi(ResidentArgs a) {
     constexpr uint32_t PAT = FAST ? PAT_GRID : PAT_DENSE;
     constexpr bool UC = FAST;                             // one cost per action
-    constexpr int NNZ = pat_count(PAT);
+    constexpr int NNZ = ROWS ? 15 : pat_count(PAT);
     constexpr int ROWB = sizeof(T) * KC;                  // bytes of an LDS row
     constexpr int SH = ROWB == 4 ? 2 : (ROWB == 8 ? 3 : 4);
     constexpr int BUF = res_rows(NS) * ROWB;              // distance of the two buffers
@@ -176,15 +89,33 @@ resident_vi(ResidentArgs a) {
     // the record of every state (they are stored in tile order: each names
     // its state)
     int* where = reinterpret_cast<int*>(lds);
-    for (int p = tid; p < S; p += blockDim.x) where[a.rec[(int64_t)(sb + p) * 8 + 7] - sb] = p;
+    if constexpr (!ROWS)
+        for (int p = tid; p < S; p += blockDim.x) where[a.rec[(int64_t)(sb + p) * 8 + 7] - sb] = p;
     __syncthreads();
-    T P[NS][NNZ], cost[UC ? 1 : NS][5];
+    T P[NS][NNZ], cost[UC ? 1 : NS][5], reward[ROWS ? NS : 1][5];
+    unsigned succ[ROWS ? NS : 1][8];       // LDS rows of the entries, 16 bits each
     unsigned o01[NS], o23[NS], o4[NS];     // LDS rows of the slots, 16 bits each; o4: accepting slots above
     unsigned acc_steps = 0;                // steps in which a lane of this wave has an accepting slot
     const int own0 = wave * 64 * NS + lane + 1;   // LDS row of the first step's state; step i: + 64 i
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
         const int l = min(own0 - 1 + 64 * i, S - 1);
+        if constexpr (ROWS) {
+            const uint4* q = a.short_rec + (int64_t)(sb + l) * 2;
+            const uint4 q0 = q[0], q1 = q[1];
+            const unsigned w[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) succ[i][e] = w[e];
+            const T* B = static_cast<const T*>(a.short_val) + (int64_t)(sb + l) * SHORT_VALUES;
+#pragma unroll
+            for (int e = 0; e < NNZ; ++e) P[i][e] = own_reg(B[e]);
+#pragma unroll
+            for (int e = 0; e < 5; ++e) {
+                cost[i][e] = own_reg(B[15 + e]);
+                reward[i][e] = own_reg(B[20 + e]);
+            }
+            continue;
+        }
         const int32_t* r = a.rec + (int64_t)(sb + where[l]) * 8;
         const int4 r0 = *reinterpret_cast<const int4*>(r), r1 = *reinterpret_cast<const int4*>(r + 4);
         auto place = [&](int s) { return s == a.zero_row ? 0u : (unsigned)(s - sb + 1); };
@@ -302,8 +233,37 @@ resident_vi(ResidentArgs a) {
             }
             put(1 - IN, (unsigned)(own0 + 64 * i) << SH, out);
         };
+        auto rows_backup = [&](int i) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(succ[i][e]));   // (as above)
+            const Row<T, KC> old = get(IN, (unsigned)(own0 + 64 * i) << SH);
+            Row<T, KC> v[5];
+#pragma unroll
+            for (int q = 0; q < 5; ++q) {
+#pragma unroll
+                for (int c = 0; c < KC; ++c) v[q].v[c] = wc[c] * cost[i][q] + wp[c] * reward[i][q];
+#pragma unroll
+                for (int e = 3 * q; e < 3 * q + 3; ++e) {
+                    const Row<T, KC> x = get(IN, e & 1 ? high_row<SH>(succ[i][e / 2]) : low_row<SH>(succ[i][e / 2]));
+#pragma unroll
+                    for (int c = 0; c < KC; ++c) v[q].v[c] = fma(P[i][e], x.v[c], v[q].v[c]);
+                }
+            }
+            Row<T, KC> out;
+#pragma unroll
+            for (int c = 0; c < KC; ++c) {
+                out.v[c] = max3(max3(v[0].v[c], v[1].v[c], v[2].v[c]), v[3].v[c], v[4].v[c]);
+                r[c] = max_abs(r[c], out.v[c] - old.v[c]);
+                if (want_y) y[c] = max_abs(y[c], out.v[c]);
+            }
+            put(1 - IN, (unsigned)(own0 + 64 * i) << SH, out);
+        };
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
+            if constexpr (ROWS) {
+                rows_backup(i);
+                continue;
+            }
             Row<T, KC> xv[NSLOT];
             fetch(i, xv);
             if (acc_steps >> i & 1) backup(i, xv, std::true_type{});
@@ -632,9 +592,9 @@ int resident_capacity(int prec, bool fast) {
 
 namespace {
 
-template <class T, int KC, int NS, bool FAST, bool INST = false>
+template <class T, int KC, int NS, bool FAST, bool INST, bool ROWS>
 void launch_res(hipStream_t s, const ResidentArgs& a, int max_states) {
-    auto* fn = &resident_vi<T, KC, NS, FAST, INST>;
+    auto* fn = &resident_vi<T, KC, NS, FAST, INST, ROWS>;
     constexpr int ROWB = sizeof(T) * KC;
     const int threads = 64 * ((max_states + 64 * NS - 1) / (64 * NS));
     const size_t bytes = (size_t)res_rows(NS) * ROWB + (((size_t)(threads * NS + 1) * ROWB + 15) & ~(size_t)15) +
@@ -650,17 +610,17 @@ void launch_res(hipStream_t s, const ResidentArgs& a, int max_states) {
     MORAP_HIP(hipGetLastError());
 }
 
-template <class T, int KC, bool FAST, int MAXNS, bool INST = false>
+template <class T, int KC, bool FAST, int MAXNS, bool INST = false, bool ROWS = false>
 void launch_steps(hipStream_t s, const ResidentArgs& a, int ns, int max_states) {
-    if (ns == 1) return launch_res<T, KC, 1, FAST, INST>(s, a, max_states);
+    if (ns == 1) return launch_res<T, KC, 1, FAST, INST, ROWS>(s, a, max_states);
     if constexpr (MAXNS >= 2)
-        if (ns == 2) return launch_res<T, KC, 2, FAST, INST>(s, a, max_states);
+        if (ns == 2) return launch_res<T, KC, 2, FAST, INST, ROWS>(s, a, max_states);
     if constexpr (MAXNS >= 3)
-        if (ns == 3) return launch_res<T, KC, 3, FAST, INST>(s, a, max_states);
+        if (ns == 3) return launch_res<T, KC, 3, FAST, INST, ROWS>(s, a, max_states);
     if constexpr (MAXNS >= 4)
-        if (ns == 4) return launch_res<T, KC, 4, FAST, INST>(s, a, max_states);
+        if (ns == 4) return launch_res<T, KC, 4, FAST, INST, ROWS>(s, a, max_states);
     if constexpr (MAXNS >= 7)
-        if (ns == 7) return launch_res<T, KC, 7, FAST, INST>(s, a, max_states);
+        if (ns == 7) return launch_res<T, KC, 7, FAST, INST, ROWS>(s, a, max_states);
     fail(MORAP_E_UNSUPPORTED, "a product does not fit the LDS-resident iteration");
 }
 
@@ -686,6 +646,20 @@ void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, Res
         else if (fast) launch_steps<double, 1, true, 4>(s, a, ns, max_states);
         else if (wide) launch_steps<double, 2, false, 2>(s, a, ns, max_states);
         else launch_steps<double, 1, false, 2>(s, a, ns, max_states);
+    }
+}
+
+void resident_short(hipStream_t s, int prec, bool wide, int max_states, ResidentArgs a) {
+    if (a.n_models <= 0) return;
+    const int ns = resident_class(max_states);
+    const int kc = !wide ? 1 : (prec == MORAP_F32 ? 4 : 2);
+    a.groups = (a.K + kc - 1) / kc;
+    if (prec == MORAP_F32) {
+        if (wide) launch_steps<float, 4, false, 4, false, true>(s, a, ns, max_states);
+        else launch_steps<float, 1, false, 4, false, true>(s, a, ns, max_states);
+    } else {
+        if (wide) launch_steps<double, 2, false, 2, false, true>(s, a, ns, max_states);
+        else launch_steps<double, 1, false, 2, false, true>(s, a, ns, max_states);
     }
 }
 

@@ -651,7 +651,20 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
                 MORAP_HIP(hipEventRecord(held.v.back().first, c->stream));
             }
             const hipStream_t s = fork.stream((int)q);
-            if (l.columns > 0) k::resident_large(s, vs.prec, wide ? l.columns : 1, l.max_states, a);
+            if (l.rows && l.columns == 0) {
+                a.short_rec = plan.short_rec.as<uint4>();
+                a.short_val = f32 ? plan.short_val32.p : plan.short_val64.p;
+                k::resident_short(s, vs.prec, wide, l.max_states, a);
+            } else if (l.rows) {
+                k::RowsArgs ra{};
+                static_cast<k::ResidentArgs&>(ra) = a;
+                ra.slice = plan.row_slice.as<int32_t>();
+                ra.batch = plan.row_batch.as<int32_t>();
+                ra.desc = plan.row_desc.as<int32_t>();
+                ra.place = plan.row_place.as<uint2>();
+                ra.value = f32 ? plan.row_value32.p : plan.row_value64.p;
+                k::resident_rows(s, vs.prec, wide ? l.columns : 1, l.max_states, ra);
+            } else if (l.columns > 0) k::resident_large(s, vs.prec, wide ? l.columns : 1, l.max_states, a);
             else k::resident(s, vs.prec, l.fast, wide, l.max_states, a);
             if (o.time_kernels) MORAP_HIP(hipEventRecord(held.v.back().second, c->stream));
         }
@@ -687,7 +700,15 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
     st.max_pair_sweeps = std::max(st.max_pair_sweeps, longest);
     st.sweeps = std::max<int64_t>(st.sweeps, (longest + chunk - 1) / chunk * chunk);
     st.resident_models = (int)part.models.size();
-    if (part.n_rest == 0) st.variant = kResidentVariant;
+    if (part.n_rest == 0) {
+        st.variant = kResidentVariant;
+        if (!c->has_blocks)   // products given as rows: the CSR sweep of that width
+            for (const auto& v : variants())
+                if (v.kind == SWEEP_CSR && kt_of(v) == std::min(vs.Kp, 64)) {
+                    st.variant = v.id;
+                    break;
+                }
+    }
     for (size_t q = 0; q < held.v.size(); ++q) {
         float t = 0;
         MORAP_HIP(hipEventElapsedTime(&t, held.v[q].first, held.v[q].second));
@@ -729,6 +750,10 @@ static void run_vi(morap_ctx* c, int g, ValueSet& vs, const uint8_t* mask, const
         if (warm) {
             swap_buf(vs.x[0], c->d_xwarm);
             ++c->buf_gen;   // graphs hold the value buffers' addresses
+        } else if (c->resident_plan.unsolved) {
+            // (values of models without a live initial state)
+            if (vs.prec == MORAP_F32) k::fill_f32(c->stream, vs.x[0].as<float>(), 0.f, (c->S + 1) * vs.Kp);
+            else k::fill_f64(c->stream, vs.x[0].as<double>(), 0.0, (c->S + 1) * vs.Kp);
         }
         k::init_pairs(c->stream, converge_args(c, vs, nullptr, o.eps_vi, 0, false));
         MORAP_HIP(hipEventRecord(wall.a, c->stream));
@@ -2102,11 +2127,19 @@ static void build_stages(morap_ctx* c) {
                          [&](int32_t x, int32_t y) { return L.lds_positions[x] > L.lds_positions[y]; });
     }
     if (!fit) L.lds_order.clear();
-    upload_vec(L.order, L.lds_order, s);
-    upload_vec(L.lds_base, base, s);
-    upload_vec(L.lds_block, block, s);
-    upload_vec(L.lds_rec, rec, s);
-    upload_vec(L.lds_init, init, s);
+    try {
+        upload_vec(L.order, L.lds_order, s);
+        upload_vec(L.lds_base, base, s);
+        upload_vec(L.lds_block, block, s);
+        upload_vec(L.lds_rec, rec, s);
+        upload_vec(L.lds_init, init, s);
+    } catch (const MorapError& e) {
+        if (e.code != MORAP_E_OOM) throw;
+        // no memory for this layout: the batched sweeps need none of it
+        MORAP_HIP(hipStreamSynchronize(s));
+        L.lds_order.clear();
+        for (DevBuf* b : {&L.order, &L.lds_base, &L.lds_block, &L.lds_rec, &L.lds_init}) b->release();
+    }
     MORAP_HIP(hipStreamSynchronize(s));
     L.U = U;
     L.gen = c->load_gen;

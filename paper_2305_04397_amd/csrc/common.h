@@ -234,7 +234,7 @@ struct ResidentPlan {
     std::vector<int32_t> rank;         // [M] place of the model in `order`
     int n_order = 0;
     std::vector<uint8_t> inst_ok;      // [M] 1: an instance's values, policy and evaluation all fit LDS
-    DevBuf order, big_base, big_block, big_rec, big_init, grid_blk32, grid_blk64;
+    DevBuf order, big_base, big_block, big_rec, big_init, grid_blk32, grid_blk64, grid_mat;
     // products given as rows: see RowsArgs
     bool unsolved = false;             // a model with states has none to solve for (its values are 0)
     DevBuf row_slice, row_batch, row_desc, row_place, row_value32, row_value64, short_rec, short_val32, short_val64;
@@ -252,7 +252,7 @@ struct ResidentPlan {
     }
     void drop(int M) {    // the device's memory too
         clear(M);
-        for (DevBuf* b : {&order, &big_base, &big_block, &big_rec, &big_init, &grid_blk32, &grid_blk64, &row_slice,
+        for (DevBuf* b : {&order, &big_base, &big_block, &big_rec, &big_init, &grid_blk32, &grid_blk64, &grid_mat, &row_slice,
                           &row_batch, &row_desc, &row_place, &row_value32, &row_value64, &short_rec, &short_val32,
                           &short_val64})
             b->release();
@@ -262,7 +262,8 @@ struct ResidentPlan {
 // Positions of a product's states sorted by block, each block's padded to
 // steps of 64 (empty: the product was not sorted, or fits no workgroup).
 struct SortedStates {
-    std::vector<int32_t> block;    // per step; with stages: its lowest << 20 and its highest << 26
+    std::vector<int32_t> block;    // per step, and << 16 where its run ends; with stages instead its lowest
+                                   // << 20 and its highest << 26
     std::vector<uint32_t> rec;     // [4 positions]; with stages: the state's << 16 in word 3
     int32_t init = 0;              // position of the initial state
 };
@@ -661,9 +662,10 @@ struct ResidentArgs {
     const uint4* short_rec;     // products given as short rows: [S][2] LDS rows of the entries, 16 bits each
     const void* short_val;      // [S][SHORT_VALUES] (precision of the solve)
     const void* grid_blk;       // compact blocks (precision of the solve), see GRID_BLK
+    const float* grid_mat;      // [blocks][4][8] a move's five slots, the probability to stay of the block
     // larger products: states sorted by block, padded to steps of 64
     const int32_t* big_base;    // [M+1] first position (a multiple of 64)
-    const int32_t* big_block;   // [positions / 64] block of the step
+    const int32_t* big_block;   // [positions / 64] block of the step, << 16: first step of the next block's run
     const uint4* big_rec;       // [positions] LDS rows of the slots (see the plan)
     const int32_t* big_init;    // [M] position of the initial state in its product
     // instances (FP64, one column each: see the instance kernels): `order`

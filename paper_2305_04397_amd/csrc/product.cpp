@@ -859,6 +859,11 @@ static SortedStates sort_states(const HostModels& hm, int m, const int32_t* stag
         if (p % 64 == 0) b = (b & 0xfffffu) | st << 20;
         b = (b & 0x3ffffffu) | st << 26;
     }
+    if (!stage)   // first step of the next block's run (fewer than 32,768 blocks)
+        for (size_t q = out.block.size(), end = q; q-- > 0;) {
+            if (q + 1 < out.block.size() && (out.block[q + 1] & 0x7fff) != out.block[q]) end = q + 1;
+            out.block[q] |= (int32_t)end << 16;
+        }
     out.init = hm.init[m] >= 0 ? place[(size_t)(hm.init[m] - s0)] : 0;
     return out;
 }
@@ -1111,7 +1116,9 @@ static void plan_resident(morap_ctx* c) {
         std::vector<int32_t> todo;
         const int most = k::resident_most_positions();
         for (int32_t m : order)
-            if (fast(m) && states(m) > k::resident_capacity(MORAP_F64, true) && states(m) <= most) todo.push_back(m);
+            if (fast(m) && states(m) > k::resident_capacity(MORAP_F64, true) && states(m) <= most &&
+                hm.blk_agent.size() / 32 < 32768)
+                todo.push_back(m);
         sorted = sort_models(hm, todo, nullptr);
         // (blocks of a few states each would be mostly padding)
         for (int32_t m : todo)
@@ -1128,6 +1135,8 @@ static void plan_resident(morap_ctx* c) {
     }
     // compact blocks: what a step loads in one go
     std::vector<double> gblk;
+    std::vector<float> gmat;   // and what a matrix instruction takes: a move's slots, in FP32
+    bool tame = true;          // costs small enough that no FP32 value overflows
     if (grid)
         for (size_t b = 0; b < hm.blk_agent.size() / 32; ++b) {
             const double* B = &hm.blk_agent[b * 32];
@@ -1136,12 +1145,20 @@ static void plan_resident(morap_ctx* c) {
                 if (k::grid_entry(e)) gblk.push_back(B[e]);
             gblk.insert(gblk.end(), B + 25, B + 30);
             gblk.resize(at + k::GRID_BLK, 0.0);
+            for (int q = 0; q < 4; ++q) {
+                for (int d = 0; d < 5; ++d) gmat.push_back((float)B[5 * q + d]);
+                gmat.push_back((float)B[20]);
+                gmat.resize(gmat.size() + 2, 0.f);
+            }
+            for (int q = 25; q < 30; ++q) tame = tame && std::fabs(B[q]) <= 1e25;
         }
+    upload(P.grid_mat, gmat, s);
     upload(P.grid_blk64, gblk, s);
     P.grid_blk32.ensure(gblk.size() * 4 + 16);
     k::to_f32(s, P.grid_blk64.as<double>(), P.grid_blk32.as<float>(), (int64_t)gblk.size());
     upload(P.big_base, base, s);
     upload(P.big_block, block, s);
+    rec.resize(rec.size() + 2 * 64 * 4, 0);   // (a wave reads two steps ahead)
     upload(P.big_rec, rec, s);
     upload(P.big_init, init, s);
 
@@ -1159,7 +1176,8 @@ static void plan_resident(morap_ctx* c) {
         for (int b = 0; b < (int)order.size(); ++b) {
             const int m = order[b];
             const bool first = states(m) <= k::resident_capacity(prec, fast(m));
-            const int columns = first || positions(m) == 0 ? 0 : k::resident_big_columns(prec, positions(m));
+            const int columns = first || positions(m) == 0 || (prec == MORAP_F32 && !tame)
+                                    ? 0 : k::resident_big_columns(prec, positions(m));
             if (!first && columns == 0) {
                 part.rest[(size_t)m] = 1;
                 ++part.n_rest;

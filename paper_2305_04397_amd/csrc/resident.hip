@@ -370,16 +370,13 @@ resident_vi(ResidentArgs a) {
 // banks; reading the 17 probabilities per lane instead would cost 1.5 (FP32)
 // or 3 (FP64) times the LDS traffic of the values themselves.
 //
-// 24 agents on 32 x 32 .. 128 x 128 grids x 32 tasks, 64 columns, FP32: 0.80
-// (4 columns), 0.53 (2) and 0.28 (1) 10^12 state-columns a second against 0.34
-// of the batched sweeps on all products of that problem; 37 FP64 columns of 49
-// products of up to 2,429 states: 2.3 ms, 10 ms before.
+// This kernel is FP64's: 37 columns of 49 products of up to 2,429 states take
+// 2.3 ms, 10 ms before.
 template <class T, int KC, int NS, bool INST = false>
 __global__ void __launch_bounds__(BIG_THREADS)
 resident_big(ResidentArgs a) {
     constexpr int ROWB = sizeof(T) * KC;
     constexpr int SH = ROWB == 4 ? 2 : (ROWB == 8 ? 3 : 4);
-    constexpr bool want_y = sizeof(T) == 4;
     constexpr int NW = BIG_THREADS / 64;
     extern __shared__ __align__(16) unsigned char lds[];
 
@@ -406,9 +403,7 @@ resident_big(ResidentArgs a) {
     const uint4* rec = a.big_rec + pos0 + s_begin * 64 + lane;
     unsigned char* hdr = lds + (((n_steps * 64 + 1) * ROWB + 15) & ~15);
     T* part = reinterpret_cast<T*>(hdr);                                     // [4 NW rows][4][res, |y|]
-    double* best = reinterpret_cast<double*>(hdr + 4 * NW * 8 * sizeof(T));  // [4] smallest change so far
-    int* stall = reinterpret_cast<int*>(best + 4);                           // [4] sweeps since it was set
-    unsigned* flag = reinterpret_cast<unsigned*>(stall + 4);
+    unsigned* flag = reinterpret_cast<unsigned*>(hdr + 4 * NW * 8 * sizeof(T));
     auto get = [&](unsigned addr) { return lds_get<T, KC>(addr); };
     auto put = [&](unsigned addr, const Row<T, KC>& r) { lds_put<T, KC>(addr, r); };
 
@@ -419,11 +414,11 @@ resident_big(ResidentArgs a) {
         it.weights(a, c, wc, wp[c]);
         // every state of the product has the same action costs
 #pragma unroll
-        for (int q = 0; q < 5; ++q) first[c][q] = wc * ablk[(int64_t)blk[-s_begin] * GRID_BLK + GRID_NNZ + q];
+        for (int q = 0; q < 5; ++q) first[c][q] = wc * ablk[(int64_t)(blk[-s_begin] & 0x7fff) * GRID_BLK + GRID_NNZ + q];
     }
     const unsigned own0 = (unsigned)(s_begin * 64 + lane + 1) << SH;   // LDS row of the first step's state
     for (int i = 0; i < cnt; ++i) {
-        const unsigned w = rec[i * 64].w & 0x7fffffffu;
+        const unsigned w = rec[i * 64].w & 0xffffu;
         Row<T, KC> v;
 #pragma unroll
         for (int c = 0; c < KC; ++c) v.v[c] = it.start(a, sb, (int)w, c);
@@ -434,10 +429,6 @@ resident_big(ResidentArgs a) {
 #pragma unroll
         for (int c = 0; c < KC; ++c) z.v[c] = 0;
         put(0, z);
-    }
-    if (want_y && tid < KC) {
-        best[tid] = a.best_res[it.pair0 + tid];
-        stall[tid] = a.stall[it.pair0 + tid];
     }
     __syncthreads();
 
@@ -451,15 +442,15 @@ resident_big(ResidentArgs a) {
             if (w >> 31) continue;   // padding
 #pragma unroll
             for (int c = 0; c < KC; ++c)
-                if (cols >> c & 1) static_cast<T*>(x)[it.place(a, sb, (int)w, c)] = v.v[c];
+                if (cols >> c & 1) static_cast<T*>(x)[it.place(a, sb, (int)(w & 0xffffu), c)] = v.v[c];
         }
     };
 
     Row<T, KC> out[NS];
     for (int n = a.sweep0 + 1; n <= a.sweep1; ++n) {
-        T r[KC], y[KC];
+        T r[KC];
 #pragma unroll
-        for (int c = 0; c < KC; ++c) r[c] = y[c] = 0;
+        for (int c = 0; c < KC; ++c) r[c] = 0;
         uint3 q = *reinterpret_cast<const uint3*>(rec);
         int b = blk[0];
 #pragma unroll
@@ -471,7 +462,7 @@ resident_big(ResidentArgs a) {
                 qn = *reinterpret_cast<const uint3*>(rec + (i + 1) * 64);
                 bn = blk[i + 1];
             }
-            const CVal B = ablk + (int64_t)b * GRID_BLK;
+            const CVal B = ablk + (int64_t)(b & 0x7fff) * GRID_BLK;
             T P[GRID_NNZ];
 #pragma unroll
             for (int e = 0; e < GRID_NNZ; ++e) P[e] = B[e];
@@ -514,7 +505,6 @@ resident_big(ResidentArgs a) {
                     }
                     out[i].v[c] = max3(max3(v[0], v[1], v[2]), v[3], v[4]);
                     r[c] = max_abs(r[c], out[i].v[c] - xv[0].v[c]);   // slot 0 is the state itself
-                    if (want_y) y[c] = max_abs(y[c], out[i].v[c]);
                 }
             };
             if (__ballot(accm != 0)) backup(std::true_type{});
@@ -524,12 +514,7 @@ resident_big(ResidentArgs a) {
             }
         }
         const T rr = row_max<T, KC>(r);
-        const T yy = want_y ? row_max<T, KC>(y) : (T)0;
-        if ((lane & 15) < 4) {
-            T* p = part + ((wave * 4 + (lane >> 4)) * 4 + (lane & 3)) * 2;
-            p[0] = rr;
-            p[1] = yy;
-        }
+        if ((lane & 15) < 4) part[((wave * 4 + (lane >> 4)) * 4 + (lane & 3)) * 2] = rr;
         // the iterate before the last, of a solve over its limit
         if (!INST && a.last && n == a.sweep1) store(a.x1, live);
         __syncthreads();   // every wave has read the old values
@@ -539,11 +524,13 @@ resident_big(ResidentArgs a) {
         if (wave == NW - 1) {
             int ln = lane;
             asm volatile("" : "+v"(ln));
-            const T res_t = part_max(part, NW, 2, ln), y_t = want_y ? part_max(part + 1, NW, 2, ln) : (T)0;
+            const T res_t = part_max(part, NW, 2, ln);
             bool now = false;
             if (ln < KC && (live >> ln & 1)) {
+                double best = 0;   // (FP32's)
+                int stall = 0;
                 bool floor_stop = false;
-                now = it.stop(a, (double)res_t, (double)y_t, best[ln], stall[ln], floor_stop);
+                now = it.stop(a, (double)res_t, 0.0, best, stall, floor_stop);
                 if (now) it.stopped(a, ln, n, floor_stop);
             }
             const unsigned fresh = (unsigned)__ballot(now);
@@ -564,14 +551,263 @@ resident_big(ResidentArgs a) {
     // the launch ends with columns running: their iterate
     store(a.x0, live);
     if constexpr (!INST)
-        if (tid < KC && (live >> tid & 1)) {
-            const int64_t i = it.pair0 + tid;
-            if (want_y) {
-                a.best_res[i] = best[tid];
-                a.stall[i] = stall[tid];
-            }
-            if (a.last) a.active[i] = 1;
+        if (a.last && tid < KC && (live >> tid & 1)) a.active[it.pair0 + tid] = 1;
+}
+
+// The same in FP32 with the sums on the matrix cores.  v_mfma_f32_4x4x1 takes
+// one multiply-add of 16 independent 4 x 4 products: four actions' probabilities
+// of a slot (the lanes of a block hold one action each) times the slot's values
+// of four states (the lanes of a block hold one state each), so five of them add
+// up the four moves of 64 states of one block in slot order, the same bits as 16
+// multiply-adds, at 0.6 of their cycles and beside the vector ALU instead of on
+// it.  A slot an action does not reach has probability 0 and adds nothing (no
+// value overflows: the plan asks for costs within 1e25).  A lane loads its
+// action's probabilities where a run of steps of one block begins, a few times
+// a sweep; loading them at every step kept the address unit of the vector
+// memory half busy, 40 of 78 cycles a step.
+//
+// 24 agents on 32 x 32 .. 128 x 128 grids x 32 tasks, 64 columns: 0.44 (1 column
+// a workgroup), 0.59 (2) and 0.80 (4) 10^12 state-columns a second; with the
+// sums on the vector ALU 0.28, 0.53 and 0.80, and 0.34 with the batched sweeps
+// on all products of that problem.
+using f32x4 = float __attribute__((ext_vector_type(4)));
+
+template <int KC, int NS>
+__global__ void __launch_bounds__(BIG_THREADS) big_mfma(ResidentArgs a) {
+    constexpr int ROWB = 4 * KC, SH = ROWB == 4 ? 2 : (ROWB == 8 ? 3 : 4);
+    constexpr int NW = BIG_THREADS / 64;
+    extern __shared__ __align__(16) unsigned char lds[];
+
+    const Item<float, KC, false> it(a);
+    if (!it.ok) return;
+    const int m = it.m;
+    unsigned live = 0;   // columns still running
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+        if (it.running(a, c)) live |= 1u << c;
+    if (!live) return;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sb = a.state_base[m];
+    const int pos0 = a.big_base[m], n_steps = (a.big_base[m + 1] - pos0) >> 6;
+    const int s_begin = wave * n_steps / NW, cnt = (wave + 1) * n_steps / NW - s_begin;
+    using CVal = const __attribute__((address_space(4))) float*;
+    const CVal ablk = (CVal)(static_cast<const float*>(a.grid_blk));
+    const char* rec = reinterpret_cast<const char*>(a.big_rec + pos0 + s_begin * 64);
+    unsigned char* hdr = lds + (((n_steps * 64 + 1) * ROWB + 15) & ~15);
+    float* part = reinterpret_cast<float*>(hdr);                                 // [4 NW rows][4][res, |y|]
+    double* best = reinterpret_cast<double*>(hdr + 4 * NW * 8 * sizeof(float));  // [4] smallest change so far
+    int* stall = reinterpret_cast<int*>(best + 4);                               // [4] sweeps since it was set
+    unsigned* flag = reinterpret_cast<unsigned*>(stall + 4);
+    auto get = [&](unsigned addr) { return lds_get<float, KC>(addr); };
+    auto put = [&](unsigned addr, const Row<float, KC>& r) { lds_put<float, KC>(addr, r); };
+
+    float wp[KC], stay0[KC];
+    f32x4 first[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+        float wc;
+        it.weights(a, c, wc, wp[c]);
+        // every state of the product has the same action costs
+        const CVal cost = ablk + (int64_t)(a.big_block[pos0 >> 6] & 0x7fff) * GRID_BLK + GRID_NNZ;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) first[c][q] = wc * cost[q];
+        stay0[c] = scalar(wc * cost[4]);
+    }
+    const unsigned own0 = (unsigned)(s_begin * 64 + lane + 1) << SH;   // LDS row of the first step's state
+    auto state_word = [&](int i) { return reinterpret_cast<const uint4*>(rec)[i * 64 + lane].w; };
+    for (int i = 0; i < cnt; ++i) {
+        const unsigned w = state_word(i) & 0xffffu;
+        Row<float, KC> v;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) v.v[c] = it.start(a, sb, (int)w, c);
+        put(own0 + ((unsigned)i << (6 + SH)), v);
+    }
+    if (tid == 0) {
+        Row<float, KC> z;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) z.v[c] = 0;
+        put(0, z);
+    }
+    if (tid < KC) {
+        best[tid] = a.best_res[it.pair0 + tid];
+        stall[tid] = a.stall[it.pair0 + tid];
+    }
+    __syncthreads();
+
+    // the values of the columns in `cols`, each thread its own states
+    auto store = [&](void* x, unsigned cols) {
+        unsigned own = own0;
+        asm volatile("" : "+v"(own));   // (no addresses kept over the sweeps)
+        for (int i = 0; i < cnt; ++i) {
+            const unsigned w = state_word(i);
+            const Row<float, KC> v = get(own + ((unsigned)i << (6 + SH)));
+            if (w >> 31) continue;   // padding
+#pragma unroll
+            for (int c = 0; c < KC; ++c)
+                if (cols >> c & 1) static_cast<float*>(x)[it.place(a, sb, (int)(w & 0xffffu), c)] = v.v[c];
         }
+    };
+    // this lane's action of a block: five slots, the probability to stay
+    struct Move {
+        f32x4 p;
+        float2 q;
+    };
+    const float* mat = a.grid_mat + (lane & 3) * 8;
+    using CInt = const __attribute__((address_space(4))) int32_t*;
+    const CInt runs = (CInt)(a.big_block + (pos0 >> 6));
+
+    Row<float, KC> out[NS];
+    for (int n = a.sweep0 + 1; n <= a.sweep1; ++n) {
+        float r[KC], y[KC];
+#pragma unroll
+        for (int c = 0; c < KC; ++c) r[c] = y[c] = 0;
+        unsigned at = (unsigned)lane * 16;
+        asm volatile("" : "+v"(at));   // (no addresses kept over the sweeps)
+        auto record = [&](int i) { return *reinterpret_cast<const uint3*>(rec + (at + i * 1024)); };
+        // one step and, inside its condition, the next: the registers of what is
+        // on its way are renamed from step to step, not copied
+        Move mv;
+        int run_end = 0;   // first step of the next run of one block
+        int k = cnt;
+        asm volatile("" : "+s"(k));    // (nor a condition per step)
+        struct Slots {
+            Row<float, KC> v[NSLOT];
+        };
+        auto gather = [&](const uint3& q) {
+            Slots x;
+            x.v[0] = get(low_row<SH>(q.x));
+            x.v[1] = get(high_row<SH>(q.x));
+            x.v[2] = get(low_row<SH>(q.y));
+            x.v[3] = get(high_row<SH>(q.y));
+            x.v[4] = get(low_row<SH>(q.z));
+            return x;
+        };
+        // (with one or two columns the next step's values are on their way too)
+        constexpr bool early = KC < 4;
+        auto steps = [&](auto self, auto I, const uint3& q, const uint3& qn, const Slots& x) {
+            constexpr int i = decltype(I)::value;
+            if (i >= k) return;
+            const uint3 q2 = record(i + 2);   // two steps ahead
+            Slots xn;
+            if constexpr (early) xn = gather(qn);   // (past the last step: in bounds, not used)
+            if (i == run_end) {
+                const int run = runs[s_begin + i];
+                run_end = (run >> 16) - s_begin;
+                const float* b = mat + (run & 0x7fff) * 32;
+                mv = Move{*reinterpret_cast<const f32x4*>(b), *reinterpret_cast<const float2*>(b + 4)};
+                // (waited for here: the steps without a load wait for less)
+                asm volatile("" : "+v"(mv.p), "+v"(mv.q.x), "+v"(mv.q.y));
+            }
+            const Slots now = early ? x : gather(q);
+            const Row<float, KC>(&xv)[NSLOT] = now.v;
+            auto slot = [&](int d) { return d < 4 ? mv.p[d] : mv.q.x; };
+            constexpr int H = KC == 4 ? 2 : KC;   // columns at a time (registers)
+            auto backup = [&](int c0, const f32x4 (&start)[H], const float (&start4)[H]) {
+                f32x4 v[H];
+                float v4[H];
+#pragma unroll
+                for (int d = 0; d < NSLOT; ++d)
+#pragma unroll
+                    for (int c = 0; c < H; ++c)
+                        v[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(slot(d), xv[d].v[c0 + c], d == 0 ? start[c] : v[c], 0, 0, 0);
+#pragma unroll
+                for (int c = 0; c < H; ++c) v4[c] = fma(mv.q.y, xv[0].v[c0 + c], start4[c]);
+                // (the maxima below are asm, whose reads of matrix results the
+                // compiler does not space)
+                if constexpr (H == 2) asm volatile("s_nop 7\n\ts_nop 7" : "+v"(v[0]), "+v"(v[1]));
+                else asm volatile("s_nop 7\n\ts_nop 7" : "+v"(v[0]));
+#pragma unroll
+                for (int c = 0; c < H; ++c) {
+                    const float best_v = max3(max3(v[c][0], v[c][1], v[c][2]), v[c][3], v4[c]);
+                    out[i].v[c0 + c] = best_v;
+                    r[c0 + c] = max_abs(r[c0 + c], best_v - xv[0].v[c0 + c]);   // slot 0 is the state itself
+                    y[c0 + c] = max_abs(y[c0 + c], best_v);
+                }
+            };
+            const unsigned accm = q.z >> 16;
+            const bool accepts = __ballot(accm != 0) != 0;
+            // probability reward: the action's mass on accepting slots
+            f32x4 mass = {0.f, 0.f, 0.f, 0.f};
+            if (accepts)
+#pragma unroll
+                for (int d = 0; d < NSLOT; ++d)
+                    mass = __builtin_amdgcn_mfma_f32_4x4x1f32(slot(d), accm >> d & 1 ? 1.f : 0.f, mass, 0, 0, 0);
+#pragma unroll
+            for (int c0 = 0; c0 < KC; c0 += H) {
+                f32x4 start[H];
+                float start4[H];
+#pragma unroll
+                for (int c = 0; c < H; ++c) {
+                    start[c] = first[c0 + c];
+                    start4[c] = stay0[c0 + c];
+                }
+                if (accepts) {
+                    const float mass4 = accm & 1 ? mv.q.y : 0.f;
+#pragma unroll
+                    for (int c = 0; c < H; ++c) {
+#pragma unroll
+                        for (int act = 0; act < 4; ++act) start[c][act] = fma(wp[c0 + c], mass[act], start[c][act]);
+                        start4[c] = fma(wp[c0 + c], mass4, start4[c]);
+                    }
+                    backup(c0, start, start4);
+                } else {
+                    backup(c0, start, start4);
+                }
+            }
+            if constexpr (i + 1 < NS) self(self, std::integral_constant<int, i + 1>{}, qn, q2, xn);
+        };
+        {
+            const uint3 q = record(0), qn = record(1);
+            Slots x;
+            if constexpr (early) x = gather(q);
+            steps(steps, std::integral_constant<int, 0>{}, q, qn, x);
+        }
+        const float rr = row_max<float, KC>(r), yy = row_max<float, KC>(y);
+        if ((lane & 15) < 4) {
+            float* p = part + ((wave * 4 + (lane >> 4)) * 4 + (lane & 3)) * 2;
+            p[0] = rr;
+            p[1] = yy;
+        }
+        // the iterate before the last, of a solve over its limit
+        if (a.last && n == a.sweep1) store(a.x1, live);
+        __syncthreads();   // every wave has read the old values
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            if (i < k) put(own0 + ((unsigned)i << (6 + SH)), out[i]);
+        if (wave == NW - 1) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            const float res_t = part_max(part, NW, 2, ln), y_t = part_max(part + 1, NW, 2, ln);
+            bool now = false;
+            if (ln < KC && (live >> ln & 1)) {
+                bool floor_stop = false;
+                now = it.stop(a, (double)res_t, (double)y_t, best[ln], stall[ln], floor_stop);
+                if (now) it.stopped(a, ln, n, floor_stop);
+            }
+            const unsigned fresh = (unsigned)__ballot(now);
+            if (ln == 0) *flag = fresh;
+        }
+        __syncthreads();
+        const unsigned f = *flag;
+        if (f) {
+            store(a.x0, f);
+            if (tid < KC && (f >> tid & 1))
+                a.c[(int64_t)(it.k0 + tid) * a.M + m] =
+                    (double)reinterpret_cast<const float*>(lds + ((unsigned)(a.big_init[m] + 1) << SH))[tid];
+            live &= ~f;
+            if (!live) return;
+        }
+    }
+    // the launch ends with columns running: their iterate
+    store(a.x0, live);
+    if (tid < KC && (live >> tid & 1)) {
+        const int64_t i = it.pair0 + tid;
+        a.best_res[i] = best[tid];
+        a.stall[i] = stall[tid];
+        if (a.last) a.active[i] = 1;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -696,7 +932,9 @@ namespace {
 template <class T, int KC, bool INST = false>
 void launch_big(hipStream_t s, const ResidentArgs& a, int max_positions) {
     constexpr int NS = 160 / (sizeof(T) * KC);
-    auto* fn = &resident_big<T, KC, NS, INST>;
+    void (*fn)(ResidentArgs);
+    if constexpr (sizeof(T) == 4) fn = &big_mfma<KC, NS>;
+    else fn = &resident_big<T, KC, NS, INST>;
     const size_t bytes = (((size_t)max_positions + 1) * sizeof(T) * KC + 15) / 16 * 16 +
                          4 * (BIG_THREADS / 64) * 8 * sizeof(T) + 64;
     MORAP_CHECK(max_positions % 64 == 0 && bytes <= LDS_BYTES && max_positions <= BIG_THREADS * NS,

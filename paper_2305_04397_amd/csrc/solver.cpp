@@ -590,6 +590,7 @@ static k::ResidentArgs resident_args(morap_ctx* c, ValueSet& vs, const k::Conver
     a.zero_row = (int32_t)c->S;
     const ResidentPlan& plan = c->resident_plan;
     a.grid_blk = f32 ? plan.grid_blk32.p : plan.grid_blk64.p;
+    a.grid_mat = plan.grid_mat.as<float>();
     a.big_base = plan.big_base.as<int32_t>();
     a.big_block = plan.big_block.as<int32_t>();
     a.big_rec = plan.big_rec.as<uint4>();

@@ -174,3 +174,12 @@ def test_sweep_limit_and_long_solves(ctx, morap):
         assert e.value.code == morap.E_NOT_CONVERGED and "column" in str(e.value)
     c, _ = ctx.solve(W, morap.Options(eps_vi=1e-9, precision="f64"))
     assert np.isfinite(c).all()
+
+
+def test_costs_too_large_for_the_matrix_path(ctx, morap):
+    """Larger FP32 products of costs above 1e25 take the batched sweeps (a
+    slot an action does not reach must add nothing); smaller ones stay."""
+    wl = _corridor((100, 4000), width=80)
+    huge = dataclasses.replace(wl, agents=[dataclasses.replace(a, cost=a.cost * 1e26) for a in wl.agents])
+    ctx.build_products(huge)
+    _compare(ctx, morap, huge, 4, "f32", 1e-6, 22, resident=1)

@@ -815,12 +815,17 @@ __global__ void __launch_bounds__(BIG_THREADS) big_mfma(ResidentArgs a) {
 // ---------------------------------------------------------------------------
 // States a workgroup can hold: 512 per register step.  The grid pattern with
 // one cost per action needs 17 probabilities a state (7 steps in FP32, 4 in
-// FP64 within 256 registers), the general block 25 and 5 costs (4 and 2).
+// FP64 within 256 registers; with two FP64 columns a fifth step spills 204
+// bytes), the general block 25 and 5 costs (4 and 2).
 static int resident_steps(int prec, bool fast) {
     return prec == MORAP_F32 ? (fast ? 7 : 4) : (fast ? 4 : 2);
 }
 
 bool has_grid_pattern(uint32_t union_pattern) { return pattern_for(union_pattern) == PAT_GRID; }
+
+// An instance's one column leaves the registers for a fifth step in FP64: its
+// solve at 2,400 states takes 0.22 ms, 0.47 with the larger products' kernel.
+int resident_inst_capacity() { return res_rows(5) - 1; }
 
 int resident_capacity(int prec, bool fast) {
     return res_rows(resident_steps(prec, fast)) - 1;
@@ -855,6 +860,8 @@ void launch_steps(hipStream_t s, const ResidentArgs& a, int ns, int max_states) 
         if (ns == 3) return launch_res<T, KC, 3, FAST, INST, ROWS>(s, a, max_states);
     if constexpr (MAXNS >= 4)
         if (ns == 4) return launch_res<T, KC, 4, FAST, INST, ROWS>(s, a, max_states);
+    if constexpr (MAXNS >= 5)
+        if (ns == 5) return launch_res<T, KC, 5, FAST, INST, ROWS>(s, a, max_states);
     if constexpr (MAXNS >= 7)
         if (ns == 7) return launch_res<T, KC, 7, FAST, INST, ROWS>(s, a, max_states);
     fail(MORAP_E_UNSUPPORTED, "a product does not fit the LDS-resident iteration");
@@ -864,7 +871,7 @@ void launch_steps(hipStream_t s, const ResidentArgs& a, int ns, int max_states) 
 
 int resident_class(int states) {
     const int ns = (states + RES_MAX_THREADS - 1) / RES_MAX_THREADS;
-    return ns <= 4 ? (ns < 1 ? 1 : ns) : 7;
+    return ns <= 5 ? (ns < 1 ? 1 : ns) : 7;
 }
 
 void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, ResidentArgs a) {
@@ -903,7 +910,7 @@ void resident_inst(hipStream_t s, bool fast, int max_states, ResidentArgs a) {
     if (a.n_models <= 0) return;
     const int ns = resident_class(max_states);
     a.groups = 1;
-    if (fast) launch_steps<double, 1, true, 4, true>(s, a, ns, max_states);
+    if (fast) launch_steps<double, 1, true, 5, true>(s, a, ns, max_states);
     else launch_steps<double, 1, false, 2, true>(s, a, ns, max_states);
 }
 

@@ -324,6 +324,15 @@ struct Fork {
             (void)hipStreamSynchronize(c->side[i]);
     }
     hipStream_t stream(int i) const { return i % (n + 1) == 0 ? c->stream : c->side[i % (n + 1) - 1]; }
+    // for a launch of that much work: the stream with the least so far
+    hipStream_t least(double work) {
+        int at = 0;
+        for (int i = 1; i <= n; ++i)
+            if (load[i] < load[at]) at = i;
+        load[at] += work;
+        return stream(at);
+    }
+    double load[4] = {0, 0, 0, 0};
     void join() {
         for (int i = 0; i < n; ++i) {
             MORAP_HIP(hipEventRecord(c->join_event[i], c->side[i]));
@@ -651,7 +660,13 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
                 held.v.back().second = take_event(c);
                 MORAP_HIP(hipEventRecord(held.v.back().first, c->stream));
             }
-            const hipStream_t s = fork.stream((int)q);
+            double work = 0;   // (the plan lists the larger products first)
+            for (int b = l.begin; b < l.begin + l.n; ++b) {
+                const int32_t m = part.models[(size_t)(b - part.launches[0].begin)];
+                work += hm.state_base[m + 1] - hm.state_base[m];
+            }
+            // (FP32 rates with one, two and four columns a workgroup)
+            const hipStream_t s = fork.least(work * (l.columns == 1 ? 1.8 : (l.columns == 2 ? 1.4 : 1.0)));
             if (l.rows && l.columns == 0) {
                 a.short_rec = plan.short_rec.as<uint4>();
                 a.short_val = f32 ? plan.short_val32.p : plan.short_val64.p;
@@ -1209,7 +1224,9 @@ struct Instances {
         for (size_t r = 1; r < first.size(); ++r) first[r] += first[r - 1];
         for (const auto& l : c->resident_plan.part[MORAP_F64].launches) {
             const int b = first[(size_t)l.begin], e = first[(size_t)(l.begin + l.n)];
-            if (e > b) vi.push_back({b, e - b, l.max_states, l.fast, l.columns > 0});
+            if (e <= b) continue;
+            if (l.inst_states > 0) vi.push_back({b, e - b, l.inst_states, l.fast, false});
+            else vi.push_back({b, e - b, l.max_states, l.fast, l.columns > 0});
         }
         order.resize((size_t)first.back());
         for (int q = 0; q < n; ++q)
@@ -1304,8 +1321,11 @@ struct Instances {
                 ev->back().second = take_event(c);
                 MORAP_HIP(hipEventRecord(ev->back().first, c->stream));
             }
-            if (r.large) k::resident_inst_large(fork.stream((int)q), r.max_states, a);
-            else k::resident_inst(fork.stream((int)q), r.fast, r.max_states, a);
+            // (an instance's time follows its size: a launch's, its largest one's
+            // and how many they are)
+            const hipStream_t s = fork.least((double)r.max_states * (1.0 + r.n / (double)c->prop.multiProcessorCount));
+            if (r.large) k::resident_inst_large(s, r.max_states, a);
+            else k::resident_inst(s, r.fast, r.max_states, a);
             if (ev) MORAP_HIP(hipEventRecord(ev->back().second, c->stream));
         }
         fork.join();
@@ -1618,7 +1638,7 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
         for (size_t q = 0; q < runs.size(); ++q) {
             ia.order = I.d_order + runs[q].begin;
             ia.n = runs[q].n;
-            kernel(fork.stream((int)q), runs[q].max_states, ia);
+            kernel(fork.least((double)ia.n * runs[q].max_states), runs[q].max_states, ia);
         }
         fork.join();
     };
@@ -2271,7 +2291,7 @@ static void run_staged_lds(morap_ctx* c, ValueSet& vs, const morap_vi_opts& o, b
                 held.v.back().second = take_event(c);
                 MORAP_HIP(hipEventRecord(held.v.back().first, s));
             }
-            k::staged_lds(fork.stream((int)q), vs.prec, l.c.columns, l.c.threads, L.lds_positions[L.lds_order[l.begin]], a);
+            k::staged_lds(fork.least((double)l.n * L.lds_positions[L.lds_order[l.begin]]), vs.prec, l.c.columns, l.c.threads, L.lds_positions[L.lds_order[l.begin]], a);
             if (o.time_kernels) MORAP_HIP(hipEventRecord(held.v.back().second, s));
         }
         fork.join();

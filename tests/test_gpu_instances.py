@@ -26,8 +26,8 @@ def ctx(morap):
     c.close()
 
 
-@pytest.mark.parametrize("sizes", [(1, 64, 511, 512, 513), (1024, 1025, 1536), (1537, 2048, 2049), (3584, 3585, 5100),
-                                   (9900, 10400)])
+@pytest.mark.parametrize("sizes", [(1, 64, 511, 512, 513), (1024, 1025, 1536), (1537, 2048, 2049), (2560, 2561),
+                                   (3584, 3585, 5100), (9900, 10400)])
 @pytest.mark.parametrize("prec,from_values", [("f64", False), ("f32", True)])
 def test_policies_and_values(ctx, morap, sizes, prec, from_values):
     """Column k assigns the task to agent k: one instance of every size.  The

@@ -76,7 +76,7 @@ def _block(morap, K):
 
 
 @pytest.mark.parametrize("sizes", [(1, 2, 63, 64, 65), (511, 512, 513), (1024, 1025), (1536, 1537), (2048, 2049),
-                                   (3583, 3584)])
+                                   (2560, 2561), (3583, 3584)])
 @pytest.mark.parametrize("prec,K", [("f32", 64), ("f32", 3), ("f32", 1)])
 def test_register_steps_f32(ctx, morap, sizes, prec, K):
     wl = _corridor(sizes)

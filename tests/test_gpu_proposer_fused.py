@@ -103,3 +103,25 @@ def test_noalloc_output_may_overlap_its_input(offset):
         finally:
             h.hipFree(p)
         assert np.array_equal(out, ref)
+
+
+@pytest.mark.parametrize("n_in,d,n", [(62, 30, 1056), (62, 30, 1057), (62, 30, 8448), (62, 30, 8449), (500, 20, 1000),
+                                      (1, 1, 70000)])
+def test_inference_of_host_rows_in_parts(n_in, d, n):
+    """Rows are independent: a call that goes in several launches gives what
+    calls of a few rows each give; a row that is not finite in the last part
+    refuses the call, and the next one is served."""
+    from paper_2305_04397_amd import morap
+    rng = np.random.default_rng(n)
+    X = rng.normal(0, 1, (n, n_in)).astype(np.float32)
+    with morap.Context(0) as c:
+        c.proposer_init(n_in, d, seed=3)
+        P = c.proposer_infer(X, d)
+        for r in sorted({0, n // 3, n // 2, n - 40}):
+            assert np.array_equal(P[r:r + 40], c.proposer_infer(X[r:r + 40], d)), r
+        bad = X.copy()
+        bad[-1, -1] = np.inf
+        with pytest.raises(morap.MorapError) as e:
+            c.proposer_infer(bad, d)
+        assert e.value.code == morap.E_INVALID
+        assert np.array_equal(c.proposer_infer(X, d), P)

@@ -19,7 +19,10 @@ captured graphs of sweep chunks; the kernel figures come from one more pass of
 the same kind with HIP events around the sweep launches (eager launches).
 
 Extra objects on the JSON line:
-  roofline      the Bellman sweep kernel: algorithmic bytes (CSR of active
+  roofline      with products whose values stay in LDS (the default workload's
+                most): vector lane operations of the value iteration per second
+                against 256 CUs x 64 lanes x 2.4 GHz; else
+                the Bellman sweep kernel: algorithmic bytes (CSR of active
                 models + one FP32 read and one write per active state-column)
                 over its summed HIP-event durations, against 8 TB/s HBM; the
                 last sweeps of a solve (under 20 % of the tiles active) run the
@@ -58,6 +61,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+VALU_PEAK = 39.3          # 10^12 lane operations a second: 256 CUs x 64 lanes x 2.4 GHz
 METRIC = "state-action backups/s + ms per point-oriented Pareto query (learned vs plain)"
 
 
@@ -76,6 +80,8 @@ def kernel_name(variant: int, prec: str) -> str:
     if variant < 0:
         return "morap::k::inst_vi_kernel"
     t = "float" if prec == "f32" else "double"
+    if variant == 41:
+        return f"void morap::k::resident_vi<{t}"
     if variant in (39, 40):
         return f"void morap::k::bellman_halo<{2 if variant == 39 else 4}"
     cpl, lps = SHAPES[(variant - 1) % 18]
@@ -501,7 +507,14 @@ def main():
     avg_s = st["ms_sweep_kernel"] / 1e3 / max(1, st["sweep_launches"])
     achieved = per_launch_bytes / avg_s / 1e9 if st["ms_sweep_kernel"] > 0 else 0.0
     kname = kernel_name(st["variant"], args.precision)
-    tb = measured_traffic(kname)
+    resident = st["resident_models"]
+    tb = None if resident else measured_traffic(kname)
+    if resident:
+        # most products iterate in LDS, all sweeps in one launch each: what
+        # bounds them is the vector ALU, 22 operations per state and column
+        # (17 multiply-adds, 3 maxima, the change and its maximum)
+        state_columns = st["backups"] * S / R
+        achieved = 22.0 * state_columns / (st["ms_vi"] / 1e3) / 1e12
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": None if tb is None else round(tb, 0),
@@ -511,6 +524,16 @@ def main():
                 "bytes_per_launch": round(per_launch_bytes, 0),
                 "timing": "HIP events on every 4th sweep launch of one extra pass (eager launches); value and "
                           "ms_per_step come from the timed steps, which replay captured graphs"}
+    if resident:
+        algorithmic = (st["bytes"] + st["bytes_tail"]) / (st["ms_vi"] / 1e3) / 1e9
+        roofline.update({"bound": "valu", "peak": VALU_PEAK, "unit": "10^12 lane operations/s",
+                         "frac": round(achieved / VALU_PEAK, 4), "achieved": round(achieved, 2),
+                         "algorithmic_gb_per_s": round(algorithmic, 1),
+                         "resident_models": resident, "bytes_per_launch": None,
+                         "timing": "22 lane operations per state and column of one extra pass over its value "
+                                   f"iteration's wall time (FP64 re-solve included), {st['ms_vi']:.1f} ms: {resident} "
+                                   "products iterate in LDS, where the algorithmic bytes are not memory traffic; "
+                                   "launches and their times are the batched sweeps' of the products beyond LDS"})
     if st["sweeps_tail"]:
         avg_t = st["ms_sweep_kernel_tail"] / 1e3 / max(1, st["sweep_launches_tail"])
         bt = st["bytes_tail"] / st["sweeps_tail"]
@@ -518,17 +541,19 @@ def main():
             "kernel": kernel_name(st["variant_tail"], args.precision), "variant": st["variant_tail"],
             "launches": st["sweeps_tail"], "launches_timed": st["sweep_launches_tail"],
             "avg_launch_us": round(avg_t * 1e6, 2), "bytes_per_launch": round(bt, 0),
-            "achieved": round(bt / avg_t / 1e9, 1) if avg_t > 0 else None,
+            "achieved": round(bt / avg_t / 1e9, 1) if avg_t > 0 and not resident else None,
             "traffic": measured_traffic(kernel_name(st["variant_tail"], args.precision)),
             "note": "the last sweeps of each solve (under 20 % of the tiles active) run the LDS-staged kernel"}
     if st["sweep_launches_refine"]:
         avg_r = st["ms_sweep_kernel_refine"] / 1e3 / st["sweep_launches_refine"]
-        ach_r = st["bytes_refine"] / max(1, st["polish_sweeps"]) / avg_r / 1e9
+        # (launches in LDS hold all sweeps of their pairs: no rate per launch)
+        ach_r = 0.0 if resident else st["bytes_refine"] / max(1, st["polish_sweeps"]) / avg_r / 1e9
         roofline["fp64_assigned_resolve"] = {
-            "achieved": round(ach_r, 1), "launches": st["polish_sweeps"],
+            "achieved": round(ach_r, 1) or None, "launches": st["polish_sweeps"],
             "launches_timed": st["sweep_launches_refine"], "avg_launch_us": round(avg_r * 1e6, 2),
             "kernel": kernel_name(st["variant_refine"], "f64")}
-    log(f"timed: {value:.3e} backups/s, {float(np.mean(step_ms)):.0f} ms per step; sweep kernel {achieved:.0f} GB/s "
+    log(f"timed: {value:.3e} backups/s, {float(np.mean(step_ms)):.0f} ms per step; "
+        f"{'value iteration' if resident else 'sweep kernel'} {achieved:.2f} {roofline['unit']} "
         f"({main_sweeps} launches, {st['sweep_launches']} timed, {st['ms_sweep_kernel']:.0f} ms; then "
         f"{st['sweeps_tail']} of the tail kernel, {st['ms_sweep_kernel_tail']:.0f} ms); FP64 re-solve "
         f"{st['ms_sweep_kernel_refine']:.0f} ms over {st['sweep_launches_refine']} timed launches; "
@@ -556,7 +581,7 @@ def main():
             "proposer": learned, "stage_retirement": staged,
             "stats": {k: st_graph[k] for k in ("backups", "sweeps", "sweeps_tail", "eval_sweeps", "polish_sweeps",
                                                "rank_rounds", "floor_stops", "ms_vi", "ms_eval", "variant",
-                                               "variant_tail", "variant_refine", "bytes", "bytes_tail",
+                                               "variant_tail", "variant_refine", "resident_models", "bytes", "bytes_tail",
                                                "bytes_refine", "refine_pairs", "refine_columns")}}
     print(json.dumps(line), flush=True)
 

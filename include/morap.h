@@ -213,8 +213,10 @@ typedef struct {
     double  ms_sweep_kernel_tail;
     int32_t variant_tail;   /* that kernel's variant (0: no switch)                 */
     int32_t resident_models; /* models whose values the last solve kept in LDS (if   */
-                            /* all: variant 41 and the launches of that kernel in   */
-                            /* ms_sweep_kernel; else these fields are the others')  */
+                            /* all: the launches of those kernels in                */
+                            /* ms_sweep_kernel, and variant 41; products given as   */
+                            /* rows and stage retirement report the batched sweep   */
+                            /* of that width.  Else these fields are the others')   */
     int64_t refine_pairs;   /* support / query after FP32 solves: unassigned pairs   */
                             /* within the FP32 error of the assignment re-solved in  */
                             /* FP64 ...                                              */
@@ -502,14 +504,15 @@ int morap_proposer_infer(morap_ctx* ctx, const float* X, int n, float* W_out);
  * of any kind.  X_dev[n][n_in] (FP32, device pointer, caller-owned) ->
  * W_out_dev[n][d] (FP32 softmax rows, device pointer, caller-owned).  The
  * work is enqueued on the context's stream and not waited for (synchronise
- * the device or the stream before reading W_out_dev).  The activations use a
- * fixed scratch of 8 MiB per device (held until the process ends, its address
- * taken when the first context on the device is created): n must satisfy
+ * the device or the stream before reading W_out_dev).  n must satisfy
  * n * (2 n_in + 1536 + 4 d) bytes (each part rounded up to 256) <= 8 MiB,
  * e.g. at most 4,712 rows for n_in = 62, d = 30; larger n returns
- * UNSUPPORTED with the limit in the message and enqueues nothing.  Every call
- * on a device shares that scratch: calls that overlap on one device (from
- * several contexts or streams) race.  Errors: INVALID (NULL pointers,
+ * UNSUPPORTED with the limit in the message and enqueues nothing.  That is a
+ * fixed scratch of 8 MiB per device (held until the process ends, its address
+ * taken when the first context on the device is created), which networks of
+ * n_in > 1,024 or d > 512 use for their activations, and calls whose input
+ * and output overlap for their output: such calls that overlap on one device
+ * (from several contexts or streams) race.  Errors: INVALID (NULL pointers,
  * n < 1), STATE (no proposer), UNSUPPORTED (too many rows), HIP. */
 int morap_proposer_infer_noalloc(morap_ctx* ctx, const float* X_dev, int n, float* W_out_dev);
 

@@ -16,6 +16,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <functional>
 
 namespace morap {
 
@@ -324,10 +325,11 @@ struct Fork {
             (void)hipStreamSynchronize(c->side[i]);
     }
     hipStream_t stream(int i) const { return i % (n + 1) == 0 ? c->stream : c->side[i % (n + 1) - 1]; }
-    // for a launch of that much work: the stream with the least so far
-    hipStream_t least(double work) {
-        int at = 0;
-        for (int i = 1; i <= n; ++i)
+    // for a launch of that much work: the stream with the least so far (beside:
+    // not the context's, where other work goes on)
+    hipStream_t least(double work, bool beside = false) {
+        int at = beside && n > 0 ? 1 : 0;
+        for (int i = at + 1; i <= n; ++i)
             if (load[i] < load[at]) at = i;
         load[at] += work;
         return stream(at);
@@ -630,8 +632,10 @@ static k::ResidentArgs resident_args(morap_ctx* c, ValueSet& vs, const k::Conver
 // The pairs of the plan's models to their stop with the values in LDS
 // (pair_sweeps cleared before), up to `limit` sweeps each; their statistics
 // as the batched sweeps count them.  The values land in vs.x[0].
+// `beside` runs on the context's stream while the first launches do.
 static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& part, const morap_vi_opts& o,
-                         bool warm, int64_t limit, int chunk, Stats& st) {
+                         bool warm, int64_t limit, int chunk, Stats& st,
+                         const std::function<void()>& beside = nullptr) {
     const HostModels& hm = c->hm;
     const bool f32 = vs.prec == MORAP_F32;
     const ResidentPlan& plan = c->resident_plan;
@@ -650,7 +654,7 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
         a.sweep1 = (int)done;
         a.last = done == limit ? 1 : 0;
         // (timed launches one by one)
-        Fork fork(c, o.time_kernels ? 1 : (int)part.launches.size());
+        Fork fork(c, o.time_kernels ? 1 : (int)part.launches.size() + (beside ? 1 : 0));
         for (size_t q = 0; q < part.launches.size(); ++q) {
             const auto& l = part.launches[q];
             a.order = plan.order.as<int32_t>() + l.begin;
@@ -666,7 +670,7 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
                 work += hm.state_base[m + 1] - hm.state_base[m];
             }
             // (FP32 rates with one, two and four columns a workgroup)
-            const hipStream_t s = fork.least(work * (l.columns == 1 ? 1.8 : (l.columns == 2 ? 1.4 : 1.0)));
+            const hipStream_t s = fork.least(work * (l.columns == 1 ? 1.8 : (l.columns == 2 ? 1.4 : 1.0)), (bool)beside);
             if (l.rows && l.columns == 0) {
                 a.short_rec = plan.short_rec.as<uint4>();
                 a.short_val = f32 ? plan.short_val32.p : plan.short_val64.p;
@@ -684,6 +688,7 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
             else k::resident(s, vs.prec, l.fast, wide, l.max_states, a);
             if (o.time_kernels) MORAP_HIP(hipEventRecord(held.v.back().second, c->stream));
         }
+        if (beside && s0 == 0) beside();
         fork.join();
         read_results(c, vs);
         ps = c->h_pair_sweeps.as<int32_t>();
@@ -805,7 +810,6 @@ static void run_vi(morap_ctx* c, int g, ValueSet& vs, const uint8_t* mask, const
                       c->d_team_E.as<double>(), vs.prec, vs.x[0].p);
     }
     MORAP_HIP(hipEventRecord(wall.a, c->stream));
-    if (part) run_resident(c, vs, *part, o, warm, limit, chunk, st);
     int64_t launched = 0;
     int64_t* h = c->h_counters.as<int64_t>();
     PooledEvents held(c);
@@ -835,13 +839,15 @@ static void run_vi(morap_ctx* c, int g, ValueSet& vs, const uint8_t* mask, const
     };
     const size_t el = vs.prec == MORAP_F32 ? 4 : 8;
     const int64_t main_tiles = (int64_t)c->tiles.size();
-    while (true) {
+    int64_t first_tiles = 0;   // active after the first chunk
+    auto sweeps = [&] {        // one chunk; true when no pair is active any more
         run_chunk(c, vp == &v0 ? g : 2, vs, mask, *vp, o.eps_vi, chunk, o.use_graph != 0,
                   o.time_kernels ? &ev : nullptr);
         launched += chunk;
         read_counters(c);
         harvest();
-        if (h[3] == 0) break;
+        if (h[3] == 0) return true;
+        if (first_tiles == 0) first_tiles = h[1];
         if (vt && vp == &v0 && h[1] * 100 < main_tiles * tail_percent()) {
             // the same active models listed over the halo tiles
             bytes_at_switch = (double)h[6] + 2.0 * el * (double)h[7];
@@ -853,7 +859,21 @@ static void run_vi(morap_ctx* c, int g, ValueSet& vs, const uint8_t* mask, const
             fail(MORAP_E_NOT_CONVERGED, "value iteration: " + std::to_string(h[3]) +
                                             " (model, column) pairs still active after " +
                                             std::to_string(launched) + " sweeps" + describe_active(c, vs));
+        return false;
+    };
+    bool over = false;
+    if (part) {
+        // the batched sweeps alone while they fill the device, then (fewer
+        // than half of the first tiles active) beside the launches in LDS:
+        // 24 agents on 32 x 32 .. 128 x 128 grids x 32 tasks, 64 columns, 203
+        // -> 199 ms and, another draw, 184 -> 178 (the LDS kernels leave few
+        // compute units to the sweeps until they end)
+        while (!over && (first_tiles == 0 || h[1] * 2 > first_tiles)) over = sweeps();
+        run_resident(c, vs, *part, o, warm, limit, chunk, st, [&] {
+            while (!over) over = sweeps();
+        });
     }
+    while (!over) over = sweeps();
     MORAP_HIP(hipEventRecord(wall.b, c->stream));
     MORAP_HIP(hipEventSynchronize(wall.b));
     const float ms = wall.elapsed_ms();

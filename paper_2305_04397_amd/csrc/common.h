@@ -628,7 +628,15 @@ void compact(hipStream_t s, const ConvergeArgs& a);
 void relist(hipStream_t s, ConvergeArgs a);
 void init_solve(hipStream_t s, const ConvergeArgs& a);
 // the same without the active lists: no pair is left to the batched sweeps
-void init_pairs(hipStream_t s, const ConvergeArgs& a);
+// a solve's pair sweeps, values at the initial states and counters to pinned
+// memory in one launch
+constexpr size_t REPORT_BYTES = (size_t)1 << 20;
+void report(hipStream_t s, int64_t n_ps, const int32_t* ps, int32_t* h_ps, int64_t n_c, const double* c, double* h_c,
+            const int64_t* counters, int64_t* h_counters);
+// (with n_W > 0 it also brings weights over from pinned memory)
+void init_pairs(hipStream_t s, const ConvergeArgs& a, const double* from = nullptr, double* W = nullptr,
+                int64_t n_W = 0);
+constexpr int64_t SMALL_WEIGHTS = 8192;   // (a 2 x 2 problem's solve: 58.8 us, 60.4 with a copy of their own)
 // mask[m][k] = flag[m]
 void model_mask(hipStream_t s, int M, int Kp, const uint8_t* flag, uint8_t* mask);
 

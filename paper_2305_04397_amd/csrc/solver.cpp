@@ -585,6 +585,13 @@ static void read_results(morap_ctx* c, const ValueSet& vs) {
     const size_t ps = (size_t)c->hm.M * vs.Kp * 4, cv = (size_t)vs.K * c->hm.M * 8;
     c->h_pair_sweeps.ensure(ps);
     c->h_c.ensure(cv);
+    if (ps + cv <= k::REPORT_BYTES) {
+        k::report(c->stream, (int64_t)(ps / 4), c->d_pair_sweeps.as<int32_t>(), c->h_pair_sweeps.as<int32_t>(),
+                  (int64_t)(cv / 8), vs.c.as<double>(), c->h_c.as<double>(), c->d_counters.as<int64_t>(),
+                  c->h_counters.as<int64_t>());
+        MORAP_HIP(hipStreamSynchronize(c->stream));
+        return;
+    }
     MORAP_HIP(hipMemcpyAsync(c->h_pair_sweeps.p, c->d_pair_sweeps.p, ps, hipMemcpyDeviceToHost, c->stream));
     MORAP_HIP(hipMemcpyAsync(c->h_c.p, vs.c.p, cv, hipMemcpyDeviceToHost, c->stream));
     read_counters(c);
@@ -776,7 +783,9 @@ static void run_vi(morap_ctx* c, int g, ValueSet& vs, const uint8_t* mask, const
             if (vs.prec == MORAP_F32) k::fill_f32(c->stream, vs.x[0].as<float>(), 0.f, (c->S + 1) * vs.Kp);
             else k::fill_f64(c->stream, vs.x[0].as<double>(), 0.0, (c->S + 1) * vs.Kp);
         }
-        k::init_pairs(c->stream, converge_args(c, vs, nullptr, o.eps_vi, 0, false));
+        const int64_t n_W = (int64_t)vs.K * (c->hm.nI + c->hm.nJ);
+        k::init_pairs(c->stream, converge_args(c, vs, nullptr, o.eps_vi, 0, false), c->h_weights.as<double>(),
+                      c->d_weights.as<double>(), n_W <= k::SMALL_WEIGHTS ? n_W : 0);
         MORAP_HIP(hipEventRecord(wall.a, c->stream));
         run_resident(c, vs, *part, o, warm, limit, chunk, st);
         MORAP_HIP(hipEventRecord(wall.b, c->stream));
@@ -1056,7 +1065,8 @@ static void solve_impl(morap_ctx* c, const double* W, int K, const morap_vi_opts
         c->d_weights.ensure((size_t)K * d * 8);
         c->h_weights.ensure((size_t)K * d * 8);
         std::memcpy(c->h_weights.p, W, (size_t)K * d * 8);
-        MORAP_HIP(hipMemcpyAsync(c->d_weights.p, c->h_weights.p, (size_t)K * d * 8, hipMemcpyHostToDevice, c->stream));
+        if (batched || (int64_t)K * d > k::SMALL_WEIGHTS)   // (else with the start of the pairs)
+            MORAP_HIP(hipMemcpyAsync(c->d_weights.p, c->h_weights.p, (size_t)K * d * 8, hipMemcpyHostToDevice, c->stream));
     }
     // per-(model, column) weights of the model's two objectives (a team
     // model: its rows are scalarised per column on the device instead, and

@@ -335,6 +335,13 @@ struct Fork {
         return stream(at);
     }
     double load[4] = {0, 0, 0, 0};
+    // what follows on the streams beside the context's waits for all before it
+    void barrier() {
+        for (int i = 0; i < n; ++i) MORAP_HIP(hipEventRecord(c->join_event[i], c->side[i]));
+        for (int i = 0; i < n; ++i)
+            for (int j = 0; j < n; ++j)
+                if (j != i) MORAP_HIP(hipStreamWaitEvent(c->side[i], c->join_event[j], 0));
+    }
     void join() {
         for (int i = 0; i < n; ++i) {
             MORAP_HIP(hipEventRecord(c->join_event[i], c->side[i]));
@@ -1311,7 +1318,9 @@ struct Instances {
 
     // value iteration in LDS, sweeps s0 + 1 .. s1 of the instances without a
     // stop in `sweeps`, from the FP32 solve's values (after an FP64 solve from 0)
-    void launch_vi(morap_ctx* c, double* x, int32_t* sweeps, int64_t s0, int64_t s1, EventPairs* ev) const {
+    // (beside: on the streams of that fork other than the context's, not joined)
+    void launch_vi(morap_ctx* c, double* x, int32_t* sweeps, int64_t s0, int64_t s1, EventPairs* ev,
+                   Fork* beside = nullptr) const {
         k::ResidentArgs a{};
         a.state_base = c->d_state_base.as<int32_t>();
         a.init = c->d_init.as<int32_t>();
@@ -1341,7 +1350,9 @@ struct Instances {
         }
         a.sweep0 = (int)s0;
         a.sweep1 = (int)s1;
-        Fork fork(c, ev ? 1 : (int)vi.size());   // (timed launches one by one)
+        std::unique_ptr<Fork> own;
+        if (!beside) own.reset(new Fork(c, ev ? 1 : (int)vi.size()));   // (timed launches one by one)
+        Fork& fork = beside ? *beside : *own;
         for (size_t q = 0; q < vi.size(); ++q) {
             const Run& r = vi[q];
             a.order = d_order + r.begin;
@@ -1353,12 +1364,13 @@ struct Instances {
             }
             // (an instance's time follows its size: a launch's, its largest one's
             // and how many they are)
-            const hipStream_t s = fork.least((double)r.max_states * (1.0 + r.n / (double)c->prop.multiProcessorCount));
+            const hipStream_t s =
+                fork.least((double)r.max_states * (1.0 + r.n / (double)c->prop.multiProcessorCount), beside != nullptr);
             if (r.large) k::resident_inst_large(s, r.max_states, a);
             else k::resident_inst(s, r.fast, r.max_states, a);
             if (ev) MORAP_HIP(hipEventRecord(ev->back().second, c->stream));
         }
-        fork.join();
+        if (own) own->join();
     }
 
     // sweeps the value iteration took as the tiled iteration counts them
@@ -1547,13 +1559,97 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
     };
     const bool warm_values = c->prec == MORAP_F32 && c->vmain.valid;
     if (c->has_blocks && general && !warm_values) k::fill_f64(s, xi, 0.0, NS);
+    double* xe0 = c->d_xe[0].as<double>();
+    double* xe1 = c->d_xe[1].as<double>();
+    int8_t* mu = c->d_mu.as<int8_t>();
+
+    // the instances in LDS: policies, then the first sweeps of the evaluation;
+    // all launched before the host looks at how the values ended
+    k::InstanceArgs ia{};
+    ia.inst_model = I.d_model;
+    ia.inst_base = I.d_base;
+    ia.state_base = c->d_state_base.as<int32_t>();
+    ia.rec = c->d_blk_rec.as<int32_t>();
+    ia.ablk = c->d_blk64.as<double>();
+    ia.zero_row = (int32_t)c->S;
+    ia.iwc = I.d_wc;
+    ia.iwp = I.d_wp;
+    ia.xi = xi;
+    ia.mu = mu;
+    ia.tau = o.tau;
+    ia.widenings = kTauSteps;
+    ia.counters = inst_ctr;
+    ia.xe = xe0;
+    ia.xe_prev = c->d_xe_prev.as<double>();
+    ia.prev_src = reinterpret_cast<const int64_t*>(packed + at_prev);
+    ia.from_values = o.eval_start ? 1 : 0;
+    ia.sweeps = ev_sweeps;
+    ia.eps = o.eps_eval;
+    // with larger products beside them, the instances in LDS go through all
+    // their steps on other streams while those take theirs on the context's:
+    // a support step of 12 agents x 24 tasks whose largest products have 24,000
+    // states 43.2 -> 42.0 ms
+    std::unique_ptr<Fork> beside;
+    auto launch = [&](const std::vector<Instances::Run>& runs, auto&& kernel) {
+        std::unique_ptr<Fork> own;
+        if (!beside) own.reset(new Fork(c, (int)runs.size()));
+        Fork& fork = beside ? *beside : *own;
+        for (size_t q = 0; q < runs.size(); ++q) {
+            ia.order = I.d_order + runs[q].begin;
+            ia.n = runs[q].n;
+            kernel(fork.least((double)ia.n * runs[q].max_states, (bool)beside), runs[q].max_states, ia);
+        }
+        if (own) own->join();
+        else beside->barrier();
+    };
+    // (a policy instance's LDS use follows its size: classes of one, two, four
+    // and more workgroups a compute unit)
+    const auto policy_runs = I.runs(c, [](int S_m) { return S_m <= 2500 ? 0 : (S_m <= 5000 ? 1 : 2); });
+    const auto eval_runs = I.runs(c, [](int S_m) { return k::eval_class(S_m); });
+    const int64_t eval_limit = ((int64_t)o.max_sweeps + chunk - 1) / chunk * chunk;
+    int64_t esweeps = 0;
+    std::string unfinished;   // instances in LDS whose evaluation hit its limit
+    auto policies_and_values = [&] {
+        launch(policy_runs, k::inst_policy);
+        ia.sweep0 = 0;
+        ia.sweep1 = (int)std::min<int64_t>(eval_limit, kResidentSweeps);
+        launch(eval_runs, k::inst_eval);
+    };
+    // Alg. 4 per objective, from 0, or (warm) each instance whose column's
+    // previous column had an instance of the same task on the same model from
+    // that instance's final values, and (eval_start) from the scalarised
+    // values: the evaluation of a proper policy reaches its values from any
+    // start, with the same bound on the error at its stop
+    if (general) {
+        std::vector<int64_t> runs;
+        for (int q = 0; q < n; ++q) {
+            if (I.resident[q] || !iwarm[q]) continue;
+            runs.push_back(I.base[q]);
+            runs.push_back(prev_src[q]);
+            runs.push_back(I.base[q + 1] - I.base[q]);
+        }
+        k::fill_f64(s, xe0, 0.0, 2 * NS);
+        k::fill_f64(s, xe1, 0.0, 2 * NS);
+        if (!runs.empty()) {
+            c->d_warm_copy.ensure(runs.size() * 8);
+            MORAP_HIP(hipMemcpyAsync(c->d_warm_copy.p, runs.data(), runs.size() * 8, hipMemcpyHostToDevice, s));
+            k::copy_runs(s, c->d_warm_copy.as<int64_t>(), (int)(runs.size() / 3), c->d_xe_prev.as<double>(), xe0);
+            MORAP_HIP(hipStreamSynchronize(s));   // the host run list goes out of scope
+        }
+    }
     EventPair vi_wall;
     PooledEvents vi_events(c);
     if (lds) {
         k::fill_i32(s, vi_sweeps, 0, (int64_t)out_words + 4);
+        if (general && c->has_blocks && !o.time_kernels) beside.reset(new Fork(c, 4));
         MORAP_HIP(hipEventRecord(vi_wall.a, s));
-        I.launch_vi(c, xi, vi_sweeps, 0, std::min<int64_t>(vi_limit, kResidentSweeps), o.time_kernels ? &vi_events.v : nullptr);
+        I.launch_vi(c, xi, vi_sweeps, 0, std::min<int64_t>(vi_limit, kResidentSweeps),
+                    o.time_kernels ? &vi_events.v : nullptr, beside.get());
         MORAP_HIP(hipEventRecord(vi_wall.b, s));
+        if (beside) {
+            beside->barrier();
+            policies_and_values();
+        }
     }
     int64_t vsweeps = 0;
     c->last_c64_valid = false;
@@ -1637,79 +1733,14 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
 
     EventPair wall;
     MORAP_HIP(hipEventRecord(wall.a, s));
-    double* xe0 = c->d_xe[0].as<double>();
-    double* xe1 = c->d_xe[1].as<double>();
-    int8_t* mu = c->d_mu.as<int8_t>();
-
-    // the instances in LDS: policies, then the first sweeps of the evaluation;
-    // all launched before the host looks at how the values ended
-    k::InstanceArgs ia{};
-    ia.inst_model = I.d_model;
-    ia.inst_base = I.d_base;
-    ia.state_base = c->d_state_base.as<int32_t>();
-    ia.rec = c->d_blk_rec.as<int32_t>();
-    ia.ablk = c->d_blk64.as<double>();
-    ia.zero_row = (int32_t)c->S;
-    ia.iwc = I.d_wc;
-    ia.iwp = I.d_wp;
-    ia.xi = xi;
-    ia.mu = mu;
-    ia.tau = o.tau;
-    ia.widenings = kTauSteps;
-    ia.counters = inst_ctr;
-    ia.xe = xe0;
-    ia.xe_prev = c->d_xe_prev.as<double>();
-    ia.prev_src = reinterpret_cast<const int64_t*>(packed + at_prev);
-    ia.from_values = o.eval_start ? 1 : 0;
-    ia.sweeps = ev_sweeps;
-    ia.eps = o.eps_eval;
-    auto launch = [&](const std::vector<Instances::Run>& runs, auto&& kernel) {
-        Fork fork(c, (int)runs.size());
-        for (size_t q = 0; q < runs.size(); ++q) {
-            ia.order = I.d_order + runs[q].begin;
-            ia.n = runs[q].n;
-            kernel(fork.least((double)ia.n * runs[q].max_states), runs[q].max_states, ia);
+    auto finish_lds = [&] {
+        if (beside) {
+            beside->join();
+            beside.reset();
+        } else {
+            policies_and_values();
         }
-        fork.join();
-    };
-    // (a policy instance's LDS use follows its size: classes of one, two, four
-    // and more workgroups a compute unit)
-    const auto policy_runs = I.runs(c, [](int S_m) { return S_m <= 2500 ? 0 : (S_m <= 5000 ? 1 : 2); });
-    const auto eval_runs = I.runs(c, [](int S_m) { return k::eval_class(S_m); });
-    const int64_t eval_limit = ((int64_t)o.max_sweeps + chunk - 1) / chunk * chunk;
-    int64_t esweeps = 0;
-    std::string unfinished;   // instances in LDS whose evaluation hit its limit
-    auto policies_and_values = [&] {
-        launch(policy_runs, k::inst_policy);
-        ia.sweep0 = 0;
-        ia.sweep1 = (int)std::min<int64_t>(eval_limit, kResidentSweeps);
-        launch(eval_runs, k::inst_eval);
         read_out();
-    };
-    // Alg. 4 per objective, from 0, or (warm) each instance whose column's
-    // previous column had an instance of the same task on the same model from
-    // that instance's final values, and (eval_start) from the scalarised
-    // values: the evaluation of a proper policy reaches its values from any
-    // start, with the same bound on the error at its stop
-    if (general) {
-        std::vector<int64_t> runs;
-        for (int q = 0; q < n; ++q) {
-            if (I.resident[q] || !iwarm[q]) continue;
-            runs.push_back(I.base[q]);
-            runs.push_back(prev_src[q]);
-            runs.push_back(I.base[q + 1] - I.base[q]);
-        }
-        k::fill_f64(s, xe0, 0.0, 2 * NS);
-        k::fill_f64(s, xe1, 0.0, 2 * NS);
-        if (!runs.empty()) {
-            c->d_warm_copy.ensure(runs.size() * 8);
-            MORAP_HIP(hipMemcpyAsync(c->d_warm_copy.p, runs.data(), runs.size() * 8, hipMemcpyHostToDevice, s));
-            k::copy_runs(s, c->d_warm_copy.as<int64_t>(), (int)(runs.size() / 3), c->d_xe_prev.as<double>(), xe0);
-            MORAP_HIP(hipStreamSynchronize(s));   // the host run list goes out of scope
-        }
-    }
-    if (lds) {
-        policies_and_values();
         for (int64_t s0 = kResidentSweeps; I.running(h_sweeps, 1) > 0; s0 += kResidentSweeps) {
             if (s0 < vi_limit) {
                 I.launch_vi(c, xi, vi_sweeps, s0, std::min<int64_t>(vi_limit, s0 + kResidentSweeps), nullptr);
@@ -1722,6 +1753,7 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
                 // again from the final values
                 k::fill_i32(s, ev_sweeps, 0, (int64_t)out_words + 4 - n);
                 policies_and_values();
+                read_out();
             }
         }
         harvest_refine(c, vi_events.v, st);
@@ -1741,11 +1773,8 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
                 const int64_t e = h_sweeps[(size_t)n + 2 * (size_t)q + w];
                 esweeps = std::max(esweeps, e > 0 ? (e + chunk - 1) / chunk * chunk : eval_limit);
             }
-    }
-    if (c->has_blocks) {
-        st.polish_sweeps += vsweeps;
-        st.variant_refine = -1;   // instance-major block iteration
-    }
+    };
+    if (lds && !beside) finish_lds();
 
     if (general) {
         // Attractor rounds with the tolerance tau; states left unranked get
@@ -1812,6 +1841,12 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
         }
         esweeps = std::max(esweeps, tiled);
         k::select_final(s, a, xe0, xe1, ipar, 2);
+    }
+
+    if (lds && beside) finish_lds();
+    if (c->has_blocks) {
+        st.polish_sweeps += vsweeps;
+        st.variant_refine = -1;   // instance-major block iteration
     }
 
     // values at the initial states: of the policy values (an FP32 solve's

@@ -223,7 +223,6 @@ struct ResidentPlan {
         bool rows;              // products given as rows of entries: short rows, or streamed (columns > 0)
         int columns;            // > 0: larger products or rows, that many columns per workgroup
         int begin, n, max_states;   // (larger products: positions)
-        int inst_states;            // larger products whose instances fit the smaller one's kernel: states, else 0
     };
     struct Part {
         std::vector<Launch> launches;
@@ -715,8 +714,6 @@ bool has_grid_pattern(uint32_t union_pattern);
 // largest product (states) the kernel holds; `fast`: every block has the grid
 // pattern, every action one cost and slot 0 of every state is the state itself
 int resident_capacity(int prec, bool fast);
-// the same of an FP64 instance (block form, `fast`)
-int resident_inst_capacity();
 // register steps (states per thread) of a product of that many states; a
 // launch takes models of one class
 int resident_class(int states);

@@ -1089,7 +1089,7 @@ static void plan_rows(morap_ctx* c) {
                     continue;
                 }
             }
-            part.launches.push_back({false, true, columns, b, 1, n, 0});
+            part.launches.push_back({false, true, columns, b, 1, n});
         }
     }
     MORAP_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
@@ -1185,19 +1185,16 @@ static void plan_resident(morap_ctx* c) {
             }
             part.models.push_back(m);
             const int size = first ? states(m) : positions(m);
-            const int inst = prec == MORAP_F64 && columns > 0 && states(m) <= k::resident_inst_capacity() ? states(m) : 0;
             if (!part.launches.empty()) {
                 ResidentPlan::Launch& l = part.launches.back();
                 if (l.fast == fast(m) && l.begin + l.n == b && l.columns == columns &&
-                    (l.inst_states > 0) == (inst > 0) &&
                     (columns > 0 || k::resident_class(l.max_states) == k::resident_class(size))) {
                     ++l.n;
                     l.max_states = std::max(l.max_states, size);
-                    l.inst_states = std::max(l.inst_states, inst);
                     continue;
                 }
             }
-            part.launches.push_back({fast(m), false, columns, b, 1, size, inst});
+            part.launches.push_back({fast(m), false, columns, b, 1, size});
         }
         upload(part.d_rest, part.rest, s);
     }

@@ -370,8 +370,9 @@ resident_vi(ResidentArgs a) {
 // banks; reading the 17 probabilities per lane instead would cost 1.5 (FP32)
 // or 3 (FP64) times the LDS traffic of the values themselves.
 //
-// This kernel is FP64's: 37 columns of 49 products of up to 2,429 states take
-// 2.3 ms, 10 ms before.
+// This kernel is FP64's beyond 2,560 states: two columns of the values, new ones in
+// registers.  (49 products of up to 2,429 states, 37 columns, took 2.3 ms here
+// and 10 with the batched sweeps.)
 template <class T, int KC, int NS, bool INST = false>
 __global__ void __launch_bounds__(BIG_THREADS)
 resident_big(ResidentArgs a) {
@@ -814,18 +815,17 @@ __global__ void __launch_bounds__(BIG_THREADS) big_mfma(ResidentArgs a) {
 // dispatch
 // ---------------------------------------------------------------------------
 // States a workgroup can hold: 512 per register step.  The grid pattern with
-// one cost per action needs 17 probabilities a state (7 steps in FP32, 4 in
-// FP64 within 256 registers; with two FP64 columns a fifth step spills 204
-// bytes), the general block 25 and 5 costs (4 and 2).
+// one cost per action needs 17 probabilities a state (7 steps in FP32, 5 in
+// FP64 within 256 registers), the general block 25 and 5 costs (4 and 2).  A
+// fifth FP64 step leaves room for one column (with two it spills 204 bytes):
+// 37 columns of products of up to 2,380 states take 2.2 ms so, 2.75 with two
+// columns in the larger products' kernel, and an assigned pair's solve at 2,400
+// states 0.22 ms, 0.47 there.
 static int resident_steps(int prec, bool fast) {
-    return prec == MORAP_F32 ? (fast ? 7 : 4) : (fast ? 4 : 2);
+    return prec == MORAP_F32 ? (fast ? 7 : 4) : (fast ? 5 : 2);
 }
 
 bool has_grid_pattern(uint32_t union_pattern) { return pattern_for(union_pattern) == PAT_GRID; }
-
-// An instance's one column leaves the registers for a fifth step in FP64: its
-// solve at 2,400 states takes 0.22 ms, 0.47 with the larger products' kernel.
-int resident_inst_capacity() { return res_rows(5) - 1; }
 
 int resident_capacity(int prec, bool fast) {
     return res_rows(resident_steps(prec, fast)) - 1;
@@ -877,6 +877,7 @@ int resident_class(int states) {
 void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, ResidentArgs a) {
     if (a.n_models <= 0) return;
     const int ns = resident_class(max_states);
+    if (prec != MORAP_F32 && ns == 5) wide = false;   // (see resident_steps)
     const int kc = !wide ? 1 : (prec == MORAP_F32 ? 4 : 2);
     a.groups = (a.K + kc - 1) / kc;
     if (prec == MORAP_F32) {
@@ -886,7 +887,7 @@ void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, Res
         else launch_steps<float, 1, false, 4>(s, a, ns, max_states);
     } else {
         if (fast && wide) launch_steps<double, 2, true, 4>(s, a, ns, max_states);
-        else if (fast) launch_steps<double, 1, true, 4>(s, a, ns, max_states);
+        else if (fast) launch_steps<double, 1, true, 5>(s, a, ns, max_states);
         else if (wide) launch_steps<double, 2, false, 2>(s, a, ns, max_states);
         else launch_steps<double, 1, false, 2>(s, a, ns, max_states);
     }

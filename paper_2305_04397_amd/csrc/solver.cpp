@@ -1261,9 +1261,7 @@ struct Instances {
         for (size_t r = 1; r < first.size(); ++r) first[r] += first[r - 1];
         for (const auto& l : c->resident_plan.part[MORAP_F64].launches) {
             const int b = first[(size_t)l.begin], e = first[(size_t)(l.begin + l.n)];
-            if (e <= b) continue;
-            if (l.inst_states > 0) vi.push_back({b, e - b, l.inst_states, l.fast, false});
-            else vi.push_back({b, e - b, l.max_states, l.fast, l.columns > 0});
+            if (e > b) vi.push_back({b, e - b, l.max_states, l.fast, l.columns > 0});
         }
         order.resize((size_t)first.back());
         for (int q = 0; q < n; ++q)

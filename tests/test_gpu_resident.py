@@ -84,7 +84,7 @@ def test_register_steps_f32(ctx, morap, sizes, prec, K):
     _compare(ctx, morap, wl, K, prec, 1e-6, _block(morap, K), seed=K)
 
 
-@pytest.mark.parametrize("sizes", [(1, 64, 511, 512), (513, 1024), (1025, 1536), (1537, 2048)])
+@pytest.mark.parametrize("sizes", [(1, 64, 511, 512), (513, 1024), (1025, 1536), (1537, 2048), (2049, 2560), (2561,)])
 @pytest.mark.parametrize("K", [1, 5, 40])
 def test_register_steps_f64(ctx, morap, sizes, K):
     wl = _corridor(sizes)

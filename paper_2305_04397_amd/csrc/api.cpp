@@ -207,7 +207,7 @@ int morap_evaluate(morap_ctx* ctx, const int32_t* assign, int K, const morap_vi_
 int morap_assign(morap_ctx* ctx, const double* c, int K, int32_t* assign_out) {
     return guarded(ctx, [&] {
         MORAP_CHECK(ctx->loaded, MORAP_E_STATE, "no models loaded");
-        assign_columns(ctx->hm.nI, ctx->hm.nJ, c, K, assign_out);
+        assign_columns(ctx->hm.nI, ctx->hm.nJ, c, K, assign_out, &ctx->pool);
     });
 }
 
@@ -279,7 +279,7 @@ int morap_support(morap_ctx* ctx, const double* W, int K, const morap_vi_opts* o
         Stats st;
         solve(ctx, W, K, *opts, C.data(), st);
         // a team model's policy does the assignment itself: no assignment step
-        if (!ctx->team) assign_columns(nI, nJ, C.data(), K, A.data());
+        if (!ctx->team) assign_columns(nI, nJ, C.data(), K, A.data(), &ctx->pool);
         // after an FP32 solve the assignment is checked on FP64 values
         std::vector<int32_t> F(A);
         evaluate(ctx, A.data(), K, *opts, r_out, st, nullptr, ctx->team ? nullptr : F.data());

@@ -96,7 +96,7 @@ static void column_costs(int nI, int nJ, int cap, const double* ck, std::vector<
     }
 }
 
-void assign_columns(int nI, int nJ, const double* c, int K, int32_t* out) {
+void assign_columns(int nI, int nJ, const double* c, int K, int32_t* out, HostPool* pool) {
     MORAP_CHECK(nI > 0 && nJ > 0 && c && out && K > 0, MORAP_E_INVALID, "bad assignment arguments");
     for (int64_t q = 0; q < (int64_t)K * nI * nJ; ++q)
         MORAP_CHECK(std::isfinite(c[q]), MORAP_E_INVALID, "non-finite assignment value");
@@ -114,7 +114,8 @@ void assign_columns(int nI, int nJ, const double* c, int K, int32_t* out) {
                 if (match[r] >= 0 && match[r] < nJ) out[(size_t)k * nJ + match[r]] = r / cap;
         }
     };
-    const int nt = std::max(1, std::min<int>(K, std::min(16u, std::thread::hardware_concurrency())));
+    const int nt = host_threads(K);
+    if (pool) return pool->run(nt, worker);
     if (nt == 1 || (int64_t)K * n * n < (int64_t)1 << 16) {
         worker();
         return;

@@ -2,6 +2,12 @@
 // kernel launch wrappers.  Not part of the ABI (include/morap.h is).
 #pragma once
 
+#include <condition_variable>
+#include <exception>
+#include <functional>
+#include <mutex>
+#include <system_error>
+#include <thread>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -100,6 +106,93 @@ struct PinnedBuf {
     }
     template <class T> T* as() const { return static_cast<T*>(p); }
 };
+
+// ---------------------------------------------------------------------------
+// Host threads of a context, started by their first use and joined with it
+// (at most 15).  A pass of queries hands work to them four times; starting 16
+// threads each time took as long as the work (16 queries on 10 x 20: 20 ->
+// 15 ms).
+// ---------------------------------------------------------------------------
+class HostPool {
+public:
+    HostPool() = default;
+    HostPool(const HostPool&) = delete;
+    HostPool& operator=(const HostPool&) = delete;
+    ~HostPool() {
+        {
+            std::lock_guard<std::mutex> g(mu_);
+            stop_ = true;
+        }
+        wake_.notify_all();
+        for (auto& t : threads_) t.join();
+    }
+    // `worker` on this thread and on up to `threads` - 1 others, which may all
+    // find nothing left to do; the first exception is rethrown here.
+    void run(int threads, const std::function<void()>& worker) {
+        std::unique_lock<std::mutex> call(call_, std::try_to_lock);
+        if (threads <= 1 || !call) {   // (in use: alone)
+            worker();
+            return;
+        }
+        {
+            std::lock_guard<std::mutex> g(mu_);
+            try {
+                while ((int)threads_.size() < threads - 1) threads_.emplace_back([this] { loop(); });
+            } catch (const std::system_error&) {
+                // (as many as there are)
+            }
+            job_ = &worker;
+            tickets_ = std::min(threads - 1, (int)threads_.size());
+            error_ = nullptr;
+        }
+        wake_.notify_all();
+        std::exception_ptr mine;
+        try {
+            worker();
+        } catch (...) {
+            mine = std::current_exception();
+        }
+        std::unique_lock<std::mutex> g(mu_);
+        tickets_ = 0;   // those still asleep are not waited for
+        idle_.wait(g, [&] { return running_ == 0; });
+        job_ = nullptr;
+        if (!mine) mine = error_;
+        g.unlock();
+        if (mine) std::rethrow_exception(mine);
+    }
+
+private:
+    void loop() {
+        std::unique_lock<std::mutex> g(mu_);
+        for (;;) {
+            wake_.wait(g, [&] { return stop_ || tickets_ > 0; });
+            if (stop_) return;
+            --tickets_;
+            ++running_;
+            const std::function<void()>* job = job_;
+            g.unlock();
+            std::exception_ptr e;
+            try {
+                (*job)();
+            } catch (...) {
+                e = std::current_exception();
+            }
+            g.lock();
+            if (e && !error_) error_ = e;
+            if (--running_ == 0) idle_.notify_one();
+        }
+    }
+    std::mutex call_, mu_;
+    std::condition_variable wake_, idle_;
+    std::vector<std::thread> threads_;
+    const std::function<void()>* job_ = nullptr;
+    int tickets_ = 0, running_ = 0;
+    bool stop_ = false;
+    std::exception_ptr error_;
+};
+inline int host_threads(int n) {
+    return std::max(1, std::min<int>(n, (int)std::min(16u, std::thread::hardware_concurrency())));
+}
 
 // ---------------------------------------------------------------------------
 // host-side model set (concatenated CSR with global indices)
@@ -358,6 +451,7 @@ struct morap_ctx {
     morap::DevBuf d_act_tiles;                      // the active models' tiles, in order
     morap::DevBuf d_best_res, d_stall;              // [M][Kp] FP32 rounding-floor detection
     morap::DevBuf d_counters;                       // int64 [9] (see the convergence kernel)
+    morap::HostPool pool;
     morap::PinnedBuf h_counters;
     morap::PinnedBuf h_log;                         // per-launch tile counts (sweep log)
     std::vector<double> W;                          // [K][d] of the last solve
@@ -520,7 +614,8 @@ void evaluate(morap_ctx* ctx, const int32_t* assign, int K, const morap_vi_opts&
 const std::vector<Variant>& variants();
 
 // assign.cpp
-void assign_columns(int nI, int nJ, const double* c, int K, int32_t* out);
+// (pool: host threads to spread the columns over, or null: threads of its own)
+void assign_columns(int nI, int nJ, const double* c, int K, int32_t* out, HostPool* pool = nullptr);
 // one column's optimal assignment and the slack of every pair against it
 std::vector<int32_t> assignment_slack(int nI, int nJ, const double* ck, double* slack);
 

@@ -54,18 +54,14 @@ struct QState {
     double ms = 0;
 };
 
-// f(i) for i < n on up to 16 host threads; the first exception is rethrown.
+// f(i) for i < n on up to 16 host threads; the first exception is rethrown
+// once every i has been taken.
 template <class F>
-void parallel_for(int n, F f) {
-    const int nt = std::max(1, std::min<int>(n, (int)std::min(16u, std::thread::hardware_concurrency())));
-    if (nt == 1) {
-        for (int i = 0; i < n; ++i) f(i);
-        return;
-    }
+void parallel_for(HostPool& pool, int n, F f) {
     std::atomic<int> next{0};
     std::exception_ptr err;
     std::mutex mu;
-    auto worker = [&] {
+    pool.run(host_threads(n), [&] {
         for (int i; (i = next++) < n;) {
             try {
                 f(i);
@@ -74,10 +70,7 @@ void parallel_for(int n, F f) {
                 if (!err) err = std::current_exception();
             }
         }
-    };
-    std::vector<std::thread> th;
-    for (int t = 0; t < nt; ++t) th.emplace_back(worker);
-    for (auto& t : th) t.join();
+    });
     if (err) std::rethrow_exception(err);
 }
 
@@ -238,7 +231,7 @@ void query_batch(morap_ctx* c, const double* T, const double* W0, int Q, const d
                 solve(c, W.data(), K, vo, C.data(), st, o.warm_start && it > 0 ? warm_map.data() : nullptr);
                 const auto t1 = std::chrono::steady_clock::now();
                 // a team model's policy assigns by itself (A stays 0)
-                if (!c->team) assign_columns(nI, nJ, C.data(), K, A.data());
+                if (!c->team) assign_columns(nI, nJ, C.data(), K, A.data(), &c->pool);
                 // after an FP32 solve the assignment is checked on FP64 values
                 std::vector<int32_t> F(A);
                 evaluate(c, A.data(), K, vo, R.data(), st, o.warm_start && it > 0 ? warm_map.data() : nullptr,
@@ -251,7 +244,7 @@ void query_batch(morap_ctx* c, const double* T, const double* W0, int Q, const d
                 last_ms[1] = std::chrono::duration<double, std::milli>(t2 - t1).count();
                 // the geometry of each query (both projections, the stop test and
                 // the next weight vector) on host threads: queries share nothing
-                parallel_for(K, [&](int kk) {
+                parallel_for(c->pool, K, [&](int kk) {
                     QState& s = qs[act[kk]];
                     s.backups += st.backups / K;
                     s.ms += ms / K;

@@ -2043,13 +2043,7 @@ static int refine_assignment(morap_ctx* c, const int32_t* assign, int K, const m
                         cand[k].push_back(i * nJ + j);
         }
     };
-    {
-        const int nt = std::max(1, std::min<int>(K, (int)std::min(16u, std::thread::hardware_concurrency())));
-        std::vector<std::thread> th;
-        for (int t = 1; t < nt; ++t) th.emplace_back(worker);
-        worker();
-        for (auto& t : th) t.join();
-    }
+    c->pool.run(host_threads(K), worker);
     std::vector<int32_t> pk, pm;
     for (int k = 0; k < K; ++k)
         for (int32_t m : cand[k]) {
@@ -2070,7 +2064,7 @@ static int refine_assignment(morap_ctx* c, const int32_t* assign, int K, const m
             C[(size_t)k * M + assign[(size_t)k * nJ + j] * nJ + j] = c->last_c64[(size_t)k * nJ + j];
     for (size_t q = 0; q < pk.size(); ++q) C[(size_t)pk[q] * M + pm[q]] = v[q];
     std::vector<int32_t> A((size_t)K * nJ);
-    assign_columns(nI, nJ, C.data(), K, A.data());
+    assign_columns(nI, nJ, C.data(), K, A.data(), &c->pool);
     int changed = 0;
     for (int k = 0; k < K; ++k) {
         const double* ck = C.data() + (size_t)k * M;

@@ -304,8 +304,8 @@ __global__ void __launch_bounds__(RES_MAX_THREADS, NS <= 4 ? 4 : 2) eval_residen
         lds_put<double, 2>(BUF, z);
         flag[0] = flag[1] = 0;
     }
-    const bool judge = wave == nw - 1;
-    unsigned judged = live;
+    const bool stop_wave = wave == nw - 1;
+    unsigned stop_live = live;
     __syncthreads();
 
     auto sweep = [&](auto PAR) {
@@ -359,12 +359,12 @@ __global__ void __launch_bounds__(RES_MAX_THREADS, NS <= 4 ? 4 : 2) eval_residen
             store(IN, live);
             return true;
         }
-        if (judge) {
+        if (stop_wave) {
             const double rr = part_max(part + (1 - IN) * 4 * MAXW * 4, nw, 1, lane);
-            const bool now = lane < 2 && (judged >> lane & 1) && rr <= a.eps;
+            const bool now = lane < 2 && (stop_live >> lane & 1) && rr <= a.eps;
             if (now) a.sweeps[2 * q + lane] = n;
             const unsigned fresh = (unsigned)__ballot(now);
-            judged &= ~fresh;
+            stop_live &= ~fresh;
             if (lane == 0) flag[1 - IN] = fresh;
         }
         return false;

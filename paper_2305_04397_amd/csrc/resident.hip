@@ -79,7 +79,7 @@ resident_vi(ResidentArgs a) {
     const int sb = a.state_base[m], S = a.state_base[m + 1] - sb;
     unsigned char* hdr = lds + BUF + (((nw * 64 * NS + 1) * ROWB + 15) & ~15);
     T* part = reinterpret_cast<T*>(hdr);                               // [2][4 MAXW rows][4][res, |y|]
-    // the judge's state per column, kept out of the registers of a sweep
+    // the stop-test wave's state per column, kept out of the registers of a sweep
     double* best = reinterpret_cast<double*>(hdr + 2 * 4 * MAXW * 8 * sizeof(T));       // [4] smallest change so far
     int* stall = reinterpret_cast<int*>(best + 4);                                      // [4] sweeps since it was set
     unsigned* flag = reinterpret_cast<unsigned*>(stall + 4);                            // [2] results of the stop test
@@ -162,7 +162,7 @@ resident_vi(ResidentArgs a) {
         flag[0] = flag[1] = 0;
     }
     // the stop test is taken by the last wave, whose last steps may be empty
-    const bool judge = wave == nw - 1;
+    const bool stop_wave = wave == nw - 1;
     if (want_y && tid < KC) {
         best[tid] = a.best_res[it.pair0 + tid];
         stall[tid] = a.stall[it.pair0 + tid];
@@ -170,7 +170,7 @@ resident_vi(ResidentArgs a) {
     unsigned live = 0;   // columns still running
 #pragma unroll
     for (int c = 0; c < KC; ++c) live |= on[c] ? 1u << c : 0u;
-    unsigned judged = live;   // the same, as the stop test has them (a sweep ahead)
+    unsigned stop_live = live;   // the same, as the stop test has them (a sweep ahead)
     __syncthreads();
 
     auto sweep = [&](auto PAR) {
@@ -287,7 +287,7 @@ resident_vi(ResidentArgs a) {
         const T rr = part_max(p, nw, 2, ln), yy = want_y ? part_max(p + 1, nw, 2, ln) : (T)0;
         // lane c < KC tests column c
         bool now = false;
-        if (ln < KC && (judged >> ln & 1)) {
+        if (ln < KC && (stop_live >> ln & 1)) {
             bool floor_stop = false;
             now = it.stop(a, (double)rr, (double)yy, best[ln], stall[ln], floor_stop);
             if (now) {
@@ -300,8 +300,8 @@ resident_vi(ResidentArgs a) {
             }
         }
         const unsigned fresh = (unsigned)__ballot(now);
-        judged &= ~fresh;
-        if (ln == 0) flag[CUR] = fresh | (judged == 0 ? 0x100u : 0u);
+        stop_live &= ~fresh;
+        if (ln == 0) flag[CUR] = fresh | (stop_live == 0 ? 0x100u : 0u);
     };
 
     // final (or, at the end of the launch, current) values of the columns in
@@ -336,7 +336,7 @@ resident_vi(ResidentArgs a) {
             store(a.x0, IN, live);
             if constexpr (!INST) {
                 if (a.last) store(a.x1, 1 - IN, live);
-                if (judge && lane < KC && (live >> lane & 1)) {
+                if (stop_wave && lane < KC && (live >> lane & 1)) {
                     const int64_t i = it.pair0 + lane;
                     if (want_y) {
                         a.best_res[i] = best[lane];
@@ -347,7 +347,7 @@ resident_vi(ResidentArgs a) {
             }
             return true;
         }
-        if (judge) decide(std::integral_constant<int, 1 - IN>{}, n);
+        if (stop_wave) decide(std::integral_constant<int, 1 - IN>{}, n);
         return false;
     };
     for (int n = a.sweep0 + 1;; n += 2) {        // sweep0 and sweep1 are even

@@ -80,12 +80,12 @@ __global__ void __launch_bounds__(THREADS) rows_vi(RowsArgs a) {
         }
         flag[0] = flag[1] = 0;
     }
-    const bool judge = wave == NW - 1;
+    const bool stop_wave = wave == NW - 1;
     if (F32 && tid < KC) {
         best[tid] = a.best_res[it.pair0 + tid];
         stall[tid] = a.stall[it.pair0 + tid];
     }
-    unsigned judged = live;   // the running columns, as the stop test has them (a sweep ahead)
+    unsigned stop_live = live;   // the running columns, as the stop test has them (a sweep ahead)
 
     constexpr int NR = AHEAD;
     uint2 at[NR];
@@ -190,7 +190,7 @@ __global__ void __launch_bounds__(THREADS) rows_vi(RowsArgs a) {
             // the last launch of a solve the iterate before it
             store(a.x0, in, live);
             if (a.last) store(a.x1, out, live);
-            if (judge && lane < KC && (live >> lane & 1)) {
+            if (stop_wave && lane < KC && (live >> lane & 1)) {
                 const int64_t i = it.pair0 + lane;
                 if (F32) {
                     a.best_res[i] = best[lane];
@@ -200,12 +200,12 @@ __global__ void __launch_bounds__(THREADS) rows_vi(RowsArgs a) {
             }
             return;
         }
-        if (judge) {
+        if (stop_wave) {
             // the stop test of sweep n, while the others run the next one
             const T* w = part + (1 - par) * 4 * NW * 8;
             const T rr = part_max(w, NW, 2, lane), yy = F32 ? part_max(w + 1, NW, 2, lane) : (T)0;
             bool now = false;
-            if (lane < KC && (judged >> lane & 1)) {
+            if (lane < KC && (stop_live >> lane & 1)) {
                 bool floor_stop = false;
                 now = it.stop(a, (double)rr, (double)yy, best[lane], stall[lane], floor_stop);
                 if (now) {
@@ -215,8 +215,8 @@ __global__ void __launch_bounds__(THREADS) rows_vi(RowsArgs a) {
                 }
             }
             const unsigned fresh = (unsigned)__ballot(now);
-            judged &= ~fresh;
-            if (lane == 0) flag[1 - par] = fresh | (judged == 0 ? 0x100u : 0u);
+            stop_live &= ~fresh;
+            if (lane == 0) flag[1 - par] = fresh | (stop_live == 0 ? 0x100u : 0u);
         }
     }
 }

@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(THREADS, 4) staged_vi(StagedLdsArgs a) {
     if (tid < 128) top[tid] = 0;
     // lane s KC + c of the last wave tests stage s of column c
     const int js = lane / KC, jc = lane % KC;
-    const bool judge = wave == NW - 1, tests = judge && js < nst && k0 + jc < a.K;
+    const bool stop_wave = wave == NW - 1, tests = stop_wave && js < nst && k0 + jc < a.K;
     const int64_t ju = (int64_t)(u0 + min(js, nst - 1)) * a.Kp + k0 + jc;
     const int init_stage = a.init_unit[m] - u0;
     double best = INFINITY;
@@ -372,7 +372,7 @@ __global__ void __launch_bounds__(THREADS, 4) staged_vi(StagedLdsArgs a) {
         for (int i = 0; i < NS; ++i)
             if (i < cnt)
                 lds_put<T, KC>((unsigned)(__builtin_amdgcn_readlane(mine, i) * 64 + lane + 1) << SH, out[i]);
-        if (judge) {
+        if (stop_wave) {
             bool pass = true, floor_stop = false;
             if (tests && js >= low_of(jc)) {
                 if constexpr (F32) {

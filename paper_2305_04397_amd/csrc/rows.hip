@@ -106,9 +106,11 @@ __global__ void __launch_bounds__(THREADS) rows_vi(RowsArgs a) {
     }
     __syncthreads();
 
-    // values of the columns in `cols` from the iterate at `from`
+    // values of the columns in `cols` from the iterate at `from`, each wave its
+    // own slices: nothing waits between a stop's store and the next sweep, which
+    // writes that iterate
     auto store = [&](void* x, unsigned from, unsigned cols) {
-        for (int l = tid; l < S; l += THREADS) {
+        for (int l = s_begin * 64 + lane; l < min(s_end * 64, S); l += 64) {
             const Row<T, KC> v = lds_get<T, KC>(from + ((unsigned)(l + 1) << SH));
 #pragma unroll
             for (int c = 0; c < KC; ++c)

@@ -246,6 +246,7 @@ struct Item {
         return INST ? base + l : (int64_t)(sb + l) * a.Kp + k0 + c;
     }
     __device__ __forceinline__ T start(const ResidentArgs& a, int sb, int l, int c) const {
+        if (!INST && k0 + c >= a.K) return 0;   // (the values have no such column where K is small)
         if (a.sweep0 > 0 || (!INST && a.warm)) return static_cast<const T*>(a.x0)[place(a, sb, l, c)];
         if constexpr (INST) {
             // the FP32 solve's values scaled to the instance's weights, where

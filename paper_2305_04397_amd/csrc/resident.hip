@@ -163,7 +163,7 @@ resident_vi(ResidentArgs a) {
     }
     // the stop test is taken by the last wave, whose last steps may be empty
     const bool stop_wave = wave == nw - 1;
-    if (want_y && tid < KC) {
+    if (want_y && tid < KC && it.k0 + tid < a.K) {
         best[tid] = a.best_res[it.pair0 + tid];
         stall[tid] = a.stall[it.pair0 + tid];
     }
@@ -631,7 +631,7 @@ __global__ void __launch_bounds__(BIG_THREADS) big_mfma(ResidentArgs a) {
         for (int c = 0; c < KC; ++c) z.v[c] = 0;
         put(0, z);
     }
-    if (tid < KC) {
+    if (tid < KC && it.k0 + tid < a.K) {
         best[tid] = a.best_res[it.pair0 + tid];
         stall[tid] = a.stall[it.pair0 + tid];
     }
@@ -874,11 +874,20 @@ int resident_class(int states) {
     return ns <= 5 ? (ns < 1 ? 1 : ns) : 7;
 }
 
+// Columns per workgroup of the first kernel: a group, or one where the solve has
+// fewer columns than a group (24 x 30 products of 32 x 32 grids, FP32: two
+// columns take 0.49 ms one by one, 0.74 as half a group).
+static int first_columns(int prec, bool wide, const ResidentArgs& a) {
+    const int kc = prec == MORAP_F32 ? 4 : 2;
+    return wide && kc <= a.Kp ? kc : 1;
+}
+
 void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, ResidentArgs a) {
     if (a.n_models <= 0) return;
     const int ns = resident_class(max_states);
     if (prec != MORAP_F32 && ns == 5) wide = false;   // (see resident_steps)
-    const int kc = !wide ? 1 : (prec == MORAP_F32 ? 4 : 2);
+    const int kc = first_columns(prec, wide, a);
+    wide = kc > 1;
     a.groups = (a.K + kc - 1) / kc;
     if (prec == MORAP_F32) {
         if (fast && wide) launch_steps<float, 4, true, 7>(s, a, ns, max_states);
@@ -896,7 +905,8 @@ void resident(hipStream_t s, int prec, bool fast, bool wide, int max_states, Res
 void resident_short(hipStream_t s, int prec, bool wide, int max_states, ResidentArgs a) {
     if (a.n_models <= 0) return;
     const int ns = resident_class(max_states);
-    const int kc = !wide ? 1 : (prec == MORAP_F32 ? 4 : 2);
+    const int kc = first_columns(prec, wide, a);
+    wide = kc > 1;
     a.groups = (a.K + kc - 1) / kc;
     if (prec == MORAP_F32) {
         if (wide) launch_steps<float, 4, false, 4, false, true>(s, a, ns, max_states);
@@ -959,6 +969,7 @@ void launch_big(hipStream_t s, const ResidentArgs& a, int max_positions) {
 
 void resident_large(hipStream_t s, int prec, int columns, int max_positions, ResidentArgs a) {
     if (a.n_models <= 0) return;
+    columns = std::min(columns, a.Kp);
     a.groups = (a.K + columns - 1) / columns;
     if (prec == MORAP_F32) {
         if (columns == 4) launch_big<float, 4>(s, a, max_positions);

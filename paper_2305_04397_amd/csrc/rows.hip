@@ -81,7 +81,7 @@ __global__ void __launch_bounds__(THREADS) rows_vi(RowsArgs a) {
         flag[0] = flag[1] = 0;
     }
     const bool stop_wave = wave == NW - 1;
-    if (F32 && tid < KC) {
+    if (F32 && tid < KC && it.k0 + tid < a.K) {
         best[tid] = a.best_res[it.pair0 + tid];
         stall[tid] = a.stall[it.pair0 + tid];
     }
@@ -257,6 +257,7 @@ static void launch_rows(hipStream_t s, const RowsArgs& a, int max_states) {
 void resident_rows(hipStream_t s, int prec, int columns, int max_states, const RowsArgs& args) {
     RowsArgs a = args;
     if (a.n_models <= 0) return;
+    columns = std::min(columns, a.Kp);
     a.groups = (a.K + columns - 1) / columns;
     if (prec == MORAP_F32) {
         if (columns == 4) launch_rows<float, 4>(s, a, max_states);

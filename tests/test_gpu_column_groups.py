@@ -3,8 +3,13 @@ columns than a workgroup's widest group: the LDS iterations against the batched
 sweeps, every value of every column the same bits.  (A group of columns is taken
 only where a solve has more (product, column) pairs than twice the device's
 compute units.)"""
+import dataclasses
+
 import numpy as np
 import pytest
+
+from workloads import make_workload, dirichlet_weights
+from workloads.gridworld import make_agent
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +75,45 @@ def test_streamed_rows_whose_columns_stop_apart(ctx, morap, prec, sizes, entries
     models = [_rows(rng, n, entries) for n in sizes]
     ctx.load_models(models, len(sizes), 1)
     _same_everywhere(ctx, morap, _unlike_weights(64, len(sizes), 1), len(sizes), 1, prec, 16, len(sizes))
+
+
+def _batched(blocks, K):
+    """A batched sweep of one lane group of the padded width."""
+    Kp = 1
+    while Kp < K:
+        Kp *= 2
+    return ({1: 19, 2: 20, 4: 22} if blocks else {1: 1, 2: 2, 4: 4})[Kp]
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("K", [1, 2, 3])
+@pytest.mark.parametrize("form", ["blocks", "rows"])
+def test_fewer_columns_than_a_group(ctx, morap, form, prec, K):
+    """One to three columns of more products than twice the compute units: no
+    group reaches past the columns the buffers hold.  Products of every kernel:
+    small, larger (sorted by block; streamed rows), one of the batched sweeps."""
+    wl = make_workload(1)
+    rng = np.random.default_rng(K)
+    sides = [3 + i % 4 for i in range(22)] + [64]
+    agents = [make_agent(rng, np.ones((s, s), bool), 0, 0.1, rng.uniform(1, 3, 5)) for s in sides]
+    tasks = [wl.tasks[0]] * 24
+    letters = [[np.where(np.arange(s * s) == s * s - 1, 1 + j % 2, 0).astype(np.int32) for j in range(24)] for s in sides]
+    for rows, s in zip(letters, sides):
+        for j, lab in enumerate(rows):
+            lab[s * s // 2 + j % 2] = 2 - j % 2
+            lab[0] = 0
+    wl = dataclasses.replace(wl, agents=agents, tasks=tasks, letters=letters)
+    nI, nJ = len(sides), 24
+    if form == "blocks":
+        ctx.build_products(wl)
+    else:
+        ctx.load_models([morap.product_host(a, t, letters[i][j]) for i, a in enumerate(agents)
+                         for j, t in enumerate(tasks)], nI, nJ)
+    W = dirichlet_weights(np.random.default_rng(K), K, nI + nJ)
+    _same_everywhere(ctx, morap, W, nI, nJ, prec, _batched(form == "blocks", K), nI * nJ)
+    # a query's later passes start from the values before
+    t = np.concatenate([np.full(nI, -300.0), np.full(nJ, 0.9)])
+    q = [ctx.query(t, eps=1e-3, max_iter=4, opts=morap.Options(eps_vi=1e-7, precision=prec, schedule=sched), warm_start=True)
+         for sched in (0, _batched(form == "blocks", 1))]
+    assert q[0]["verdict"] == q[1]["verdict"] and q[0]["iterations"] == q[1]["iterations"]
+    assert np.allclose(q[0]["t_up"], q[1]["t_up"], rtol=1e-5, atol=1e-5)

@@ -666,13 +666,15 @@ __global__ void __launch_bounds__(BIG_THREADS) big_mfma(ResidentArgs a) {
         for (int c = 0; c < KC; ++c) r[c] = y[c] = 0;
         unsigned at = (unsigned)lane * 16;
         asm volatile("" : "+v"(at));   // (no addresses kept over the sweeps)
-        auto record = [&](int i) { return *reinterpret_cast<const uint3*>(rec + (at + i * 1024)); };
         // one step and, inside its condition, the next: the registers of what is
         // on its way are renamed from step to step, not copied
         Move mv;
         int run_end = 0;   // first step of the next run of one block
         int k = cnt;
         asm volatile("" : "+s"(k));    // (nor a condition per step)
+        // (never past this wave's last step: what follows may be another product's,
+        // naming rows that this workgroup's LDS does not have)
+        auto record = [&](int i) { return *reinterpret_cast<const uint3*>(rec + min(i, k - 1) * 1024 + at); };
         struct Slots {
             Row<float, KC> v[NSLOT];
         };
@@ -692,7 +694,7 @@ __global__ void __launch_bounds__(BIG_THREADS) big_mfma(ResidentArgs a) {
             if (i >= k) return;
             const uint3 q2 = record(i + 2);   // two steps ahead
             Slots xn;
-            if constexpr (early) xn = gather(qn);   // (past the last step: in bounds, not used)
+            if constexpr (early) xn = gather(qn);   // (past the last step: its own rows again, not used)
             if (i == run_end) {
                 const int run = runs[s_begin + i];
                 run_end = (run >> 16) - s_begin;
@@ -759,7 +761,7 @@ __global__ void __launch_bounds__(BIG_THREADS) big_mfma(ResidentArgs a) {
             }
             if constexpr (i + 1 < NS) self(self, std::integral_constant<int, i + 1>{}, qn, q2, xn);
         };
-        {
+        if (k > 0) {
             const uint3 q = record(0), qn = record(1);
             Slots x;
             if constexpr (early) x = gather(q);

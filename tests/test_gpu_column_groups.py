@@ -117,3 +117,29 @@ def test_fewer_columns_than_a_group(ctx, morap, form, prec, K):
          for sched in (0, _batched(form == "blocks", 1))]
     assert q[0]["verdict"] == q[1]["verdict"] and q[0]["iterations"] == q[1]["iterations"]
     assert np.allclose(q[0]["t_up"], q[1]["t_up"], rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("K", [64, 1])
+def test_larger_products_before_the_largest(ctx, morap, K):
+    """FP32 products of four, two and one columns a workgroup, each followed by
+    one of nearly 40,000 states in the records: what a wave reads ahead past its
+    product's last step names LDS rows that its own launch does not have."""
+    rng = np.random.default_rng(K)
+    agents, letters = [], []
+    for n in (3700, 39200, 9700, 39500, 19000, 39700, 3585):
+        free = np.zeros((-(-(n + 1) // 200), 200), bool)
+        free.ravel()[:n + 1] = True
+        a = make_agent(rng, free, 0, 0.1, rng.uniform(1.0, 3.0, 5))
+        lab = np.zeros(a.n_states, np.int32)
+        lab[-1] = 1
+        agents.append(a)
+        letters.append([lab])
+    base = make_workload(1)
+    task = dataclasses.replace(base.tasks[0], kind="reach", k=1, n_locs=2, n_letters=2, q0=0,
+                               delta=np.array([[0, 1], [1, 1]], np.int32), accepting=np.array([0, 1], np.uint8),
+                               waypoints_uv=np.zeros((0, 2, 2)), avoid_uv=None)
+    wl = dataclasses.replace(base, agents=agents, tasks=[task], letters=letters)
+    ctx.build_products(wl)
+    n = len(agents)
+    W = dirichlet_weights(np.random.default_rng(K), K, n + 1)
+    _same_everywhere(ctx, morap, W, n, 1, "f32", 37 if K == 64 else 19, n)

@@ -316,6 +316,7 @@ struct ResidentPlan {
         bool rows;              // products given as rows of entries: short rows, or streamed (columns > 0)
         int columns;            // > 0: larger products or rows, that many columns per workgroup
         int begin, n, max_states;   // (larger products: positions)
+        int first;                  // place of its first model in the part's `models` (which leave out the rest)
     };
     struct Part {
         std::vector<Launch> launches;

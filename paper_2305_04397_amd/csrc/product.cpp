@@ -1089,7 +1089,7 @@ static void plan_rows(morap_ctx* c) {
                     continue;
                 }
             }
-            part.launches.push_back({false, true, columns, b, 1, n});
+            part.launches.push_back({false, true, columns, b, 1, n, b});
         }
     }
     MORAP_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
@@ -1194,7 +1194,7 @@ static void plan_resident(morap_ctx* c) {
                     continue;
                 }
             }
-            part.launches.push_back({fast(m), false, columns, b, 1, size});
+            part.launches.push_back({fast(m), false, columns, b, 1, size, (int)part.models.size() - 1});
         }
         upload(part.d_rest, part.rest, s);
     }

@@ -679,8 +679,8 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
                 MORAP_HIP(hipEventRecord(held.v.back().first, c->stream));
             }
             double work = 0;   // (the plan lists the larger products first)
-            for (int b = l.begin; b < l.begin + l.n; ++b) {
-                const int32_t m = part.models[(size_t)(b - part.launches[0].begin)];
+            for (int b = l.first; b < l.first + l.n; ++b) {
+                const int32_t m = part.models[(size_t)b];
                 work += hm.state_base[m + 1] - hm.state_base[m];
             }
             // (FP32 rates with one, two and four columns a workgroup)
@@ -754,8 +754,8 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
         if (sweep_log()) {
             const auto& l = part.launches[q % part.launches.size()];
             double work = 0;   // state-columns of the launch's models
-            for (int b = l.begin; b < l.begin + l.n; ++b) {
-                const int32_t m = part.models[(size_t)b - (size_t)part.launches[0].begin];
+            for (int b = l.first; b < l.first + l.n; ++b) {
+                const int32_t m = part.models[(size_t)b];
                 for (int k = 0; k < vs.K; ++k)
                     work += (double)ps[(size_t)m * vs.Kp + k] * (hm.state_base[m + 1] - hm.state_base[m]);
             }

@@ -194,9 +194,8 @@ int policy_capacity() { return (int)((LDS_BYTES - 1024) / sizeof(uint4)); }
 void inst_policy(hipStream_t s, int max_states, const InstanceArgs& a) {
     if (a.n <= 0) return;
     MORAP_CHECK(max_states <= policy_capacity(), MORAP_E_UNSUPPORTED, "an instance does not fit the policy kernel");
-    static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&inst_policy_kernel),
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES - 1024);
-    MORAP_HIP(granted);
+    static OncePerDevice granted;
+    grant_lds(granted, &inst_policy_kernel, LDS_BYTES - 1024);
     hipLaunchKernelGGL(inst_policy_kernel, dim3((unsigned)a.n), dim3(POLICY_THREADS), (size_t)max_states * sizeof(uint4), s,
                        a);
     MORAP_HIP(hipGetLastError());
@@ -476,9 +475,8 @@ static void launch_eval(hipStream_t s, int max_states, const InstanceArgs& a) {
     const size_t bytes = (size_t)res_rows(NS) * 16 + (size_t)(threads * NS + 1) * 16 + 2 * 4 * MAXW * 4 * 8 + 64;
     MORAP_CHECK(threads <= RES_MAX_THREADS && max_states < res_rows(NS) && bytes <= LDS_BYTES, MORAP_E_UNSUPPORTED,
                 "an instance does not fit the LDS-resident evaluation");
-    static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&eval_resident<NS>),
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-    MORAP_HIP(granted);
+    static OncePerDevice granted;
+    grant_lds(granted, &eval_resident<NS>);
     hipLaunchKernelGGL(eval_resident<NS>, dim3((unsigned)a.n), dim3((unsigned)threads), bytes, s, a);
     MORAP_HIP(hipGetLastError());
 }
@@ -500,9 +498,8 @@ void inst_eval(hipStream_t s, int max_states, const InstanceArgs& a) {
         default: break;
     }
     MORAP_CHECK(max_states <= eval_capacity(), MORAP_E_UNSUPPORTED, "an instance does not fit the LDS-resident evaluation");
-    static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&eval_big),
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-    MORAP_HIP(granted);
+    static OncePerDevice granted;
+    grant_lds(granted, &eval_big);
     const size_t bytes = (size_t)(max_states + 1) * 16 + 4 * (BIG_THREADS / 64) * 4 * 8 + 64;
     hipLaunchKernelGGL(eval_big, dim3((unsigned)a.n), dim3(BIG_THREADS), bytes, s, a);
     MORAP_HIP(hipGetLastError());

@@ -3,6 +3,7 @@
 #pragma once
 #include "common.h"
 #include "kern.h"
+#include "once_per_device.h"
 
 #include <type_traits>
 
@@ -15,6 +16,18 @@ constexpr int BIG_THREADS = 1024;             // of the kernel for larger produc
 constexpr int EVAL_BIG_STEPS = 10;            // states per thread of the evaluation of larger products
 constexpr int GRID_NNZ = 17;                  // nonzero entries of the grid pattern
 constexpr size_t LDS_BYTES = 160 * 1024;      // of a compute unit
+
+// Dynamic LDS beyond 64 KB has to be asked for, once per kernel (whose `granted`
+// this is) and device.
+template <class F>
+void grant_lds(OncePerDevice& granted, F* fn, size_t bytes = LDS_BYTES) {
+    int device = 0;
+    MORAP_HIP(hipGetDevice(&device));
+    granted(device, [&] {
+        MORAP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)bytes));
+    });
+}
 
 // rows of one LDS buffer with ns states per thread (row 0 is the zero row):
 // the second buffer lies at this fixed distance, which the 16-bit offset of

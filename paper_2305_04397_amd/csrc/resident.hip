@@ -844,10 +844,8 @@ void launch_res(hipStream_t s, const ResidentArgs& a, int max_states) {
                          2 * 4 * MAXW * 8 * sizeof(T) + 64;
     MORAP_CHECK(threads <= RES_MAX_THREADS && max_states < res_rows(NS) && bytes <= LDS_BYTES, MORAP_E_UNSUPPORTED,
                 "a product does not fit the LDS-resident iteration");
-    // dynamic LDS beyond 64 KB has to be asked for, once per kernel
-    static const hipError_t granted =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-    MORAP_HIP(granted);
+    static OncePerDevice granted;
+    grant_lds(granted, fn);
     const unsigned blocks = INST ? (unsigned)a.n_models : 8u * (unsigned)((a.n_models + 7) / 8) * (unsigned)a.groups;
     hipLaunchKernelGGL(fn, dim3(blocks), dim3((unsigned)threads), bytes, s, a);
     MORAP_HIP(hipGetLastError());
@@ -959,9 +957,8 @@ void launch_big(hipStream_t s, const ResidentArgs& a, int max_positions) {
                          4 * (BIG_THREADS / 64) * 8 * sizeof(T) + 64;
     MORAP_CHECK(max_positions % 64 == 0 && bytes <= LDS_BYTES && max_positions <= BIG_THREADS * NS,
                 MORAP_E_UNSUPPORTED, "a product does not fit the LDS-resident iteration");
-    static const hipError_t granted =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-    MORAP_HIP(granted);
+    static OncePerDevice granted;
+    grant_lds(granted, fn);
     const unsigned blocks = INST ? (unsigned)a.n_models : 8u * (unsigned)((a.n_models + 7) / 8) * (unsigned)a.groups;
     hipLaunchKernelGGL(fn, dim3(blocks), dim3(BIG_THREADS), bytes, s, a);
     MORAP_HIP(hipGetLastError());

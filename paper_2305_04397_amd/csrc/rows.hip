@@ -240,9 +240,8 @@ static void launch_rows(hipStream_t s, const RowsArgs& a, int max_states) {
     auto* fn = &rows_vi<T, KC, THREADS>;
     const size_t bytes = rows_bytes(sizeof(T) == 4 ? MORAP_F32 : MORAP_F64, KC, max_states, THREADS);
     MORAP_CHECK(bytes <= LDS_BYTES, MORAP_E_UNSUPPORTED, "a product does not fit the LDS-resident iteration");
-    static const hipError_t granted =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-    MORAP_HIP(granted);
+    static OncePerDevice granted;
+    grant_lds(granted, fn);
     hipLaunchKernelGGL(fn, dim3(8u * (unsigned)((a.n_models + 7) / 8) * (unsigned)a.groups), dim3(THREADS), bytes, s, a);
     MORAP_HIP(hipGetLastError());
 }

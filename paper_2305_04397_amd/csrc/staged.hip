@@ -473,9 +473,8 @@ static void launch_staged(hipStream_t s, const StagedLdsArgs& a, int max_positio
     const size_t bytes = staged_bytes(sizeof(T) == 4 ? MORAP_F32 : MORAP_F64, KC, max_positions);
     MORAP_CHECK(max_positions % 64 == 0 && bytes <= LDS_BYTES && max_positions <= THREADS * 160 / (int)(sizeof(T) * KC),
                 MORAP_E_UNSUPPORTED, "a product does not fit the LDS-resident iteration");
-    static const hipError_t granted =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-    MORAP_HIP(granted);
+    static OncePerDevice granted;
+    grant_lds(granted, fn);
     hipLaunchKernelGGL(fn, dim3(8u * (unsigned)((a.n_models + 7) / 8) * (unsigned)a.groups), dim3(THREADS), bytes, s, a);
     MORAP_HIP(hipGetLastError());
 }

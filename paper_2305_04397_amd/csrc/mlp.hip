@@ -30,6 +30,7 @@
 //   * bias_grad: column sums of a BF16 gradient.
 #include "common.h"
 
+#include <exception>
 #include <mutex>
 
 #include <cmath>
@@ -584,6 +585,17 @@ uint64_t splitmix64(uint64_t x) {
 // copied from where they are (pinned memory is kept, so it is bounded).
 constexpr size_t STAGED = (size_t)8 << 20;
 
+// Left by an error: waits for the stream, where a copy may still read the
+// caller's rows or the pinned ones that the next call writes.
+struct Drain {
+    hipStream_t s;
+    int before = std::uncaught_exceptions();
+    explicit Drain(hipStream_t s_) : s(s_) {}
+    ~Drain() {
+        if (std::uncaught_exceptions() > before) (void)hipStreamSynchronize(s);
+    }
+};
+
 // infinite or NaN among X[0 .. count), which is copied to `to` (or not: null)
 static bool nonfinite(const float* __restrict X, float* __restrict to, size_t count) {
     uint32_t bad = 0;
@@ -940,17 +952,12 @@ struct Proposer {
     template <class F>
     void in_parts(hipStream_t s, int n, F&& f) {
         const int step = std::max(up((n + PARTS - 1) / PARTS, ROWS), up((256 << 10) / (n_in * 4), ROWS));
-        try {
-            for (int r = 0, q = 0; r < n; r += step, ++q) {
-                f(r, std::min(step, n - r));
-                if (!done[q]) MORAP_HIP(hipEventCreateWithFlags(&done[q], hipEventDisableTiming));
-                MORAP_HIP(hipEventRecord(done[q], s));
-                parts = q + 1;
-                part_rows = step;
-            }
-        } catch (...) {
-            (void)hipStreamSynchronize(s);   // (what is under way reads the pinned rows)
-            throw;
+        for (int r = 0, q = 0; r < n; r += step, ++q) {
+            f(r, std::min(step, n - r));
+            if (!done[q]) MORAP_HIP(hipEventCreateWithFlags(&done[q], hipEventDisableTiming));
+            MORAP_HIP(hipEventRecord(done[q], s));
+            parts = q + 1;
+            part_rows = step;
         }
     }
     hipEvent_t done[PARTS] = {};
@@ -968,6 +975,7 @@ struct Proposer {
     // one step on n host rows; returns the mean loss
     double step(hipStream_t s, const float* X, const float* T, int n, const morap_train_opts* o, bool apply,
                 float* grads_out) {
+        const Drain drain(s);
         upload_rows(s, X, n, true);
         upload_targets(s, T, n);
         forward(s, n, target.as<float>());
@@ -993,6 +1001,7 @@ struct Proposer {
     }
 
     void infer(hipStream_t s, const float* X, int n, float* out, bool check) {
+        const Drain drain(s);
         if (pinned_rows(n)) {
             stage_x.ensure((size_t)n * n_in * 4);
             stage_out.ensure((size_t)n * d * 4);

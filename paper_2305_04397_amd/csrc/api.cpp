@@ -75,6 +75,8 @@ int morap_create(morap_ctx** out, int device, void* hip_stream) {
         return MORAP_E_OOM;
     }
     c->device = device;
+    c->meter.owner = c;
+    c->meter.reclaim = [](void* owner) { return drop_layouts(static_cast<morap_ctx*>(owner)); };
     const int rc = guarded(c, [&] {
         MORAP_HIP(hipGetDeviceProperties(&c->prop, device));
         proposer_scratch_init(device);   // the allocation-free inference's scratch address

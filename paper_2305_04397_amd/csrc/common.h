@@ -49,9 +49,14 @@ struct MorapError : std::runtime_error {
 // ---------------------------------------------------------------------------
 // Device bytes held by a context and its optional budget (0 = none).  The
 // context's meter is current on the thread during every call on it, and each
-// buffer remembers the meter that paid for it.
+// buffer remembers the meter that paid for it.  Where memory or the budget runs
+// out, `reclaim` is asked once to free what the context can do without (true:
+// something was freed).
 struct AllocMeter {
     int64_t budget = 0, used = 0;
+    bool (*reclaim)(void* owner) = nullptr;
+    void* owner = nullptr;
+    bool reclaimed() { return reclaim && reclaim(owner); }
 };
 extern thread_local AllocMeter* g_meter;
 
@@ -77,12 +82,18 @@ struct DevBuf {
         release();
         if (n == 0) n = 16;
         AllocMeter* m = g_meter;
-        if (m && m->budget > 0 && m->used + (int64_t)n > m->budget)
+        auto over = [&] { return m && m->budget > 0 && m->used + (int64_t)n > m->budget; };
+        if (over() && !(m->reclaimed() && !over()))
             fail(MORAP_E_OOM, "device memory budget of " + std::to_string(m->budget) + " bytes exceeded (" +
                                   std::to_string(m->used) + " held, " + std::to_string(n) + " more requested)");
         hipError_t e = hipMalloc(&p, n);
+        if (e != hipSuccess && m && m->reclaimed()) {
+            (void)hipGetLastError();
+            e = hipMalloc(&p, n);
+        }
         if (e != hipSuccess) {
             p = nullptr;
+            (void)hipGetLastError();   // (reported here, not by the next launch)
             fail(MORAP_E_OOM, "hipMalloc of " + std::to_string(n) + " bytes failed: " + hipGetErrorString(e));
         }
         bytes = n;
@@ -344,12 +355,20 @@ struct ResidentPlan {
         inst_ok.assign((size_t)M, 0);
         unsolved = false;
     }
-    void drop(int M) {    // the device's memory too
+    size_t drop(int M) {  // the device's memory too: its bytes
         clear(M);
+        size_t bytes = 0;
+        for (Part& q : part) {
+            bytes += q.d_rest.bytes;
+            q.d_rest.release();
+        }
         for (DevBuf* b : {&order, &big_base, &big_block, &big_rec, &big_init, &grid_blk32, &grid_blk64, &grid_mat, &row_slice,
                           &row_batch, &row_desc, &row_place, &row_value32, &row_value64, &short_rec, &short_val32,
-                          &short_val64})
+                          &short_val64}) {
+            bytes += b->bytes;
             b->release();
+        }
+        return bytes;
     }
 };
 
@@ -387,6 +406,15 @@ struct StagedLayout {
     // falling number of positions (every live model, or none)
     std::vector<int32_t> lds_order, lds_positions;   // [n], [M]
     DevBuf order, lds_base, lds_block, lds_rec, lds_init;
+    size_t drop_lds() {   // the batched sweeps take every model: the bytes freed
+        lds_order.clear();
+        size_t bytes = 0;
+        for (DevBuf* b : {&order, &lds_base, &lds_block, &lds_rec, &lds_init}) {
+            bytes += b->bytes;
+            b->release();
+        }
+        return bytes;
+    }
     PinnedBuf h_unit_sweeps;
     // solve state
     DevBuf active, res, ymax, wc, wp, final_par, pair_sweeps, best_res, stall;   // [U][Kp]
@@ -507,6 +535,7 @@ struct morap_ctx {
 
     // value iteration with the values in LDS (built per upload)
     morap::ResidentPlan resident_plan;
+    int layouts_in_use = 0;                         // > 0: a call builds or reads the layouts in LDS order
     morap::DevBuf d_weights;                        // [K][d] weights of the solve
     morap::DevBuf d_rest_mask;                      // [M][Kp] pairs left to the batched sweeps
     morap::PinnedBuf h_pair_sweeps, h_weights, h_c;
@@ -586,6 +615,17 @@ void product_host(const morap_agent* a, const morap_dfa* t, const int32_t* lette
                   int32_t* state_row, int32_t* row_ptr, int32_t* col, double* prob, double* rew, uint8_t* to_done,
                   int32_t* states);
 void upload_models(morap_ctx* ctx);
+// Frees the layouts in LDS order, which every solve can do without (the batched
+// sweeps take its models until the next upload), unless a call uses them; true
+// when there were any.
+bool drop_layouts(morap_ctx* ctx);
+struct LayoutsInUse {
+    morap_ctx* c;
+    explicit LayoutsInUse(morap_ctx* ctx) : c(ctx) { ++c->layouts_in_use; }
+    LayoutsInUse(const LayoutsInUse&) = delete;
+    LayoutsInUse& operator=(const LayoutsInUse&) = delete;
+    ~LayoutsInUse() { --c->layouts_in_use; }
+};
 void load_team_model(morap_ctx* ctx, int n_agents, int n_tasks, const morap_model* model, const int32_t* obj);
 // agents, tasks and objectives of the loaded models (a team model: its own)
 inline int n_agents_of(const morap_ctx* c) { return c->team ? c->team_nI : c->hm.nI; }

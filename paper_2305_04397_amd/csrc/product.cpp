@@ -1204,6 +1204,18 @@ static void plan_resident(morap_ctx* c) {
         P.inst_ok[(size_t)m] = !P.part[MORAP_F64].rest[(size_t)m] && !hm.blk_zero_prob[(size_t)m] && states(m) <= most;
 }
 
+bool drop_layouts(morap_ctx* c) {
+    if (c->layouts_in_use > 0) return false;
+    (void)hipStreamSynchronize(c->stream);
+    size_t bytes = c->resident_plan.drop(c->hm.M) + c->staged.drop_lds();
+    for (DevBuf* b : {&c->d_weights, &c->d_rest_mask}) {   // (what their solves alone hold)
+        bytes += b->bytes;
+        b->release();
+    }
+    ++c->buf_gen;   // (captured sweeps may hold the mask's address)
+    return bytes > 0;
+}
+
 void upload_models(morap_ctx* c) {
     const HostModels& hm = c->hm;
     hipStream_t s = c->stream;
@@ -1296,6 +1308,7 @@ void upload_models(morap_ctx* c) {
         k::to_f32(s, c->d_blk64.as<double>(), c->d_blk32.as<float>(), (int64_t)hm.blk_agent.size());
     }
     try {
+        const LayoutsInUse building(c);
         plan_resident(c);
     } catch (const MorapError& e) {
         if (e.code != MORAP_E_OOM) throw;

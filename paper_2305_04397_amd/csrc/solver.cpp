@@ -954,10 +954,28 @@ static void solve_impl(morap_ctx* c, const double* W, int K, const morap_vi_opts
 static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const morap_vi_opts& o, double* r_out,
                           Stats& st, const int32_t* warm);
 
+// f(false) with the layouts in LDS order; where that runs out of memory which they
+// hold, f(true) without them: what fits beside the batched sweeps is not refused
+// for them.
+template <class F>
+static void with_layouts(morap_ctx* c, F&& f) {
+    try {
+        const LayoutsInUse use(c);
+        return f(false);
+    } catch (const MorapError& e) {
+        if (e.code != MORAP_E_OOM || !drop_layouts(c)) throw;
+    }
+    f(true);
+}
+
 void solve(morap_ctx* c, const double* W, int K, const morap_vi_opts& o, double* c_out, Stats& st,
            const int32_t* warm) {
     Stats local;
-    solve_impl(c, W, K, o, c_out, local, warm);
+    with_layouts(c, [&](bool again) {
+        local = Stats();
+        // (again: the values a warm start reads may be gone)
+        solve_impl(c, W, K, o, c_out, local, again ? nullptr : warm);
+    });
     add_stats(st, local);
     add_stats(c->cum, local);
 }
@@ -971,23 +989,26 @@ void evaluate(morap_ctx* c, const int32_t* assign, int K, const morap_vi_opts& o
               const int32_t* warm, int32_t* refine) {
     Stats local;
     c->eval_prev_valid = c->eval_prev_valid && c->prev_eval_gen == c->load_gen;
-    try {
-        evaluate_impl(c, assign, K, o, r_out, local, warm);
-        if (refine) {
-            std::copy(assign, assign + (size_t)K * c->hm.nJ, refine);
-            if (!c->team && c->prec == MORAP_F32 && c->has_blocks && c->last_c64_valid &&
-                refine_assignment(c, assign, K, o, local, refine) > 0) {
-                // again with the new assignment, each instance started from
-                // the first evaluation's values where the pair is unchanged
-                std::vector<int32_t> same(K);
-                for (int k = 0; k < K; ++k) same[k] = k;
-                evaluate_impl(c, refine, K, o, r_out, local, same.data());
+    with_layouts(c, [&](bool) {
+        local = Stats();
+        try {
+            evaluate_impl(c, assign, K, o, r_out, local, warm);
+            if (refine) {
+                std::copy(assign, assign + (size_t)K * c->hm.nJ, refine);
+                if (!c->team && c->prec == MORAP_F32 && c->has_blocks && c->last_c64_valid &&
+                    refine_assignment(c, assign, K, o, local, refine) > 0) {
+                    // again with the new assignment, each instance started from
+                    // the first evaluation's values where the pair is unchanged
+                    std::vector<int32_t> same(K);
+                    for (int k = 0; k < K; ++k) same[k] = k;
+                    evaluate_impl(c, refine, K, o, r_out, local, same.data());
+                }
             }
+        } catch (...) {
+            c->eval_prev_valid = false;
+            throw;
         }
-    } catch (...) {
-        c->eval_prev_valid = false;
-        throw;
-    }
+    });
     add_stats(st, local);
     add_stats(c->cum, local);
 }
@@ -2215,8 +2236,7 @@ static void build_stages(morap_ctx* c) {
         if (e.code != MORAP_E_OOM) throw;
         // no memory for this layout: the batched sweeps need none of it
         MORAP_HIP(hipStreamSynchronize(s));
-        L.lds_order.clear();
-        for (DevBuf* b : {&L.order, &L.lds_base, &L.lds_block, &L.lds_rec, &L.lds_init}) b->release();
+        L.drop_lds();
     }
     MORAP_HIP(hipStreamSynchronize(s));
     L.U = U;
@@ -2651,7 +2671,10 @@ static void solve_staged_impl(morap_ctx* c, const double* W, int K, const morap_
 
 void solve_staged(morap_ctx* c, const double* W, int K, const morap_vi_opts& o, double* c_out, Stats& st) {
     Stats local;
-    solve_staged_impl(c, W, K, o, c_out, local);
+    with_layouts(c, [&](bool) {
+        local = Stats();
+        solve_staged_impl(c, W, K, o, c_out, local);
+    });
     add_stats(st, local);
     add_stats(c->cum, local);
 }

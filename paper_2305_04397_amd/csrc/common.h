@@ -614,7 +614,7 @@ void team_model_mo_host(const morap_agent* agents, int n_agents, const morap_dfa
 void product_host(const morap_agent* a, const morap_dfa* t, const int32_t* letters, int32_t* sizes,
                   int32_t* state_row, int32_t* row_ptr, int32_t* col, double* prob, double* rew, uint8_t* to_done,
                   int32_t* states);
-void upload_models(morap_ctx* ctx);
+void upload_models(morap_ctx* ctx, bool team = false);
 // Frees the layouts in LDS order, which every solve can do without (the batched
 // sweeps take its models until the next upload), unless a call uses them; true
 // when there were any.

@@ -702,7 +702,7 @@ void build_products(morap_ctx* c, const morap_agent* agents, int nI, const morap
     upload_models(c);
 }
 
-void load_models(morap_ctx* c, const morap_model* models, int n, int nI, int nJ) {
+static void load_models_as(morap_ctx* c, const morap_model* models, int n, int nI, int nJ, bool team) {
     MORAP_CHECK(models && nI > 0 && nJ > 0 && n == nI * nJ, MORAP_E_INVALID, "need n_models = n_agents * n_tasks");
     std::vector<Built> parts(n);
     for (int m = 0; m < n; ++m) {
@@ -743,7 +743,11 @@ void load_models(morap_ctx* c, const morap_model* models, int n, int nI, int nJ)
         b.states_sq.assign((size_t)2 * md.n_states, 0);
     }
     concat(c, parts, nI, nJ);
-    upload_models(c);
+    upload_models(c, team);
+}
+
+void load_models(morap_ctx* c, const morap_model* models, int n, int nI, int nJ) {
+    load_models_as(c, models, n, nI, nJ, false);
 }
 
 template <class T>
@@ -1216,7 +1220,8 @@ bool drop_layouts(morap_ctx* c) {
     return bytes > 0;
 }
 
-void upload_models(morap_ctx* c) {
+// (team: a team model's solves are batched sweeps, which need no layout in LDS order)
+void upload_models(morap_ctx* c, bool team) {
     const HostModels& hm = c->hm;
     hipStream_t s = c->stream;
     c->loaded = false;
@@ -1309,7 +1314,8 @@ void upload_models(morap_ctx* c) {
     }
     try {
         const LayoutsInUse building(c);
-        plan_resident(c);
+        if (team) c->resident_plan.drop(hm.M);
+        else plan_resident(c);
     } catch (const MorapError& e) {
         if (e.code != MORAP_E_OOM) throw;
         // no memory for the layouts in LDS order: the batched sweeps need none
@@ -1425,7 +1431,7 @@ void load_team_model(morap_ctx* c, int nA, int nT, const morap_model* model, con
     const int d = nA + nT;
     for (int64_t r = 0; r < 2 * (int64_t)model->n_rows; ++r)
         MORAP_CHECK(obj[r] >= 0 && obj[r] < d, MORAP_E_INVALID, "objective index out of range");
-    load_models(c, model, 1, 1, 1);
+    load_models_as(c, model, 1, 1, 1, true);
     c->loaded = false;
     std::vector<int32_t> o(obj, obj + 2 * (size_t)model->n_rows);
     upload(c->d_obj, o, c->stream);

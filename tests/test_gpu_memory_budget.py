@@ -5,7 +5,7 @@ upload needs their memory."""
 import numpy as np
 import pytest
 
-from workloads import make_workload, dirichlet_weights
+from workloads import make_workload, tiny_workload, dirichlet_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -128,3 +128,16 @@ def test_proposer_beside_the_layouts(morap):
         c.set_memory_budget(_least_budget(morap, load) + network)
         load(c)
         c.proposer_init(1024, 512, seed=1)
+
+
+def test_team_models_hold_no_layout(morap):
+    """A team model's solves are batched sweeps: beyond the same model's arrays it
+    holds two objectives a row, a policy and d values a state."""
+    n = 3
+    team = morap.team_model_mo_host(tiny_workload(42, n, n, width=3, height=2, kinds=("reach",), k=1, p_slip=0.25))
+    model = {k: v for k, v in team.items() if k != "obj"}
+    S, R = len(team["state_row"]) - 1, len(team["row_ptr"]) - 1
+    plain = _least_budget(morap, lambda c: c.load_models([model], 1, 1))
+    with morap.Context(0) as c:
+        c.load_team_model(team, n, n)
+        assert c.set_memory_budget(0) <= plain + 8 * R + 4 * S + 8 * 2 * n * S + 1024

@@ -342,7 +342,8 @@ struct ResidentPlan {
     DevBuf order, big_base, big_block, big_rec, big_init, grid_blk32, grid_blk64, grid_mat;
     // products given as rows: see RowsArgs
     bool unsolved = false;             // a model with states has none to solve for (its values are 0)
-    DevBuf row_slice, row_batch, row_desc, row_place, row_value32, row_value64, short_rec, short_val32, short_val64;
+    DevBuf row_slice, row_batch, row_desc, row_place, row_value32, row_value64, short_base, short_rec, short_val32,
+        short_val64;
     Part part[2];                      // MORAP_F64, MORAP_F32
 
     void clear(int M) {   // every model to the batched sweeps
@@ -363,8 +364,8 @@ struct ResidentPlan {
             q.d_rest.release();
         }
         for (DevBuf* b : {&order, &big_base, &big_block, &big_rec, &big_init, &grid_blk32, &grid_blk64, &grid_mat, &row_slice,
-                          &row_batch, &row_desc, &row_place, &row_value32, &row_value64, &short_rec, &short_val32,
-                          &short_val64}) {
+                          &row_batch, &row_desc, &row_place, &row_value32, &row_value64, &short_base, &short_rec,
+                          &short_val32, &short_val64}) {
             bytes += b->bytes;
             b->release();
         }
@@ -803,8 +804,9 @@ struct ResidentArgs {
     int64_t* counters;          // [8]: pairs stopped at the rounding floor
     double eps, unit, floor;
     int stall_sweeps, warm, sweep0, sweep1, last;
-    const uint4* short_rec;     // products given as short rows: [S][2] LDS rows of the entries, 16 bits each
-    const void* short_val;      // [S][SHORT_VALUES] (precision of the solve)
+    const int32_t* short_base;  // products given as short rows: [M] first of their states, in that layout
+    const uint4* short_rec;     // [its states][2] LDS rows of the entries, 16 bits each
+    const void* short_val;      // [its states][SHORT_VALUES] (precision of the solve)
     const void* grid_blk;       // compact blocks (precision of the solve), see GRID_BLK
     const float* grid_mat;      // [blocks][4][8] a move's five slots, the probability to stay of the block
     // larger products: states sorted by block, padded to steps of 64
@@ -844,6 +846,25 @@ void resident_rows(hipStream_t s, int prec, int columns, int max_states, const R
 // products given as rows whose states have at most five rows of at most three
 // entries (resident_capacity with `fast` false, classes as the block form's)
 void resident_short(hipStream_t s, int prec, bool wide, int max_states, ResidentArgs a);
+// The layouts of products given as rows, from the arrays of the upload (FP64 and
+// the same in FP32).
+struct RowsLayout {
+    int M, n_slices;
+    int64_t S;
+    const int32_t *state_base, *state_model, *state_row, *row_ptr, *col;
+    const double *prob, *rew;
+    const int32_t* short_base;           // [M], -1: not in this layout
+    uint4* short_rec;
+    double* short_val64;
+    float* short_val32;
+    const int32_t *slice, *batch;        // as in RowsArgs, and the batches' contents
+    int32_t* desc;
+    uint2* place;
+    double* value64;
+    float* value32;
+};
+void lay_out_short(hipStream_t s, const RowsLayout& a);
+void lay_out_rows(hipStream_t s, const RowsLayout& a);
 constexpr int SHORT_VALUES = 26;   // probabilities [5][3], cost and probability rewards [5]; one unused
 // every block's nonzero entries lie within the grid pattern
 bool has_grid_pattern(uint32_t union_pattern);

@@ -916,159 +916,116 @@ static void plan_rows(morap_ctx* c) {
         if (hm.init[m] >= 0) most = std::max(most, states(m));
     }
     if (order.empty() || k::rows_columns(MORAP_F32, most) == 0) return;
+    // What the layouts' sizes follow from, per model: whether its rows are short
+    // (at most five a state, of at most three entries), else or beyond FP64's
+    // short rows the batches of every slice.  The device lays them out.
     struct Model {
-        std::vector<int32_t> batch, desc;   // per slice, per batch
-        std::vector<uint16_t> place;
-        std::vector<double> value;
-        std::vector<uint16_t> brief;        // [states][16], empty: the rows are not short
-        std::vector<double> brief_value;    // [states][SHORT_VALUES]
-        bool fit = false;
-    };
-    // at most five rows of at most three entries a state, a missing entry at
-    // the zero row, a missing row as the state's first
-    auto short_rows = [&](int m, Model& x) {
-        const int32_t s0 = hm.state_base[m], n = states(m);
-        std::vector<uint16_t> place((size_t)n * 16, 0);
-        std::vector<double> val((size_t)n * k::SHORT_VALUES, 0.0);
-        for (int32_t l = 0; l < n; ++l) {
-            const int32_t r0 = hm.state_row[s0 + l], nr = hm.state_row[s0 + l + 1] - r0;
-            if (nr > 5) return;
-            double* v = &val[(size_t)l * k::SHORT_VALUES];
-            for (int j = 0; j < 5; ++j) {
-                const int32_t r = r0 + (j < nr ? j : 0), e = hm.row_ptr[r], ne = hm.row_ptr[r + 1] - e;
-                if (ne > 3) return;
-                for (int u = 0; u < ne; ++u) {
-                    place[(size_t)l * 16 + 3 * j + u] = (uint16_t)(hm.col[(size_t)e + u] - s0 + 1);
-                    v[3 * j + u] = hm.prob[(size_t)e + u];
-                }
-                v[15 + j] = hm.rew[2 * (size_t)r];
-                v[20 + j] = hm.rew[2 * (size_t)r + 1];
-            }
-        }
-        x.brief.swap(place);
-        x.brief_value.swap(val);
+        bool brief = true, fit = true;
+        std::vector<int32_t> batch;
     };
     std::vector<Model> built((size_t)hm.M);
     std::atomic<size_t> next{0};
-    std::atomic<bool> bad{false}, fit{true};
-    auto build = [&](int m, Model& x) {
+    std::atomic<bool> fit{true};
+    auto measure = [&](int m, Model& x) {
         const int32_t s0 = hm.state_base[m], n = states(m);
-        const int64_t nnz = hm.row_ptr[hm.state_row[s0 + n]] - hm.row_ptr[hm.state_row[s0]];
-        const int64_t n_rows = hm.state_row[s0 + n] - hm.state_row[s0];
-        const int32_t wp_row = (n + 63) / 64 * 64 + 1;
+        const int32_t r0 = hm.state_row[s0], r1 = hm.state_row[s0 + n];
+        if (n > k::resident_capacity(MORAP_F32, false)) x.brief = false;
+        int32_t most_rows = 0, most_entries = 0;
+        for (int32_t g = s0; x.brief && g < s0 + n; ++g) most_rows = std::max(most_rows, hm.state_row[g + 1] - hm.state_row[g]);
+        for (int32_t r = r0; x.brief && r < r1; ++r) most_entries = std::max(most_entries, hm.row_ptr[r + 1] - hm.row_ptr[r]);
+        if (most_rows > 5 || most_entries > 3) x.brief = false;
+        if (x.brief && n <= k::resident_capacity(MORAP_F64, false)) return;
+        int64_t total = 0;
         std::vector<int32_t> len;
         for (int32_t b = 0; b < n; b += 64) {
-            auto state = [&](int q) { return s0 + std::min(b + q, n - 1); };
-            auto rows = [&](int q) { return hm.state_row[state(q) + 1] - hm.state_row[state(q)]; };
-            // row j of lane q (its first where it has no such row)
-            auto row_of = [&](int q, int j) { return hm.state_row[state(q)] + (j < rows(q) ? j : 0); };
-            int nr = 0;
-            for (int q = 0; q < 64; ++q) nr = std::max(nr, rows(q));
-            len.assign((size_t)nr, 0);
-            int64_t total = 0;
-            for (int j = 0; j < nr; ++j) {
-                for (int q = 0; q < 64; ++q) {
-                    const int32_t r = row_of(q, j);
-                    len[(size_t)j] = std::max(len[(size_t)j], hm.row_ptr[r + 1] - hm.row_ptr[r]);
-                }
-                total += 2 + len[(size_t)j];
+            len.clear();
+            int32_t least = INT32_MAX, first = 0;   // fewest rows, longest first row
+            for (int32_t g = s0 + b; g < s0 + std::min(b + 64, n); ++g) {
+                const int32_t r = hm.state_row[g], nr = hm.state_row[g + 1] - r;
+                if (nr > (int32_t)len.size()) len.resize((size_t)nr, 0);
+                for (int32_t j = 0; j < nr; ++j) len[(size_t)j] = std::max(len[(size_t)j], hm.row_ptr[r + j + 1] - hm.row_ptr[r + j]);
+                least = std::min(least, nr);
             }
-            const int64_t batches = (total + 3) / 4;
-            const size_t at = x.value.size(), d0 = x.desc.size();
-            // (the lanes of a last slice of few states repeat one of them)
-            if ((double)(at + (size_t)batches * 256) > 8.0 * (double)(nnz + 2 * n_rows) * ((n + 63) / 64 * 64) / n + 512) return;
-            x.place.resize(at + (size_t)batches * 256, 0);
-            x.value.resize(at + (size_t)batches * 256, 0.0);
-            x.desc.resize(d0 + (size_t)batches, 0);
-            int64_t e0 = 0;   // the row's first place in the slice
-            for (int j = 0; j < nr; ++j) {
-                for (int q = 0; q < 64; ++q) {
-                    const int32_t r = row_of(q, j), e = hm.row_ptr[r], n_e = hm.row_ptr[r + 1] - e;
-                    auto index = [&](int64_t u) {
-                        const int64_t f = e0 + u;
-                        return at + (size_t)(f / 4) * 256 + (size_t)q * 4 + (size_t)(f & 3);
-                    };
-                    x.place[index(0)] = (uint16_t)wp_row;
-                    x.value[index(0)] = hm.rew[2 * (size_t)r + 1];
-                    x.place[index(1)] = (uint16_t)(wp_row + 1);
-                    x.value[index(1)] = hm.rew[2 * (size_t)r];
-                    for (int u = 0; u < n_e; ++u) {
-                        x.place[index(2 + u)] = (uint16_t)(hm.col[(size_t)e + u] - s0 + 1);
-                        x.value[index(2 + u)] = hm.prob[(size_t)e + u];
-                    }
-                }
-                e0 += 2 + len[(size_t)j];
-                x.desc[d0 + (size_t)((e0 - 1) / 4)] |= 1 << ((e0 - 1) & 3);
+            // (a state repeats its first row where it has fewer)
+            for (int32_t g = s0 + b; least < (int32_t)len.size() && g < s0 + std::min(b + 64, n); ++g) {
+                const int32_t r = hm.state_row[g], nr = hm.state_row[g + 1] - r;
+                first = hm.row_ptr[r + 1] - hm.row_ptr[r];
+                for (int32_t j = nr; j < (int32_t)len.size(); ++j) len[(size_t)j] = std::max(len[(size_t)j], first);
             }
-            x.desc.back() |= 16;
-            x.batch.push_back((int32_t)batches);
+            int64_t places = 0;
+            for (int32_t l : len) places += 2 + l;
+            x.batch.push_back((int32_t)((places + 3) / 4));
+            total += x.batch.back();
         }
-        x.fit = true;
+        const int64_t nnz = hm.row_ptr[r1] - hm.row_ptr[r0], n_rows = r1 - r0;
+        // (the lanes of a last slice of few states repeat one of them)
+        x.fit = (double)(total * 256) <= 8.0 * (double)(nnz + 2 * n_rows) * ((n + 63) / 64 * 64) / n + 512;
     };
     auto worker = [&] {
-        try {
-            for (size_t t; (t = next++) < order.size();) {
-                Model& x = built[(size_t)order[t]];
-                if (states(order[t]) <= k::resident_capacity(MORAP_F32, false)) short_rows(order[t], x);
-                if (x.brief.empty() || states(order[t]) > k::resident_capacity(MORAP_F64, false)) build(order[t], x);
-                else x.fit = true;
-                if (!x.fit) fit = false;
-            }
-        } catch (...) {
-            bad = true;
+        for (size_t t; (t = next++) < order.size();) {
+            Model& x = built[(size_t)order[t]];
+            measure(order[t], x);
+            if (!x.fit) fit = false;
         }
     };
-    const int nt = (int)std::min<size_t>(order.size(), std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
-    std::vector<std::thread> th;
-    for (int k = 1; k < nt; ++k) th.emplace_back(worker);
-    worker();
-    for (auto& k : th) k.join();
-    MORAP_CHECK(!bad, MORAP_E_OOM, "laying out the rows failed (host memory)");
+    // (waking the context's threads takes as long as a quarter of a million rows)
+    c->pool.run(hm.R() < (1 << 18) ? 1 : host_threads((int)std::min<size_t>(order.size(), 1 << 16)), worker);
     if (!fit) return;
-    std::vector<int32_t> slice((size_t)hm.M + 1, 0), batch(1, 0), desc;
-    size_t total = 0;
-    for (const Model& x : built) total += x.value.size();
-    if (total / 256 >= (1u << 30)) return;
-    bool any_short = false;
-    for (const Model& x : built) any_short |= !x.brief.empty();
-    const size_t n_short = any_short ? (size_t)hm.S() : 0;
-    std::vector<uint16_t> brief(n_short * 16, 0);
-    std::vector<double> brief_value(n_short * k::SHORT_VALUES, 0.0);
+    std::vector<int32_t> slice((size_t)hm.M + 1, 0), batch(1, 0), short_base((size_t)hm.M, -1);
+    int64_t batches = 0, n_short = 0;
     for (int m = 0; m < hm.M; ++m) {
         const Model& x = built[(size_t)m];
-        if (x.brief.empty()) continue;
-        std::copy(x.brief.begin(), x.brief.end(), brief.begin() + (int64_t)hm.state_base[m] * 16);
-        std::copy(x.brief_value.begin(), x.brief_value.end(),
-                  brief_value.begin() + (int64_t)hm.state_base[m] * k::SHORT_VALUES);
-    }
-    upload(P.short_rec, brief, s);
-    upload(P.short_val64, brief_value, s);
-    P.short_val32.ensure(brief_value.size() * 4 + 16);
-    k::to_f32(s, P.short_val64.as<double>(), P.short_val32.as<float>(), (int64_t)brief_value.size());
-    std::vector<uint16_t> place;
-    std::vector<double> value;
-    place.reserve(total + 256);
-    value.reserve(total + 256);
-    for (int m = 0; m < hm.M; ++m) {
-        const Model& x = built[(size_t)m];
-        for (int32_t n : x.batch) batch.push_back(batch.back() + n);
         slice[(size_t)m + 1] = slice[(size_t)m] + (int32_t)x.batch.size();
-        desc.insert(desc.end(), x.desc.begin(), x.desc.end());
-        place.insert(place.end(), x.place.begin(), x.place.end());
-        value.insert(value.end(), x.value.begin(), x.value.end());
+        for (int32_t n : x.batch) batches += n;
     }
-    // an empty batch behind the last one
-    desc.push_back(0);
-    place.insert(place.end(), 256, 0);
-    value.insert(value.end(), 256, 0.0);
-    upload(P.row_slice, slice, s);
-    upload(P.row_batch, batch, s);
-    upload(P.row_desc, desc, s);
-    upload(P.row_place, place, s);
-    upload(P.row_value64, value, s);
-    P.row_value32.ensure(value.size() * 4 + 16);
-    k::to_f32(s, P.row_value64.as<double>(), P.row_value32.as<float>(), (int64_t)value.size());
-    auto brief_of = [&](int m) { return !built[(size_t)m].brief.empty(); };
+    if (batches >= (1 << 30)) return;
+    batch.reserve((size_t)slice.back() + 1);
+    for (int32_t m : order)
+        if (built[(size_t)m].brief) {
+            short_base[(size_t)m] = (int32_t)n_short;
+            n_short += states(m);
+        }
+    for (int m = 0; m < hm.M; ++m)
+        for (int32_t n : built[(size_t)m].batch) batch.push_back(batch.back() + n);
+    k::RowsLayout a{};
+    a.M = hm.M;
+    a.S = hm.S();
+    a.state_base = c->d_state_base.as<int32_t>();
+    a.state_model = c->d_state_model.as<int32_t>();
+    a.state_row = c->d_state_row.as<int32_t>();
+    a.row_ptr = c->d_row_ptr.as<int32_t>();
+    a.col = c->d_col.as<int32_t>();
+    a.prob = c->d_prob64.as<double>();
+    a.rew = c->d_rew64.as<double>();
+    if (n_short > 0) {
+        upload(P.short_base, short_base, s);
+        P.short_rec.ensure((size_t)n_short * 32);
+        P.short_val64.ensure((size_t)n_short * k::SHORT_VALUES * 8);
+        P.short_val32.ensure((size_t)n_short * k::SHORT_VALUES * 4);
+        a.short_base = P.short_base.as<int32_t>();
+        a.short_rec = P.short_rec.as<uint4>();
+        a.short_val64 = P.short_val64.as<double>();
+        a.short_val32 = P.short_val32.as<float>();
+        k::lay_out_short(s, a);
+    }
+    if (batches > 0) {
+        const size_t all = (size_t)batches + 1;   // an empty batch behind the last one
+        upload(P.row_slice, slice, s);
+        upload(P.row_batch, batch, s);
+        P.row_desc.ensure(all * 4);
+        P.row_place.ensure(all * 64 * 8);
+        P.row_value64.ensure(all * 256 * 8);
+        P.row_value32.ensure(all * 256 * 4);
+        a.n_slices = slice.back();
+        a.slice = P.row_slice.as<int32_t>();
+        a.batch = P.row_batch.as<int32_t>();
+        a.desc = P.row_desc.as<int32_t>();
+        a.place = P.row_place.as<uint2>();
+        a.value64 = P.row_value64.as<double>();
+        a.value32 = P.row_value32.as<float>();
+        k::lay_out_rows(s, a);
+    }
+    auto brief_of = [&](int m) { return built[(size_t)m].brief; };
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
         return brief_of(a) != brief_of(b) ? brief_of(b) : states(a) > states(b);
     });

@@ -101,12 +101,13 @@ resident_vi(ResidentArgs a) {
     for (int i = 0; i < NS; ++i) {
         const int l = min(own0 - 1 + 64 * i, S - 1);
         if constexpr (ROWS) {
-            const uint4* q = a.short_rec + (int64_t)(sb + l) * 2;
+            const int64_t at = (int64_t)a.short_base[m] + l;
+            const uint4* q = a.short_rec + at * 2;
             const uint4 q0 = q[0], q1 = q[1];
             const unsigned w[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) succ[i][e] = w[e];
-            const T* B = static_cast<const T*>(a.short_val) + (int64_t)(sb + l) * SHORT_VALUES;
+            const T* B = static_cast<const T*>(a.short_val) + at * SHORT_VALUES;
 #pragma unroll
             for (int e = 0; e < NNZ; ++e) P[i][e] = own_reg(B[e]);
 #pragma unroll

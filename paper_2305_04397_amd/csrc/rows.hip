@@ -223,6 +223,117 @@ __global__ void __launch_bounds__(THREADS) rows_vi(RowsArgs a) {
     }
 }
 
+// The layouts, on the device at upload: the host only measures them.  Laying them
+// out on the host, two copies of every value in memory and two over the link, took
+// 2.0 of 4.0 ms of loading 48 products of 16 x 16 grids x 8 tasks.
+//
+// Short rows: one thread a state.
+__global__ void __launch_bounds__(256) short_layout_kernel(RowsLayout a) {
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (g >= a.S) return;
+    const int m = a.state_model[g];
+    if (a.short_base[m] < 0) return;
+    const int s0 = a.state_base[m];
+    const int64_t at = a.short_base[m] + (g - s0);
+    const int r0 = a.state_row[g], nr = a.state_row[g + 1] - r0;
+    unsigned w[8] = {};
+    double v[SHORT_VALUES] = {};
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {   // a missing entry at the zero row, a missing row as the first
+        const int r = r0 + (j < nr ? j : 0), e = a.row_ptr[r], ne = a.row_ptr[r + 1] - e;
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            if (u >= ne) continue;
+            const int p = 3 * j + u;
+            w[p / 2] |= (unsigned)(a.col[e + u] - s0 + 1) << (p % 2 * 16);
+            v[p] = a.prob[e + u];
+        }
+        v[15 + j] = a.rew[2 * (int64_t)r];
+        v[20 + j] = a.rew[2 * (int64_t)r + 1];
+    }
+    a.short_rec[2 * at] = make_uint4(w[0], w[1], w[2], w[3]);
+    a.short_rec[2 * at + 1] = make_uint4(w[4], w[5], w[6], w[7]);
+#pragma unroll
+    for (int e = 0; e < SHORT_VALUES; ++e) {
+        a.short_val64[at * SHORT_VALUES + e] = v[e];
+        a.short_val32[at * SHORT_VALUES + e] = (float)v[e];
+    }
+}
+
+void lay_out_short(hipStream_t s, const RowsLayout& a) {
+    hipLaunchKernelGGL(short_layout_kernel, dim3((unsigned)((a.S + 255) / 256)), dim3(256), 0, s, a);
+    MORAP_HIP(hipGetLastError());
+}
+
+// Streamed rows: one wave a slice, and one for the empty batch behind the last.
+__global__ void __launch_bounds__(64) rows_layout_kernel(RowsLayout a) {
+    const int sl = blockIdx.x, lane = threadIdx.x;
+    const int64_t b0 = a.batch[sl];
+    unsigned p[4] = {0, 0, 0, 0};
+    double v[4] = {0, 0, 0, 0};
+    int f = 0, bits = 0;   // places of the slice so far; ends of rows in the batch
+    auto flush = [&](int extra) {
+        const int64_t b = b0 + (f - 1) / 4, at = b * 64 + lane;
+        a.place[at] = make_uint2(p[0] | p[1] << 16, p[2] | p[3] << 16);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            a.value64[at * 4 + u] = v[u];
+            a.value32[at * 4 + u] = (float)v[u];
+            p[u] = 0;
+            v[u] = 0;
+        }
+        if (lane == 0) a.desc[b] = bits | extra;
+        bits = 0;
+    };
+    if (sl == a.n_slices) {
+        f = 1;
+        flush(0);
+        return;
+    }
+    int lo = 0, hi = a.M;   // the slice's model: slice[lo] <= sl < slice[lo + 1]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        if (a.slice[mid] <= sl) lo = mid;
+        else hi = mid;
+    }
+    const int s0 = a.state_base[lo], n = a.state_base[lo + 1] - s0;
+    const int g = s0 + min((sl - a.slice[lo]) * 64 + lane, n - 1);
+    const int r0 = a.state_row[g], rows = a.state_row[g + 1] - r0;
+    const unsigned wp_row = (unsigned)((n + 63) / 64 * 64 + 1);
+    auto largest = [](int x) {
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) x = max(x, __shfl_xor(x, o, 64));
+        return x;
+    };
+    auto put = [&](unsigned row, double x) {   // (the wave's places are in lockstep)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if ((f & 3) == u) {
+                p[u] = row;
+                v[u] = x;
+            }
+        ++f;
+    };
+    const int most = largest(rows);
+    for (int j = 0; j < most; ++j) {
+        const int r = r0 + (j < rows ? j : 0), e = a.row_ptr[r], ne = a.row_ptr[r + 1] - e;
+        const int len = 2 + largest(ne);
+        for (int i = 0; i < len; ++i) {
+            if (i < 2) put(wp_row + i, a.rew[2 * (int64_t)r + 1 - i]);
+            else if (i - 2 < ne) put((unsigned)(a.col[e + i - 2] - s0 + 1), a.prob[e + i - 2]);
+            else put(0, 0);
+            const bool last = i + 1 == len;
+            if (last) bits |= 1 << ((f - 1) & 3);
+            if ((f & 3) == 0 || (last && j + 1 == most)) flush(last && j + 1 == most ? 16 : 0);
+        }
+    }
+}
+
+void lay_out_rows(hipStream_t s, const RowsLayout& a) {
+    hipLaunchKernelGGL(rows_layout_kernel, dim3((unsigned)a.n_slices + 1), dim3(64), 0, s, a);
+    MORAP_HIP(hipGetLastError());
+}
+
 static size_t rows_bytes(int prec, int columns, int states, int threads) {
     const size_t el = prec == MORAP_F32 ? 4 : 8;
     const size_t rows = (size_t)(states + 63) / 64 * 64 + 3;

@@ -686,6 +686,7 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
             // (FP32 rates with one, two and four columns a workgroup)
             const hipStream_t s = fork.least(work * (l.columns == 1 ? 1.8 : (l.columns == 2 ? 1.4 : 1.0)), (bool)beside);
             if (l.rows && l.columns == 0) {
+                a.short_base = plan.short_base.as<int32_t>();
                 a.short_rec = plan.short_rec.as<uint4>();
                 a.short_val = f32 ? plan.short_val32.p : plan.short_val64.p;
                 k::resident_short(s, vs.prec, wide, l.max_states, a);

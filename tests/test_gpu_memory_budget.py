@@ -141,3 +141,27 @@ def test_team_models_hold_no_layout(morap):
     with morap.Context(0) as c:
         c.load_team_model(team, n, n)
         assert c.set_memory_budget(0) <= plain + 8 * R + 4 * S + 8 * 2 * n * S + 1024
+
+
+def test_short_rows_hold_memory_for_their_products_alone(morap):
+    """A product of short rows beside streamed ones: 344 bytes for each of its own
+    states (with what the sizes need), 3,588 a batch of the others."""
+    rng = np.random.default_rng(4)
+
+    def rows(n, per_state, entries):
+        R = n * per_state
+        p = rng.random((R, entries)) + 0.05
+        p *= 0.95 / p.sum(1, keepdims=True)
+        return {"state_row": np.arange(0, R + 1, per_state), "row_ptr": np.arange(0, R * entries + 1, entries),
+                "col": rng.integers(0, n, R * entries).astype(np.int32), "prob": p.ravel(),
+                "rew": np.stack([-rng.uniform(0.5, 2.0, R), rng.uniform(0, 0.05, R)], 1), "to_done": np.ones(R), "init": 0}
+    models = [rows(70, 2, 3), rows(4000, 2, 4), rows(3000, 2, 4)]
+    batches = (63 + 47) * (2 * (2 + 4) // 4)
+    load = lambda c: c.load_models(models, 3, 1)  # noqa: E731
+    with morap.Context(0) as c:
+        load(c)
+        W = dirichlet_weights(np.random.default_rng(1), 4, 4)
+        held = c.set_memory_budget(0)
+        assert c.solve(W, morap.Options())[1]["resident_models"] == 3
+    layouts = held - _least_budget(morap, load)
+    assert layouts <= 344 * 70 + 3588 * (batches + 1) + 4096

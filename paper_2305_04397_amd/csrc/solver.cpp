@@ -351,6 +351,15 @@ struct Fork {
     }
 };
 
+// Streams for launches in LDS beside a chain of short ones on the context's
+// stream.  A process has four hardware queues; with a third stream here and a
+// caller's work on the null stream two of them share one, and where that is the
+// chain's it waits for whole LDS launches: evaluations of 64 columns of 6 x 8
+// products of up to 143,000 states 213 (three) and 208 ms (two), of one column 17.6
+// and 12.9; the support step of 12 x 24 42.8 and 39.2 ms.  (A solve with more
+// pairs in LDS than fit at once is 1 % faster with three.)
+constexpr int kBeside = 2;
+
 // one chunk of `n` sweeps (n even): sweep, converge, compact per sweep;
 // `ev` (optional) receives an event pair around every sweep kernel
 static void enqueue_chunk(morap_ctx* c, ValueSet& vs, const uint8_t* mask, const Variant& v, double eps, int n,
@@ -668,7 +677,8 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
         a.sweep1 = (int)done;
         a.last = done == limit ? 1 : 0;
         // (timed launches one by one)
-        Fork fork(c, o.time_kernels ? 1 : (int)part.launches.size() + (beside ? 1 : 0));
+        Fork fork(c, o.time_kernels ? 1 : (!beside ? (int)part.launches.size()
+                                                   : 1 + std::min((int)part.launches.size(), wide ? 3 : kBeside)));
         for (size_t q = 0; q < part.launches.size(); ++q) {
             const auto& l = part.launches[q];
             a.order = plan.order.as<int32_t>() + l.begin;
@@ -1530,7 +1540,10 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
     // per instance): the sweeps between two host checks launch only these.
     auto live_tiles = [&](const uint8_t* dflags, int width, k::InstArgs& out) {
         std::vector<uint8_t> f((size_t)width * n);
-        MORAP_HIP(hipMemcpy(f.data(), dflags, f.size(), hipMemcpyDeviceToHost));
+        // (copies on this stream: the null stream's queue can be one that a stream
+        // with launches in LDS shares, and would wait for them)
+        MORAP_HIP(hipMemcpyAsync(f.data(), dflags, f.size(), hipMemcpyDeviceToHost, s));
+        MORAP_HIP(hipStreamSynchronize(s));
         c->h_live_tiles.clear();
         int64_t states = 0;
         for (size_t t = 0; t < tiles.size() / 2; ++t) {
@@ -1545,8 +1558,8 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
         }
         c->d_live_tiles.ensure(c->h_live_tiles.size() * 4 + 8);
         if (!c->h_live_tiles.empty())
-            MORAP_HIP(hipMemcpy(c->d_live_tiles.p, c->h_live_tiles.data(), c->h_live_tiles.size() * 4,
-                                hipMemcpyHostToDevice));
+            MORAP_HIP(hipMemcpyAsync(c->d_live_tiles.p, c->h_live_tiles.data(), c->h_live_tiles.size() * 4,
+                                     hipMemcpyHostToDevice, s));
         out = a;
         out.inst_tiles = c->d_live_tiles.as<int32_t>();
         out.n_tiles = (int)(c->h_live_tiles.size() / 2);
@@ -1661,7 +1674,7 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
     PooledEvents vi_events(c);
     if (lds) {
         k::fill_i32(s, vi_sweeps, 0, (int64_t)out_words + 4);
-        if (general && c->has_blocks && !o.time_kernels) beside.reset(new Fork(c, 4));
+        if (general && c->has_blocks && !o.time_kernels) beside.reset(new Fork(c, 1 + kBeside));
         MORAP_HIP(hipEventRecord(vi_wall.a, s));
         I.launch_vi(c, xi, vi_sweeps, 0, std::min<int64_t>(vi_limit, kResidentSweeps),
                     o.time_kernels ? &vi_events.v : nullptr, beside.get());

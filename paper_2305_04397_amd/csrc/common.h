@@ -334,6 +334,7 @@ struct ResidentPlan {
         std::vector<int32_t> models;   // of all launches
         std::vector<uint8_t> rest;     // [M] 1: left to the batched sweeps
         int n_rest = 0;
+        double rest_share = 0;         // of all states, in those models
         DevBuf d_rest;                 // the same on the device
     };
     std::vector<int32_t> rank;         // [M] place of the model in `order`
@@ -352,6 +353,7 @@ struct ResidentPlan {
             q.models.clear();
             q.rest.assign((size_t)M, 0);
             q.n_rest = 0;
+            q.rest_share = 0;
         }
         inst_ok.assign((size_t)M, 0);
         unsolved = false;

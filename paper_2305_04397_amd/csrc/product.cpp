@@ -1141,6 +1141,7 @@ static void plan_resident(morap_ctx* c) {
                                     ? 0 : k::resident_big_columns(prec, positions(m));
             if (!first && columns == 0) {
                 part.rest[(size_t)m] = 1;
+                part.rest_share += (double)states(m) / (double)hm.S();
                 ++part.n_rest;
                 continue;
             }

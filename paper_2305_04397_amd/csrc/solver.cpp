@@ -480,10 +480,15 @@ static const Variant& choose_variant(morap_ctx* c, ValueSet& vs, const uint8_t* 
     const int64_t key = ((int64_t)vs.prec << 40) | ((int64_t)(refine ? 1 : (mask ? 2 : 0)) << 32) | vs.Kp;
     for (auto& t : c->tuned)
         if (t.first == key) return variant_by_id(t.second);
-    // the largest products beside products in LDS: the wave gather sweep (two
-    // states in flight) hands over to the LDS-staged kernel at the first
-    // check that finds under 20 % of the tiles active, as a rule the first
-    if (mask && !refine && c->has_halo && vs.prec == MORAP_F32 && vs.Kp % 64 == 0) return variant_by_id(37);
+    // The largest products beside products in LDS, not timed (a timing takes a
+    // third of a first solve): the LDS-staged kernel with four states in flight
+    // where they hold a third of the states (2 x 12 products of up to 140,000
+    // states, 87 % of all, 64 columns: 169 ms, 183 with the gather sweep and its
+    // hand-over; 20 x 15 products, 43 %: 197 and 210).  Below, few tiles stay active
+    // and either will do (27 %: 201 and 199): the wave gather sweep, which hands
+    // over to the staged kernel where a check finds under 20 % of the tiles active.
+    if (mask && !refine && c->has_halo && vs.prec == MORAP_F32 && vs.Kp % 64 == 0)
+        return variant_by_id(c->resident_plan.part[vs.prec].rest_share > 1.0 / 3 ? 40 : 37);
     auto cand = candidates(vs.Kp, refine, c->has_blocks, c->has_halo && vs.prec == MORAP_F32);
     MORAP_CHECK(!cand.empty(), MORAP_E_UNSUPPORTED, "no sweep variant for this column count");
     int best = cand[0].id;

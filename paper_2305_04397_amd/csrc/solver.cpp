@@ -2465,9 +2465,12 @@ static void solve_staged_impl(morap_ctx* c, const double* W, int K, const morap_
         MORAP_CHECK(v->kind == SWEEP_BLOCK && Kp % kt_of(*v) == 0, MORAP_E_UNSUPPORTED,
                     "stage retirement runs a neighbourhood-block sweep whose k-tile divides the padded width");
     } else {
-        const int64_t key = ((int64_t)prec << 40) | Kp;
-        for (auto& t : c->tuned)
-            if (t.first == key && variant_by_id(t.second).kind == SWEEP_BLOCK) v = &variant_by_id(t.second);
+        // (also where some products' plain solves stay in LDS)
+        for (int64_t rest : {0, 2})
+            for (auto& t : c->tuned)
+                if (!v && t.first == (((int64_t)prec << 40) | (rest << 32) | Kp) &&
+                    variant_by_id(t.second).kind == SWEEP_BLOCK)
+                    v = &variant_by_id(t.second);
         if (!v)
             for (const auto& x : variants())
                 if (x.kind == SWEEP_BLOCK && kt_of(x) == std::min(Kp, 64) &&

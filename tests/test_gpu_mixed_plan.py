@@ -102,3 +102,20 @@ def test_sweep_kernel_of_the_products_beyond_lds(sizes, variant):
         c0, s0 = ctx.solve(W, morap.Options(eps_vi=1e-6, precision="f32", schedule=37))
         assert np.array_equal(c1, c0) and s1["backups"] == s0["backups"] and s1["sweeps"] == s0["sweeps"]
         assert all(np.array_equal(x, ctx.get_values(k, 0)) for x, k in zip(x1, (0, 63)))
+
+
+def test_staged_solve_takes_the_sweep_its_plain_solve_was_timed_for():
+    """A staged solve after a plain one whose sweep kernel was timed on the
+    products beyond LDS takes that kernel (FP64, 16 columns)."""
+    import numpy as np
+    from paper_2305_04397_amd import morap
+    from workloads import dirichlet_weights
+    W = dirichlet_weights(np.random.default_rng(3), 16, 4)
+    o = morap.Options(eps_vi=1e-6, precision="f64")
+    with morap.Context(0) as ctx:
+        ctx.build_products(_corridors((45000, 30000, 3000)))
+        c0, s0 = ctx.solve(W, o)
+        assert s0["resident_models"] == 1 and 18 < s0["variant"] <= 38
+        c1, s1 = ctx.solve_staged(W, o)
+        assert s1["variant"] == s0["variant"]
+        assert np.abs(c1 - c0).max() <= 1e-4

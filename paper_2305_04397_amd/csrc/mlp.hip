@@ -260,7 +260,6 @@ struct RowArgs {
     // activations and the gradients of the layers' outputs; rows past n are 0
     uint16_t *xt, *ht[NLAYER - 1], *gt[NLAYER];
     int n, n_in, d, ld;
-    int first;               // first workgroup (of 16 rows) of the launch
     float inv_b;
 };
 
@@ -295,7 +294,7 @@ __global__ void __launch_bounds__(1024) mlp_rows(RowArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, kg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int row0 = (blockIdx.x + a.first) * ROWS;
+    const int row0 = blockIdx.x * ROWS;
     const int ldx = rows_ldx(a.n_in), ldz = rows_ldz(a.d), ldg = rows_ldg(a.d);
     uint16_t* xs = reinterpret_cast<uint16_t*>(lds);
     uint16_t* h = xs + ROWS * ldx;                                   // [3][ROWS][LDH]
@@ -580,10 +579,72 @@ uint64_t splitmix64(uint64_t x) {
 
 }  // namespace
 
-// Host rows reach the device through pinned memory, checked while they are
-// copied there; calls of more than this many floats are checked in place and
-// copied from where they are (pinned memory is kept, so it is bounded).
-constexpr size_t STAGED = (size_t)8 << 20;
+// Host arrays travel through a ring of pinned slots, checked or copied while the
+// slots before are on their way.  The ring is kept, so it is small: the first use
+// of fresh pinned memory costs 0.35 ms a megabyte (inference of 5,000 rows of
+// 1,024 -> 512 with all rows in pinned memory of their own: 12.9 ms the first time,
+// 1.2 later).
+class Ring {
+public:
+    static constexpr int SLOTS = 4;
+    static constexpr size_t FLOATS = (size_t)1 << 18;   // a slot's
+    Ring() = default;
+    Ring(const Ring&) = delete;
+    Ring& operator=(const Ring&) = delete;
+    ~Ring() {
+        for (hipEvent_t e : done_)
+            if (e) (void)hipEventDestroy(e);
+    }
+    // a call that takes that many slots (nothing of an earlier one is on its way);
+    // one that takes each at most once waits for the stream, not for events of its
+    // own (a step of 4,096 rows of 62 -> 30: 168 us, 213 with them)
+    void start(hipStream_t s, size_t uses) {
+        mem_.ensure(SLOTS * FLOATS * 4);
+        for (Slot& q : slot_) q = Slot();
+        at_ = 0;
+        s_ = s;
+        events_ = uses > SLOTS;
+    }
+    static size_t slots(size_t count) { return (count + FLOATS - 1) / FLOATS; }
+    // the next slot, free again
+    float* next() {
+        wait(at_);
+        return mem_.as<float>() + (size_t)at_ * FLOATS;
+    }
+    // that slot is in use until what the stream holds now has run; then the first
+    // `count` of its floats belong at `to` (or nowhere)
+    void used(float* to = nullptr, size_t count = 0) {
+        if (events_) {
+            if (!done_[at_]) MORAP_HIP(hipEventCreateWithFlags(&done_[at_], hipEventDisableTiming));
+            MORAP_HIP(hipEventRecord(done_[at_], s_));
+        }
+        slot_[at_] = Slot{true, to, count};
+        at_ = (at_ + 1) % SLOTS;
+    }
+    // all slots, oldest first
+    void finish() {
+        for (int q = 0; q < SLOTS; ++q) wait((at_ + q) % SLOTS);
+    }
+    void wait(int q) {
+        if (!slot_[q].busy) return;
+        MORAP_HIP(events_ ? hipEventSynchronize(done_[q]) : hipStreamSynchronize(s_));
+        if (slot_[q].to) std::memcpy(slot_[q].to, mem_.as<float>() + (size_t)q * FLOATS, slot_[q].count * 4);
+        slot_[q].busy = false;
+    }
+
+private:
+    struct Slot {
+        bool busy = false;
+        float* to = nullptr;
+        size_t count = 0;
+    };
+    PinnedBuf mem_;
+    hipEvent_t done_[SLOTS] = {};
+    Slot slot_[SLOTS];
+    int at_ = 0;
+    hipStream_t s_ = nullptr;
+    bool events_ = false;
+};
 
 // Left by an error: waits for the stream, where a copy may still read the
 // caller's rows or the pinned ones that the next call writes.
@@ -653,7 +714,8 @@ struct Proposer {
     DevBuf xb, h[NLAYER - 1], g[NLAYER - 1], logits, prob, target, gout, loss, xf;
     int ld = 0;                       // rows of the transposed copies (fused training)
     DevBuf xt, ht[NLAYER - 1], gt[NLAYER];
-    PinnedBuf stage_x, stage_t, stage_out;   // host rows on their way
+    Ring ring;                        // host arrays on their way
+    PinnedBuf outputs;                // of an inference, at most OUTPUTS floats
 
     Proposer(int n_in_, int d_) : n_in(n_in_), d(d_) {
         const int sizes[NLAYER + 1] = {n_in, HID, HID, HID, d};
@@ -741,9 +803,8 @@ struct Proposer {
         t = 0;
     }
 
-    // everything local to a row for rows [r0, r1) of n (r0 a multiple of 16);
-    // with targets all rows, r1 = n rounded up to 32
-    void fused_rows(hipStream_t s, int n, int r0, int r1, const float* x, float* out, const float* T, float* loss_out) {
+    // everything local to a row
+    void fused_rows(hipStream_t s, int n, const float* x, float* out, const float* T, float* loss_out) {
         RowArgs a{};
         a.x = x;
         a.mu = mu.as<float>();
@@ -760,10 +821,9 @@ struct Proposer {
         a.n_in = n_in;
         a.d = d;
         a.inv_b = 1.f / (float)n;
-        a.first = r0 / ROWS;
         const size_t bytes = rows_lds(n_in, d, T != nullptr);
         MORAP_CHECK(bytes <= 160 * 1024, MORAP_E_UNSUPPORTED, "the network does not fit the fused kernel");
-        const dim3 grid(blocks_for(r1 - r0, ROWS));
+        const dim3 grid(blocks_for(T ? up(n, 32) : n, ROWS));   // (training: the transposed copies' padding too)
         if (!T) {
             hipLaunchKernelGGL(mlp_rows<false>, grid, dim3(1024), bytes, s, a);
             MORAP_HIP(hipGetLastError());
@@ -823,7 +883,7 @@ struct Proposer {
     // forward of n rows already in xf (FP32); logits then softmax into prob
     void forward(hipStream_t s, int n, const float* T_dev) {
         if (fused)
-            fused_rows(s, n, 0, T_dev ? up(n, 32) : n, xf.as<float>(), prob.as<float>(), T_dev, loss.as<float>());
+            fused_rows(s, n, xf.as<float>(), prob.as<float>(), T_dev, loss.as<float>());
         else forward_into(s, n, own_acts(), T_dev);
     }
 
@@ -916,114 +976,95 @@ struct Proposer {
         MORAP_HIP(hipGetLastError());
     }
 
-    // n x n_in host rows to xf; finite is what they have to be if `check`
-    void upload_rows(hipStream_t s, const float* X, int n, bool check) {
-        const size_t count = (size_t)n * n_in;
-        const bool staged = count <= STAGED;
-        float* to = nullptr;
-        if (staged) {
-            stage_x.ensure(count * 4);
-            to = stage_x.as<float>();
-        }
-        const bool bad = nonfinite(X, to, count);
-        MORAP_CHECK(!check || !bad, MORAP_E_INVALID, "X must be finite");
-        ensure_rows(n);
-        MORAP_HIP(hipMemcpyAsync(xf.p, staged ? to : X, count * 4, hipMemcpyHostToDevice, s));
-    }
-    void upload_targets(hipStream_t s, const float* T, int n) {
-        const size_t count = (size_t)n * d;
-        check_targets(T, n, d);
-        if (count <= STAGED) {
-            stage_t.ensure(count * 4);
-            std::memcpy(stage_t.p, T, count * 4);
-            T = stage_t.as<float>();
-        }
-        MORAP_HIP(hipMemcpyAsync(target.p, T, count * 4, hipMemcpyHostToDevice, s));
-    }
-
-    // Inference reads host rows from pinned memory and writes there, each row
-    // once: a call's rows go in up to PARTS launches, the host copying (and
-    // checking) one part while the device works on those before.  4,000 rows of
-    // 182 -> 150 take 0.24 ms; 0.32 with one copy there, one launch and one copy
-    // back.  (A training step is no faster so: the device would wait for its
-    // rows where now they arrive while the host checks the targets.)
-    static constexpr int PARTS = 8;
-    bool pinned_rows(int n) const { return fused && (size_t)n * (n_in + d) <= STAGED; }
-    template <class F>
-    void in_parts(hipStream_t s, int n, F&& f) {
-        const int step = std::max(up((n + PARTS - 1) / PARTS, ROWS), up((256 << 10) / (n_in * 4), ROWS));
-        for (int r = 0, q = 0; r < n; r += step, ++q) {
-            f(r, std::min(step, n - r));
-            if (!done[q]) MORAP_HIP(hipEventCreateWithFlags(&done[q], hipEventDisableTiming));
-            MORAP_HIP(hipEventRecord(done[q], s));
-            parts = q + 1;
-            part_rows = step;
+    // host floats to the device; `check`: finite is what they have to be
+    void upload(hipStream_t s, float* dst, const float* from, size_t count, bool check) {
+        bool bad = false;
+        for (size_t i = 0; i < count; i += Ring::FLOATS) {
+            const size_t part = std::min(Ring::FLOATS, count - i);
+            float* p = ring.next();
+            bad |= nonfinite(from + i, p, part);
+            MORAP_CHECK(!check || !bad, MORAP_E_INVALID, "X must be finite");
+            MORAP_HIP(hipMemcpyAsync(dst + i, p, part * 4, hipMemcpyHostToDevice, s));
+            ring.used();
         }
     }
-    hipEvent_t done[PARTS] = {};
-    int parts = 0, part_rows = 0;
-    ~Proposer() {
-        for (hipEvent_t e : done)
-            if (e) (void)hipEventDestroy(e);
-    }
-    void rows_in(const float* X, int r, int n, bool check) {
-        const size_t at = (size_t)r * n_in;
-        const bool bad = nonfinite(X + at, stage_x.as<float>() + at, (size_t)n * n_in);
-        MORAP_CHECK(!check || !bad, MORAP_E_INVALID, "X must be finite");
+    // device floats to the host, there after ring.finish()
+    void download(hipStream_t s, float* to, const float* src, size_t count) {
+        for (size_t i = 0; i < count; i += Ring::FLOATS) {
+            const size_t part = std::min(Ring::FLOATS, count - i);
+            MORAP_HIP(hipMemcpyAsync(ring.next(), src + i, part * 4, hipMemcpyDeviceToHost, s));
+            ring.used(to + i, part);
+        }
     }
 
     // one step on n host rows; returns the mean loss
     double step(hipStream_t s, const float* X, const float* T, int n, const morap_train_opts* o, bool apply,
                 float* grads_out) {
         const Drain drain(s);
-        upload_rows(s, X, n, true);
-        upload_targets(s, T, n);
+        ring.start(s, Ring::slots((size_t)n * n_in) + Ring::slots((size_t)n * d) + Ring::slots((size_t)n) +
+                          (grads_out ? Ring::slots((size_t)n_params) : 0));
+        ensure_rows(n);
+        upload(s, xf.as<float>(), X, (size_t)n * n_in, true);
+        check_targets(T, n, d);
+        upload(s, target.as<float>(), T, (size_t)n * d, false);
         forward(s, n, target.as<float>());
         backward(s, n);
         if (apply) adam(s, *o);
-        std::vector<float> far;
-        const size_t got = (size_t)n + (grads_out ? n_params : 0);
-        float* l;
-        if (got <= STAGED) {
-            stage_out.ensure(got * 4);
-            l = stage_out.as<float>();
-        } else {
-            far.resize(got);
-            l = far.data();
-        }
-        MORAP_HIP(hipMemcpyAsync(l, loss.p, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-        if (grads_out) MORAP_HIP(hipMemcpyAsync(l + n, grad.p, n_params * 4, hipMemcpyDeviceToHost, s));
-        MORAP_HIP(hipStreamSynchronize(s));
-        if (grads_out) std::memcpy(grads_out, l + n, n_params * 4);
+        losses.resize((size_t)n);
+        download(s, losses.data(), loss.as<float>(), (size_t)n);
+        if (grads_out) download(s, grads_out, grad.as<float>(), (size_t)n_params);
+        ring.finish();
         double sum = 0;
-        for (int i = 0; i < n; ++i) sum += l[i];
+        for (int i = 0; i < n; ++i) sum += losses[(size_t)i];
         return sum / n;
     }
+    std::vector<float> losses;
 
+    // Inference with the fused kernel reads host rows from the ring's slots and
+    // writes to pinned memory, each row once: a call's rows go in parts, at most 8
+    // where the slots hold them, the host copying and checking one while the device
+    // works on those before; the outputs leave when every row has been read (the
+    // arrays may overlap, and a refused call writes none).  4,000 rows of
+    // 182 -> 150 take 0.24 ms; 0.32 with one copy there, one launch and one copy
+    // back.  (A training step is no faster so: the device would wait for its
+    // rows where now they arrive while the host checks the targets.)
+    static constexpr size_t OUTPUTS = (size_t)1 << 22;
     void infer(hipStream_t s, const float* X, int n, float* out, bool check) {
         const Drain drain(s);
-        if (pinned_rows(n)) {
-            stage_x.ensure((size_t)n * n_in * 4);
-            stage_out.ensure((size_t)n * d * 4);
-            float *x = stage_x.as<float>(), *p = stage_out.as<float>();
-            in_parts(s, n, [&](int r, int rows) {
-                rows_in(X, r, rows, check);
-                fused_rows(s, n, r, r + rows, x, p, nullptr, nullptr);
-            });
-            for (int q = 0, r = 0; q < parts; ++q, r += part_rows) {
-                MORAP_HIP(hipEventSynchronize(done[q]));
-                std::memcpy(out + (size_t)r * d, p + (size_t)r * d, (size_t)std::min(part_rows, n - r) * d * 4);
+        const size_t count = (size_t)n * d;
+        const bool pinned = fused && count <= OUTPUTS;
+        const int step = std::min<int>(std::max(up((n + 7) / 8, ROWS), up((256 << 10) / (n_in * 4), ROWS)),
+                                       (int)(Ring::FLOATS / n_in) / ROWS * ROWS);
+        const int parts = (n + step - 1) / step;
+        // (pinned outputs leave part by part, on events)
+        ring.start(s, pinned ? (parts > 1 ? Ring::SLOTS + 1 : 1)
+                             : (fused ? (size_t)parts : Ring::slots((size_t)n * n_in)) + Ring::slots(count));
+        if (!pinned) ensure_rows(n);
+        if (!fused) {
+            upload(s, xf.as<float>(), X, (size_t)n * n_in, check);
+            forward(s, n, nullptr);
+        } else {
+            if (pinned) outputs.ensure(count * 4);
+            float* p = pinned ? outputs.as<float>() : prob.as<float>();
+            for (int r = 0; r < n; r += step) {
+                const int rows = std::min(step, n - r);
+                float* x = ring.next();
+                const bool bad = nonfinite(X + (size_t)r * n_in, x, (size_t)rows * n_in);
+                MORAP_CHECK(!check || !bad, MORAP_E_INVALID, "X must be finite");
+                fused_rows(s, rows, x, p + (size_t)r * d, nullptr, nullptr);
+                ring.used();
             }
+        }
+        if (!pinned) {
+            download(s, out, prob.as<float>(), count);
+            ring.finish();
             return;
         }
-        upload_rows(s, X, n, check);
-        forward(s, n, nullptr);
-        const size_t count = (size_t)n * d;
-        const bool staged = count <= STAGED;
-        if (staged) stage_out.ensure(count * 4);
-        MORAP_HIP(hipMemcpyAsync(staged ? stage_out.p : out, prob.p, count * 4, hipMemcpyDeviceToHost, s));
-        MORAP_HIP(hipStreamSynchronize(s));
-        if (staged) std::memcpy(out, stage_out.p, count * 4);
+        for (int q = 0; q < parts; ++q) {
+            if (q >= parts - Ring::SLOTS) ring.wait(q % Ring::SLOTS);   // (those before have given up their slots)
+            const size_t r = (size_t)q * step;
+            std::memcpy(out + r * d, outputs.as<float>() + r * d, std::min((size_t)step, n - r) * d * 4);
+        }
     }
 };
 
@@ -1175,7 +1216,7 @@ int morap_proposer_infer_noalloc(morap_ctx* ctx, const float* X_dev, int n, floa
             const size_t count = (size_t)n * p.d;
             const bool shared = x0 < w0 + count * 4 && w0 < x0 + (size_t)n * p.n_in * 4;
             float* out = shared ? reinterpret_cast<float*>(scratch_of(ctx->device)) : W_out_dev;
-            p.fused_rows(ctx->stream, n, 0, n, X_dev, out, nullptr, nullptr);
+            p.fused_rows(ctx->stream, n, X_dev, out, nullptr, nullptr);
             if (shared) {
                 hipLaunchKernelGGL(copy_kernel, dim3(blocks_for((int64_t)count)), dim3(256), 0, ctx->stream, out,
                                    W_out_dev, (int64_t)count);

@@ -246,6 +246,7 @@ struct HostModels {
     // [M] 1: the model's agent lists a successor with probability 0 (the
     // blocks do not tell it from an unused slot; attractor ranks do)
     std::vector<uint8_t> blk_zero_prob;
+    double largest_reward = 0;         // magnitude of a cost or probability reward
     int64_t S() const { return (int64_t)state_row.size() - 1; }
     int64_t R() const { return (int64_t)row_ptr.size() - 1; }
     int64_t N() const { return (int64_t)col.size(); }
@@ -842,6 +843,10 @@ struct RowsArgs : ResidentArgs {
     const uint2* place;         // [batches][64] four LDS rows, 16 bits each
     const void* value;          // [batches][64][4] rewards and probabilities
 };
+// Largest reward of a problem whose values may stay in LDS: at any sweep limit no
+// value overflows, so there is no infinity and no NaN to treat as the batched
+// sweeps' maxima do (which pass over a NaN and start at minus infinity).
+constexpr double largest_reward(int prec) { return prec == MORAP_F32 ? 1e29 : 1e298; }
 // columns per workgroup of a product of that many states, 0 if it does not fit
 int rows_columns(int prec, int states);
 void resident_rows(hipStream_t s, int prec, int columns, int max_states, const RowsArgs& a);

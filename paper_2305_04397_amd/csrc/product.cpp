@@ -27,6 +27,7 @@ struct Built {
     std::vector<int32_t> state_row{0}, row_ptr{0}, col, states_sq;
     std::vector<double> prob, rew;
     std::vector<uint8_t> to_done;
+    double largest = 0;   // magnitude of a reward
 };
 
 void validate_agent(const morap_agent& a, int i) {
@@ -147,6 +148,7 @@ Built build_one(const morap_agent& a, const morap_dfa& t, const int32_t* letters
                 }
             }
             b.rew.push_back(-a.cost[r]);
+            b.largest = std::max(b.largest, std::fabs(a.cost[r]));
             b.rew.push_back(mass_acc);
             b.to_done.push_back(hits_done);
             b.row_ptr.push_back((int32_t)b.col.size());
@@ -170,6 +172,7 @@ static void concat(morap_ctx* c, std::vector<Built>& parts, int nI, int nJ) {
     hm.M = nI * nJ;
     int64_t S = 0, R = 0, N = 0;
     for (auto& b : parts) {
+        hm.largest_reward = std::max(hm.largest_reward, b.largest);
         S += (int64_t)b.state_row.size() - 1;
         R += (int64_t)b.row_ptr.size() - 1;
         N += (int64_t)b.col.size();
@@ -735,6 +738,7 @@ static void load_models_as(morap_ctx* c, const morap_model* models, int n, int n
             MORAP_CHECK(sum <= 1.0 + 1e-6, MORAP_E_INVALID, who + "a row sums above 1");
             MORAP_CHECK(std::isfinite(md.rew[2 * r]) && std::isfinite(md.rew[2 * r + 1]), MORAP_E_INVALID,
                         who + "non-finite reward");
+            b.largest = std::max(b.largest, std::max(std::fabs(md.rew[2 * r]), std::fabs(md.rew[2 * r + 1])));
         }
         b.col.assign(md.col, md.col + md.nnz);
         b.prob.assign(md.prob, md.prob + md.nnz);
@@ -1034,7 +1038,7 @@ static void plan_rows(morap_ctx* c) {
     P.n_order = (int)order.size();
     for (int b = 0; b < P.n_order; ++b) P.rank[(size_t)order[b]] = b;
     for (int prec : {MORAP_F64, MORAP_F32}) {
-        if (k::rows_columns(prec, most) == 0) continue;
+        if (k::rows_columns(prec, most) == 0 || hm.largest_reward > k::largest_reward(prec)) continue;
         ResidentPlan::Part& part = P.part[prec];
         part.models = order;
         for (int b = 0; b < (int)order.size(); ++b) {
@@ -1134,7 +1138,7 @@ static void plan_resident(morap_ctx* c) {
     for (int b = 0; b < P.n_order; ++b) P.rank[(size_t)order[b]] = b;
     for (int prec : {MORAP_F64, MORAP_F32}) {
         ResidentPlan::Part& part = P.part[prec];
-        for (int b = 0; b < (int)order.size(); ++b) {
+        for (int b = 0; b < (int)order.size() && hm.largest_reward <= k::largest_reward(prec); ++b) {
             const int m = order[b];
             const bool first = states(m) <= k::resident_capacity(prec, fast(m));
             const int columns = first || positions(m) == 0 || (prec == MORAP_F32 && !tame)
@@ -1163,7 +1167,8 @@ static void plan_resident(morap_ctx* c) {
     MORAP_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
     const int most = std::min(k::policy_capacity(), k::eval_capacity());
     for (int32_t m : order)
-        P.inst_ok[(size_t)m] = !P.part[MORAP_F64].rest[(size_t)m] && !hm.blk_zero_prob[(size_t)m] && states(m) <= most;
+        P.inst_ok[(size_t)m] = hm.largest_reward <= k::largest_reward(MORAP_F64) &&
+                               !P.part[MORAP_F64].rest[(size_t)m] && !hm.blk_zero_prob[(size_t)m] && states(m) <= most;
 }
 
 bool drop_layouts(morap_ctx* c) {

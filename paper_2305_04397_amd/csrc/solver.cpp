@@ -2492,7 +2492,7 @@ static void solve_staged_impl(morap_ctx* c, const double* W, int K, const morap_
     // every live product in LDS, unless the caller fixed the sweep kernel;
     // several columns per workgroup unless all pairs run at once anyway
     const bool wide = (int64_t)L.lds_order.size() * K > 2 * (int64_t)c->prop.multiProcessorCount;
-    bool lds = o.schedule == 0 && !L.lds_order.empty();
+    bool lds = o.schedule == 0 && !L.lds_order.empty() && c->hm.largest_reward <= k::largest_reward(prec);
     for (int32_t m : L.lds_order) lds = lds && staged_class(L, m, prec, wide).columns > 0;
     if (lds) {
         c->d_weights.ensure((size_t)K * d * 8);

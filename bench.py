@@ -20,8 +20,13 @@ the same kind with HIP events around the sweep launches (eager launches).
 
 Extra objects on the JSON line:
   roofline      with products whose values stay in LDS (the default workload's
-                most): vector lane operations of the value iteration per second
-                against 256 CUs x 64 lanes x 2.4 GHz; else
+                most): the operations of the whole value iteration per second,
+                22 a state and column, against the vector rate of 256 CUs x 64
+                lanes x 2.4 GHz (FP32 products of more than 3,584 states have
+                16 of the 22 on the matrix cores, and the time holds the batched
+                sweeps of products beyond LDS, under `batched`: a rate in those
+                units, not the vector units' utilisation, which
+                profiles/lds_kernels_counters.txt has per kernel); else
                 the Bellman sweep kernel: algorithmic bytes (CSR of active
                 models + one FP32 read and one write per active state-column)
                 over its summed HIP-event durations, against 8 TB/s HBM; the
@@ -510,9 +515,10 @@ def main():
     resident = st["resident_models"]
     tb = None if resident else measured_traffic(kname)
     if resident:
-        # most products iterate in LDS, all sweeps in one launch each: what
-        # bounds them is the vector ALU, 22 operations per state and column
-        # (17 multiply-adds, 3 maxima, the change and its maximum)
+        # most products iterate in LDS, all sweeps in one launch each: 22
+        # operations per state and column (17 multiply-adds, 3 maxima, the
+        # change and its maximum); 16 of the multiply-adds are matrix
+        # instructions in FP32 products of more than 3,584 states
         state_columns = st["backups"] * S / R
         achieved = 22.0 * state_columns / (st["ms_vi"] / 1e3) / 1e12
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -526,14 +532,21 @@ def main():
                           "ms_per_step come from the timed steps, which replay captured graphs"}
     if resident:
         algorithmic = (st["bytes"] + st["bytes_tail"]) / (st["ms_vi"] / 1e3) / 1e9
-        roofline.update({"bound": "valu", "peak": VALU_PEAK, "unit": "10^12 lane operations/s",
+        batched = {k: roofline.pop(k) for k in ("kernel", "variant", "launches", "launches_timed", "avg_launch_us")}
+        t = "float" if args.precision == "f32" else "double"
+        larger = "void morap::k::big_mfma<" if t == "float" else f"void morap::k::resident_big<{t}"
+        roofline.update({"bound": "valu", "peak": VALU_PEAK, "unit": "10^12 operations/s",
                          "frac": round(achieved / VALU_PEAK, 4), "achieved": round(achieved, 2),
+                         "kernel": f"{kernel_name(41, args.precision)}, {larger}",
                          "algorithmic_gb_per_s": round(algorithmic, 1),
                          "resident_models": resident, "bytes_per_launch": None,
-                         "timing": "22 lane operations per state and column of one extra pass over its value "
-                                   f"iteration's wall time (FP64 re-solve included), {st['ms_vi']:.1f} ms: {resident} "
-                                   "products iterate in LDS, where the algorithmic bytes are not memory traffic; "
-                                   "launches and their times are the batched sweeps' of the products beyond LDS"})
+                         "batched": batched if main_sweeps and st["variant"] != 41 else None,
+                         "timing": "22 operations per state and column (vector multiply-adds, maxima and changes; in "
+                                   "FP32 products of more than 3,584 states 16 of them on the matrix cores) of one "
+                                   f"extra pass over its value iteration's wall time, {st['ms_vi']:.1f} ms, FP64 "
+                                   f"re-solve and batched sweeps included: {resident} products iterate in LDS, where "
+                                   "the algorithmic bytes are not memory traffic; `batched` are the sweeps of the "
+                                   "products beyond LDS"})
     if st["sweeps_tail"]:
         avg_t = st["ms_sweep_kernel_tail"] / 1e3 / max(1, st["sweep_launches_tail"])
         bt = st["bytes_tail"] / st["sweeps_tail"]

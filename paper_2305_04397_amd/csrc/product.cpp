@@ -947,7 +947,8 @@ static void plan_rows(morap_ctx* c) {
             for (int32_t g = s0 + b; g < s0 + std::min(b + 64, n); ++g) {
                 const int32_t r = hm.state_row[g], nr = hm.state_row[g + 1] - r;
                 if (nr > (int32_t)len.size()) len.resize((size_t)nr, 0);
-                for (int32_t j = 0; j < nr; ++j) len[(size_t)j] = std::max(len[(size_t)j], hm.row_ptr[r + j + 1] - hm.row_ptr[r + j]);
+                for (int32_t j = 0; j < nr; ++j)
+                    len[(size_t)j] = std::max(len[(size_t)j], hm.row_ptr[r + j + 1] - hm.row_ptr[r + j]);
                 least = std::min(least, nr);
             }
             // (a state repeats its first row where it has fewer)

@@ -372,8 +372,8 @@ resident_vi(ResidentArgs a) {
 // or 3 (FP64) times the LDS traffic of the values themselves.
 //
 // This kernel is FP64's beyond 2,560 states: two columns of the values, new ones in
-// registers.  (49 products of up to 2,429 states, 37 columns, took 2.3 ms here
-// and 10 with the batched sweeps.)
+// registers.  (48 products of 3,143 to 8,319 states, 37 columns: 2.7 ms here, 13.2
+// with the batched sweeps.)
 template <class T, int KC, int NS, bool INST = false>
 __global__ void __launch_bounds__(BIG_THREADS)
 resident_big(ResidentArgs a) {

@@ -698,7 +698,8 @@ static void run_resident(morap_ctx* c, ValueSet& vs, const ResidentPlan::Part& p
                 const int32_t m = part.models[(size_t)b];
                 work += hm.state_base[m + 1] - hm.state_base[m];
             }
-            // (FP32 rates with one, two and four columns a workgroup)
+            // (FP32 rates with one, two and four columns a workgroup; FP64's are
+            // weighed alike)
             const hipStream_t s = fork.least(work * (l.columns == 1 ? 1.8 : (l.columns == 2 ? 1.4 : 1.0)), (bool)beside);
             if (l.rows && l.columns == 0) {
                 a.short_base = plan.short_base.as<int32_t>();
@@ -1646,7 +1647,6 @@ static void evaluate_impl(morap_ctx* c, const int32_t* assign, int K, const mora
     const auto eval_runs = I.runs(c, [](int S_m) { return k::eval_class(S_m); });
     const int64_t eval_limit = ((int64_t)o.max_sweeps + chunk - 1) / chunk * chunk;
     int64_t esweeps = 0;
-    std::string unfinished;   // instances in LDS whose evaluation hit its limit
     auto policies_and_values = [&] {
         launch(policy_runs, k::inst_policy);
         ia.sweep0 = 0;
@@ -2387,7 +2387,8 @@ static void run_staged_lds(morap_ctx* c, ValueSet& vs, const morap_vi_opts& o, b
                 held.v.back().second = take_event(c);
                 MORAP_HIP(hipEventRecord(held.v.back().first, s));
             }
-            k::staged_lds(fork.least((double)l.n * L.lds_positions[L.lds_order[l.begin]]), vs.prec, l.c.columns, l.c.threads, L.lds_positions[L.lds_order[l.begin]], a);
+            const int positions = L.lds_positions[L.lds_order[l.begin]];   // (the largest product's)
+            k::staged_lds(fork.least((double)l.n * positions), vs.prec, l.c.columns, l.c.threads, positions, a);
             if (o.time_kernels) MORAP_HIP(hipEventRecord(held.v.back().second, s));
         }
         fork.join();
@@ -2421,7 +2422,8 @@ static void run_staged_lds(morap_ctx* c, ValueSet& vs, const morap_vi_opts& o, b
         }
     // (counted as the batched sweeps are: to the next look at the counters)
     const int64_t check = std::max(2, o.check_every);
-    st.sweeps += std::min<int64_t>(o.max_sweeps, std::max<int64_t>((longest + check - 1) / check * check, std::min<int64_t>(check, o.max_sweeps)));
+    const int64_t looked = std::max<int64_t>((longest + check - 1) / check * check, check);
+    st.sweeps += std::min<int64_t>(o.max_sweeps, looked);
     const int32_t* ps = c->h_pair_sweeps.as<int32_t>();
     st.max_pair_sweeps = std::max<int64_t>(st.max_pair_sweeps, *std::max_element(ps, ps + (size_t)M * Kp));
     st.floor_stops += c->h_counters.as<int64_t>()[8];

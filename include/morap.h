@@ -64,7 +64,9 @@ int morap_destroy(morap_ctx* ctx);
 /* Device memory budget of the context in bytes (0 = none, the default).  An
  * allocation that would take the context's device memory beyond it fails
  * with MORAP_E_OOM, as a failed hipMalloc does; what the context already
- * holds is kept.  used_out (nullable) receives the bytes the context holds
+ * holds is kept, but for the layouts of the kernels that keep values in LDS,
+ * which are freed first (solves then take the batched sweeps until the next
+ * upload).  used_out (nullable) receives the bytes the context holds
  * now.  Errors: INVALID (negative budget). */
 int morap_set_memory_budget(morap_ctx* ctx, int64_t bytes, int64_t* used_out);
 
